@@ -15,6 +15,7 @@
 #include "handle.h"
 #include "probe.h"
 #include "sort_internal.h"
+#include "tree_internal.h"
 
 using namespace envpot;
 
@@ -43,6 +44,8 @@ void free_device(env_potential* h) {
     h->d_boys_field = nullptr;
     free_update_state(h->upd);
     h->upd = nullptr;
+    free_tree(h->tree);
+    h->tree = nullptr;
     h->d_rec = nullptr;
     h->d_segs = nullptr;
     h->d_boxes = nullptr;
@@ -85,6 +88,16 @@ namespace envpot {
 // precisions; the device-sized launch uses the same target).
 constexpr int64_t kWantWavesPerSimd = 48;
 
+// Launch shape of a tree evaluation.
+void tree_shape(const env_potential* h, int64_t n, int* np, int* k_out) {
+    *np = tree_np(n, h->precision == ENV_PREC_FP64);
+    const int64_t blocks = (n + 64 * *np - 1) / (64 * *np);
+    const int64_t want = tree_want(blocks, h->cu_count);
+    int k = 0;
+    while (k < kMaxSplitLog2 && (blocks << k) < want) ++k;
+    *k_out = k;
+}
+
 void choose_shape(const env_potential* h, int64_t n, int* np_out, int* k_out) {
     const bool fp64 = h->precision == ENV_PREC_FP64;
     // a tuned shape for a point count within a factor 2 of n wins
@@ -95,7 +108,9 @@ void choose_shape(const env_potential* h, int64_t n, int* np_out, int* k_out) {
         if (d < bestd) { bestd = d; best = &t; }
     }
     int np, k = 0;
-    if (best && bestd <= std::log(2.0)) {
+    if (h->tree && !(best && bestd <= std::log(2.0))) {
+        tree_shape(h, n, &np, &k);
+    } else if (best && bestd <= std::log(2.0)) {
         np = best->np;
         k = best->klog;
     } else {
@@ -135,6 +150,9 @@ EvalArgs make_args(const env_potential* h, const double* points, int64_t n, doub
     a.boxes = h->use_boxes ? h->d_boxes : nullptr;
     a.out = out;
     a.bp = h->bp;
+    a.tree = h->tree ? tree_view(*h->tree) : TreeView{};
+    a.tree.S = 1 << k;
+    a.order = nullptr;
     return a;
 }
 
@@ -143,8 +161,6 @@ env_status eval_devsized(env_potential* h, const double* points, const int64_t* 
     if (!h->on_device) return ENV_E_STATE;
     if (n_max <= 0) return ENV_OK;
     if (part_cap < n_max) return ENV_E_ARG;
-    const bool fp64 = h->precision == ENV_PREC_FP64;
-    const int np = fp64 ? 2 : 4;
     DevSizedArgs d;
     d.a = make_args(h, points, 0, part, 0);
     d.m = m;
@@ -155,19 +171,34 @@ env_status eval_devsized(env_potential* h, const double* points, const int64_t* 
         d.split_off[k] = h->split_off[k];
     }
     d.part_cap = part_cap;
-    d.want_waves = int64_t(h->cu_count) * 4 * kWantWavesPerSimd;  // the rule of choose_shape
+    // the rule of choose_shape
+    d.want = int64_t(h->cu_count) * (h->tree ? 1 : 4 * kWantWavesPerSimd);
     d.counter = counter;
     DeviceGuard g(h->device);
-    if (launch_potential_devsized(d, devsized_grid(h->precision, h->cu_count), h->precision, np, stream) != 0 ||
-        launch_sum_devsized(d, np, n_max, out, stream) != 0)
-        return ENV_E_DEVICE;
-    return ENV_OK;
+    hipStream_t st = static_cast<hipStream_t>(stream);
+    uint32_t* order = nullptr;
+    if (h->tree && env_int("ENVPOT_NO_SORT", 0) == 0) {
+        if (hipMallocAsync(reinterpret_cast<void**>(&order), size_t(kOrderSmallMax) * sizeof(uint32_t), st) != hipSuccess)
+            return ENV_E_NOMEM;
+        d.a.order = order;
+        if (order_points(points, 0, m, order, stream) != 0) {
+            (void)hipFreeAsync(order, st);
+            return ENV_E_DEVICE;
+        }
+    }
+    env_status rc = ENV_OK;
+    if (launch_potential_devsized(d, devsized_grid(h->precision, h->tree != nullptr, h->cu_count), h->precision, stream) != 0 ||
+        launch_sum_devsized(d, h->precision, n_max, out, stream) != 0)
+        rc = ENV_E_DEVICE;
+    if (order) (void)hipFreeAsync(order, st);
+    return rc;
 }
 
 }  // namespace envpot
 
 namespace {
-env_status eval_core(env_potential* h, const double* points, int64_t n, double* out, void* stream);
+env_status eval_core(env_potential* h, const double* points, int64_t n, const uint32_t* order, double* out,
+                     void* stream);
 }  // namespace
 
 extern "C" {
@@ -419,6 +450,11 @@ env_status env_potential_create(const env_nucleus* nuclei, int32_t n_nuclei,
             else if (st == ENV_OK && src.device_fold) st = ENV_E_DEVICE;
         }
         lap("update tables");
+        if (st == ENV_OK && h->upd && merge && env_int("ENVPOT_NO_TREE", 0) == 0) {
+            h->tree = build_tree(*h->upd, h->d_rec, pl.nuc, pl.group_nuc_begin, pl.group_nuc_end, fp64, &st);
+            if (h->tree) h->device_bytes += h->tree->device_bytes;
+            lap("tree");
+        }
         // the first fold of the density, on the device
         if (st == ENV_OK && src.device_fold) st = env_potential_update_density(h, P, nullptr);
         lap("device fold");
@@ -444,9 +480,26 @@ env_status env_potential_eval(env_potential* h, const double* points, int64_t n,
     if (h->on_host) return host_eval(h, points, n, out);
     if (!h->on_device) return ENV_E_STATE;
     DeviceGuard g(h->device);
-    if (n < kSortMinPoints || n > int64_t(INT32_MAX) || env_int("ENVPOT_NO_SORT", 0) != 0 ||
-        stream_capturing(stream))
-        return eval_core(h, points, n, out, stream);
+    const bool no_sort = env_int("ENVPOT_NO_SORT", 0) != 0;
+    if (h->tree) {
+        // the kernels read the points through a spatial order (Morton order
+        // for large calls, unless the stream is being captured) and the sum
+        // of the splits writes the values in the caller's order
+        const bool large = n >= kSortMinPoints && n <= int64_t(INT32_MAX) && !stream_capturing(stream);
+        if (no_sort || !(large || order_small(n))) return eval_core(h, points, n, nullptr, out, stream);
+        uint32_t* order = nullptr;
+        hipStream_t st = static_cast<hipStream_t>(stream);
+        if (hipMallocAsync(reinterpret_cast<void**>(&order), size_t(n) * sizeof(uint32_t), st) != hipSuccess)
+            return ENV_E_NOMEM;
+        env_status rc = ENV_OK;
+        if ((large ? sort_order(points, n, order, stream) : order_points(points, n, nullptr, order, stream)) != 0)
+            rc = ENV_E_DEVICE;
+        if (rc == ENV_OK) rc = eval_core(h, points, n, order, out, stream);
+        (void)hipFreeAsync(order, st);
+        return rc;
+    }
+    if (n < kSortMinPoints || n > int64_t(INT32_MAX) || no_sort || stream_capturing(stream))
+        return eval_core(h, points, n, nullptr, out, stream);
     // large calls: evaluate the points in Morton order, then restore the caller's order
     hipStream_t st = static_cast<hipStream_t>(stream);
     double *spts = nullptr, *sout = nullptr;
@@ -458,7 +511,7 @@ env_status env_potential_eval(env_potential* h, const double* points, int64_t n,
         hipMallocAsync(reinterpret_cast<void**>(&order), size_t(n) * sizeof(uint32_t), st) != hipSuccess)
         rc = ENV_E_NOMEM;
     if (rc == ENV_OK && sort_points(points, n, spts, order, stream) != 0) rc = ENV_E_DEVICE;
-    if (rc == ENV_OK) rc = eval_core(h, spts, n, sout, stream);
+    if (rc == ENV_OK) rc = eval_core(h, spts, n, nullptr, sout, stream);
     if (rc == ENV_OK && scatter_values(sout, order, n, out, stream) != 0) rc = ENV_E_DEVICE;
     (void)hipFreeAsync(order, st);
     (void)hipFreeAsync(sout, st);
@@ -493,22 +546,25 @@ int timed_launch(env_potential* h, const EvalArgs& a, int S, int np, void* strea
     return rc;
 }
 
-env_status eval_core(env_potential* h, const double* points, int64_t n, double* out, void* stream) {
+env_status eval_core(env_potential* h, const double* points, int64_t n, const uint32_t* order, double* out,
+                     void* stream) {
     int np, k;
     choose_shape(h, n, &np, &k);
     const int S = 1 << k;
     hipStream_t st = static_cast<hipStream_t>(stream);
     if (S == 1) {
-        const EvalArgs a = make_args(h, points, n, out, 0);
+        EvalArgs a = make_args(h, points, n, out, 0);
+        a.order = order;
         return timed_launch(h, a, 1, np, stream) == 0 ? ENV_OK : ENV_E_DEVICE;
     }
     double* part = nullptr;
     if (hipMallocAsync(reinterpret_cast<void**>(&part), size_t(S) * size_t(n) * sizeof(double), st) !=
         hipSuccess)
         return ENV_E_NOMEM;
-    const EvalArgs a = make_args(h, points, n, part, k);
+    EvalArgs a = make_args(h, points, n, part, k);
+    a.order = order;
     int rc = timed_launch(h, a, S, np, stream);
-    if (rc == 0) rc = launch_sum_splits(part, S, n, out, stream);
+    if (rc == 0) rc = launch_sum_splits(part, S, n, order, out, stream);
     (void)hipFreeAsync(part, st);
     return rc == 0 ? ENV_OK : ENV_E_DEVICE;
 }
@@ -542,7 +598,8 @@ env_status env_potential_autotune(env_potential* h, const double* points, int64_
                    h->tuned.end());
     for (int a = 0; a < 2 && rc == ENV_OK; ++a) {
         for (int k = 0; k <= kMaxSplitLog2 && rc == ENV_OK; ++k) {
-            const int64_t waves = ((n + 64 * nps[a] - 1) / (64 * nps[a])) << k;
+            // (a workgroup of a tree evaluation has four waves for one block)
+            const int64_t waves = (((n + 64 * nps[a] - 1) / (64 * nps[a])) << k) * (h->tree ? 4 : 1);
             if (waves < int64_t(h->cu_count) * 4 || (k > 0 && waves > int64_t(h->cu_count) * 4 * 96))
                 continue;
             h->tuned.push_back({n, nps[a], k});

@@ -8,6 +8,9 @@
 // plan's own buffers (outside any graph: the sort library may record
 // memory-set nodes), the persistent kernel reads those buffers, and a scatter
 // kernel inside the graph writes the values back in the caller's order.
+// With multipole trees only the order is kept: the kernels read the points
+// and write the values through it, and smaller instances get an order too,
+// from a kernel of the graph.
 // While the caller's stream is being captured the plan uses a second
 // argument table that reads and writes the caller's buffers directly.
 #include <hip/hip_runtime.h>
@@ -27,6 +30,7 @@ using namespace envpot;
 struct env_batch {
     int device = -1;
     int precision = ENV_PREC_FP32C;
+    bool tree = false;  // every handle has a multipole tree
     int np = 4;
     int gran = 16;      // items per workgroup's fair share of the work (split granularity;
                         // the autotuner's pick on the 64-instance workload)
@@ -52,6 +56,11 @@ struct env_batch {
     double* d_spts = nullptr;           // sorted points (3 per point)
     double* d_sout = nullptr;           // values in sorted order
     uint32_t* d_order = nullptr;
+    // with trees the kernels read the points through d_order: the large
+    // instances' part is sorted outside the graph, the small ones' in it
+    OrderDesc* d_small = nullptr;
+    int n_small = 0;
+    std::vector<int64_t> small_off;     // offset of a small instance's order, -1: none
     int n_sum = 0;
     int64_t max_n_sum = 0;
     int n_scat = 0;
@@ -81,7 +90,8 @@ void free_shape(env_batch* b) {
     for (void* p : {static_cast<void*>(b->d_items), static_cast<void*>(b->d_part), static_cast<void*>(b->d_sum),
                     static_cast<void*>(b->d_sum_direct), static_cast<void*>(b->d_args),
                     static_cast<void*>(b->d_args_direct), static_cast<void*>(b->d_scat),
-                    static_cast<void*>(b->d_spts), static_cast<void*>(b->d_sout), static_cast<void*>(b->d_order)})
+                    static_cast<void*>(b->d_spts), static_cast<void*>(b->d_sout), static_cast<void*>(b->d_order),
+                    static_cast<void*>(b->d_small)})
         (void)hipFree(p);
     b->d_items = nullptr;
     b->d_part = nullptr;
@@ -90,6 +100,7 @@ void free_shape(env_batch* b) {
     b->d_scat = nullptr;
     b->d_spts = b->d_sout = nullptr;
     b->d_order = nullptr;
+    b->d_small = nullptr;
     b->shape_valid = false;
     b->args_valid = false;
     drop_graph(b);
@@ -97,17 +108,19 @@ void free_shape(env_batch* b) {
 
 // Instances evaluated in Morton order (the rule of a single evaluation,
 // including its ENVPOT_NO_SORT switch).
-bool sorts(int64_t n) {
+bool sorts_off() {
     const char* ns = std::getenv("ENVPOT_NO_SORT");
-    return n >= kSortMinPoints && n <= int64_t(INT32_MAX) && !(ns && *ns && std::atoi(ns) != 0);
+    return ns && *ns && std::atoi(ns) != 0;
 }
+
+bool sorts(int64_t n) { return n >= kSortMinPoints && n <= int64_t(INT32_MAX) && !sorts_off(); }
 
 // Work items for point counts n: per instance a split factor such that an
 // item costs at most ~1/gran of a workgroup's fair share, items sorted by
 // decreasing cost.
 env_status build_shape(env_batch* b, const int64_t* n) {
     free_shape(b);
-    const int per = kBlock * b->np;
+    const int per = (b->tree ? 64 : kBlock) * b->np;
     const double* w = b->precision == ENV_PREC_FP64 ? kW64 : kW32;
     std::vector<double> pcost(b->n_inst, 0.0);
     double total = 0.0;
@@ -115,6 +128,8 @@ env_status build_shape(env_batch* b, const int64_t* n) {
         const env_info& in = b->hs[i]->info;
         for (int L = 0; L <= kLMax; ++L) pcost[i] += double(in.n_pairs_by_L[L]) * w[L];
         pcost[i] += 0.6 * in.n_nuclei + 1.0;
+        // with a tree a point meets its surroundings pair by pair and the rest by groups
+        if (b->tree) pcost[i] = std::min(pcost[i], 2.0e4) + 50.0 * in.n_groups;
         total += double(n[i]) * pcost[i];
     }
     const double target = std::max(1.0, total / (double(b->gran) * b->grid));
@@ -124,7 +139,9 @@ env_status build_shape(env_batch* b, const int64_t* n) {
     b->sort_off.assign(b->n_inst, -1);
     b->items.clear();
     std::vector<double> cost;
-    int64_t part_words = 0, sorted = 0;
+    int64_t part_words = 0, sorted = 0, small = 0;
+    b->small_off.assign(b->n_inst, -1);
+    b->n_small = 0;
     b->n_sum = 0;
     b->max_n_sum = 0;
     b->n_scat = 0;
@@ -146,6 +163,10 @@ env_status build_shape(env_batch* b, const int64_t* n) {
             sorted += n[i];
             ++b->n_scat;
             b->max_n_scat = std::max(b->max_n_scat, n[i]);
+        } else if (b->tree && order_small(n[i]) && !sorts_off()) {
+            b->small_off[i] = small;
+            small += n[i];
+            ++b->n_small;
         }
         const int64_t nb = (n[i] + per - 1) / per;
         for (int64_t pb = 0; pb < nb; ++pb) {
@@ -171,8 +192,11 @@ env_status build_shape(env_batch* b, const int64_t* n) {
     if (!dm(&b->d_items, ni * sizeof(BatchItem)) || !dm(&b->d_args, size_t(b->n_inst) * sizeof(EvalArgs)) ||
         !dm(&b->d_args_direct, size_t(b->n_inst) * sizeof(EvalArgs)) || !dm(&b->d_sum, ns * sizeof(SumDesc)) ||
         !dm(&b->d_sum_direct, ns * sizeof(SumDesc)) || !dm(&b->d_scat, nsc * sizeof(ScatterDesc)) ||
-        !dm(&b->d_part, size_t(part_words) * sizeof(double)) || !dm(&b->d_spts, size_t(sorted) * 3 * sizeof(double)) ||
-        !dm(&b->d_sout, size_t(sorted) * sizeof(double)) || !dm(&b->d_order, size_t(sorted) * sizeof(uint32_t))) {
+        !dm(&b->d_part, size_t(part_words) * sizeof(double)) ||
+        !dm(&b->d_spts, b->tree ? 0 : size_t(sorted) * 3 * sizeof(double)) ||
+        !dm(&b->d_sout, b->tree ? 0 : size_t(sorted) * sizeof(double)) ||
+        !dm(&b->d_order, size_t(sorted + small) * sizeof(uint32_t)) ||
+        !dm(&b->d_small, size_t(b->n_small) * sizeof(OrderDesc))) {
         free_shape(b);
         return ENV_E_NOMEM;
     }
@@ -195,17 +219,26 @@ env_status upload_args(env_batch* b, const double* const* points, double* const*
     std::vector<EvalArgs> args(b->n_inst), direct(b->n_inst);
     std::vector<SumDesc> sums, sums_direct;
     std::vector<ScatterDesc> scat;
+    std::vector<OrderDesc> small;
     for (int i = 0; i < b->n_inst; ++i) {
         env_potential* h = b->hs[i];
-        const bool split = b->part_off[i] >= 0, sorted = b->sort_off[i] >= 0;
+        const bool split = b->part_off[i] >= 0, sorted = !b->tree && b->sort_off[i] >= 0;
         double* part = split ? b->d_part + b->part_off[i] : nullptr;
+        uint32_t* order = nullptr;         // with a tree; orders of small instances follow the large ones'
+        const bool by_cell = b->small_off[i] >= 0;
+        if (by_cell) order = b->d_order + b->sorted_points + b->small_off[i];
+        else if (b->tree && b->sort_off[i] >= 0) order = b->d_order + b->sort_off[i];
+        uint32_t* order_direct = by_cell ? order : nullptr;
+        if (by_cell) small.push_back({points[i], order, b->n[i]});
         const double* spts = sorted ? b->d_spts + 3 * b->sort_off[i] : points[i];
         double* sout = sorted ? b->d_sout + b->sort_off[i] : out[i];
         args[i] = make_args(h, spts, b->n[i], split ? part : sout, b->klog[i]);
         direct[i] = make_args(h, points[i], b->n[i], split ? part : out[i], b->klog[i]);
+        args[i].order = order;
+        direct[i].order = order_direct;
         if (split) {
-            sums.push_back({part, sout, b->n[i], 1 << b->klog[i], 0});
-            sums_direct.push_back({part, out[i], b->n[i], 1 << b->klog[i], 0});
+            sums.push_back({part, sout, b->n[i], order, 1 << b->klog[i], 0});
+            sums_direct.push_back({part, out[i], b->n[i], order_direct, 1 << b->klog[i], 0});
         }
         if (sorted) scat.push_back({sout, b->d_order + b->sort_off[i], out[i], b->n[i]});
     }
@@ -216,7 +249,8 @@ env_status upload_args(env_batch* b, const double* const* points, double* const*
         !up(b->d_args_direct, direct.data(), direct.size() * sizeof(EvalArgs)) ||
         !up(b->d_sum, sums.data(), sums.size() * sizeof(SumDesc)) ||
         !up(b->d_sum_direct, sums_direct.data(), sums_direct.size() * sizeof(SumDesc)) ||
-        !up(b->d_scat, scat.data(), scat.size() * sizeof(ScatterDesc)))
+        !up(b->d_scat, scat.data(), scat.size() * sizeof(ScatterDesc)) ||
+        !up(b->d_small, small.data(), small.size() * sizeof(OrderDesc)))
         return ENV_E_DEVICE;
     b->pts.assign(points, points + b->n_inst);
     b->out.assign(out, out + b->n_inst);
@@ -230,7 +264,9 @@ env_status upload_args(env_batch* b, const double* const* points, double* const*
 env_status sort_inputs(env_batch* b, void* stream) {
     for (int i = 0; i < b->n_inst; ++i) {
         if (b->sort_off[i] < 0) continue;
-        if (sort_points(b->pts[i], b->n[i], b->d_spts + 3 * b->sort_off[i], b->d_order + b->sort_off[i], stream) != 0)
+        uint32_t* order = b->d_order + b->sort_off[i];
+        if ((b->tree ? sort_order(b->pts[i], b->n[i], order, stream)
+                     : sort_points(b->pts[i], b->n[i], b->d_spts + 3 * b->sort_off[i], order, stream)) != 0)
             return ENV_E_DEVICE;
     }
     return ENV_OK;
@@ -247,9 +283,10 @@ int launch_all(env_batch* b, void* stream, bool sorted) {
     a.boys = b->hs[0]->d_boys;
     a.rows32 = b->hs[0]->bp.rows32;
     a.pad = 0;
-    int rc = launch_persistent(a, b->grid, b->precision, b->np, stream);
+    int rc = order_points_multi(b->d_small, b->n_small, stream);
+    if (rc == 0) rc = launch_persistent(a, b->grid, b->precision, b->np, b->tree, stream);
     if (rc == 0) rc = launch_sum_multi(sorted ? b->d_sum : b->d_sum_direct, b->n_sum, b->max_n_sum, stream);
-    if (rc == 0 && sorted) rc = scatter_values_multi(b->d_scat, b->n_scat, b->max_n_scat, stream);
+    if (rc == 0 && sorted && !b->tree) rc = scatter_values_multi(b->d_scat, b->n_scat, b->max_n_scat, stream);
     return rc;
 }
 
@@ -274,8 +311,10 @@ env_status env_batch_create(env_potential* const* hs, int32_t n_inst, env_batch*
     b->n_inst = n_inst;
     b->cu_count = hs[0]->cu_count;
     b->hs.assign(hs, hs + n_inst);
+    b->tree = std::all_of(hs, hs + n_inst, [](const env_potential* h) { return h->tree != nullptr; });
+    if (b->tree) b->np = 2;
     DeviceGuard g(b->device);
-    b->grid = persistent_grid(b->precision, b->np, b->cu_count);
+    b->grid = persistent_grid(b->precision, b->np, b->tree, b->cu_count);
     if (hipMalloc(reinterpret_cast<void**>(&b->d_counter), sizeof(unsigned long long)) != hipSuccess) {
         delete b;
         return ENV_E_NOMEM;
@@ -360,7 +399,7 @@ env_status set_shape(env_batch* b, int np, int gran, const double* const* points
                      double* const* out) {
     b->np = np;
     b->gran = gran;
-    b->grid = persistent_grid(b->precision, np, b->cu_count);
+    b->grid = persistent_grid(b->precision, np, b->tree, b->cu_count);
     env_status s = build_shape(b, n);
     if (s == ENV_OK) s = upload_args(b, points, out);
     return s;

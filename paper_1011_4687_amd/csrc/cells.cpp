@@ -248,7 +248,7 @@ env_status env_cells_eval(env_cells* h, const double* points, int64_t n, double*
         return ENV_E_NOMEM;
     a.out = part;
     int rc = envpot::launch_cells(a, S, h->precision, np, stream);
-    if (rc == 0) rc = envpot::launch_sum_splits(part, S, n, out, stream);
+    if (rc == 0) rc = envpot::launch_sum_splits(part, S, n, nullptr, out, stream);
     (void)hipFreeAsync(part, st);
     return rc == 0 ? ENV_OK : ENV_E_DEVICE;
 }

@@ -96,6 +96,23 @@ struct BoysParams {
     int32_t pad;
 };
 
+struct TreeTest;
+struct TreeNode;
+
+// What the evaluation kernels read of a multipole tree (tree_internal.h).
+struct TreeView {
+    const TreeTest* test;    // per node
+    const TreeNode* node;    // per node
+    const float* thr;        // per node a row: squared radius from which order p suffices
+    const double* coef;      // per node: centre, scale, (cos, sin) coefficients by (m, n)
+    const double* beta;      // recursion coefficients, same (m, n) index
+    const int32_t* first;    // per tree: its root; the nodes of a tree are contiguous
+    const uint32_t* rec;     // own pair records
+    const double* nuc;       // own nuclei, 4 doubles each
+    int32_t n_trees;         // 0: no tree (every pair on its own, segment by segment)
+    int32_t S;               // split factor of the launch
+};
+
 struct EvalArgs {
     const double* pts;      // n x 3
     int64_t n;
@@ -107,6 +124,8 @@ struct EvalArgs {
     double* out;            // S == 1: V; S > 1: partial sums [S][n]
     const double* boxes;    // per unsplit segment (Segment::box), or nullptr: test every pair
     BoysParams bp;
+    TreeView tree;
+    const uint32_t* order;  // with a tree: evaluate pts[order[i]] as point i (S == 1: and write out[order[i]]), or nullptr
 };
 
 // One work item of the persistent batched kernel.
@@ -140,7 +159,7 @@ struct DevSizedArgs {
     int64_t seg_off[kMaxSplitLog2 + 1];
     int64_t split_off[kMaxSplitLog2 + 1];
     int64_t part_cap;              // float64 elements of a.out
-    int64_t want_waves;            // waves the split factor aims for
+    int64_t want;                  // waves the split factor aims for (with a tree: compute units)
     unsigned long long* counter;   // zeroed by a kernel before the launch
 };
 
@@ -148,6 +167,7 @@ struct SumDesc {                  // fixed-order sum of S partials of one instan
     const double* part;
     double* out;
     int64_t n;
+    const uint32_t* order;       // out[order[i]], or nullptr: out[i]
     int32_t S;
     int32_t pad;
 };
@@ -207,17 +227,17 @@ void build_boys_tables(std::vector<float>& t32, std::vector<double>& t64, BoysPa
 
 // Kernel launchers (kernels.hip).
 int launch_potential(const EvalArgs& a, int S, int precision, int np, void* stream);
-int launch_sum_splits(const double* partial, int S, int64_t n, double* out, void* stream);
+// out[i] (with order: out[order[i]]) = sum over the S partials of point i, in fixed order.
+int launch_sum_splits(const double* partial, int S, int64_t n, const uint32_t* order, double* out, void* stream);
 // Boxes (kSegBoxWords doubles each) of the unsplit segments segs[0, n_segs),
 // one workgroup per segment; empty segments get r2far max = +inf.
 int launch_segment_boxes(const Segment* segs, int n_segs, const uint32_t* rec, int fp64, double* boxes,
                          void* stream);
-int launch_persistent(const BatchArgs& b, int grid, int precision, int np, void* stream);
+int launch_persistent(const BatchArgs& b, int grid, int precision, int np, bool tree, void* stream);
 int launch_sum_multi(const SumDesc* d, int n_desc, int64_t max_n, void* stream);
-int persistent_grid(int precision, int np, int cu_count);
-int launch_potential_devsized(const DevSizedArgs& d, int grid, int precision, int np, void* stream);
-int launch_sum_devsized(const DevSizedArgs& d, int np, int64_t n_max, double* out, void* stream);
-int devsized_klog(int64_t m, int np, int64_t want_waves, int64_t part_cap);
-int devsized_grid(int precision, int cu_count);
+int persistent_grid(int precision, int np, bool tree, int cu_count);
+int launch_potential_devsized(const DevSizedArgs& d, int grid, int precision, void* stream);
+int launch_sum_devsized(const DevSizedArgs& d, int precision, int64_t n_max, double* out, void* stream);
+int devsized_grid(int precision, bool tree, int cu_count);
 
 }  // namespace envpot

@@ -130,7 +130,7 @@ env_status field_core(env_potential* h, const double* points, int64_t n, double*
         return ENV_E_NOMEM;
     a.out = part;
     int rc = launch_field(a, S, h->precision, np, stream);
-    if (rc == 0) rc = launch_sum_splits(part, S, 4 * n, out, stream);
+    if (rc == 0) rc = launch_sum_splits(part, S, 4 * n, nullptr, out, stream);
     (void)hipFreeAsync(part, st);
     return rc == 0 ? ENV_OK : ENV_E_DEVICE;
 }

@@ -9,6 +9,8 @@
 
 namespace envpot {
 
+struct Tree;
+
 // What a handle created with ENV_FORCE_CPU needs besides its pair list: the
 // FP64 Boys table and far-field thresholds, and every pair's far-field
 // coefficients (same offsets as the pair list's D).
@@ -42,6 +44,7 @@ struct env_potential {
     void* d_boys_field = nullptr;       // Boys table of the field (one order more)
     envpot::FieldParams fp{};
     envpot::UpdateState* upd = nullptr;  // density update tables (device)
+    envpot::Tree* tree = nullptr;        // multipole tree; without one every pair is evaluated
     int64_t rec_words = 0;              // words of d_rec
     int64_t n_segs_all = 0;             // segments of d_segs (every split factor)
     int64_t seg_off[envpot::kMaxSplitLog2 + 1] = {};    // per split factor 2^k: first segment

@@ -32,9 +32,13 @@
 // once per segment, which costs less than the latency a third wave hides.
 #include <hip/hip_runtime.h>
 
+#include <type_traits>
+
 #include "device_math.h"
 #include "envpot_internal.h"
 #include "hermite_gen.h"
+#include "sort_internal.h"
+#include "tree_internal.h"
 
 namespace envpot {
 namespace {
@@ -673,6 +677,451 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) voi
     block_work<NP, F64>(a, blockIdx.x, blockIdx.y, tab32);
 }
 
+// ------------------------------------------------------------ multipole tree
+
+// Lists of one workgroup: every wave appends to its own part.
+constexpr int kNearWave = 128;  // nodes whose own items are to be evaluated
+constexpr int kFarWave = 128;   // accepted nodes
+constexpr int kChunkCap = 256;  // runs of up to 64 nodes of open trees, one per wave step
+
+// LDS of the tree evaluation besides the Boys table.  acc is used after the
+// lists.
+template <int NP>
+struct TreeShared {
+    union {
+        struct {
+            int32_t near_node[4][kNearWave];
+            int32_t near_cost[4][kNearWave];
+            int32_t far_node[4][kFarWave];
+            int32_t list_node[4 * kNearWave];   // the waves' parts one after the other
+            int64_t list_cost[4 * kNearWave];   // ... and the exclusive prefix of their cost
+            int32_t list_far[4 * kFarWave];
+            int32_t list_order[4 * kFarWave];
+            int32_t chunk_begin[kChunkCap];
+            int32_t chunk_end[kChunkCap];
+        };
+        double acc[4][64 * NP];
+    };
+    uint64_t scan[4];
+    int32_t count[4];                            // near | far << 16, per wave
+    int32_t more[4];
+};
+
+// Exclusive prefix sum over the workgroup in thread order; total in *sum.
+__device__ __forceinline__ uint64_t block_scan(uint64_t v, uint64_t* tmp, uint64_t* sum) {
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    uint64_t x = v;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+        const uint64_t y = __shfl_up(x, o);
+        if (lane >= o) x += y;
+    }
+    __syncthreads();
+    if (lane == 63) tmp[wave] = x;
+    __syncthreads();
+    uint64_t base = 0, all = 0;
+#pragma unroll
+    for (int w = 0; w < 4; ++w) {
+        if (w < wave) base += tmp[w];
+        all += tmp[w];
+    }
+    *sum = all;
+    return base + x - v;
+}
+
+// Potential of one accepted node at M points, to order p: the harmonic
+// polynomial at X s / |X|^2 by a Clenshaw recursion in the degree for every
+// m and Horner's rule in (x + iy) over m; with
+//   Q_{n+1} = z Q_n - beta_n rho^2 Q_{n-1}   (monic in z),
+// two fused multiply-adds per coefficient and one multiply per (n, m).
+template <int M>
+__device__ __forceinline__ void tree_far(const GLB double* __restrict__ co, const GLB double* __restrict__ beta, int P,
+                                         int p, const double* cx, const double* cy, const double* cz, double* ele) {
+    const double px = co[0], py = co[1], pz = co[2], s = co[3];
+    double x[M], y[M], z[M], u[M], ri[M], ar[M], ai[M];
+#pragma unroll
+    for (int k = 0; k < M; ++k) {
+        const double X = cx[k] - px, Y = cy[k] - py, Z = cz[k] - pz;
+        ri[k] = rsqrt_far(__builtin_fma(X, X, __builtin_fma(Y, Y, Z * Z)));
+        const double sr = s * ri[k], f = sr * ri[k];
+        x[k] = X * f;
+        y[k] = Y * f;
+        z[k] = Z * f;
+        u[k] = sr * sr;
+        ar[k] = ai[k] = 0.0;
+    }
+    for (int m = p; m > 0; --m) {
+        const int at = tree_index(P, m, m);
+        const GLB double* c = co + kTreeHead + 2 * (at + p - m);
+        const GLB double* b = beta + at;
+        double r1[M], i1[M], r2[M], i2[M];
+#pragma unroll
+        for (int k = 0; k < M; ++k) {
+            r1[k] = c[0];
+            i1[k] = c[1];
+            r2[k] = i2[k] = 0.0;
+        }
+        for (int n = p - m - 1; n >= 0; --n) {
+            c -= 2;
+            const double cr = c[0], ci = c[1], bt = b[n];
+#pragma unroll
+            for (int k = 0; k < M; ++k) {
+                const double v = -bt * u[k];
+                const double tr = __builtin_fma(z[k], r1[k], __builtin_fma(v, r2[k], cr));
+                const double ti = __builtin_fma(z[k], i1[k], __builtin_fma(v, i2[k], ci));
+                r2[k] = r1[k];
+                i2[k] = i1[k];
+                r1[k] = tr;
+                i1[k] = ti;
+            }
+        }
+#pragma unroll
+        for (int k = 0; k < M; ++k) {
+            const double tr = __builtin_fma(ar[k], x[k], __builtin_fma(-ai[k], y[k], r1[k]));
+            ai[k] = __builtin_fma(ar[k], y[k], __builtin_fma(ai[k], x[k], -i1[k]));
+            ar[k] = tr;
+        }
+    }
+    {
+        const GLB double* c = co + kTreeHead + 2 * p;
+        double r1[M], r2[M];
+#pragma unroll
+        for (int k = 0; k < M; ++k) {
+            r1[k] = c[0];
+            r2[k] = 0.0;
+        }
+        for (int n = p - 1; n >= 0; --n) {
+            c -= 2;
+            const double cr = c[0], bt = beta[n];
+#pragma unroll
+            for (int k = 0; k < M; ++k) {
+                const double tr = __builtin_fma(z[k], r1[k], __builtin_fma(-bt * u[k], r2[k], cr));
+                r2[k] = r1[k];
+                r1[k] = tr;
+            }
+        }
+#pragma unroll
+        for (int k = 0; k < M; ++k)
+            ele[k] = __builtin_fma(ri[k], __builtin_fma(ar[k], x[k], __builtin_fma(-ai[k], y[k], r1[k])), ele[k]);
+    }
+}
+
+// Items [a, b) of a run of cnt items of weight W that starts at cost c,
+// within the cost range [lo, hi): an item belongs to the range its first
+// cost unit lies in.
+template <int W>
+__device__ __forceinline__ void run_share(int64_t c, int cnt, int64_t lo, int64_t hi, int& a, int& b) {
+    const int64_t top = int64_t(cnt) * W;
+    const int64_t l = lo - c, h = hi - c;
+    const uint32_t lc = uint32_t(l < 0 ? 0 : (l > top ? top : l)), hc = uint32_t(h < 0 ? 0 : (h > top ? top : h));
+    a = int((lc + W - 1) / W);
+    b = int((hc + W - 1) / W);
+}
+
+template <int L, int NP, bool F64>
+__device__ __forceinline__ void tree_run(const GLB uint32_t* __restrict__ rec, int64_t& word, int64_t& c, int cnt,
+                                         int64_t lo, int64_t hi, const double* cx, const double* cy, const double* cz,
+                                         const float* tab32, const GLB double* __restrict__ boys64, double* ele) {
+    int a, b;
+    run_share<kTreeW[L]>(c, cnt, lo, hi, a, b);
+    if (b > a) {
+        if constexpr (F64) pairs_f64<L, NP, false>(rec + word + int64_t(a) * rec64_words(L), b - a, cx, cy, cz, boys64, ele);
+        else pairs_f32<L, NP, false>(rec + word + int64_t(a) * rec32_words(L), b - a, cx, cy, cz, 0.0, 0.0, 0.0, tab32, ele);
+    }
+    c += int64_t(cnt) * kTreeW[L];
+    word += int64_t(cnt) * (F64 ? rec64_words(L) : rec32_words(L));
+}
+
+__device__ __forceinline__ double wave_min(double v) {
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) v = fmin(v, __shfl_xor(v, o));
+    return wave_uniform(v);
+}
+
+// Squared distance of the block's box from a node's centre.
+__device__ __forceinline__ double box_r2(const double* c, const double* lo, const double* hi) {
+    double r2 = 0.0;
+#pragma unroll
+    for (int d = 0; d < 3; ++d) {
+        const double g = fmax(0.0, fmax(lo[d] - c[d], c[d] - hi[d]));
+        r2 = __builtin_fma(g, g, r2);
+    }
+    return r2;
+}
+
+// One workgroup's share (split s of S) of a block of 64 NP points: every
+// wave holds all of the block's points.  The workgroup tests the nodes
+// against the block's bounding box, one node per thread, and collects the
+// accepted ones with the order they need and the nodes whose own items are
+// to be evaluated; the own items' cost is then cut into S x 4 equal parts
+// and part 4 s + w is wave w's, the accepted nodes go round the parts.  All
+// S workgroups of a block build the same lists, so the cut is exact however
+// the near work is spread over the tree, and the sums have a fixed order.
+template <int NP, bool F64>
+__device__ __forceinline__ void tree_work(const PTS double* __restrict__ pts, const PTS uint32_t* __restrict__ order,
+                                          int64_t n, const TreeView& tv,
+                                          const GLB double* __restrict__ boys64, double* __restrict__ out,
+                                          int64_t pblock, int s, const float* tab32, TreeShared<NP>& sh) {
+    constexpr int P = tree_order(F64);
+    constexpr int TR = tree_thr_row(P);
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int64_t base = pblock * (64 * NP);
+    double cx[NP], cy[NP], cz[NP], ve[NP];
+    double lo[3] = {HUGE_VAL, HUGE_VAL, HUGE_VAL}, hi[3] = {-HUGE_VAL, -HUGE_VAL, -HUGE_VAL};
+#pragma unroll
+    for (int k = 0; k < NP; ++k) {
+        const int64_t i = base + lane + 64 * k;
+        int64_t ic = i < n ? i : n - 1;  // ragged tail: recompute the last point
+        if (order) ic = order[ic];
+        cx[k] = pts[3 * ic];
+        cy[k] = pts[3 * ic + 1];
+        cz[k] = pts[3 * ic + 2];
+        ve[k] = 0.0;
+        lo[0] = fmin(lo[0], cx[k]);
+        lo[1] = fmin(lo[1], cy[k]);
+        lo[2] = fmin(lo[2], cz[k]);
+        hi[0] = fmax(hi[0], cx[k]);
+        hi[1] = fmax(hi[1], cy[k]);
+        hi[2] = fmax(hi[2], cz[k]);
+    }
+#pragma unroll
+    for (int d = 0; d < 3; ++d) {
+        lo[d] = wave_min(lo[d]);
+        hi[d] = -wave_min(-hi[d]);
+    }
+    const int parts = 4 * tv.S, part = 4 * s + wave;
+    const GLB TreeNode* nodes = glb(tv.node);
+    const GLB uint32_t* rec = glb(tv.rec);
+    const GLB double* nuc = glb(tv.nuc);
+    const GLB double* coef = glb(tv.coef);
+    const GLB double* beta = glb(tv.beta);
+    int nn = 0, nf = 0;  // entries of this wave's part of the lists
+
+    // Evaluate the collected lists: they are put together in wave order, cut
+    // by cost, and every wave evaluates its share.
+    auto evaluate = [&]() {
+        int nw[4], fw[4];
+#pragma unroll
+        for (int w = 0; w < 4; ++w) {
+            const int c = __builtin_amdgcn_readfirstlane(sh.count[w]);
+            nw[w] = c & 0xffff;
+            fw[w] = c >> 16;
+        }
+        const int n_near = nw[0] + nw[1] + nw[2] + nw[3], n_far = fw[0] + fw[1] + fw[2] + fw[3];
+        auto part_of = [](const int* c, int e, int& w) {  // entry e of the concatenation: its part and place
+            w = 0;
+            while (w < 3 && e >= c[w]) e -= c[w++];
+            return e;
+        };
+        uint64_t own = 0, cost;
+        constexpr int kEach = 4 * kNearWave / kBlock;
+        int32_t node[kEach], pc[kEach];
+#pragma unroll
+        for (int q = 0; q < kEach; ++q) {
+            const int e = kEach * tid + q;
+            node[q] = pc[q] = 0;
+            if (e < n_near) {
+                int w;
+                const int f = part_of(nw, e, w);
+                node[q] = sh.near_node[w][f];
+                pc[q] = sh.near_cost[w][f];
+            }
+            own += uint64_t(pc[q]);
+        }
+        uint64_t at = block_scan(own, sh.scan, &cost);
+#pragma unroll
+        for (int q = 0; q < kEach; ++q) {
+            const int e = kEach * tid + q;
+            if (e < n_near) {
+                sh.list_node[e] = node[q];
+                sh.list_cost[e] = int64_t(at);
+            }
+            at += uint64_t(pc[q]);
+        }
+        // the order every accepted node needs
+        for (int e = tid; e < n_far; e += kBlock) {
+            int w;
+            const int f = part_of(fw, e, w);
+            const int nd = sh.far_node[w][f];
+            const float4* th = reinterpret_cast<const float4*>(tv.thr + int64_t(nd) * TR);
+            const double cc[3] = {tv.test[nd].c[0], tv.test[nd].c[1], tv.test[nd].c[2]};
+            const float rf = float(box_r2(cc, lo, hi) * (1.0 - 1e-6));
+            int o = 0;
+#pragma unroll
+            for (int q = 0; q < TR / 4; ++q) {
+                const float4 v = th[q];
+                o += (v.x > rf) + (v.y > rf) + (v.z > rf) + (v.w > rf);
+            }
+            sh.list_far[e] = nd;
+            sh.list_order[e] = o < P ? o : P;
+        }
+        __syncthreads();
+        const int64_t total = int64_t((uint64_t(__builtin_amdgcn_readfirstlane(uint32_t(cost >> 32))) << 32) |
+                                      __builtin_amdgcn_readfirstlane(uint32_t(cost)));
+        const int64_t clo = total / parts * part + total % parts * part / parts;
+        const int64_t chi = total / parts * (part + 1) + total % parts * (part + 1) / parts;
+        if (chi > clo) {
+            int a = 0, b = n_near;  // the last node whose cost begins at clo or before
+            while (b - a > 1) {
+                const int mid = (a + b) >> 1;
+                if (sh.list_cost[mid] <= clo) a = mid;
+                else b = mid;
+            }
+            for (int e = __builtin_amdgcn_readfirstlane(a); e < n_near; ++e) {
+                const uint64_t cv = uint64_t(sh.list_cost[e]);
+                int64_t c = int64_t((uint64_t(__builtin_amdgcn_readfirstlane(uint32_t(cv >> 32))) << 32) |
+                                    __builtin_amdgcn_readfirstlane(uint32_t(cv)));
+                if (c >= chi) break;
+                const GLB TreeNode* nd = nodes + __builtin_amdgcn_readfirstlane(sh.list_node[e]);
+                int64_t word = nd->rec_off;
+                tree_run<0, NP, F64>(rec, word, c, nd->cnt[0], clo, chi, cx, cy, cz, tab32, boys64, ve);
+                tree_run<1, NP, F64>(rec, word, c, nd->cnt[1], clo, chi, cx, cy, cz, tab32, boys64, ve);
+                tree_run<2, NP, F64>(rec, word, c, nd->cnt[2], clo, chi, cx, cy, cz, tab32, boys64, ve);
+                tree_run<3, NP, F64>(rec, word, c, nd->cnt[3], clo, chi, cx, cy, cz, tab32, boys64, ve);
+                tree_run<4, NP, F64>(rec, word, c, nd->cnt[4], clo, chi, cx, cy, cz, tab32, boys64, ve);
+                const int nb = nd->nuc_begin;
+                int qa, qb;
+                run_share<kTreeW[kLMax + 1]>(c, nd->nuc_end - nb, clo, chi, qa, qb);
+                for (int q = nb + qa; q < nb + qb; ++q) {
+                    const double qx = nuc[4 * q], qy = nuc[4 * q + 1], qz = nuc[4 * q + 2], qZ = nuc[4 * q + 3];
+#pragma unroll
+                    for (int k = 0; k < NP; ++k) {
+                        const double dx = cx[k] - qx, dy = cy[k] - qy, dz = cz[k] - qz;
+                        ve[k] -= qZ * rsqrt(__builtin_fma(dx, dx, __builtin_fma(dy, dy, dz * dz)));
+                    }
+                }
+            }
+        }
+        constexpr int M = NP < 2 ? NP : 2;
+        for (int e = part; e < n_far; e += parts) {
+            const int nd = __builtin_amdgcn_readfirstlane(sh.list_far[e]);
+            const int p = __builtin_amdgcn_readfirstlane(sh.list_order[e]);
+            const GLB double* co = coef + int64_t(nd) * tree_words(P);
+#pragma unroll
+            for (int k = 0; k < NP; k += M) tree_far<M>(co, beta, P, p, cx + k, cy + k, cz + k, ve + k);
+        }
+    };
+    // Class of a node: 2 accepted, 1 its own items are evaluated, 0 neither
+    // (its parent is accepted, or it has none of its own).
+    auto classify = [&](const TreeTest& t) -> int {
+        const double rp = box_r2(t.pc, lo, hi), r2 = box_r2(t.c, lo, hi);
+        if (rp >= double(t.pr2) && rp < 1e300) return 0;
+        if (r2 >= double(t.r2) && r2 < 1e300) return 2;
+        return t.cost > 0 ? 1 : 0;
+    };
+    auto append = [&](int cls, int nd, int cost) {
+        const uint64_t mf = __builtin_amdgcn_ballot_w64(cls == 2), mn = __builtin_amdgcn_ballot_w64(cls == 1);
+        auto below = [](uint64_t m) {
+            return __builtin_amdgcn_mbcnt_hi(uint32_t(m >> 32), __builtin_amdgcn_mbcnt_lo(uint32_t(m), 0));
+        };
+        if (cls == 2) sh.far_node[wave][nf + below(mf)] = nd;
+        if (cls == 1) {
+            const int f = nn + below(mn);
+            sh.near_node[wave][f] = nd;
+            sh.near_cost[wave][f] = cost;
+        }
+        nf += __popcll(mf);
+        nn += __popcll(mn);
+    };
+    auto room = [&]() { return nn <= kNearWave - 64 && nf <= kFarWave - 64; };
+    // Meeting point of the waves: the lists are evaluated when some wave has
+    // no room for another step or `last` is set; false when some wave has
+    // steps left (`left`).
+    auto meet = [&](bool left, bool last) -> bool {
+        if (lane == 0) {
+            sh.count[wave] = nn | nf << 16;
+            sh.more[wave] = (left ? 1 : 0) | (room() ? 0 : 2);
+        }
+        __syncthreads();
+        const int m = __builtin_amdgcn_readfirstlane(sh.more[0] | sh.more[1] | sh.more[2] | sh.more[3]);
+        if ((m & 2) || (last && !(m & 1))) {
+            evaluate();
+            nn = nf = 0;
+        }
+        __syncthreads();
+        return !(m & 1);
+    };
+
+    for (int t0 = 0; t0 < tv.n_trees; t0 += kBlock) {
+        // roots: accepted, or the tree is open and its nodes are tested in
+        // runs of 64
+        int cls = 0, root = 0, count = 0, cost = 0;
+        if (t0 + tid < tv.n_trees) {
+            root = tv.first[t0 + tid];
+            const TreeTest t = tv.test[root];
+            cls = classify(t);
+            cost = t.cost;
+            if (cls != 2) count = tv.first[t0 + tid + 1] - root - 1;
+        }
+        append(cls, root, cost);
+        uint64_t sum;
+        const int runs = (count + 63) >> 6;
+        const int at = int(block_scan(uint64_t(runs), sh.scan, &sum));
+        const int total = __builtin_amdgcn_readfirstlane(int(sum));
+        for (int w0 = 0; w0 == 0 || w0 < total; w0 += kChunkCap) {
+            for (int r = max(0, w0 - at); r < runs && at + r < w0 + kChunkCap; ++r) {
+                sh.chunk_begin[at + r - w0] = root + 1 + 64 * r;
+                sh.chunk_end[at + r - w0] = root + 1 + min(count, 64 * r + 64);
+            }
+            __syncthreads();
+            const int here = min(kChunkCap, total - w0);
+            const bool final = t0 + kBlock >= tv.n_trees && w0 + kChunkCap >= total;
+            int c = wave;
+            do {
+                if (c < here && room()) {
+                    int nd = sh.chunk_begin[c] + lane, end = sh.chunk_end[c];
+                    TreeTest t;
+                    if (nd < end) t = tv.test[nd];
+                    for (;;) {
+                        // the next run's tests are loaded while this one's are made
+                        const int cn = c + 4;
+                        int ndn = 0, endn = 0;
+                        TreeTest tn;
+                        if (cn < here) {
+                            ndn = sh.chunk_begin[cn] + lane;
+                            endn = sh.chunk_end[cn];
+                            if (ndn < endn) tn = tv.test[ndn];
+                        }
+                        append(nd < end ? classify(t) : 0, nd, t.cost);
+                        c = cn;
+                        if (c >= here || !room()) break;
+                        nd = ndn;
+                        end = endn;
+                        t = tn;
+                    }
+                }
+            } while (!meet(c < here, final));
+        }
+    }
+    // the waves' sums in wave order
+#pragma unroll
+    for (int k = 0; k < NP; ++k) sh.acc[wave][lane + 64 * k] = ve[k];
+    __syncthreads();
+    for (int j = tid; j < 64 * NP; j += kBlock) {
+        const double v = (sh.acc[0][j] + sh.acc[1][j]) + (sh.acc[2][j] + sh.acc[3][j]);
+        if (base + j < n) {
+            const int64_t o = base + j;
+            out[(int64_t)s * n + (order && tv.S == 1 ? int64_t(order[o]) : o)] = -v;
+        }
+    }
+    __syncthreads();  // the next work item writes the lists
+}
+
+template <int NP, bool F64>
+__device__ __forceinline__ void tree_block(const EvalArgs& a, int64_t pblock, int s, const float* tab32,
+                                           TreeShared<NP>& sh) {
+    tree_work<NP, F64>(gpts(a.pts), gpts(a.order), a.n, a.tree, glb(static_cast<const double*>(a.boys)), a.out, pblock, s, tab32, sh);
+}
+
+template <int NP, bool F64>
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) void k_tree_potential(EvalArgs a) {
+    __shared__ float tab32[F64 ? 1 : kBoysMaxRowsF32 * kBoysRowF32];
+    __shared__ TreeShared<NP> sh;
+    load_boys_lds<F64>(a.boys, a.bp.rows32, tab32);
+    tree_block<NP, F64>(a, blockIdx.x, blockIdx.y, tab32, sh);
+}
+
 // A copy of *p read word by word through the constant address space.
 template <class T>
 __device__ __forceinline__ T load_const(const T* p) {
@@ -690,9 +1139,10 @@ __device__ __forceinline__ T load_const(const T* p) {
 // Items are sorted by decreasing estimated cost, so the long ones start
 // first.  Every workgroup reaches the exit test once the counter passes
 // n_items, so the grid always drains.
-template <int NP, bool F64>
+template <int NP, bool F64, bool TREE>
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) void k_potential_persistent(BatchArgs b) {
     __shared__ float tab32[F64 ? 1 : kBoysMaxRowsF32 * kBoysRowF32];
+    __shared__ typename std::conditional<TREE, TreeShared<NP>, int>::type sh;
     __shared__ unsigned long long item_sh;
     load_boys_lds<F64>(b.boys, b.rows32, tab32);
     for (;;) {
@@ -708,59 +1158,104 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) voi
         // scalar loads the compiler may repeat instead of holding the values
         const BatchItem w = load_const(b.items + it);
         const EvalArgs a = load_const(b.args + w.inst);
-        block_work<NP, F64>(a, w.pblock, w.split, tab32);
+        if constexpr (TREE) tree_block<NP, F64>(a, w.pblock, w.split, tab32, sh);
+        else block_work<NP, F64>(a, w.pblock, w.split, tab32);
     }
 }
 
-// Split factor 2^k of a device-sized evaluation of m points (host and
-// device use this one rule, so both kernels agree on k).
-__host__ __device__ __forceinline__ int devsized_k(int64_t m, int np, int64_t want_waves, int64_t part_cap) {
-    const int64_t waves = (m + 64 * np - 1) / (64 * np);
+// Points per lane and split factor 2^k of a device-sized evaluation of m
+// points (host and device use this one rule, so both kernels agree).
+__host__ __device__ __forceinline__ int devsized_shape(int64_t m, bool fp64, bool tree, int64_t want, int64_t part_cap,
+                                                       int* np) {
+    *np = tree ? tree_np(m, fp64) : (fp64 ? 2 : 4);
+    const int64_t units = (m + 64 * *np - 1) / (64 * *np);
+    if (tree) want = tree_want(units, want);
     int k = 0;
-    while (k < kMaxSplitLog2 && (waves << k) < want_waves && (m << (k + 1)) <= part_cap) ++k;
+    while (k < kMaxSplitLog2 && (units << k) < want && (m << (k + 1)) <= part_cap) ++k;
     return k;
 }
 
-// Persistent kernel of a device-sized evaluation: the items (point block,
-// split) of the shape chosen from m are numbered it = pblock * 2^k + s and
-// taken from the counter until it reaches their count; every workgroup
-// reaches that exit test, so the grid drains (also for m = 0).
-template <int NP, bool F64>
-__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) void k_potential_devsized(DevSizedArgs d) {
-    __shared__ float tab32[F64 ? 1 : kBoysMaxRowsF32 * kBoysRowF32];
-    __shared__ unsigned long long item_sh;
-    load_boys_lds<F64>(d.a.boys, d.a.bp.rows32, tab32);
-    const int64_t m = *d.m;
-    const int k = devsized_k(m, NP, d.want_waves, d.part_cap);
-    const int64_t n_items = ((m + (int64_t)kBlock * NP - 1) / ((int64_t)kBlock * NP)) << k;
-    EvalArgs a = d.a;
-    a.n = m;
-    a.segs = d.segs_all + d.seg_off[k];
-    a.split = d.split_all + d.split_off[k];
+// Drain the items (point block of `per` points, split) of m points:
+// item it = block * 2^k + s.  Every workgroup reaches the exit test once the
+// counter passes their count, so the grid drains (also for m = 0).
+template <class F>
+__device__ __forceinline__ void drain(int64_t m, int64_t per, int k, unsigned long long* counter,
+                                      unsigned long long* item_sh, F work) {
+    const int64_t n_items = ((m + per - 1) / per) << k;
     for (;;) {
-        if (threadIdx.x == 0) item_sh = atomicAdd(d.counter, 1ull);
+        if (threadIdx.x == 0) *item_sh = atomicAdd(counter, 1ull);
         __syncthreads();
-        const unsigned long long it_v = item_sh;
+        const unsigned long long it_v = *item_sh;
         __syncthreads();
         const int64_t it = (int64_t)(((uint64_t)__builtin_amdgcn_readfirstlane((uint32_t)(it_v >> 32)) << 32) |
                                      (uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)it_v));
         if (it >= n_items) break;
-        block_work<NP, F64>(a, it >> k, (int)(it & ((1 << k) - 1)), tab32);
+        work(it >> k, (int)(it & ((1 << k) - 1)));
     }
 }
+
+// Persistent kernel of a device-sized evaluation: the shape is chosen from m.
+template <bool F64, bool TREE>
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) void k_potential_devsized(DevSizedArgs d) {
+    constexpr int NP = TREE || F64 ? 2 : 4;
+    __shared__ float tab32[F64 ? 1 : kBoysMaxRowsF32 * kBoysRowF32];
+    __shared__ typename std::conditional<TREE, TreeShared<NP>, int>::type sh;
+    __shared__ unsigned long long item_sh;
+    load_boys_lds<F64>(d.a.boys, d.a.bp.rows32, tab32);
+    const int64_t m = *d.m;
+    int np;
+    const int k = devsized_shape(m, F64, TREE, d.want, d.part_cap, &np);
+    EvalArgs a = d.a;
+    a.n = m;
+    if constexpr (TREE) {
+        a.tree.S = 1 << k;
+        if (!order_small(m)) a.order = nullptr;
+        if (np == NP) {
+            drain(m, 64 * NP, k, d.counter, &item_sh,
+                  [&](int64_t b, int s) { tree_block<NP, F64>(a, b, s, tab32, sh); });
+        } else {
+            auto& sh1 = reinterpret_cast<TreeShared<1>&>(sh);
+            drain(m, 64, k, d.counter, &item_sh, [&](int64_t b, int s) { tree_block<1, F64>(a, b, s, tab32, sh1); });
+        }
+    } else {
+        a.segs = d.segs_all + d.seg_off[k];
+        a.split = d.split_all + d.split_off[k];
+        drain(m, kBlock * NP, k, d.counter, &item_sh,
+              [&](int64_t b, int s) { block_work<NP, F64>(a, b, s, tab32); });
+    }
+}
+
+__device__ __forceinline__ double sum_partials(const double* __restrict__ part, int S, int64_t n);
 
 // Fixed-order sum of the 2^k partials of a device-sized evaluation into
 // out[0, m); the grid covers the largest possible m.
 __global__ __launch_bounds__(kBlock) void k_sum_devsized(const double* __restrict__ part, const int64_t* m_ptr,
-                                                         int np, int64_t want_waves, int64_t part_cap,
+                                                         int fp64, int tree, int64_t want, int64_t part_cap,
+                                                         const uint32_t* __restrict__ order,
                                                          double* __restrict__ out) {
     const int64_t m = *m_ptr;
     const int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
     if (i >= m) return;
-    const int S = 1 << devsized_k(m, np, want_waves, part_cap);
-    double s = 0.0;
-    for (int k = 0; k < S; ++k) s += part[(int64_t)k * m + i];
-    out[i] = s;
+    int np;
+    const int S = 1 << devsized_shape(m, fp64 != 0, tree != 0, want, part_cap, &np);
+    const bool ordered = order && order_small(m);
+    // one split: the partials are the values, in the points' own order
+    const int64_t o = ordered && S > 1 ? int64_t(order[i]) : i;
+    out[o] = sum_partials(part + i, S, m);
+}
+
+// Fixed-order sum of the S partials (stride n apart) of one point: eight
+// interleaved sums, then pairwise.  Eight loads are in flight at a time.
+__device__ __forceinline__ double sum_partials(const double* __restrict__ part, int S, int64_t n) {
+    double s[8] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
+    int k = 0;
+    for (; k + 8 <= S; k += 8)
+#pragma unroll
+        for (int j = 0; j < 8; ++j) s[j] += part[(int64_t)(k + j) * n];
+#pragma unroll
+    for (int j = 0; j < 8; ++j)
+        if (k + j < S) s[j] += part[(int64_t)(k + j) * n];
+    return ((s[0] + s[1]) + (s[2] + s[3])) + ((s[4] + s[5]) + (s[6] + s[7]));
 }
 
 __global__ void k_reset_counter(unsigned long long* c) {
@@ -773,9 +1268,7 @@ __global__ __launch_bounds__(kBlock) void k_sum_splits_multi(const SumDesc* __re
     const SumDesc q = d[blockIdx.y];
     const int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
     if (i >= q.n) return;
-    double s = 0.0;
-    for (int k = 0; k < q.S; ++k) s += q.part[(int64_t)k * q.n + i];
-    q.out[i] = s;
+    q.out[q.order ? int64_t(q.order[i]) : i] = sum_partials(q.part + i, q.S, q.n);
 }
 
 // Box of an unsplit segment (one workgroup per segment): the smallest and
@@ -822,25 +1315,54 @@ __global__ __launch_bounds__(kBlock) void k_segment_boxes(const Segment* __restr
     }
 }
 
-__global__ __launch_bounds__(kBlock) void k_sum_splits(const double* __restrict__ part, int S,
-                                                       int64_t n, double* __restrict__ out) {
+// Eight threads per point, each one of the eight interleaved sums (small
+// calls: a thread per point would walk up to 256 partials with few others
+// beside it; 32 points, 256 splits: 57 us before).  The same order as
+// sum_partials.
+__global__ __launch_bounds__(kBlock) void k_sum_splits8(const double* __restrict__ part, int S, int64_t n,
+                                                        const uint32_t* __restrict__ order,
+                                                        double* __restrict__ out) {
+    const int64_t i = (int64_t)blockIdx.x * (kBlock / 8) + (threadIdx.x >> 3);
+    const int j = threadIdx.x & 7;
+    double s = 0.0;
+    if (i < n) {
+#pragma unroll 8
+        for (int k = j; k < S; k += 8) s += part[(int64_t)k * n + i];
+    }
+    s += __shfl_xor(s, 1);
+    s += __shfl_xor(s, 2);
+    s += __shfl_xor(s, 4);
+    if (i < n && j == 0) out[order ? int64_t(order[i]) : i] = s;
+}
+
+__global__ __launch_bounds__(kBlock) void k_sum_splits(const double* __restrict__ part, int S, int64_t n,
+                                                       const uint32_t* __restrict__ order,
+                                                       double* __restrict__ out) {
     const int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
     if (i >= n) return;
-    double s = 0.0;
-    for (int k = 0; k < S; ++k) s += part[(int64_t)k * n + i];
-    out[i] = s;
+    out[order ? int64_t(order[i]) : i] = sum_partials(part + i, S, n);
 }
 
 }  // namespace
 
 int launch_potential(const EvalArgs& a, int S, int precision, int np, void* stream) {
     hipStream_t st = static_cast<hipStream_t>(stream);
-    const int64_t per = (int64_t)kBlock * np;
+    const bool tree = a.tree.n_trees > 0;
+    const int64_t per = (int64_t)(tree ? 64 : kBlock) * np;
     const dim3 grid((unsigned)((a.n + per - 1) / per), (unsigned)S);
     const dim3 block(kBlock);
     if (precision == ENV_PREC_FP64) {
-        if (np == 2) hipLaunchKernelGGL((k_potential<2, true>), grid, block, 0, st, a);
-        else hipLaunchKernelGGL((k_potential<1, true>), grid, block, 0, st, a);
+        if (tree) {
+            if (np == 2) hipLaunchKernelGGL((k_tree_potential<2, true>), grid, block, 0, st, a);
+            else hipLaunchKernelGGL((k_tree_potential<1, true>), grid, block, 0, st, a);
+        } else {
+            if (np == 2) hipLaunchKernelGGL((k_potential<2, true>), grid, block, 0, st, a);
+            else hipLaunchKernelGGL((k_potential<1, true>), grid, block, 0, st, a);
+        }
+    } else if (tree) {
+        if (np == 1) hipLaunchKernelGGL((k_tree_potential<1, false>), grid, block, 0, st, a);
+        else if (np == 4) hipLaunchKernelGGL((k_tree_potential<4, false>), grid, block, 0, st, a);
+        else hipLaunchKernelGGL((k_tree_potential<2, false>), grid, block, 0, st, a);
     } else {
         if (np == 1) hipLaunchKernelGGL((k_potential<1, false>), grid, block, 0, st, a);
         else if (np == 4) hipLaunchKernelGGL((k_potential<4, false>), grid, block, 0, st, a);
@@ -849,67 +1371,66 @@ int launch_potential(const EvalArgs& a, int S, int precision, int np, void* stre
     return hipGetLastError() == hipSuccess ? 0 : -1;
 }
 
-int launch_persistent(const BatchArgs& b, int grid, int precision, int np, void* stream) {
+namespace {
+
+using PersistentKernel = void (*)(BatchArgs);
+
+template <bool TREE>
+PersistentKernel persistent_kernel(int precision, int np) {
+    if (precision == ENV_PREC_FP64)
+        return np == 2 ? k_potential_persistent<2, true, TREE> : k_potential_persistent<1, true, TREE>;
+    return np == 1 ? k_potential_persistent<1, false, TREE>
+                   : (np == 2 ? k_potential_persistent<2, false, TREE> : k_potential_persistent<4, false, TREE>);
+}
+
+PersistentKernel persistent_kernel(int precision, int np, bool tree) {
+    return tree ? persistent_kernel<true>(precision, np) : persistent_kernel<false>(precision, np);
+}
+
+using DevSizedKernel = void (*)(DevSizedArgs);
+
+DevSizedKernel devsized_kernel(int precision, bool tree) {
+    if (precision == ENV_PREC_FP64) return tree ? k_potential_devsized<true, true> : k_potential_devsized<true, false>;
+    return tree ? k_potential_devsized<false, true> : k_potential_devsized<false, false>;
+}
+
+template <class K>
+int resident_grid(K kernel, int cu_count) {
+    int per_cu = 0;
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kernel, kBlock, 0) != hipSuccess || per_cu < 1) per_cu = 1;
+    return per_cu * cu_count;
+}
+
+}  // namespace
+
+int launch_persistent(const BatchArgs& b, int grid, int precision, int np, bool tree, void* stream) {
     hipStream_t st = static_cast<hipStream_t>(stream);
     hipLaunchKernelGGL(k_reset_counter, dim3(1), dim3(64), 0, st, b.counter);
-    if (precision == ENV_PREC_FP64) {
-        if (np == 2) hipLaunchKernelGGL((k_potential_persistent<2, true>), dim3(grid), dim3(kBlock), 0, st, b);
-        else hipLaunchKernelGGL((k_potential_persistent<1, true>), dim3(grid), dim3(kBlock), 0, st, b);
-    } else {
-        if (np == 1) hipLaunchKernelGGL((k_potential_persistent<1, false>), dim3(grid), dim3(kBlock), 0, st, b);
-        else if (np == 2) hipLaunchKernelGGL((k_potential_persistent<2, false>), dim3(grid), dim3(kBlock), 0, st, b);
-        else hipLaunchKernelGGL((k_potential_persistent<4, false>), dim3(grid), dim3(kBlock), 0, st, b);
-    }
+    hipLaunchKernelGGL(persistent_kernel(precision, np, tree), dim3(grid), dim3(kBlock), 0, st, b);
     return hipGetLastError() == hipSuccess ? 0 : -1;
 }
 
-int devsized_klog(int64_t m, int np, int64_t want_waves, int64_t part_cap) {
-    return devsized_k(m, np, want_waves, part_cap);
+int devsized_grid(int precision, bool tree, int cu_count) {
+    return resident_grid(devsized_kernel(precision, tree), cu_count);
 }
 
-int devsized_grid(int precision, int cu_count) {
-    int per_cu = 0;
-    const hipError_t e =
-        precision == ENV_PREC_FP64
-            ? hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_potential_devsized<2, true>, kBlock, 0)
-            : hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_potential_devsized<4, false>, kBlock, 0);
-    if (e != hipSuccess || per_cu < 1) per_cu = 1;
-    return per_cu * cu_count;
-}
-
-int launch_potential_devsized(const DevSizedArgs& d, int grid, int precision, int np, void* stream) {
+int launch_potential_devsized(const DevSizedArgs& d, int grid, int precision, void* stream) {
     hipStream_t st = static_cast<hipStream_t>(stream);
     hipLaunchKernelGGL(k_reset_counter, dim3(1), dim3(64), 0, st, d.counter);
-    if (precision == ENV_PREC_FP64) {
-        if (np != 2) return -1;
-        hipLaunchKernelGGL((k_potential_devsized<2, true>), dim3(grid), dim3(kBlock), 0, st, d);
-    } else {
-        if (np != 4) return -1;
-        hipLaunchKernelGGL((k_potential_devsized<4, false>), dim3(grid), dim3(kBlock), 0, st, d);
-    }
+    hipLaunchKernelGGL(devsized_kernel(precision, d.a.tree.n_trees > 0), dim3(grid), dim3(kBlock), 0, st, d);
     return hipGetLastError() == hipSuccess ? 0 : -1;
 }
 
-int launch_sum_devsized(const DevSizedArgs& d, int np, int64_t n_max, double* out, void* stream) {
+int launch_sum_devsized(const DevSizedArgs& d, int precision, int64_t n_max, double* out, void* stream) {
     if (n_max <= 0) return 0;
     const dim3 grid((unsigned)((n_max + kBlock - 1) / kBlock));
-    hipLaunchKernelGGL(k_sum_devsized, grid, dim3(kBlock), 0, static_cast<hipStream_t>(stream), d.a.out, d.m, np,
-                       d.want_waves, d.part_cap, out);
+    hipLaunchKernelGGL(k_sum_devsized, grid, dim3(kBlock), 0, static_cast<hipStream_t>(stream), d.a.out, d.m,
+                       precision == ENV_PREC_FP64 ? 1 : 0, d.a.tree.n_trees > 0 ? 1 : 0, d.want, d.part_cap, d.a.order, out);
     return hipGetLastError() == hipSuccess ? 0 : -1;
 }
 
-int persistent_grid(int precision, int np, int cu_count) {
-    int per_cu = 0;
-    hipError_t e;
-    if (precision == ENV_PREC_FP64)
-        e = np == 2 ? hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_potential_persistent<2, true>, kBlock, 0)
-                    : hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_potential_persistent<1, true>, kBlock, 0);
-    else
-        e = np == 1 ? hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_potential_persistent<1, false>, kBlock, 0)
-          : np == 2 ? hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_potential_persistent<2, false>, kBlock, 0)
-                    : hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_potential_persistent<4, false>, kBlock, 0);
-    if (e != hipSuccess || per_cu < 1) per_cu = 1;
-    return per_cu * cu_count;
+int persistent_grid(int precision, int np, bool tree, int cu_count) {
+    return resident_grid(persistent_kernel(precision, np, tree), cu_count);
 }
 
 int launch_sum_multi(const SumDesc* d, int n_desc, int64_t max_n, void* stream) {
@@ -927,10 +1448,16 @@ int launch_segment_boxes(const Segment* segs, int n_segs, const uint32_t* rec, i
     return hipGetLastError() == hipSuccess ? 0 : -1;
 }
 
-int launch_sum_splits(const double* partial, int S, int64_t n, double* out, void* stream) {
-    const dim3 grid((unsigned)((n + kBlock - 1) / kBlock));
-    hipLaunchKernelGGL(k_sum_splits, grid, dim3(kBlock), 0, static_cast<hipStream_t>(stream),
-                       partial, S, n, out);
+int launch_sum_splits(const double* partial, int S, int64_t n, const uint32_t* order, double* out, void* stream) {
+    hipStream_t st = static_cast<hipStream_t>(stream);
+    if (S > 8 && n < 65536) {
+        const int per = kBlock / 8;
+        hipLaunchKernelGGL(k_sum_splits8, dim3((unsigned)((n + per - 1) / per)), dim3(kBlock), 0, st, partial, S, n,
+                           order, out);
+    } else {
+        hipLaunchKernelGGL(k_sum_splits, dim3((unsigned)((n + kBlock - 1) / kBlock)), dim3(kBlock), 0, st, partial, S,
+                           n, order, out);
+    }
     return hipGetLastError() == hipSuccess ? 0 : -1;
 }
 

@@ -7,9 +7,11 @@
 // until the process ends; every call on one device uses that device's copy.
 #include <hip/hip_runtime.h>
 
+#include <cstdlib>
 #include <mutex>
 
 #include "handle.h"
+#include "sort_internal.h"
 
 using namespace envpot;
 
@@ -59,15 +61,24 @@ env_status env_potential_eval_noalloc(env_potential* h, const double* points, in
     // until the partials fit the array
     int np = 0, k = 0;
     choose_shape(h, n, &np, &k);
-    while (k > 0 && (int64_t(1) << k) * n > kScratchDoubles) --k;
+    // with a tree, the order of a small call's points takes the array's end
+    uint32_t* order = nullptr;
+    int64_t cap = kScratchDoubles;
+    const char* ns = std::getenv("ENVPOT_NO_SORT");
+    if (h->tree && order_small(n) && !(ns && *ns && std::atoi(ns) != 0)) {
+        cap -= kOrderSmallMax / 2;
+        order = reinterpret_cast<uint32_t*>(part + cap);
+        if (order_points(points, n, nullptr, order, stream) != 0) return ENV_E_DEVICE;
+    }
+    while (k > 0 && (int64_t(1) << k) * n > cap) --k;
     const int S = 1 << k;
-    if (S == 1) return launch_potential(make_args(h, points, n, out, 0), 1, h->precision, np, stream) == 0
-                           ? ENV_OK
-                           : ENV_E_DEVICE;
+    EvalArgs a = make_args(h, points, n, S == 1 ? out : part, k);
+    a.order = order;
+    if (S == 1) return launch_potential(a, 1, h->precision, np, stream) == 0 ? ENV_OK : ENV_E_DEVICE;
     // every (split, point) partial is written by the potential kernel before
     // the fixed-order sum reads it, so nothing needs clearing between calls
-    if (launch_potential(make_args(h, points, n, part, k), S, h->precision, np, stream) != 0 ||
-        launch_sum_splits(part, S, n, out, stream) != 0)
+    if (launch_potential(a, S, h->precision, np, stream) != 0 ||
+        launch_sum_splits(part, S, n, order, out, stream) != 0)
         return ENV_E_DEVICE;
     return ENV_OK;
 }

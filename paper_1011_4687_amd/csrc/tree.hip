@@ -1,0 +1,1114 @@
+// Build and refresh of the multipole tree (tree_internal.h).
+//
+// Build, once per handle: the cell and level of every item from its group's
+// cube and its far-field radius (one thread per item); a radix sort of
+// (group, cell code, level, type); the host turns the unique runs into nodes
+// (a few words per run); a second, stable sort by (node, type) places every
+// record.  Refresh, after each density fold: a copy of the records into the
+// tree's order, the moments of every node's own items (a workgroup per 128
+// items), then one launch per depth from the leaves up, a workgroup per
+// node: the sum with its children's moments, the evaluation coefficients and
+// accepted radii, and the shift to its parent's centre.
+//
+// Harmonics: R_n^m(x) = r^n P_n^m(cos) e^{i m phi} / (n+m)! without the
+// Condon-Shortley phase, R_m^m = (x+iy)^m / (2^m m!),
+//   R_{n+1}^m = ((2n+1) z R_n^m - r^2 R_{n-1}^m) / ((n+1)^2 - m^2),
+// R_n^{-m} = (-1)^m conj R_n^m, and
+//   d/dz R_n^m = R_{n-1}^m, (d/dx - i d/dy) R_n^m = R_{n-1}^{m-1},
+//   (d/dx + i d/dy) R_n^m = -R_{n-1}^{m+1}.
+// A pair's Hermite density acts as derivatives on 1/|r - P|, so its moments
+// about c are M_n^m = sum_{k<=L} sum_j Q_k^j R_{n-k}^{m-j}(P - c) with Q the
+// densities D_tuv folded through those rules; a child's moments shift by the
+// same sum with k up to n.  The potential of a node at X = r - c is
+//   (1/R) sum_{n,m>=0} (2 - d_m0) (n-m)! (n+m)! Re[conj(M_n^m) R_n^m(X/R^2)].
+#include <hip/hip_runtime.h>
+
+#include <hipcub/hipcub.hpp>
+
+#include <algorithm>
+#include <cmath>
+#include <cstring>
+#include <limits>
+#include <new>
+
+#include "tree_internal.h"
+#include "update_internal.h"
+
+namespace envpot {
+namespace {
+
+constexpr int kB = 256;
+
+// Doubles of Tree::d_tab: recursion coefficients of the evaluation, factor
+// from moment to evaluation coefficient, weight of |M|^2 in a degree's norm,
+// fold of D_tuv into Q_k^j (35 components x 5 values of j, complex), factor
+// of the step to R_n^m in its recursion.
+constexpr int tab_beta() { return 0; }
+constexpr int tab_fac(int P) { return tree_ncoef(P); }
+constexpr int tab_norm(int P) { return 2 * tree_ncoef(P); }
+constexpr int tab_fold(int P) { return 3 * tree_ncoef(P); }
+constexpr int tab_den(int P) { return tab_fold(P) + 35 * 5 * 2; }
+constexpr int tab_words(int P) { return tab_den(P) + tree_ncoef(P); }
+constexpr int kGeo = 6;   // doubles per node in d_geo: centre, item radius, far radius, pad
+
+__host__ __device__ inline int rec_words_of(int L, bool fp64) { return fp64 ? rec64_words(L) : rec32_words(L); }
+__device__ inline int64_t gid() { return int64_t(blockIdx.x) * kB + threadIdx.x; }
+unsigned grid_of(int64_t n) { return unsigned((n + kB - 1) / kB); }
+
+// Centre and far-field radius of item i (pairs, then nuclei).
+__device__ inline void item_geo(const UpdPair* pairs, const uint32_t* rec, const double* nuc, int64_t n_pairs,
+                                int fp64, int64_t i, double* c, double* rf) {
+    if (i < n_pairs) {
+        const uint32_t* r = rec + pairs[i].word;
+        const double* d = reinterpret_cast<const double*>(r);
+        c[0] = d[0];
+        c[1] = d[1];
+        c[2] = d[2];
+        *rf = sqrt(fp64 ? d[3] : double(reinterpret_cast<const float*>(r)[6])) * (1.0 + 1e-6);
+    } else {
+        const double* d = nuc + 4 * (i - n_pairs);
+        c[0] = d[0];
+        c[1] = d[1];
+        c[2] = d[2];
+        *rf = 0.0;
+    }
+}
+
+// Cube of each group's items: smallest corner and edge.
+__global__ __launch_bounds__(kB) void k_tree_cubes(const UpdPair* pairs, const uint32_t* rec, const double* nuc,
+                                                   int64_t n_pairs, int fp64, const int64_t* gpb,
+                                                   const int32_t* gnb, const int32_t* gne, double* cube) {
+    __shared__ double red[6][kB];
+    const int g = blockIdx.x, t = threadIdx.x;
+    double v[6] = {HUGE_VAL, HUGE_VAL, HUGE_VAL, -HUGE_VAL, -HUGE_VAL, -HUGE_VAL};
+    const int64_t np = gpb[g + 1] - gpb[g], nn = gne[g] - gnb[g];
+    for (int64_t k = t; k < np + nn; k += kB) {
+        double c[3], rf;
+        item_geo(pairs, rec, nuc, n_pairs, fp64, k < np ? gpb[g] + k : n_pairs + gnb[g] + (k - np), c, &rf);
+        for (int d = 0; d < 3; ++d) {
+            v[d] = fmin(v[d], c[d]);
+            v[3 + d] = fmax(v[3 + d], c[d]);
+        }
+    }
+    for (int d = 0; d < 6; ++d) red[d][t] = v[d];
+    __syncthreads();
+    for (int w = kB / 2; w > 0; w >>= 1) {
+        if (t < w)
+            for (int d = 0; d < 3; ++d) {
+                red[d][t] = fmin(red[d][t], red[d][t + w]);
+                red[3 + d][t] = fmax(red[3 + d][t], red[3 + d][t + w]);
+            }
+        __syncthreads();
+    }
+    if (t == 0) {
+        double e = 0.0;
+        for (int d = 0; d < 3; ++d) {
+            cube[4 * g + d] = red[d][0];
+            e = fmax(e, red[3 + d][0] - red[d][0]);
+        }
+        cube[4 * g + 3] = np + nn > 0 ? e * (1.0 + 1e-9) : 0.0;
+    }
+}
+
+// Sort key of every item: group (27 bits), cell code of its level left
+// aligned (30), level (4), type (3): cells come out in preorder.
+__global__ __launch_bounds__(kB) void k_tree_keys(const UpdPair* pairs, const uint32_t* rec, const double* nuc,
+                                                  const int32_t* nuc_group, int64_t n_pairs, int64_t n_items,
+                                                  int fp64, const double* cube, unsigned long long* key,
+                                                  uint32_t* val) {
+    const int64_t i = gid();
+    if (i >= n_items) return;
+    double c[3], rf;
+    item_geo(pairs, rec, nuc, n_pairs, fp64, i, c, &rf);
+    const int g = i < n_pairs ? pairs[i].group : nuc_group[i - n_pairs];
+    const int type = i < n_pairs ? pairs[i].L : kLMax + 1;
+    const double* q = cube + 4 * g;
+    double h = q[3];
+    int level = 0;
+    while (level < kTreeLevels && h > 0.0 && rf * kTreeKappa <= 0.5 * h) {
+        h *= 0.5;
+        ++level;
+    }
+    unsigned long long code = 0;
+    if (level > 0) {
+        const double inv = double(1 << kTreeLevels) / q[3];
+        uint32_t s[3];
+        for (int d = 0; d < 3; ++d) {
+            const double x = (c[d] - q[d]) * inv;
+            const int top = (1 << kTreeLevels) - 1;
+            s[d] = x <= 0.0 ? 0u : (x >= double(top) ? uint32_t(top) : uint32_t(x));
+        }
+        for (int l = 0; l < level; ++l) {
+            const int b = kTreeLevels - 1 - l;
+            code |= (unsigned long long)((((s[0] >> b) & 1u) << 2) | (((s[1] >> b) & 1u) << 1) | ((s[2] >> b) & 1u))
+                    << (3 * b);
+        }
+    }
+    key[i] = ((unsigned long long)g << 37) | (code << 7) | ((unsigned long long)level << 3) |
+             (unsigned long long)type;
+    val[i] = uint32_t(i);
+}
+
+__global__ __launch_bounds__(kB) void k_tree_heads(const unsigned long long* key, int64_t n, int32_t* head) {
+    const int64_t i = gid();
+    if (i >= n) return;
+    head[i] = (i == 0 || key[i] != key[i - 1]) ? 1 : 0;
+}
+
+// runid: inclusive scan of the heads; the first item of every run.
+__global__ __launch_bounds__(kB) void k_tree_runs(const unsigned long long* key, const int32_t* runid, int64_t n,
+                                                  unsigned long long* rkey, uint32_t* rstart) {
+    const int64_t i = gid();
+    if (i >= n) return;
+    if (i == 0 || key[i] != key[i - 1]) {
+        rkey[runid[i] - 1] = key[i];
+        rstart[runid[i] - 1] = uint32_t(i);
+    }
+}
+
+__global__ __launch_bounds__(kB) void k_tree_nodekeys(const unsigned long long* key, const int32_t* runid,
+                                                      const int32_t* run_node, int64_t n, uint32_t* nkey) {
+    const int64_t i = gid();
+    if (i >= n) return;
+    nkey[i] = uint32_t(run_node[runid[i] - 1]) * kTreeTypes + uint32_t(key[i] & 7ull);
+}
+
+// Place every item: word of a pair's record, copy of a nucleus.
+__global__ __launch_bounds__(kB) void k_tree_place(const uint32_t* nkey, const uint32_t* val, const uint32_t* start,
+                                                   const TreeNode* node, int64_t n_pairs, int64_t n_items, int fp64,
+                                                   const double* nuc, int64_t* word, double* tnuc,
+                                                   int32_t* item_node) {
+    const int64_t i = gid();
+    if (i >= n_items) return;
+    const uint32_t k = nkey[i];
+    const int nd = int(k / kTreeTypes), type = int(k % kTreeTypes);
+    const int64_t rank = i - int64_t(start[k]);
+    const int64_t it = val[i];
+    item_node[it] = nd;
+    if (type <= kLMax) {
+        int64_t w = node[nd].rec_off;
+        for (int L = 0; L < type; ++L) w += int64_t(node[nd].cnt[L]) * rec_words_of(L, fp64 != 0);
+        word[it] = w + rank * rec_words_of(type, fp64 != 0);
+    } else {
+        const int64_t o = node[nd].nuc_begin + rank;
+        for (int d = 0; d < 4; ++d) tnuc[4 * o + d] = nuc[4 * (it - n_pairs) + d];
+    }
+}
+
+// Doubles as unsigned integers of the same order (for atomic min and max).
+__device__ inline unsigned long long ordered(double x) {
+    const unsigned long long b = (unsigned long long)__double_as_longlong(x);
+    return (b >> 63) ? ~b : (b | 0x8000000000000000ull);
+}
+__host__ __device__ inline double unordered(unsigned long long u) {
+    const unsigned long long b = (u >> 63) ? (u & 0x7fffffffffffffffull) : ~u;
+    double d;
+    __builtin_memcpy(&d, &b, 8);
+    return d;
+}
+
+// Bounding box of every node's subtree: each item climbs its ancestors until
+// it changes nothing (minimum and maximum do not depend on the order).
+__global__ __launch_bounds__(kB) void k_tree_bounds(const UpdPair* pairs, const uint32_t* rec, const double* nuc,
+                                                    int64_t n_pairs, int64_t n_items, int fp64,
+                                                    const int32_t* item_node, const int32_t* parent,
+                                                    unsigned long long* box) {
+    const int64_t i = gid();
+    if (i >= n_items) return;
+    double c[3], rf;
+    item_geo(pairs, rec, nuc, n_pairs, fp64, i, c, &rf);
+    for (int nd = item_node[i]; nd >= 0; nd = parent[nd])
+        for (int d = 0; d < 3; ++d) {
+            const unsigned long long u = ordered(c[d]);
+            if (box[6 * int64_t(nd) + d] > u) atomicMin(&box[6 * int64_t(nd) + d], u);
+            if (box[6 * int64_t(nd) + 3 + d] < u) atomicMax(&box[6 * int64_t(nd) + 3 + d], u);
+        }
+}
+
+__global__ __launch_bounds__(kB) void k_tree_centres(const unsigned long long* box, int64_t n_nodes, double* geo,
+                                                     unsigned long long* rad) {
+    const int64_t i = gid();
+    if (i >= n_nodes) return;
+    for (int d = 0; d < 3; ++d)
+        geo[kGeo * i + d] = 0.5 * (unordered(box[6 * i + d]) + unordered(box[6 * i + 3 + d]));
+    rad[2 * i] = rad[2 * i + 1] = 0ull;
+}
+
+// Largest |item - centre| and largest |item - centre| + far-field radius.
+__global__ __launch_bounds__(kB) void k_tree_radii(const UpdPair* pairs, const uint32_t* rec, const double* nuc,
+                                                   int64_t n_pairs, int64_t n_items, int fp64,
+                                                   const int32_t* item_node, const int32_t* parent, const double* geo,
+                                                   unsigned long long* rad) {
+    const int64_t i = gid();
+    if (i >= n_items) return;
+    double c[3], rf;
+    item_geo(pairs, rec, nuc, n_pairs, fp64, i, c, &rf);
+    for (int nd = item_node[i]; nd >= 0; nd = parent[nd]) {
+        const double* q = geo + kGeo * int64_t(nd);
+        const double dx = c[0] - q[0], dy = c[1] - q[1], dz = c[2] - q[2];
+        const double d = sqrt(dx * dx + dy * dy + dz * dz) * (1.0 + 1e-12);
+        // non-negative doubles order like their bits
+        const unsigned long long a = (unsigned long long)__double_as_longlong(d),
+                                 f = (unsigned long long)__double_as_longlong(d + rf);
+        if (rad[2 * int64_t(nd)] < a) atomicMax(&rad[2 * int64_t(nd)], a);
+        if (rad[2 * int64_t(nd) + 1] < f) atomicMax(&rad[2 * int64_t(nd) + 1], f);
+    }
+}
+
+__global__ __launch_bounds__(kB) void k_tree_radii_out(const unsigned long long* rad, int64_t n_nodes, double* geo) {
+    const int64_t i = gid();
+    if (i >= n_nodes) return;
+    geo[kGeo * i + 3] = __longlong_as_double((long long)rad[2 * i]);
+    geo[kGeo * i + 4] = __longlong_as_double((long long)rad[2 * i + 1]);
+    geo[kGeo * i + 5] = 0.0;
+}
+
+// ---------------------------------------------------------------- refresh
+
+// One thread per pair and 8-byte word of the largest record would leave most
+// idle; a quarter wave per pair copies its record.
+__global__ __launch_bounds__(kB) void k_tree_copy(const UpdPair* pairs, const int64_t* word, int64_t n_pairs,
+                                                  int fp64, const uint32_t* rec, uint32_t* trec) {
+    const int64_t i = int64_t(blockIdx.x) * (kB / 16) + (threadIdx.x >> 4);
+    if (i >= n_pairs) return;
+    const int lane = threadIdx.x & 15;
+    const UpdPair q = pairs[i];
+    const int nw = rec_words_of(q.L, fp64 != 0) / 2;
+    const uint64_t* s = reinterpret_cast<const uint64_t*>(rec + q.word);
+    uint64_t* d = reinterpret_cast<uint64_t*>(trec + word[i]);
+    for (int k = lane; k < nw; k += 16) d[k] = s[k];
+}
+
+// A share of one node's own items (in their order: pairs by L, then nuclei).
+struct Chunk {
+    int32_t node, begin, end;
+};
+
+struct MomentArgs {
+    const Chunk* chunk;          // chunks in node order
+    const int32_t* chunk_begin;  // per node + 1
+    const int32_t* by_depth;     // the nodes of this launch
+    const TreeNode* node;
+    const uint32_t* rec;
+    const double* nuc;
+    const int32_t* child;
+    const int32_t* child_begin;
+    const int32_t* parent;
+    const double* geo;
+    const double* tab;
+    double* part;                // per chunk: moments about the node's centre, absolute charge
+    double* up;                  // per node: its moments about its parent's centre, absolute charge
+    double* coef;
+    float* thr;
+    TreeTest* test;
+    double eps;
+};
+
+struct Cplx {
+    double r, i;
+};
+
+constexpr int kBatch = 8;        // items whose harmonics are in LDS at once
+constexpr int kChunk = 128;      // items per chunk
+constexpr int part_words(int P) { return 2 * tree_ncoef(P) + 2; }
+
+// Scale of a node's moments (by s^-n): no power of a coordinate overflows.
+__device__ __forceinline__ double node_scale(const double* geo) {
+    const double s = fmax(geo[3], 0.1 * geo[4]);
+    return s > 0.0 ? s : 1.0;
+}
+
+// R_n^m(x) for m >= 0 of one x, by the thread of order m, into tab[index].
+template <int P>
+__device__ __forceinline__ void harmonics(double x, double y, double z, int m, const double* den, Cplx* tab) {
+    double cr = 1.0, ci = 0.0;
+    for (int k = 1; k <= m; ++k) {
+        const double f = den[tree_index(P, k, k)], nr = (cr * x - ci * y) * f;
+        ci = (cr * y + ci * x) * f;
+        cr = nr;
+    }
+    const double r2 = x * x + y * y + z * z;
+    Cplx a{0.0, 0.0}, b{cr, ci};  // R_{n-1}, R_n
+    const int at = tree_index(P, m, m);
+    tab[at] = b;
+    for (int n = m; n < P; ++n) {
+        const double f = den[at + n + 1 - m], u = (2 * n + 1) * z;
+        const Cplx c{(u * b.r - r2 * a.r) * f, (u * b.i - r2 * a.i) * f};
+        a = b;
+        b = c;
+        tab[at + n + 1 - m] = c;
+    }
+}
+
+// acc += sum_{k <= kmax} sum_j Q_k^j R_{n-k}^{m-j}; Q and R hold their
+// m >= 0 parts at tree_index(PQ, k, j) and tree_index(P, n, m).
+template <int P, int PQ>
+__device__ __forceinline__ void shift_add(const Cplx* Q, const Cplx* R, int kmax, int n, int m, Cplx& acc) {
+    const int kt = kmax < n ? kmax : n;
+    for (int k = 0; k <= kt; ++k) {
+        const int nn = n - k;
+        const int j0 = max(-k, m - nn), j1 = min(k, m + nn);  // |m - j| <= n - k
+        for (int j = j0; j <= j1; ++j) {
+            Cplx q = Q[tree_index(PQ, k, j < 0 ? -j : j)];
+            if (j < 0) {
+                q.i = -q.i;
+                if (j & 1) {
+                    q.r = -q.r;
+                    q.i = -q.i;
+                }
+            }
+            const int mm = m - j;
+            Cplx r = R[tree_index(P, nn, mm < 0 ? -mm : mm)];
+            if (mm < 0) {
+                r.i = -r.i;
+                if (mm & 1) {
+                    r.r = -r.r;
+                    r.i = -r.i;
+                }
+            }
+            acc.r += q.r * r.r - q.i * r.i;
+            acc.i += q.r * r.i + q.i * r.r;
+        }
+    }
+}
+
+// Index of Hermite component (a, b, c) among those of order up to L.
+__device__ __forceinline__ int comp_index(int L, int a, int b, int c) {
+    const int m = L - a;
+    // components with a smaller first exponent, then with a smaller second
+    const int first = (L + 1) * (L + 2) * (L + 3) / 6 - (m + 1) * (m + 2) * (m + 3) / 6;
+    return first + b * (m + 1) - b * (b - 1) / 2 + c;
+}
+
+// (n, m) of coefficient t.
+template <int P>
+__device__ __forceinline__ void coef_nm(int t, int& n, int& m) {
+    m = 0;
+    while (m <= P && t >= P + 1 - m) {
+        t -= P + 1 - m;
+        ++m;
+    }
+    n = m + t;
+}
+
+// Moments of one chunk of own items about their node's centre; a workgroup
+// per chunk, thread t owns coefficient t.  Bound by the LDS reads of the
+// shifts (two complex values per multiply-add).
+template <int P, bool F64>
+__global__ __launch_bounds__(kB) void k_tree_p2m(MomentArgs A) {
+    constexpr int NC = tree_ncoef(P);
+    static_assert(NC <= kB, "one thread per coefficient");
+    static_assert(kBatch * (P + 1) <= kB, "one thread per item and order");
+    __shared__ Cplx R[kBatch][NC];
+    __shared__ Cplx Q[kBatch][15];  // order 4
+    __shared__ double xs[kBatch][3];
+    __shared__ const double* item[kBatch];
+    __shared__ int ls[kBatch];
+    __shared__ double fold[350];
+    __shared__ double den[NC];
+    __shared__ double qabs[15 * kBatch];
+    const int t = threadIdx.x;
+    for (int k = t; k < 350; k += kB) fold[k] = A.tab[tab_fold(P) + k];
+    if (t < NC) den[t] = A.tab[tab_den(P) + t];
+    // (k, j) of this thread's Q
+    int qk = 0, qj = t % 15;
+    while (qj > qk) qj -= ++qk;
+    const Chunk ck = A.chunk[blockIdx.x];
+    const TreeNode node = A.node[ck.node];
+    const double* geo = A.geo + kGeo * int64_t(ck.node);
+    const double inv = 1.0 / node_scale(geo);
+    int n, m;
+    coef_nm<P>(t, n, m);
+    Cplx acc{0.0, 0.0};
+    double qa = 0.0;
+    __syncthreads();
+    for (int i0 = ck.begin; i0 < ck.end; i0 += kBatch) {
+        const int nb = min(kBatch, ck.end - i0);
+        if (t < nb) {
+            int i = i0 + t, L = 0;
+            int64_t w = node.rec_off;
+            while (L <= kLMax && i >= node.cnt[L]) {
+                i -= node.cnt[L];
+                w += int64_t(node.cnt[L]) * rec_words_of(L, F64);
+                ++L;
+            }
+            const double* d = L <= kLMax ? reinterpret_cast<const double*>(A.rec + w + int64_t(i) * rec_words_of(L, F64))
+                                         : A.nuc + 4 * int64_t(node.nuc_begin + i);
+            item[t] = d;
+            ls[t] = L;
+            xs[t][0] = (d[0] - geo[0]) * inv;
+            xs[t][1] = (d[1] - geo[1]) * inv;
+            xs[t][2] = (d[2] - geo[2]) * inv;
+        }
+        __syncthreads();
+        if (t < 15 * nb) {  // Q_k^j of an item, scaled by s^-k, from its components of order k
+            const int it = t / 15, L = ls[it];
+            const double* d = item[it];
+            const float* f32 = reinterpret_cast<const float*>(d);
+            Cplx o{0.0, 0.0};
+            double size = 0.0;
+            if (L > kLMax) {
+                if (qk == 0) {
+                    o.r = -d[3];
+                    size = fabs(d[3]);
+                }
+            } else if (qk <= L) {
+                const int nc = kNComp[L];
+                for (int a = 0; a <= qk; ++a)
+                    for (int b = 0; b <= qk - a; ++b) {
+                        const int c = qk - a - b;
+                        // index of (a, b, c) at this L and at order 4
+                        const int at = comp_index(L, a, b, c);
+                        const double D = F64 ? d[kRec64Head + nc + at] : double(f32[kRec32Head + nc + at]);
+                        const double* f = fold + 10 * comp_index(kLMax, a, b, c) + 2 * qj;
+                        o.r += D * f[0];
+                        o.i += D * f[1];
+                        size += fabs(D);
+                    }
+                // against 1/R where the pair's far field begins
+                const double ir = rsqrt(F64 ? d[3] : double(f32[6]));
+                for (int k = 0; k < qk; ++k) {
+                    o.r *= inv;
+                    o.i *= inv;
+                    size *= ir;
+                }
+            }
+            Q[it][tree_index(4, qk, qj)] = o;
+            if (qj == 0) qa += size;
+        }
+        __syncthreads();
+        if (t < nb * (P + 1)) {
+            const int it = t / (P + 1);
+            harmonics<P>(xs[it][0], xs[it][1], xs[it][2], t % (P + 1), den, R[it]);
+        }
+        __syncthreads();
+        if (t < NC)
+            for (int it = 0; it < nb; ++it) shift_add<P, 4>(Q[it], R[it], ls[it] > kLMax ? 0 : ls[it], n, m, acc);
+        __syncthreads();
+    }
+    double* o = A.part + int64_t(part_words(P)) * blockIdx.x;
+    if (t < NC) {
+        o[2 * t] = acc.r;
+        o[2 * t + 1] = acc.i;
+    }
+    if (t < 15 * kBatch) qabs[t] = qa;
+    __syncthreads();
+    if (t == 0) {
+        double q = 0.0;
+        for (int k = 0; k < 15 * kBatch; ++k) q += qabs[k];
+        o[2 * NC] = q;
+    }
+}
+
+// One node of a depth: the sum of its chunks' moments and of its children's
+// shifted ones (fixed order), its evaluation coefficients and accepted
+// radii, and its moments shifted to its parent's centre.  A workgroup per
+// node; bound by latency (the shift's chain on the few nodes of a depth).
+template <int P>
+__global__ __launch_bounds__(kB) void k_tree_nodes(MomentArgs A) {
+    constexpr int NC = tree_ncoef(P);
+    __shared__ Cplx M[NC];
+    __shared__ Cplx R[NC];
+    __shared__ double den[NC];
+    __shared__ double bn[P + 1];
+    __shared__ float thr_sh[tree_thr_row(P)];
+    const int t = threadIdx.x;
+    const int nd = A.by_depth[blockIdx.x];
+    const double* geo = A.geo + kGeo * int64_t(nd);
+    const double c0 = geo[0], c1 = geo[1], c2 = geo[2], arad = geo[3], rfar = geo[4];
+    const double s = node_scale(geo);
+    int n, m;
+    coef_nm<P>(t, n, m);
+    const int w = t < NC ? 2 * t : 2 * NC;  // every thread past the coefficients adds up the charge
+    Cplx acc{0.0, 0.0};
+    if (t < NC) den[t] = A.tab[tab_den(P) + t];
+    __syncthreads();
+#pragma unroll 4
+    for (int c = A.chunk_begin[nd]; c < A.chunk_begin[nd + 1]; ++c) {
+        const double* q = A.part + int64_t(part_words(P)) * c + w;
+        acc.r += q[0];
+        acc.i += q[1];
+    }
+    double racc = 0.0;
+    for (int c = A.child_begin[nd]; c < A.child_begin[nd + 1]; ++c) {
+        const int ch = A.child[c];
+        const double* q = A.up + int64_t(part_words(P)) * ch + w;
+        acc.r += q[0];
+        acc.i += q[1];
+        const double* cg = A.geo + kGeo * int64_t(ch);
+        const double dx = cg[0] - c0, dy = cg[1] - c1, dz = cg[2] - c2;
+        racc = fmax(racc, (sqrt(double(A.test[ch].r2)) + sqrt(dx * dx + dy * dy + dz * dz)) * (1.0 + 1e-9));
+    }
+    if (t < NC) {
+        M[t] = acc;
+        double* co = A.coef + int64_t(tree_words(P)) * nd + kTreeHead;
+        const double f = A.tab[tab_fac(P) + t];
+        co[2 * t] = acc.r * f;
+        co[2 * t + 1] = acc.i * f;
+    }
+    __shared__ double charge;
+    if (t == NC) charge = acc.r;
+    const int par = A.parent[nd];
+    double ratio = 0.0;
+    if (par >= 0) {
+        const double* pg = A.geo + kGeo * int64_t(par);
+        const double inv = 1.0 / node_scale(pg);
+        ratio = s * inv;
+        if (t <= P) harmonics<P>((c0 - pg[0]) * inv, (c1 - pg[1]) * inv, (c2 - pg[2]) * inv, t, den, R);
+    }
+    if (t == 0) {
+        double* co = A.coef + int64_t(tree_words(P)) * nd;
+        co[0] = c0;
+        co[1] = c1;
+        co[2] = c2;
+        co[3] = s;
+    }
+    __syncthreads();
+    if (t <= P) {
+        double b = 0.0;
+        for (int mm = 0; mm <= t; ++mm) {
+            const Cplx v = M[tree_index(P, t, mm)];
+            b += A.tab[tab_norm(P) + tree_index(P, t, mm)] * (v.r * v.r + v.i * v.i);
+        }
+        bn[t] = sqrt(b);
+    }
+    __syncthreads();
+    if (t < tree_thr_row(P)) {
+        // smallest radius (at least the far-field radius and outside the
+        // items) from which the degrees above t stay below eps |charge|/R:
+        // sum_{n>t} B_n x^n + tail <= eps |charge|, x = s/R, where the tail
+        // beyond P continues the largest of the last three B_n four times over
+        const double tol = A.eps * charge;
+        const double rmin = fmax(rfar, 1.02 * arad);
+        double r2 = HUGE_VAL;
+        if (t <= P) {
+            const double tail = 4.0 * fmax(bn[P], fmax(bn[P - 1], bn[P - 2]));
+            const double xmax = rmin > 0.0 ? s / rmin : 0.98;
+            auto over = [&](double x) {
+                double v = tail * x / (1.0 - x);
+                for (int k = P; k > t; --k) v = (v + bn[k]) * x;
+                for (int k = 0; k < t; ++k) v *= x;
+                return !(v <= tol);
+            };
+            if (!over(xmax)) {
+                r2 = s / xmax;
+                r2 *= r2;
+            } else {
+                double lo = 0.0, hi = 40.0;  // x = xmax 2^-lo is too large, 2^-hi small enough
+                if (!over(xmax * exp2(-hi))) {
+                    for (int it = 0; it < 12; ++it) {
+                        const double mid = 0.5 * (lo + hi);
+                        if (over(xmax * exp2(-mid))) lo = mid;
+                        else hi = mid;
+                    }
+                    r2 = s / (xmax * exp2(-hi));
+                    r2 *= r2;
+                }
+            }
+            r2 = fmax(r2, racc * racc);  // a node is accepted only where all its children would be
+        }
+        thr_sh[t] = float(r2 * (1.0 + 1e-6));
+    }
+    // meanwhile the other waves shift the moments to the parent's centre
+    if (par >= 0) {
+        __shared__ Cplx Q[NC];
+        if (t < NC) {
+            double f = 1.0;
+            for (int k = 0; k < n; ++k) f *= ratio;
+            Q[t] = Cplx{M[t].r * f, M[t].i * f};
+        }
+        __syncthreads();
+        Cplx u{0.0, 0.0};
+        if (t < NC) shift_add<P, P>(Q, R, P, n, m, u);
+        double* o = A.up + int64_t(part_words(P)) * nd;
+        if (t < NC) {
+            o[2 * t] = u.r;
+            o[2 * t + 1] = u.i;
+        }
+        if (t == 0) o[2 * NC] = charge;
+    }
+    __syncthreads();
+    if (t < tree_thr_row(P)) {
+        // radii do not grow with the order
+        float v = thr_sh[t];
+        for (int k = 0; k < t && k <= P; ++k) v = fminf(v, thr_sh[k]);
+        if (t > P) v = 0.0f;
+        A.thr[int64_t(tree_thr_row(P)) * nd + t] = v;
+        if (t == P) {
+            TreeTest q;
+            q.c[0] = c0;
+            q.c[1] = c1;
+            q.c[2] = c2;
+            q.r2 = v;
+            q.pc[0] = q.pc[1] = q.pc[2] = 0.0;
+            q.pr2 = HUGE_VALF;
+            q.cost = A.node[nd].cost;
+            q.pad = 0;
+            A.test[nd] = q;
+        }
+    }
+}
+
+// Every node's copy of its parent's test.
+__global__ __launch_bounds__(kB) void k_tree_parents(const int32_t* parent, int64_t n_nodes, TreeTest* test) {
+    const int64_t i = gid();
+    if (i >= n_nodes) return;
+    const int p = parent[i];
+    if (p < 0) return;
+    for (int d = 0; d < 3; ++d) test[i].pc[d] = test[p].c[d];
+    test[i].pr2 = test[p].r2;
+}
+
+// ------------------------------------------------------------------- host
+
+struct Run {
+    uint32_t code;
+    int32_t level, type;
+    int64_t count;
+};
+
+struct HostNode {
+    int32_t parent;
+    int32_t depth;
+    int64_t cnt[kTreeTypes];
+};
+
+struct Builder {
+    const std::vector<Run>& runs;
+    std::vector<int64_t> cost;        // prefix
+    std::vector<HostNode> nodes;
+    std::vector<int32_t> run_node;
+
+    explicit Builder(const std::vector<Run>& r) : runs(r), cost(r.size() + 1, 0), run_node(r.size(), -1) {
+        for (size_t i = 0; i < r.size(); ++i) cost[i + 1] = cost[i] + r[i].count * kTreeW[r[i].type];
+    }
+    static int digit(uint32_t code, int level) { return int((code >> (3 * (kTreeLevels - 1 - level))) & 7u); }
+    void own(int32_t nd, size_t a, size_t b) {
+        for (size_t i = a; i < b; ++i) {
+            run_node[i] = nd;
+            nodes[size_t(nd)].cnt[runs[i].type] += runs[i].count;
+        }
+    }
+    void build(size_t a, size_t b, int level, int32_t parent, int depth) {
+        const int32_t nd = int32_t(nodes.size());
+        nodes.push_back(HostNode{parent, depth, {}});
+        if (cost[b] - cost[a] < kTreeMinCost) {
+            own(nd, a, b);
+            return;
+        }
+        for (; level < kTreeLevels; ++level) {
+            size_t i = a;  // the cell's own runs come first
+            while (i < b && runs[i].level == level) ++i;
+            if (i == b) break;
+            // a cell with nothing of its own and one child is that child
+            if (i == a && digit(runs[a].code, level) == digit(runs[b - 1].code, level)) continue;
+            own(nd, a, i);
+            while (i < b) {
+                size_t j = i;
+                const int d = digit(runs[i].code, level);
+                while (j < b && digit(runs[j].code, level) == d) ++j;
+                if (cost[j] - cost[i] < kTreeMinCost / 4) own(nd, i, j);
+                else build(i, j, level + 1, nd, depth + 1);
+                i = j;
+            }
+            return;
+        }
+        own(nd, a, b);
+    }
+};
+
+std::vector<double> tables(int P) {
+    std::vector<double> t(size_t(tab_words(P)), 0.0);
+    auto fact = [](int k) {
+        double f = 1.0;
+        for (int i = 2; i <= k; ++i) f *= i;
+        return f;
+    };
+    for (int m = 0; m <= P; ++m) {
+        double lead = 1.0;  // coefficient of z^(n-m) (x+iy)^m in R_n^m
+        for (int k = 1; k <= m; ++k) lead *= 0.5 / k;
+        for (int n = m; n <= P; ++n) {
+            const int i = tree_index(P, n, m);
+            const double w = (m ? 2.0 : 1.0) * fact(n - m) * fact(n + m);
+            t[size_t(tab_beta() + i)] =
+                (double(n + 1) * (n + 1) - double(m) * m) / (4.0 * double(n + 1) * (n + 1) - 1.0);
+            t[size_t(tab_fac(P) + i)] = w * lead;
+            t[size_t(tab_norm(P) + i)] = w;
+            t[size_t(tab_den(P) + i)] = n == m ? (m ? 0.5 / m : 1.0) : 1.0 / (double(n - m) * double(n + m));
+            lead *= (2 * n + 1) / (double(n + 1 - m) * double(n + 1 + m));
+        }
+    }
+    // d/dx = (a - b)/2, d/dy = (i/2)(a + b), d/dz = c, where a, b, c lower n by
+    // one and move m by -1, +1, 0: the (t, u, v) derivative is a polynomial in
+    // them, its a^alpha b^beta term one of Q_k^j with j = alpha - beta
+    for (int a = 0; a <= kLMax; ++a)
+        for (int b = 0; b <= kLMax - a; ++b)
+            for (int c = 0; c <= kLMax - a - b; ++c) {
+                double re[9] = {0}, im[9] = {0};  // by j + 4
+                re[4] = 1.0;
+                auto step = [&](double ar, double ai, double br, double bi) {  // times (a's factor, b's factor)
+                    double nr[9] = {0}, ni[9] = {0};
+                    for (int j = 0; j < 9; ++j) {
+                        if (j + 1 < 9) {
+                            nr[j + 1] += re[j] * ar - im[j] * ai;
+                            ni[j + 1] += re[j] * ai + im[j] * ar;
+                        }
+                        if (j > 0) {
+                            nr[j - 1] += re[j] * br - im[j] * bi;
+                            ni[j - 1] += re[j] * bi + im[j] * br;
+                        }
+                    }
+                    std::copy(nr, nr + 9, re);
+                    std::copy(ni, ni + 9, im);
+                };
+                for (int k = 0; k < a; ++k) step(0.5, 0.0, -0.5, 0.0);
+                for (int k = 0; k < b; ++k) step(0.0, 0.5, 0.0, 0.5);
+                double* f = &t[size_t(tab_fold(P) + 10 * hermite_index(kLMax, a, b, c))];
+                for (int j = 0; j <= 4; ++j) {
+                    f[2 * j] = re[4 + j];
+                    f[2 * j + 1] = im[4 + j];
+                }
+            }
+    return t;
+}
+
+// Temporary device memory of the build.
+struct Temp {
+    std::vector<void*> p;
+    template <class T>
+    T* get(int64_t n) {
+        void* q = nullptr;
+        if (hipMalloc(&q, size_t(std::max<int64_t>(n, 1)) * sizeof(T)) != hipSuccess) return nullptr;
+        p.push_back(q);
+        return static_cast<T*>(q);
+    }
+    ~Temp() {
+        for (void* q : p) (void)hipFree(q);
+    }
+};
+
+template <class T>
+T* keep(Tree* t, int64_t n) {
+    void* q = nullptr;
+    const size_t nb = size_t(std::max<int64_t>(n, 1)) * sizeof(T);
+    if (hipMalloc(&q, nb) != hipSuccess) return nullptr;
+    t->owned.push_back(q);
+    t->device_bytes += int64_t(nb);
+    return static_cast<T*>(q);
+}
+
+template <class T>
+bool put(T* d, const std::vector<T>& v, hipStream_t st) {
+    return v.empty() || hipMemcpyAsync(d, v.data(), v.size() * sizeof(T), hipMemcpyHostToDevice, st) == hipSuccess;
+}
+
+int bits_for(uint64_t top) {  // smallest b with 2^b > top
+    int b = 1;
+    while (b < 64 && (uint64_t(1) << b) <= top) ++b;
+    return b;
+}
+
+#define TREE_LAUNCH(n, kern, ...)                                                              \
+    do {                                                                                       \
+        if ((n) > 0) {                                                                         \
+            hipLaunchKernelGGL(kern, dim3(grid_of(n)), dim3(kB), 0, st, __VA_ARGS__);             \
+            if (hipGetLastError() != hipSuccess) return ENV_E_DEVICE;                          \
+        }                                                                                      \
+    } while (0)
+#define TREE_CHECK(x)                        \
+    do {                                     \
+        if (!(x)) return ENV_E_DEVICE;       \
+    } while (0)
+
+env_status build(Tree* t, const UpdateState& u, const uint32_t* d_rec, const std::vector<double>& nuc,
+                 const std::vector<int32_t>& nuc_begin, const std::vector<int32_t>& nuc_end) {
+    hipStream_t st = nullptr;
+    if (hipStreamCreateWithFlags(&st, hipStreamNonBlocking) != hipSuccess) return ENV_E_DEVICE;
+    struct Guard {
+        hipStream_t s;
+        ~Guard() {
+            (void)hipStreamSynchronize(s);
+            (void)hipStreamDestroy(s);
+        }
+    };
+    Temp tmp;       // freed after the stream has drained (declared before the guard)
+    Guard guard{st};
+    const int fp64 = t->fp64 ? 1 : 0, P = t->P;
+    const int64_t n_pairs = t->n_pairs, n_nuc = t->n_nuc, n = n_pairs + n_nuc;
+    const int ng = u.n_groups;
+    std::vector<int32_t> nuc_group(size_t(n_nuc), 0);
+    for (int g = 0; g < ng; ++g)
+        for (int32_t k = nuc_begin[g]; k < nuc_end[g]; ++k) nuc_group[size_t(k)] = g;
+    double* d_nuc0 = tmp.get<double>(4 * n_nuc);
+    int32_t* d_ng = tmp.get<int32_t>(n_nuc);
+    int32_t* d_gnb = tmp.get<int32_t>(ng);
+    int32_t* d_gne = tmp.get<int32_t>(ng);
+    double* d_cube = tmp.get<double>(4 * int64_t(ng));
+    unsigned long long* key = tmp.get<unsigned long long>(n);
+    unsigned long long* key_s = tmp.get<unsigned long long>(n);
+    uint32_t* val = tmp.get<uint32_t>(n);
+    uint32_t* val_s = tmp.get<uint32_t>(n);
+    int32_t* head = tmp.get<int32_t>(n);
+    int32_t* runid = tmp.get<int32_t>(n);
+    uint32_t* nkey = tmp.get<uint32_t>(n);
+    uint32_t* nkey_s = tmp.get<uint32_t>(n);
+    int32_t* item_node = tmp.get<int32_t>(n);
+    if (!d_nuc0 || !d_ng || !d_gnb || !d_gne || !d_cube || !key || !key_s || !val || !val_s || !head || !runid ||
+        !nkey || !nkey_s || !item_node)
+        return ENV_E_NOMEM;
+    TREE_CHECK(put(d_nuc0, nuc, st) && put(d_ng, nuc_group, st) && put(d_gnb, nuc_begin, st) &&
+               put(d_gne, nuc_end, st));
+    hipLaunchKernelGGL(k_tree_cubes, dim3(unsigned(ng)), dim3(kB), 0, st, u.d_pairs, d_rec, d_nuc0, n_pairs, fp64,
+                       u.d_gpb, d_gnb, d_gne, d_cube);
+    TREE_CHECK(hipGetLastError() == hipSuccess);
+    TREE_LAUNCH(n, k_tree_keys, u.d_pairs, d_rec, d_nuc0, d_ng, n_pairs, n, fp64, d_cube, key, val);
+    size_t tb = 0;
+    const int kb = 37 + bits_for(uint64_t(std::max(ng - 1, 0)));
+    TREE_CHECK(hipcub::DeviceRadixSort::SortPairs(nullptr, tb, key, key_s, val, val_s, int(n), 0, kb, st) ==
+               hipSuccess);
+    void* work = tmp.get<char>(int64_t(tb));
+    if (!work) return ENV_E_NOMEM;
+    TREE_CHECK(hipcub::DeviceRadixSort::SortPairs(work, tb, key, key_s, val, val_s, int(n), 0, kb, st) ==
+               hipSuccess);
+    TREE_LAUNCH(n, k_tree_heads, key_s, n, head);
+    size_t ts = 0;
+    TREE_CHECK(hipcub::DeviceScan::InclusiveSum(nullptr, ts, head, runid, int(n), st) == hipSuccess);
+    void* work2 = tmp.get<char>(int64_t(ts));
+    if (!work2) return ENV_E_NOMEM;
+    TREE_CHECK(hipcub::DeviceScan::InclusiveSum(work2, ts, head, runid, int(n), st) == hipSuccess);
+    int32_t n_runs = 0;
+    TREE_CHECK(hipMemcpyAsync(&n_runs, runid + (n - 1), sizeof(int32_t), hipMemcpyDeviceToHost, st) == hipSuccess &&
+               hipStreamSynchronize(st) == hipSuccess);
+    unsigned long long* d_rkey = tmp.get<unsigned long long>(n_runs);
+    uint32_t* d_rstart = tmp.get<uint32_t>(n_runs);
+    int32_t* d_run_node = tmp.get<int32_t>(n_runs);
+    if (!d_rkey || !d_rstart || !d_run_node) return ENV_E_NOMEM;
+    TREE_LAUNCH(n, k_tree_runs, key_s, runid, n, d_rkey, d_rstart);
+    std::vector<unsigned long long> rkey(static_cast<size_t>(n_runs));
+    std::vector<uint32_t> rstart(static_cast<size_t>(n_runs));
+    TREE_CHECK(hipMemcpyAsync(rkey.data(), d_rkey, rkey.size() * 8, hipMemcpyDeviceToHost, st) == hipSuccess &&
+               hipMemcpyAsync(rstart.data(), d_rstart, rstart.size() * 4, hipMemcpyDeviceToHost, st) == hipSuccess &&
+               hipStreamSynchronize(st) == hipSuccess);
+
+    // nodes
+    std::vector<Run> runs(static_cast<size_t>(n_runs));
+    std::vector<size_t> group_at;  // first run of every tree
+    for (size_t i = 0; i < runs.size(); ++i) {
+        runs[i].type = int32_t(rkey[i] & 7ull);
+        runs[i].level = int32_t((rkey[i] >> 3) & 15ull);
+        runs[i].code = uint32_t((rkey[i] >> 7) & 0x3fffffffull);
+        runs[i].count = (i + 1 < runs.size() ? int64_t(rstart[i + 1]) : n) - int64_t(rstart[i]);
+        if (i == 0 || (rkey[i] >> 37) != (rkey[i - 1] >> 37)) group_at.push_back(i);
+    }
+    group_at.push_back(runs.size());
+    Builder b(runs);
+    std::vector<int32_t> first;
+    for (size_t g = 0; g + 1 < group_at.size(); ++g) {
+        first.push_back(int32_t(b.nodes.size()));
+        b.build(group_at[g], group_at[g + 1], 0, -1, 0);
+    }
+    first.push_back(int32_t(b.nodes.size()));
+    const int64_t nn = int64_t(b.nodes.size());
+    t->n_nodes = nn;
+    t->n_trees = int32_t(first.size()) - 1;
+    std::vector<TreeNode> node(static_cast<size_t>(nn));
+    std::vector<uint32_t> start(size_t(nn) * kTreeTypes);
+    std::vector<int32_t> parent(static_cast<size_t>(nn)), by_depth(static_cast<size_t>(nn)), child,
+        child_begin(size_t(nn) + 1, 0);
+    std::vector<Chunk> chunk;
+    std::vector<int32_t> chunk_begin(size_t(nn) + 1, 0);
+    int64_t words = 0, item = 0, nucs = 0;
+    int max_depth = 0;
+    for (int64_t k = 0; k < nn; ++k) {
+        const HostNode& h = b.nodes[size_t(k)];
+        TreeNode& o = node[size_t(k)];
+        int64_t cost = 0;
+        o.rec_off = words;
+        for (int ty = 0; ty < kTreeTypes; ++ty) {
+            start[size_t(k) * kTreeTypes + ty] = uint32_t(item);
+            item += h.cnt[ty];
+            cost += h.cnt[ty] * kTreeW[ty];
+            if (ty <= kLMax) {
+                o.cnt[ty] = int32_t(h.cnt[ty]);
+                words += h.cnt[ty] * rec_words_of(ty, t->fp64);
+            }
+        }
+        o.nuc_begin = int32_t(nucs);
+        nucs += h.cnt[kTreeTypes - 1];
+        o.nuc_end = int32_t(nucs);
+        o.cost = int32_t(cost);
+        const int64_t items = h.cnt[0] + h.cnt[1] + h.cnt[2] + h.cnt[3] + h.cnt[4] + h.cnt[5];
+        for (int64_t a = 0; a < items; a += kChunk)
+            chunk.push_back(Chunk{int32_t(k), int32_t(a), int32_t(std::min<int64_t>(items, a + kChunk))});
+        chunk_begin[size_t(k) + 1] = int32_t(chunk.size());
+        parent[size_t(k)] = h.parent;
+        max_depth = std::max(max_depth, int(h.depth));
+        if (h.parent >= 0) ++child_begin[size_t(h.parent) + 1];
+    }
+    for (int64_t k = 0; k < nn; ++k) child_begin[size_t(k) + 1] += child_begin[size_t(k)];
+    child.resize(size_t(child_begin[size_t(nn)]));
+    {
+        std::vector<int32_t> at(child_begin.begin(), child_begin.end() - 1);
+        for (int64_t k = 0; k < nn; ++k)
+            if (parent[size_t(k)] >= 0) child[size_t(at[size_t(parent[size_t(k)])]++)] = int32_t(k);
+        t->level_begin.assign(size_t(max_depth) + 2, 0);
+        for (int64_t k = 0; k < nn; ++k) ++t->level_begin[size_t(b.nodes[size_t(k)].depth) + 1];
+        for (int d = 0; d <= max_depth; ++d) t->level_begin[size_t(d) + 1] += t->level_begin[size_t(d)];
+        std::vector<int32_t> lv(t->level_begin.begin(), t->level_begin.end() - 1);
+        for (int64_t k = 0; k < nn; ++k) by_depth[size_t(lv[size_t(b.nodes[size_t(k)].depth)]++)] = int32_t(k);
+    }
+    t->rec_words = words;
+    const std::vector<double> tab = tables(P);
+    t->d_test = keep<TreeTest>(t, nn);
+    t->d_node = keep<TreeNode>(t, nn);
+    t->d_thr = keep<float>(t, nn * tree_thr_row(P));
+    t->d_coef = keep<double>(t, nn * tree_words(P));
+    t->d_tab = keep<double>(t, tab_words(P));
+    t->d_first = keep<int32_t>(t, int64_t(first.size()));
+    t->d_rec = keep<uint32_t>(t, words);
+    t->d_nuc = keep<double>(t, 4 * n_nuc);
+    t->d_word = keep<int64_t>(t, n_pairs);
+    t->d_parent = keep<int32_t>(t, nn);
+    t->d_child = keep<int32_t>(t, int64_t(child.size()));
+    t->d_child_begin = keep<int32_t>(t, nn + 1);
+    t->d_by_depth = keep<int32_t>(t, nn);
+    t->d_geo = keep<double>(t, nn * kGeo);
+    t->n_chunks = int64_t(chunk.size());
+    t->d_chunk = keep<Chunk>(t, t->n_chunks);
+    t->d_chunk_begin = keep<int32_t>(t, nn + 1);
+    uint32_t* d_start = tmp.get<uint32_t>(int64_t(start.size()));
+    unsigned long long* d_box = tmp.get<unsigned long long>(6 * nn);
+    unsigned long long* d_rad = tmp.get<unsigned long long>(2 * nn);
+    if (!t->d_test || !t->d_node || !t->d_thr || !t->d_coef || !t->d_tab || !t->d_first || !t->d_rec || !t->d_nuc ||
+        !t->d_word || !t->d_parent || !t->d_child || !t->d_child_begin || !t->d_by_depth || !t->d_geo || !t->d_chunk ||
+        !t->d_chunk_begin ||
+        !d_start || !d_box || !d_rad)
+        return ENV_E_NOMEM;
+    std::vector<unsigned long long> box0(6 * size_t(nn));
+    for (size_t k = 0; k < size_t(nn); ++k)
+        for (int d = 0; d < 6; ++d) box0[6 * k + size_t(d)] = d < 3 ? ~0ull : 0ull;
+    TREE_CHECK(put(t->d_node, node, st) && put(t->d_tab, tab, st) && put(t->d_first, first, st) &&
+               put(t->d_parent, parent, st) && put(t->d_child, child, st) && put(t->d_child_begin, child_begin, st) &&
+               put(t->d_by_depth, by_depth, st) && put(d_start, start, st) && put(d_run_node, b.run_node, st) &&
+               put(d_box, box0, st) && put(static_cast<Chunk*>(t->d_chunk), chunk, st) &&
+               put(t->d_chunk_begin, chunk_begin, st));
+    // records by (node, type), in pair order within
+    TREE_LAUNCH(n, k_tree_nodekeys, key_s, runid, d_run_node, n, nkey);
+    const int nb = bits_for(uint64_t(nn) * kTreeTypes);
+    size_t tb2 = 0;
+    TREE_CHECK(hipcub::DeviceRadixSort::SortPairs(nullptr, tb2, nkey, nkey_s, val_s, val, int(n), 0, nb, st) ==
+               hipSuccess);
+    void* work3 = tmp.get<char>(int64_t(tb2));
+    if (!work3) return ENV_E_NOMEM;
+    TREE_CHECK(hipcub::DeviceRadixSort::SortPairs(work3, tb2, nkey, nkey_s, val_s, val, int(n), 0, nb, st) ==
+               hipSuccess);
+    TREE_LAUNCH(n, k_tree_place, nkey_s, val, d_start, t->d_node, n_pairs, n, fp64, d_nuc0, t->d_word, t->d_nuc,
+                item_node);
+    // geometry
+    TREE_LAUNCH(n, k_tree_bounds, u.d_pairs, d_rec, d_nuc0, n_pairs, n, fp64, item_node, t->d_parent, d_box);
+    TREE_LAUNCH(nn, k_tree_centres, d_box, nn, t->d_geo, d_rad);
+    TREE_LAUNCH(n, k_tree_radii, u.d_pairs, d_rec, d_nuc0, n_pairs, n, fp64, item_node, t->d_parent, t->d_geo, d_rad);
+    TREE_LAUNCH(nn, k_tree_radii_out, d_rad, nn, t->d_geo);
+    TREE_CHECK(hipStreamSynchronize(st) == hipSuccess);
+    return ENV_OK;
+}
+
+}  // namespace
+
+Tree* build_tree(const UpdateState& u, const uint32_t* d_rec, const std::vector<double>& nuc,
+                 const std::vector<int32_t>& nuc_begin, const std::vector<int32_t>& nuc_end, bool fp64,
+                 env_status* st) {
+    *st = ENV_OK;
+    const int64_t n_nuc = int64_t(nuc.size() / 4), n = u.n_pairs + n_nuc;
+    if (u.n_pairs < kTreeMinPairs || n > kTreeMaxItems || u.n_groups <= 0 || u.n_groups >= (1 << 27) ||
+        int64_t(nuc_begin.size()) != u.n_groups || int64_t(nuc_end.size()) != u.n_groups)
+        return nullptr;
+    Tree* t = new (std::nothrow) Tree;
+    if (!t) {
+        *st = ENV_E_NOMEM;
+        return nullptr;
+    }
+    t->fp64 = fp64;
+    t->P = tree_order(fp64);
+    t->n_pairs = u.n_pairs;
+    t->n_nuc = n_nuc;
+    try {
+        *st = build(t, u, d_rec, nuc, nuc_begin, nuc_end);
+    } catch (const std::bad_alloc&) {
+        *st = ENV_E_NOMEM;
+    }
+    if (*st != ENV_OK) {
+        free_tree(t);
+        return nullptr;
+    }
+    return t;
+}
+
+void free_tree(Tree* t) {
+    if (!t) return;
+    for (void* p : t->owned) (void)hipFree(p);
+    delete t;
+}
+
+int refresh_tree(const Tree& t, const UpdateState& u, const uint32_t* d_rec, void* stream) {
+    hipStream_t st = static_cast<hipStream_t>(stream);
+    if (t.n_pairs > 0) {
+        const int per = kB / 16;
+        hipLaunchKernelGGL(k_tree_copy, dim3(unsigned((t.n_pairs + per - 1) / per)), dim3(kB), 0, st, u.d_pairs,
+                           t.d_word, t.n_pairs, t.fp64 ? 1 : 0, d_rec, t.d_rec);
+        if (hipGetLastError() != hipSuccess) return -1;
+    }
+    MomentArgs a{};
+    a.chunk = static_cast<const Chunk*>(t.d_chunk);
+    a.chunk_begin = t.d_chunk_begin;
+    a.node = t.d_node;
+    a.rec = t.d_rec;
+    a.nuc = t.d_nuc;
+    a.child = t.d_child;
+    a.child_begin = t.d_child_begin;
+    a.parent = t.d_parent;
+    a.geo = t.d_geo;
+    a.tab = t.d_tab;
+    a.coef = t.d_coef;
+    a.thr = t.d_thr;
+    a.test = t.d_test;
+    a.eps = t.fp64 ? kTreeEps64 : kTreeEps32;
+    const size_t pw = size_t(part_words(t.P)) * sizeof(double);
+    if (hipMallocAsync(reinterpret_cast<void**>(&a.part), size_t(t.n_chunks) * pw, st) != hipSuccess) return -1;
+    if (hipMallocAsync(reinterpret_cast<void**>(&a.up), size_t(t.n_nodes) * pw, st) != hipSuccess) {
+        (void)hipFreeAsync(a.part, st);
+        return -1;
+    }
+    if (t.fp64) hipLaunchKernelGGL((k_tree_p2m<kTreeOrd64, true>), dim3(unsigned(t.n_chunks)), dim3(kB), 0, st, a);
+    else hipLaunchKernelGGL((k_tree_p2m<kTreeOrd32, false>), dim3(unsigned(t.n_chunks)), dim3(kB), 0, st, a);
+    bool ok = hipGetLastError() == hipSuccess;
+    for (int d = int(t.level_begin.size()) - 2; d >= 0 && ok; --d) {
+        const int n = t.level_begin[size_t(d) + 1] - t.level_begin[size_t(d)];
+        if (n <= 0) continue;
+        a.by_depth = t.d_by_depth + t.level_begin[size_t(d)];
+        if (t.fp64) hipLaunchKernelGGL((k_tree_nodes<kTreeOrd64>), dim3(unsigned(n)), dim3(kB), 0, st, a);
+        else hipLaunchKernelGGL((k_tree_nodes<kTreeOrd32>), dim3(unsigned(n)), dim3(kB), 0, st, a);
+        ok = hipGetLastError() == hipSuccess;
+    }
+    (void)hipFreeAsync(a.up, st);
+    (void)hipFreeAsync(a.part, st);
+    if (!ok) return -1;
+    hipLaunchKernelGGL(k_tree_parents, dim3(grid_of(t.n_nodes)), dim3(kB), 0, st, t.d_parent, t.n_nodes, t.d_test);
+    return hipGetLastError() == hipSuccess ? 0 : -1;
+}
+
+TreeView tree_view(const Tree& t) {
+    TreeView v{};
+    v.test = t.d_test;
+    v.node = t.d_node;
+    v.thr = t.d_thr;
+    v.coef = t.d_coef;
+    v.beta = t.d_tab + tab_beta();
+    v.first = t.d_first;
+    v.rec = t.d_rec;
+    v.nuc = t.d_nuc;
+    v.n_trees = t.n_trees;
+    return v;
+}
+
+}  // namespace envpot

@@ -1,0 +1,128 @@
+// Multipole tree of an environment (not part of the C ABI).
+//
+// Every fragment group's items (its primitive pairs and its nuclei) sit in a
+// tree of cells.  A pair belongs to the smallest cell whose edge is not
+// below kTreeKappa times the pair's far-field radius, so a cell's own pairs
+// have radii in step with its size and a node's whole subtree is in the far
+// field a few cell edges away.  A node holds the multipole moments of its
+// subtree (electrons minus nuclei, FP64) about the middle of its items; a
+// block of points farther from that centre than the node's accepted radius
+// evaluates the node once, any other block evaluates the node's own items
+// and looks at its children.
+#pragma once
+
+#include <cstdint>
+#include <vector>
+
+#include "envpot_internal.h"
+
+namespace envpot {
+
+// Highest order of the moments: with cells in step with the pairs' radii an
+// accepted node lies at least about 4 of its radii away, where these orders
+// reach the tolerances below (potential: mean order used 6.5 and 14.3 on the
+// 200-atom ensemble; higher maxima save nothing).
+constexpr int kTreeOrd32 = 12;
+constexpr int kTreeOrd64 = 20;
+// Truncation tolerance of one node, relative to the sum of its items'
+// absolute charges over the distance: a quarter of (FP32C) and half of
+// (FP64) the tolerance of the Boys function's far form (2^-28, 2^-56).
+constexpr double kTreeEps32 = 9.313225746154785e-10;   // 2^-30
+constexpr double kTreeEps64 = 6.938893903907228e-18;   // 2^-57
+constexpr double kTreeKappa = 0.2;
+constexpr int kTreeLevels = 10;            // 3 bits of the cell code per level
+constexpr int kTreeTypes = kLMax + 2;      // items of a node: pairs by L, then nuclei
+// Cost of one own item by type (an L = 0 pair is 4), for the shares of waves.
+constexpr int kTreeW[kTreeTypes] = {4, 6, 10, 18, 30, 3};
+// A subtree cheaper than kTreeMinCost is one node; a child cheaper than a
+// quarter of that joins its parent's own items (a node's evaluation costs as
+// much as about 20 pairs).
+constexpr int64_t kTreeMinCost = 600;
+// Fewer pairs than this are evaluated without a tree, pair by pair in
+// segments (1,830 pairs: 1024 points 46 us without, 78 with).
+constexpr int64_t kTreeMinPairs = 8192;
+constexpr int64_t kTreeMaxItems = int64_t(1) << 26;   // run costs stay below 2^31
+
+constexpr int tree_order(bool fp64) { return fp64 ? kTreeOrd64 : kTreeOrd32; }
+constexpr int tree_ncoef(int P) { return (P + 1) * (P + 2) / 2; }        // (n, m >= 0)
+constexpr int tree_index(int P, int n, int m) { return m * (P + 1) - m * (m - 1) / 2 + (n - m); }
+constexpr int tree_thr_row(int P) { return (P + 1 + 3) & ~3; }           // floats per node
+constexpr int kTreeHead = 4;                                             // doubles before the coefficients
+constexpr int tree_words(int P) { return kTreeHead + 2 * tree_ncoef(P); }// doubles per node
+
+// Points per lane of a tree evaluation of n points: two, or one where that
+// leaves too few blocks (200 atoms: FP32C 1.66 ms for 131,072 points with two,
+// 1.78 with four, 1.82 with one; 32 points 53 us with one, 61 with two; FP64
+// 1000 points 0.25 / 0.28 ms with one / two, 131,072 points 5.5 / 5.0).
+constexpr int tree_np(int64_t n, bool fp64) { return n <= (fp64 ? 2048 : 512) ? 1 : 2; }
+// Workgroups that the split factor of a tree evaluation aims for, per compute
+// unit: each of a block's workgroups tests the tree's nodes again, so the
+// fewest that still even out the blocks' different work; few blocks differ
+// little (1000 points FP32C: 0.14 ms with 4, 0.20 with 16; 131,072 points
+// 1.66 ms with 16, 1.90 with 8).
+constexpr int64_t tree_want(int64_t blocks, int64_t cu_count) { return cu_count * (blocks <= 64 ? 4 : 16); }
+
+// Acceptance test of a node: centre and squared accepted radius, its own and
+// its parent's (a root's parent is never accepted: +inf); cost of its own
+// items.
+struct TreeTest {
+    double c[3], pc[3];
+    float r2, pr2;
+    int32_t cost, pad;
+};
+
+// A node's own items.
+struct TreeNode {
+    int64_t rec_off;        // first own pair record (4-byte words), pairs by L
+    int32_t cnt[kLMax + 1]; // own pairs per L
+    int32_t nuc_begin, nuc_end;
+    int32_t cost;           // sum of kTreeW over the own items
+};
+
+// Device side of one handle's tree.
+struct Tree {
+    int P = 0;
+    bool fp64 = false;
+    int32_t n_trees = 0;
+    int64_t n_nodes = 0, n_pairs = 0, n_nuc = 0, rec_words = 0;
+    std::vector<int32_t> level_begin;   // nodes by depth: ranges of d_by_depth
+    TreeTest* d_test = nullptr;
+    TreeNode* d_node = nullptr;
+    float* d_thr = nullptr;
+    double* d_coef = nullptr;
+    double* d_tab = nullptr;            // beta, conversion and moment tables
+    int32_t* d_first = nullptr;
+    uint32_t* d_rec = nullptr;
+    double* d_nuc = nullptr;
+    int64_t* d_word = nullptr;          // per pair (pair-list order): word of its record in d_rec
+    int32_t* d_parent = nullptr;        // per node
+    int32_t* d_child = nullptr;         // children lists
+    int32_t* d_child_begin = nullptr;   // per node + 1
+    int32_t* d_by_depth = nullptr;
+    double* d_geo = nullptr;            // per node: centre, item radius, far radius, (pad)
+    void* d_chunk = nullptr;            // shares of the nodes' own items
+    int32_t* d_chunk_begin = nullptr;   // per node + 1
+    int64_t n_chunks = 0;
+    int64_t device_bytes = 0;
+    std::vector<void*> owned;
+};
+
+struct UpdateState;
+
+// Build the tree of a handle whose records and update tables are on the
+// current device (synchronous).  nullptr with *st == ENV_OK when the input
+// does not fit the tree's index widths: the handle then evaluates pair by
+// pair.  nuc/nuc ranges: the handle's nuclei, grouped.
+Tree* build_tree(const UpdateState& u, const uint32_t* d_rec, const std::vector<double>& nuc,
+                 const std::vector<int32_t>& nuc_begin, const std::vector<int32_t>& nuc_end, bool fp64,
+                 env_status* st);
+void free_tree(Tree* t);
+
+// Copy the handle's records into the tree's order and recompute every
+// node's moments, coefficients and accepted radii (after each density fold),
+// asynchronous on the stream.
+int refresh_tree(const Tree& t, const UpdateState& u, const uint32_t* d_rec, void* stream);
+
+TreeView tree_view(const Tree& t);
+
+}  // namespace envpot

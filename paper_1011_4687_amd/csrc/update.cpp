@@ -15,6 +15,7 @@
 
 #include "devbuild_internal.h"
 #include "handle.h"
+#include "tree_internal.h"
 #include "update_internal.h"
 
 namespace envpot {
@@ -526,6 +527,7 @@ env_status env_potential_update_density(env_potential* h, const env_density* P, 
     if (launch_update_pairs(A, stream) != 0) return fail();
     if (launch_update_members(A, stream) != 0) return fail();
     if (launch_update_clusters(A, stream) != 0) return fail();
+    if (h->tree && refresh_tree(*h->tree, *u, h->d_rec, stream) != 0) return fail();
     if (hipStreamSynchronize(st) != hipSuccess) return ENV_E_DEVICE;
     lap("scale, records");
     h->info.electrons = electrons;

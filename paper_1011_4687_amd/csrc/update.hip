@@ -194,29 +194,50 @@ __global__ __launch_bounds__(kUpdBlock) void k_upd_members(UpdateArgs A) {
 
 // Merged far-field coefficients of a cluster: the members' h summed in FP64
 // in member order at the cluster's L (same exponents (a, b, c), re-indexed).
+// A wave per cluster, a lane per coefficient; the members' L and places are
+// read 64 at a time, so the loads of h do not wait for one another (a thread
+// per cluster walked its members one dependent load after the other: 2.3 ms
+// for 792 clusters of 63,672 members).
+constexpr int kClWaves = kUpdBlock / 64;
 __global__ __launch_bounds__(kUpdBlock) void k_upd_clusters(UpdateArgs A) {
-    const int64_t c = int64_t(blockIdx.x) * kUpdBlock + threadIdx.x;
+    const int64_t c = int64_t(blockIdx.x) * kClWaves + (threadIdx.x >> 6);
     if (c >= A.n_clusters) return;
+    const int lane = threadIdx.x & 63;
     const UpdCluster cl = A.clusters[c];
     const int Lc = cl.L, ncc = (Lc + 1) * (Lc + 2) * (Lc + 3) / 6;
-    double hsum[35];
-    for (int k = 0; k < ncc; ++k) hsum[k] = 0.0;
-    for (int64_t m = cl.begin; m < cl.end; ++m) {
-        const int Lm = A.pairs[A.members[m]].L;
-        const double* h = A.hm + A.moff[m];
-        int im = 0;
-        for (int a = 0; a <= Lm; ++a)
-            for (int b = 0; b <= Lm - a; ++b)
-                for (int cc = 0; cc <= Lm - a - b; ++cc, ++im) hsum[hidx(Lc, a, b, cc)] += h[im];
+    int ea = 0, eb = 0, ec = 0;  // this lane's exponents
+    if (lane < ncc) {
+        int k = lane;
+        while (k >= (Lc - ea + 1) * (Lc - ea + 2) / 2) {
+            k -= (Lc - ea + 1) * (Lc - ea + 2) / 2;
+            ++ea;
+        }
+        while (k >= Lc - ea - eb + 1) {
+            k -= Lc - ea - eb + 1;
+            ++eb;
+        }
+        ec = k;
     }
+    double hsum = 0.0;
+    for (int64_t m0 = cl.begin; m0 < cl.end; m0 += 64) {
+        const int n = int(cl.end - m0 < 64 ? cl.end - m0 : 64);
+        int Lv = 0;
+        int64_t ov = 0;
+        if (lane < n) {
+            Lv = A.pairs[A.members[m0 + lane]].L;
+            ov = A.moff[m0 + lane];
+        }
+#pragma unroll 8
+        for (int k = 0; k < n; ++k) {
+            const int Lm = __shfl(Lv, k);
+            const int64_t o = __shfl(ov, k);
+            if (lane < ncc && ea + eb + ec <= Lm) hsum += A.hm[o + hidx(Lm, ea, eb, ec)];
+        }
+    }
+    if (lane >= ncc) return;
     uint32_t* r = A.rec + cl.word;
-    if (A.fp64) {
-        double* rd = reinterpret_cast<double*>(r);
-        for (int k = 0; k < ncc; ++k) rd[kClHead64 + k] = hsum[k];
-    } else {
-        float* f = reinterpret_cast<float*>(r + kClHead32);
-        for (int k = 0; k < ncc; ++k) f[k] = float(hsum[k]);
-    }
+    if (A.fp64) reinterpret_cast<double*>(r)[kClHead64 + lane] = hsum;
+    else reinterpret_cast<float*>(r + kClHead32)[lane] = float(hsum);
 }
 
 unsigned blocks_for(int64_t n) { return unsigned((n + kUpdBlock - 1) / kUpdBlock); }
@@ -356,7 +377,7 @@ int launch_update_members(const UpdateArgs& a, void* stream) {
 
 int launch_update_clusters(const UpdateArgs& a, void* stream) {
     if (a.n_clusters <= 0) return 0;
-    hipLaunchKernelGGL(k_upd_clusters, dim3(blocks_for(a.n_clusters)), dim3(kUpdBlock), 0,
+    hipLaunchKernelGGL(k_upd_clusters, dim3(unsigned((a.n_clusters + kClWaves - 1) / kClWaves)), dim3(kUpdBlock), 0,
                        static_cast<hipStream_t>(stream), a);
     return hipGetLastError() == hipSuccess ? 0 : -1;
 }
