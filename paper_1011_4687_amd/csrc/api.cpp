@@ -92,10 +92,7 @@ constexpr int64_t kWantWavesPerSimd = 48;
 void tree_shape(const env_potential* h, int64_t n, int* np, int* k_out) {
     *np = tree_np(n, h->precision == ENV_PREC_FP64);
     const int64_t blocks = (n + 64 * *np - 1) / (64 * *np);
-    const int64_t want = tree_want(blocks, h->cu_count);
-    int k = 0;
-    while (k < kMaxSplitLog2 && (blocks << k) < want) ++k;
-    *k_out = k;
+    *k_out = tree_klog(blocks, h->cu_count, kMaxSplitLog2);
 }
 
 void choose_shape(const env_potential* h, int64_t n, int* np_out, int* k_out) {
@@ -451,7 +448,8 @@ env_status env_potential_create(const env_nucleus* nuclei, int32_t n_nuclei,
         }
         lap("update tables");
         if (st == ENV_OK && h->upd && merge && env_int("ENVPOT_NO_TREE", 0) == 0) {
-            h->tree = build_tree(*h->upd, h->d_rec, pl.nuc, pl.group_nuc_begin, pl.group_nuc_end, fp64, &st);
+            h->tree = build_tree(tree_source(*h->upd, h->d_rec, h->fp, fp64), pl.nuc, pl.group_nuc_begin, pl.group_nuc_end, fp64,
+                                 &st);
             if (h->tree) h->device_bytes += h->tree->device_bytes;
             lap("tree");
         }

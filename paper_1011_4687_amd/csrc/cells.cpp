@@ -15,6 +15,8 @@
 #include "cells_internal.h"
 #include "envpot_internal.h"
 #include "handle.h"
+#include "sort_internal.h"
+#include "tree_internal.h"
 
 struct env_cells {
     int device = -1;
@@ -26,6 +28,7 @@ struct env_cells {
     double* d_nuc = nullptr;
     int32_t* d_split = nullptr;    // split tables for S = 1, 2, ..., 64
     int64_t split_off[envpot::kMaxSplitLog2 + 1] = {};
+    envpot::Tree* tree = nullptr;  // cells and nuclei as point charges, for the batched mode
     double* d_part = nullptr;      // single-point mode: one partial per workgroup
     unsigned int* d_ticket = nullptr;
     int one_grid = 128;            // workgroups of single-point mode 0
@@ -52,6 +55,7 @@ void free_cells(env_cells* h) {
     (void)resident_stop(h);
     if (h->rstream) (void)hipStreamDestroy(h->rstream);
     if (h->box) (void)hipHostFree(h->box);
+    envpot::free_tree(h->tree);
     (void)hipFree(h->d_relay);
     (void)hipFree(h->d_rpart);
     (void)hipFree(h->d_rticket);
@@ -137,6 +141,48 @@ void cells_shape(const env_cells* h, int64_t n, int* np, int* klog) {
     *klog = k;
 }
 
+// Batched evaluation through the tree: the potential kernel on a tree
+// without pairs.
+env_status tree_eval(const env_cells* h, const double* points, int64_t n, double* out, void* stream) {
+    using namespace envpot;
+    hipStream_t st = static_cast<hipStream_t>(stream);
+    const int np = tree_np(n, h->precision == ENV_PREC_FP64);
+    int k = tree_klog((n + 64 * np - 1) / (64 * np), h->cu_count, kMaxSplitLog2);
+    if (const char* e = std::getenv("ENVPOT_CELLS_SPLIT_LOG2")) {  // tuning override
+        const int v = std::atoi(e);
+        if (v >= 0 && v <= kMaxSplitLog2) k = v;
+    }
+    const int S = 1 << k;
+    const char* ns = std::getenv("ENVPOT_NO_SORT");
+    const bool no_sort = ns && *ns && std::atoi(ns) != 0;
+    const bool large = n >= kSortMinPoints && n <= int64_t(INT32_MAX) && !stream_capturing(stream);
+    uint32_t* order = nullptr;
+    double* part = nullptr;
+    env_status rc = ENV_OK;
+    if (!no_sort && (large || order_small(n))) {
+        if (hipMallocAsync(reinterpret_cast<void**>(&order), size_t(n) * sizeof(uint32_t), st) != hipSuccess)
+            return ENV_E_NOMEM;
+        if ((large ? sort_order(points, n, order, stream) : order_points(points, n, nullptr, order, stream)) != 0)
+            rc = ENV_E_DEVICE;
+    }
+    if (rc == ENV_OK && S > 1 &&
+        hipMallocAsync(reinterpret_cast<void**>(&part), size_t(S) * size_t(n) * sizeof(double), st) != hipSuccess)
+        rc = ENV_E_NOMEM;
+    EvalArgs a{};
+    a.pts = points;
+    a.n = n;
+    a.out = S > 1 ? part : out;
+    a.tree = tree_view(*h->tree);
+    a.tree.S = S;
+    a.order = order;
+    if (rc == ENV_OK && (launch_potential(a, S, h->precision, np, stream) != 0 ||
+                         (S > 1 && launch_sum_splits(part, S, n, order, out, stream) != 0)))
+        rc = ENV_E_DEVICE;
+    if (part) (void)hipFreeAsync(part, st);
+    if (order) (void)hipFreeAsync(order, st);
+    return rc;
+}
+
 }  // namespace
 
 extern "C" {
@@ -210,6 +256,30 @@ env_status env_cells_create(const env_nucleus* nuclei, int32_t n_nuclei, const d
         if (st == ENV_OK && hipMalloc(reinterpret_cast<void**>(&h->d_ticket), sizeof(unsigned int)) != hipSuccess)
             st = ENV_E_NOMEM;
         if (st == ENV_OK && hipMemset(h->d_ticket, 0, sizeof(unsigned int)) != hipSuccess) st = ENV_E_DEVICE;
+        // the tree's charges: the nuclei, then minus the cells, one group
+        const char* nt = std::getenv("ENVPOT_NO_TREE");
+        if (st == ENV_OK && !(nt && *nt && std::atoi(nt) != 0)) {
+            nuc.reserve(nuc.size() + 4 * size_t(n_cells));
+            for (int64_t m = 0; m < n_cells; ++m)
+                nuc.insert(nuc.end(), {cells[4 * m], cells[4 * m + 1], cells[4 * m + 2], -cells[4 * m + 3]});
+            int64_t* no_pairs = nullptr;
+            if (hipMalloc(reinterpret_cast<void**>(&no_pairs), 2 * sizeof(int64_t)) != hipSuccess) st = ENV_E_NOMEM;
+            if (st == ENV_OK && hipMemset(no_pairs, 0, 2 * sizeof(int64_t)) != hipSuccess) st = ENV_E_DEVICE;
+            envpot::TreeSource src;
+            src.group_pairs = no_pairs;
+            src.n_groups = 1;
+            const bool fp64 = h->precision == ENV_PREC_FP64;
+            src.order = fp64 ? envpot::kTreeOrdCells64 : envpot::kTreeOrdCells32;
+            src.eps = fp64 ? envpot::kTreeEpsCells64 : envpot::kTreeEpsCells32;
+            src.nuc_eps = src.eps;
+            const int32_t count = int32_t(std::min<size_t>(nuc.size() / 4, size_t(INT32_MAX)));
+            if (st == ENV_OK && hipStreamSynchronize(nullptr) == hipSuccess)
+                h->tree = envpot::build_tree(src, nuc, {0}, {count}, fp64, &st);
+            if (st == ENV_OK && h->tree &&
+                (envpot::refresh_tree(*h->tree, src, nullptr) != 0 || hipStreamSynchronize(nullptr) != hipSuccess))
+                st = ENV_E_DEVICE;
+            (void)hipFree(no_pairs);
+        }
     } catch (const std::bad_alloc&) {
         st = ENV_E_NOMEM;
     }
@@ -227,6 +297,11 @@ env_status env_cells_eval(env_cells* h, const double* points, int64_t n, double*
     if (n == 0) return ENV_OK;
     if (!points || !out) return ENV_E_ARG;
     DeviceGuard g(h->device);
+    // FP64 calls of a few hundred points are quicker cell by cell (268,398
+    // cells: 300 points 0.18 ms against 0.20, 1000 0.22 against 0.26; 64
+    // points 0.18 against 0.10, 4000 0.60 against 0.54)
+    const bool direct = h->precision == ENV_PREC_FP64 && n > 128 && n < 2048;
+    if (h->tree && !direct) return tree_eval(h, points, n, out, stream);
     int np, k;
     cells_shape(h, n, &np, &k);
     const int S = 1 << k;

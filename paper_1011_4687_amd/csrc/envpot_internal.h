@@ -106,11 +106,14 @@ struct TreeView {
     const float* thr;        // per node a row: squared radius from which order p suffices
     const double* coef;      // per node: centre, scale, (cos, sin) coefficients by (m, n)
     const double* beta;      // recursion coefficients, same (m, n) index
+    const double* gamma;     // factor of the z derivative, likewise
     const int32_t* first;    // per tree: its root; the nodes of a tree are contiguous
     const uint32_t* rec;     // own pair records
     const double* nuc;       // own nuclei, 4 doubles each
     int32_t n_trees;         // 0: no tree (every pair on its own, segment by segment)
     int32_t S;               // split factor of the launch
+    int32_t P;               // highest order
+    int32_t pad;
 };
 
 struct EvalArgs {
@@ -229,6 +232,8 @@ void build_boys_tables(std::vector<float>& t32, std::vector<double>& t64, BoysPa
 int launch_potential(const EvalArgs& a, int S, int precision, int np, void* stream);
 // out[i] (with order: out[order[i]]) = sum over the S partials of point i, in fixed order.
 int launch_sum_splits(const double* partial, int S, int64_t n, const uint32_t* order, double* out, void* stream);
+// The same for rows of 4: out[4 order[i] + c], S x n x 4 partials.
+int launch_sum_rows4(const double* partial, int S, int64_t n, const uint32_t* order, double* out, void* stream);
 // Boxes (kSegBoxWords doubles each) of the unsplit segments segs[0, n_segs),
 // one workgroup per segment; empty segments get r2far max = +inf.
 int launch_segment_boxes(const Segment* segs, int n_segs, const uint32_t* rec, int fp64, double* boxes,

@@ -8,6 +8,7 @@
 #include "field_internal.h"
 #include "handle.h"
 #include "sort_internal.h"
+#include "tree_internal.h"
 
 namespace envpot {
 
@@ -51,7 +52,8 @@ void build_field_tables(const BoysParams& bp, std::vector<float>& t32, std::vect
 using namespace envpot;
 
 namespace {
-env_status field_core(env_potential* h, const double* points, int64_t n, double* out, void* stream);
+env_status field_core(env_potential* h, const double* points, int64_t n, const uint32_t* order, double* out,
+                      void* stream);
 }  // namespace
 
 extern "C" {
@@ -64,8 +66,23 @@ env_status env_potential_eval_field(env_potential* h, const double* points, int6
     if (!h->on_device) return ENV_E_STATE;
     DeviceGuard g(h->device);
     const char* ns = std::getenv("ENVPOT_NO_SORT");
-    if (n < kSortMinPoints || n > int64_t(INT32_MAX) || (ns && std::atoi(ns) != 0) || stream_capturing(stream))
-        return field_core(h, points, n, out, stream);
+    const bool no_sort = ns && std::atoi(ns) != 0;
+    if (h->tree) {  // the points through a spatial order, as env_potential_eval
+        const bool large = n >= kSortMinPoints && n <= int64_t(INT32_MAX) && !stream_capturing(stream);
+        if (no_sort || !(large || order_small(n))) return field_core(h, points, n, nullptr, out, stream);
+        hipStream_t st = static_cast<hipStream_t>(stream);
+        uint32_t* order = nullptr;
+        if (hipMallocAsync(reinterpret_cast<void**>(&order), size_t(n) * sizeof(uint32_t), st) != hipSuccess)
+            return ENV_E_NOMEM;
+        env_status rc = ENV_OK;
+        if ((large ? sort_order(points, n, order, stream) : order_points(points, n, nullptr, order, stream)) != 0)
+            rc = ENV_E_DEVICE;
+        if (rc == ENV_OK) rc = field_core(h, points, n, order, out, stream);
+        (void)hipFreeAsync(order, st);
+        return rc;
+    }
+    if (n < kSortMinPoints || n > int64_t(INT32_MAX) || no_sort || stream_capturing(stream))
+        return field_core(h, points, n, nullptr, out, stream);
     // large calls: evaluate the points in Morton order, then restore the caller's order
     hipStream_t st = static_cast<hipStream_t>(stream);
     double *spts = nullptr, *sout = nullptr;
@@ -77,7 +94,7 @@ env_status env_potential_eval_field(env_potential* h, const double* points, int6
         hipMallocAsync(reinterpret_cast<void**>(&order), size_t(n) * sizeof(uint32_t), st) != hipSuccess)
         rc = ENV_E_NOMEM;
     if (rc == ENV_OK && sort_points(points, n, spts, order, stream) != 0) rc = ENV_E_DEVICE;
-    if (rc == ENV_OK) rc = field_core(h, spts, n, sout, stream);
+    if (rc == ENV_OK) rc = field_core(h, spts, n, nullptr, sout, stream);
     if (rc == ENV_OK && scatter_rows4(sout, order, n, out, stream) != 0) rc = ENV_E_DEVICE;
     (void)hipFreeAsync(order, st);
     (void)hipFreeAsync(sout, st);
@@ -89,10 +106,13 @@ env_status env_potential_eval_field(env_potential* h, const double* points, int6
 
 namespace {
 
-env_status field_core(env_potential* h, const double* points, int64_t n, double* out, void* stream) {
+env_status field_core(env_potential* h, const double* points, int64_t n, const uint32_t* order, double* out,
+                      void* stream) {
     // two points per lane at four waves per SIMD (mid workload: FP32C 46 ms
-    // against 53 ms with one; FP64 79 against 81 ms)
-    int np = 2;
+    // against 53 ms with one; FP64 79 against 81 ms); with a tree one (its
+    // blocks are half as wide and the far form holds more per point: FP32C
+    // 2.9 ms against 3.1, FP64 9.4 against 9.9)
+    int np = h->tree ? 1 : 2;
     if (const char* e = std::getenv("ENVPOT_FIELD_NP")) {  // tuning override
         const int v = std::atoi(e);
         if (v == 1 || v == 2) np = v;
@@ -103,7 +123,11 @@ env_status field_core(env_potential* h, const double* points, int64_t n, double*
     const int64_t waves = (n + 64 * np - 1) / (64 * np);
     const int64_t want = int64_t(h->cu_count) * 4 * 48;
     int k = 0;
-    while (k < kMaxSplitLog2 && waves * (int64_t(1) << k) < want) ++k;
+    if (h->tree) {
+        k = tree_klog(waves, h->cu_count, kMaxSplitLog2);
+    } else {
+        while (k < kMaxSplitLog2 && waves * (int64_t(1) << k) < want) ++k;
+    }
     if (const char* e = std::getenv("ENVPOT_FIELD_SPLIT_LOG2")) {  // tuning override
         const int v = std::atoi(e);
         if (v >= 0 && v <= kMaxSplitLog2) k = v;
@@ -119,6 +143,9 @@ env_status field_core(env_potential* h, const double* points, int64_t n, double*
     a.boys = h->d_boys_field;
     a.boxes = h->use_boxes ? h->d_boxes : nullptr;
     a.fp = h->fp;
+    a.tree = h->tree ? tree_view_field(*h->tree) : TreeView{};
+    a.tree.S = S;
+    a.order = order;
     hipStream_t st = static_cast<hipStream_t>(stream);
     if (S == 1) {
         a.out = out;
@@ -130,7 +157,7 @@ env_status field_core(env_potential* h, const double* points, int64_t n, double*
         return ENV_E_NOMEM;
     a.out = part;
     int rc = launch_field(a, S, h->precision, np, stream);
-    if (rc == 0) rc = launch_sum_splits(part, S, 4 * n, nullptr, out, stream);
+    if (rc == 0) rc = launch_sum_rows4(part, S, n, order, out, stream);
     (void)hipFreeAsync(part, st);
     return rc == 0 ? ENV_OK : ENV_E_DEVICE;
 }

@@ -28,6 +28,7 @@
 #include "envpot_internal.h"
 #include "field_gen.h"
 #include "field_internal.h"
+#include "tree_eval.h"
 
 namespace envpot {
 namespace {
@@ -554,14 +555,170 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) voi
                          blockIdx.y, tab32);
 }
 
+// ------------------------------------------------------------ multipole tree
+
+// V and its gradient of one accepted node at one point, to order p, added to
+// a[0..3].  The polynomials Q_n of every m go up in the degree with their
+// derivative by r^2, Q'_n, beside them:
+//   Q_{n+1} = z Q_n - beta_n rho^2 Q_{n-1},
+//   Q'_{n+1} = z Q'_n - beta_n (rho^2 Q'_{n-1} + Q_{n-1}),
+//   d(w^m Q_n)/dz = gamma_n w^m Q_{n-1}   (r^2 taken along),
+// so H and its three derivatives come from one pass over the coefficients
+// (13 operations per (n, m), against 5 for the potential alone).
+__device__ __forceinline__ void tree_far_field(const GLB double* __restrict__ co, const GLB double* __restrict__ beta,
+                                               const GLB double* __restrict__ gamma, int P, int p, double px, double py,
+                                               double pz, double* a) {
+    const double s = co[3];
+    // X = P - C is the existing convention's minus: gradients with respect to
+    // the node's centre, as the pairs' with respect to theirs
+    const double X = co[0] - px, Y = co[1] - py, Z = co[2] - pz;
+    const double ri = rsqrt_far(__builtin_fma(X, X, __builtin_fma(Y, Y, Z * Z)));
+    const double sr = s * ri, f = sr * ri;
+    const double x = -X * f, y = -Y * f, z = -Z * f, u = sr * sr;
+    // sums over m by Horner's rule: sum a_m w^m, its derivative by w, sum b_m w^m, sum g_m w^m
+    double ar = 0.0, ai = 0.0, dr = 0.0, di = 0.0, br = 0.0, bi = 0.0, gr = 0.0, gi = 0.0;
+    for (int m = p; m >= 0; --m) {
+        const int at = tree_index(P, m, m);
+        const GLB double* c = co + kTreeHead + 2 * at;
+        const GLB double* be = beta + at;
+        const GLB double* ga = gamma + at;
+        double q0 = 0.0, q1 = 1.0, d0 = 0.0, d1 = 0.0;  // Q_{n-1}, Q_n, Q'_{n-1}, Q'_n
+        double sar = c[0], sai = c[1], sbr = 0.0, sbi = 0.0, sgr = 0.0, sgi = 0.0;
+        for (int n = 1; n <= p - m; ++n) {
+            const double bt = n > 1 ? be[n - 2] : 0.0;  // beta of degree m + n - 1
+            const double cr = c[2 * n], ci = c[2 * n + 1];
+            const double g = ga[n] * q1;
+            const double q2 = __builtin_fma(z, q1, -(bt * u) * q0);
+            const double d2 = __builtin_fma(z, d1, -bt * __builtin_fma(u, d0, q0));
+            sar = __builtin_fma(cr, q2, sar);
+            sai = __builtin_fma(ci, q2, sai);
+            sbr = __builtin_fma(cr, d2, sbr);
+            sbi = __builtin_fma(ci, d2, sbi);
+            sgr = __builtin_fma(cr, g, sgr);
+            sgi = __builtin_fma(ci, g, sgi);
+            q0 = q1;
+            q1 = q2;
+            d0 = d1;
+            d1 = d2;
+        }
+        // (coefficients are conj(c) w^m: the imaginary parts enter negated)
+        const double ndr = __builtin_fma(dr, x, __builtin_fma(-di, y, ar)), ndi = __builtin_fma(dr, y, __builtin_fma(di, x, ai));
+        dr = ndr;
+        di = ndi;
+        double t = __builtin_fma(ar, x, __builtin_fma(-ai, y, sar));
+        ai = __builtin_fma(ar, y, __builtin_fma(ai, x, -sai));
+        ar = t;
+        t = __builtin_fma(br, x, __builtin_fma(-bi, y, sbr));
+        bi = __builtin_fma(br, y, __builtin_fma(bi, x, -sbi));
+        br = t;
+        t = __builtin_fma(gr, x, __builtin_fma(-gi, y, sgr));
+        gi = __builtin_fma(gr, y, __builtin_fma(gi, x, -sgi));
+        gr = t;
+    }
+    // H = Re sum a w^m; d/dx and d/dy of w^m Q: m w^{m-1} (1, i) Q + w^m 2 (x, y) Q'
+    const double hx = __builtin_fma(2.0 * x, br, dr), hy = __builtin_fma(2.0 * y, br, -di), hz = gr;
+    const double t = ri * ri * ri;
+    const double tw = t * __builtin_fma(2.0, __builtin_fma(x, hx, __builtin_fma(y, hy, z * hz)), ar);
+    a[0] = __builtin_fma(ri, ar, a[0]);
+    // gradient by the point: t (s dH - X W); by the centre: its negative
+    a[1] = __builtin_fma(-tw, X, __builtin_fma(-t * s, hx, a[1]));
+    a[2] = __builtin_fma(-tw, Y, __builtin_fma(-t * s, hy, a[2]));
+    a[3] = __builtin_fma(-tw, Z, __builtin_fma(-t * s, hz, a[3]));
+}
+
+template <int NP, bool F64>
+struct FieldEval {
+    const double *cx, *cy, *cz;
+    const float* tab32;
+    const GLB double* boys64;
+    const FieldParams& fp;
+    const GLB double* gamma;
+    int P;
+    double (*ge)[4];
+
+    template <int L>
+    __device__ __forceinline__ void run(const GLB uint32_t* __restrict__ rec, int n) {
+        if constexpr (F64) pairs_f64<L, NP, false>(rec, n, cx, cy, cz, boys64, fp.ratio64[L], ge);
+        else pairs_f32<L, NP, false>(rec, n, cx, cy, cz, tab32, fp.ratio32[L], ge);
+    }
+    __device__ __forceinline__ void nucleus(double qx, double qy, double qz, double qZ) {
+#pragma unroll
+        for (int k = 0; k < NP; ++k) {
+            const double dx = cx[k] - qx, dy = cy[k] - qy, dz = cz[k] - qz;
+            const double ri = rsqrt(__builtin_fma(dx, dx, __builtin_fma(dy, dy, dz * dz)));
+            const double zr = qZ * ri, f = zr * ri * ri;
+            ge[k][0] -= zr;
+            ge[k][1] -= f * dx;
+            ge[k][2] -= f * dy;
+            ge[k][3] -= f * dz;
+        }
+    }
+    __device__ __forceinline__ void far(const GLB double* __restrict__ co, const GLB double* __restrict__ beta, int p) {
+#pragma unroll
+        for (int k = 0; k < NP; ++k) tree_far_field(co, beta, gamma, P, p, cx[k], cy[k], cz[k], ge[k]);
+    }
+};
+
+// Split s of the field at point block pblock (64 NP points).
+template <int NP, bool F64>
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) void k_tree_field(FieldArgs a) {
+    __shared__ float tab32[F64 ? 1 : kFieldMaxRowsF32 * kFieldRowF32];
+    __shared__ TreeShared<64 * NP * 4> sh;
+    if constexpr (!F64) {
+        const float* g = static_cast<const float*>(a.boys);
+        for (int i = threadIdx.x; i < a.fp.rows32 * kFieldRowF32; i += kBlock) tab32[i] = g[i];
+        __syncthreads();
+    }
+    const PTS double* __restrict__ pts = gpts(a.pts);
+    const PTS uint32_t* __restrict__ order = gpts(a.order);
+    const int64_t n = a.n, base = (int64_t)blockIdx.x * (64 * NP);
+    const int s = blockIdx.y, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    double cx[NP], cy[NP], cz[NP], ge[NP][4], lo[3], hi[3];
+#pragma unroll
+    for (int k = 0; k < NP; ++k) {
+        const int64_t i = base + lane + 64 * k;
+        int64_t ic = i < n ? i : n - 1;  // ragged tail: recompute the last point
+        if (order) ic = order[ic];
+        cx[k] = pts[3 * ic];
+        cy[k] = pts[3 * ic + 1];
+        cz[k] = pts[3 * ic + 2];
+#pragma unroll
+        for (int c = 0; c < 4; ++c) ge[k][c] = 0.0;
+    }
+    block_box<NP>(cx, cy, cz, lo, hi);
+    FieldEval<NP, F64> ev{cx, cy, cz, tab32, glb(static_cast<const double*>(a.boys)), a.fp, glb(a.tree.gamma), a.tree.P, ge};
+    tree_walk<F64>(a.tree, s, lo, hi, sh.lists, ev);
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < NP; ++k)
+#pragma unroll
+        for (int c = 0; c < 4; ++c) sh.acc[wave][4 * (lane + 64 * k) + c] = ge[k][c];
+    __syncthreads();
+    // V = nuclear - electronic; E = -grad V = nuclear field - (electronic gradient)
+    for (int j = tid; j < 64 * NP * 4; j += kBlock) {
+        const double v = (sh.acc[0][j] + sh.acc[1][j]) + (sh.acc[2][j] + sh.acc[3][j]);
+        const int64_t o = base + (j >> 2);
+        if (o < n) a.out[4 * ((int64_t)s * n + (order && a.tree.S == 1 ? int64_t(order[o]) : o)) + (j & 3)] = -v;
+    }
+}
+
 }  // namespace
 
 int launch_field(const FieldArgs& a, int S, int precision, int np, void* stream) {
     hipStream_t st = static_cast<hipStream_t>(stream);
-    const int64_t per = (int64_t)kBlock * np;
+    const bool tree = a.tree.n_trees > 0;
+    const int64_t per = (int64_t)(tree ? 64 : kBlock) * np;
     const dim3 grid((unsigned)((a.n + per - 1) / per), (unsigned)S);
     const dim3 block(kBlock);
-    if (precision == ENV_PREC_FP64) {
+    if (tree) {
+        if (precision == ENV_PREC_FP64) {
+            if (np == 2) hipLaunchKernelGGL((k_tree_field<2, true>), grid, block, 0, st, a);
+            else hipLaunchKernelGGL((k_tree_field<1, true>), grid, block, 0, st, a);
+        } else {
+            if (np == 2) hipLaunchKernelGGL((k_tree_field<2, false>), grid, block, 0, st, a);
+            else hipLaunchKernelGGL((k_tree_field<1, false>), grid, block, 0, st, a);
+        }
+    } else if (precision == ENV_PREC_FP64) {
         if (np == 2) hipLaunchKernelGGL((k_field<2, true>), grid, block, 0, st, a);
         else hipLaunchKernelGGL((k_field<1, true>), grid, block, 0, st, a);
     } else {

@@ -38,6 +38,8 @@ struct FieldArgs {
     const double* boxes;     // segment boxes (Segment::box), or nullptr: test every pair
     double* out;             // S == 1: [n][4] (V, Ex, Ey, Ez); S > 1: partials [S][n][4]
     FieldParams fp;
+    TreeView tree;           // with a tree (field radii): V and E through it
+    const uint32_t* order;   // ... at pts[order[i]], or nullptr
 };
 
 // Host tables and thresholds (both precisions; bp holds the potential's thresholds).

@@ -38,7 +38,7 @@
 #include "envpot_internal.h"
 #include "hermite_gen.h"
 #include "sort_internal.h"
-#include "tree_internal.h"
+#include "tree_eval.h"
 
 namespace envpot {
 namespace {
@@ -441,14 +441,6 @@ __device__ __forceinline__ int clusters_f64(const GLB uint32_t* __restrict__ rec
     return i;
 }
 
-// The value of v in the first active lane, as a wave-uniform (scalar) value.
-__device__ __forceinline__ double wave_uniform(double v) {
-    const uint64_t b = __builtin_bit_cast(uint64_t, v);
-    const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)b);
-    const uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)(b >> 32));
-    return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
-}
-
 // One workgroup's share: points of point block `pblock` against the pair
 // range of split `s` (all of it when S == 1).
 template <int NP, bool F64>
@@ -679,61 +671,15 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) voi
 
 // ------------------------------------------------------------ multipole tree
 
-// Lists of one workgroup: every wave appends to its own part.
-constexpr int kNearWave = 128;  // nodes whose own items are to be evaluated
-constexpr int kFarWave = 128;   // accepted nodes
-constexpr int kChunkCap = 256;  // runs of up to 64 nodes of open trees, one per wave step
-
-// LDS of the tree evaluation besides the Boys table.  acc is used after the
-// lists.
-template <int NP>
-struct TreeShared {
-    union {
-        struct {
-            int32_t near_node[4][kNearWave];
-            int32_t near_cost[4][kNearWave];
-            int32_t far_node[4][kFarWave];
-            int32_t list_node[4 * kNearWave];   // the waves' parts one after the other
-            int64_t list_cost[4 * kNearWave];   // ... and the exclusive prefix of their cost
-            int32_t list_far[4 * kFarWave];
-            int32_t list_order[4 * kFarWave];
-            int32_t chunk_begin[kChunkCap];
-            int32_t chunk_end[kChunkCap];
-        };
-        double acc[4][64 * NP];
-    };
-    uint64_t scan[4];
-    int32_t count[4];                            // near | far << 16, per wave
-    int32_t more[4];
-};
-
-// Exclusive prefix sum over the workgroup in thread order; total in *sum.
-__device__ __forceinline__ uint64_t block_scan(uint64_t v, uint64_t* tmp, uint64_t* sum) {
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    uint64_t x = v;
-#pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-        const uint64_t y = __shfl_up(x, o);
-        if (lane >= o) x += y;
-    }
-    __syncthreads();
-    if (lane == 63) tmp[wave] = x;
-    __syncthreads();
-    uint64_t base = 0, all = 0;
-#pragma unroll
-    for (int w = 0; w < 4; ++w) {
-        if (w < wave) base += tmp[w];
-        all += tmp[w];
-    }
-    *sum = all;
-    return base + x - v;
-}
-
 // Potential of one accepted node at M points, to order p: the harmonic
 // polynomial at X s / |X|^2 by a Clenshaw recursion in the degree for every
 // m and Horner's rule in (x + iy) over m; with
 //   Q_{n+1} = z Q_n - beta_n rho^2 Q_{n-1}   (monic in z),
-// two fused multiply-adds per coefficient and one multiply per (n, m).
+// two fused multiply-adds per coefficient and one multiply per (n, m), all
+// in FP64 (FP64 and FP32 FMA rates are within 15 %, and rounded to FP32 the
+// moments of the nodes near by would add an error of the FP32C kernel's own
+// size).  Bound by FP64 FMA issue; the two steps per iteration change places
+// so that no value is moved, and their coefficients come with one load.
 template <int M>
 __device__ __forceinline__ void tree_far(const GLB double* __restrict__ co, const GLB double* __restrict__ beta, int P,
                                          int p, const double* cx, const double* cy, const double* cz, double* ele) {
@@ -761,18 +707,26 @@ __device__ __forceinline__ void tree_far(const GLB double* __restrict__ co, cons
             i1[k] = c[1];
             r2[k] = i2[k] = 0.0;
         }
-        for (int n = p - m - 1; n >= 0; --n) {
-            c -= 2;
-            const double cr = c[0], ci = c[1], bt = b[n];
+        int n = p - m - 1;
+        for (; n > 0; n -= 2) {
+            c -= 4;
+            const double cr = c[2], ci = c[3], dr = c[0], di = c[1], bt = b[n], bu = b[n - 1];
+#pragma unroll
+            for (int k = 0; k < M; ++k) {
+                const double v = -bt * u[k], w = -bu * u[k];
+                r2[k] = __builtin_fma(z[k], r1[k], __builtin_fma(v, r2[k], cr));
+                i2[k] = __builtin_fma(z[k], i1[k], __builtin_fma(v, i2[k], ci));
+                r1[k] = __builtin_fma(z[k], r2[k], __builtin_fma(w, r1[k], dr));
+                i1[k] = __builtin_fma(z[k], i2[k], __builtin_fma(w, i1[k], di));
+            }
+        }
+        if (n == 0) {
+            const double cr = c[-2], ci = c[-1], bt = b[0];
 #pragma unroll
             for (int k = 0; k < M; ++k) {
                 const double v = -bt * u[k];
-                const double tr = __builtin_fma(z[k], r1[k], __builtin_fma(v, r2[k], cr));
-                const double ti = __builtin_fma(z[k], i1[k], __builtin_fma(v, i2[k], ci));
-                r2[k] = r1[k];
-                i2[k] = i1[k];
-                r1[k] = tr;
-                i1[k] = ti;
+                r1[k] = __builtin_fma(z[k], r1[k], __builtin_fma(v, r2[k], cr));
+                i1[k] = __builtin_fma(z[k], i1[k], __builtin_fma(v, i2[k], ci));
             }
         }
 #pragma unroll
@@ -790,15 +744,20 @@ __device__ __forceinline__ void tree_far(const GLB double* __restrict__ co, cons
             r1[k] = c[0];
             r2[k] = 0.0;
         }
-        for (int n = p - 1; n >= 0; --n) {
-            c -= 2;
-            const double cr = c[0], bt = beta[n];
+        int n = p - 1;
+        for (; n > 0; n -= 2) {
+            c -= 4;
+            const double cr = c[2], dr = c[0], bt = beta[n], bu = beta[n - 1];
 #pragma unroll
             for (int k = 0; k < M; ++k) {
-                const double tr = __builtin_fma(z[k], r1[k], __builtin_fma(-bt * u[k], r2[k], cr));
-                r2[k] = r1[k];
-                r1[k] = tr;
+                r2[k] = __builtin_fma(z[k], r1[k], __builtin_fma(-bt * u[k], r2[k], cr));
+                r1[k] = __builtin_fma(z[k], r2[k], __builtin_fma(-bu * u[k], r1[k], dr));
             }
+        }
+        if (n == 0) {
+            const double cr = c[-2], bt = beta[0];
+#pragma unroll
+            for (int k = 0; k < M; ++k) r1[k] = __builtin_fma(z[k], r1[k], __builtin_fma(-bt * u[k], r2[k], cr));
         }
 #pragma unroll
         for (int k = 0; k < M; ++k)
@@ -806,69 +765,42 @@ __device__ __forceinline__ void tree_far(const GLB double* __restrict__ co, cons
     }
 }
 
-// Items [a, b) of a run of cnt items of weight W that starts at cost c,
-// within the cost range [lo, hi): an item belongs to the range its first
-// cost unit lies in.
-template <int W>
-__device__ __forceinline__ void run_share(int64_t c, int cnt, int64_t lo, int64_t hi, int& a, int& b) {
-    const int64_t top = int64_t(cnt) * W;
-    const int64_t l = lo - c, h = hi - c;
-    const uint32_t lc = uint32_t(l < 0 ? 0 : (l > top ? top : l)), hc = uint32_t(h < 0 ? 0 : (h > top ? top : h));
-    a = int((lc + W - 1) / W);
-    b = int((hc + W - 1) / W);
-}
-
-template <int L, int NP, bool F64>
-__device__ __forceinline__ void tree_run(const GLB uint32_t* __restrict__ rec, int64_t& word, int64_t& c, int cnt,
-                                         int64_t lo, int64_t hi, const double* cx, const double* cy, const double* cz,
-                                         const float* tab32, const GLB double* __restrict__ boys64, double* ele) {
-    int a, b;
-    run_share<kTreeW[L]>(c, cnt, lo, hi, a, b);
-    if (b > a) {
-        if constexpr (F64) pairs_f64<L, NP, false>(rec + word + int64_t(a) * rec64_words(L), b - a, cx, cy, cz, boys64, ele);
-        else pairs_f32<L, NP, false>(rec + word + int64_t(a) * rec32_words(L), b - a, cx, cy, cz, 0.0, 0.0, 0.0, tab32, ele);
-    }
-    c += int64_t(cnt) * kTreeW[L];
-    word += int64_t(cnt) * (F64 ? rec64_words(L) : rec32_words(L));
-}
-
-__device__ __forceinline__ double wave_min(double v) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v = fmin(v, __shfl_xor(v, o));
-    return wave_uniform(v);
-}
-
-// Squared distance of the block's box from a node's centre.
-__device__ __forceinline__ double box_r2(const double* c, const double* lo, const double* hi) {
-    double r2 = 0.0;
-#pragma unroll
-    for (int d = 0; d < 3; ++d) {
-        const double g = fmax(0.0, fmax(lo[d] - c[d], c[d] - hi[d]));
-        r2 = __builtin_fma(g, g, r2);
-    }
-    return r2;
-}
-
-// One workgroup's share (split s of S) of a block of 64 NP points: every
-// wave holds all of the block's points.  The workgroup tests the nodes
-// against the block's bounding box, one node per thread, and collects the
-// accepted ones with the order they need and the nodes whose own items are
-// to be evaluated; the own items' cost is then cut into S x 4 equal parts
-// and part 4 s + w is wave w's, the accepted nodes go round the parts.  All
-// S workgroups of a block build the same lists, so the cut is exact however
-// the near work is spread over the tree, and the sums have a fixed order.
 template <int NP, bool F64>
-__device__ __forceinline__ void tree_work(const PTS double* __restrict__ pts, const PTS uint32_t* __restrict__ order,
-                                          int64_t n, const TreeView& tv,
-                                          const GLB double* __restrict__ boys64, double* __restrict__ out,
-                                          int64_t pblock, int s, const float* tab32, TreeShared<NP>& sh) {
-    constexpr int P = tree_order(F64);
-    constexpr int TR = tree_thr_row(P);
-    const int tid = threadIdx.x, lane = tid & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int64_t base = pblock * (64 * NP);
-    double cx[NP], cy[NP], cz[NP], ve[NP];
-    double lo[3] = {HUGE_VAL, HUGE_VAL, HUGE_VAL}, hi[3] = {-HUGE_VAL, -HUGE_VAL, -HUGE_VAL};
+struct PotentialEval {
+    const double *cx, *cy, *cz;
+    const float* tab32;
+    const GLB double* boys64;
+    double* ve;  // electrons minus nuclei
+    int P;
+
+    template <int L>
+    __device__ __forceinline__ void run(const GLB uint32_t* __restrict__ rec, int n) {
+        if constexpr (F64) pairs_f64<L, NP, false>(rec, n, cx, cy, cz, boys64, ve);
+        else pairs_f32<L, NP, false>(rec, n, cx, cy, cz, 0.0, 0.0, 0.0, tab32, ve);
+    }
+    __device__ __forceinline__ void nucleus(double qx, double qy, double qz, double qZ) {
+#pragma unroll
+        for (int k = 0; k < NP; ++k) {
+            const double dx = cx[k] - qx, dy = cy[k] - qy, dz = cz[k] - qz;
+            ve[k] -= qZ * rsqrt(__builtin_fma(dx, dx, __builtin_fma(dy, dy, dz * dz)));
+        }
+    }
+    __device__ __forceinline__ void far(const GLB double* __restrict__ co, const GLB double* __restrict__ beta, int p) {
+        constexpr int M = NP < 2 ? NP : 2;
+#pragma unroll
+        for (int k = 0; k < NP; k += M) tree_far<M>(co, beta, P, p, cx + k, cy + k, cz + k, ve + k);
+    }
+};
+
+// Split s of the potential at point block pblock (64 NP points).
+template <int NP, bool F64>
+__device__ __forceinline__ void tree_block(const EvalArgs& a, int64_t pblock, int s, const float* tab32,
+                                           TreeShared<64 * NP>& sh) {
+    const PTS double* __restrict__ pts = gpts(a.pts);
+    const PTS uint32_t* __restrict__ order = gpts(a.order);
+    const int64_t n = a.n, base = pblock * (64 * NP);
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    double cx[NP], cy[NP], cz[NP], ve[NP], lo[3], hi[3];
 #pragma unroll
     for (int k = 0; k < NP; ++k) {
         const int64_t i = base + lane + 64 * k;
@@ -878,246 +810,27 @@ __device__ __forceinline__ void tree_work(const PTS double* __restrict__ pts, co
         cy[k] = pts[3 * ic + 1];
         cz[k] = pts[3 * ic + 2];
         ve[k] = 0.0;
-        lo[0] = fmin(lo[0], cx[k]);
-        lo[1] = fmin(lo[1], cy[k]);
-        lo[2] = fmin(lo[2], cz[k]);
-        hi[0] = fmax(hi[0], cx[k]);
-        hi[1] = fmax(hi[1], cy[k]);
-        hi[2] = fmax(hi[2], cz[k]);
     }
-#pragma unroll
-    for (int d = 0; d < 3; ++d) {
-        lo[d] = wave_min(lo[d]);
-        hi[d] = -wave_min(-hi[d]);
-    }
-    const int parts = 4 * tv.S, part = 4 * s + wave;
-    const GLB TreeNode* nodes = glb(tv.node);
-    const GLB uint32_t* rec = glb(tv.rec);
-    const GLB double* nuc = glb(tv.nuc);
-    const GLB double* coef = glb(tv.coef);
-    const GLB double* beta = glb(tv.beta);
-    int nn = 0, nf = 0;  // entries of this wave's part of the lists
-
-    // Evaluate the collected lists: they are put together in wave order, cut
-    // by cost, and every wave evaluates its share.
-    auto evaluate = [&]() {
-        int nw[4], fw[4];
-#pragma unroll
-        for (int w = 0; w < 4; ++w) {
-            const int c = __builtin_amdgcn_readfirstlane(sh.count[w]);
-            nw[w] = c & 0xffff;
-            fw[w] = c >> 16;
-        }
-        const int n_near = nw[0] + nw[1] + nw[2] + nw[3], n_far = fw[0] + fw[1] + fw[2] + fw[3];
-        auto part_of = [](const int* c, int e, int& w) {  // entry e of the concatenation: its part and place
-            w = 0;
-            while (w < 3 && e >= c[w]) e -= c[w++];
-            return e;
-        };
-        uint64_t own = 0, cost;
-        constexpr int kEach = 4 * kNearWave / kBlock;
-        int32_t node[kEach], pc[kEach];
-#pragma unroll
-        for (int q = 0; q < kEach; ++q) {
-            const int e = kEach * tid + q;
-            node[q] = pc[q] = 0;
-            if (e < n_near) {
-                int w;
-                const int f = part_of(nw, e, w);
-                node[q] = sh.near_node[w][f];
-                pc[q] = sh.near_cost[w][f];
-            }
-            own += uint64_t(pc[q]);
-        }
-        uint64_t at = block_scan(own, sh.scan, &cost);
-#pragma unroll
-        for (int q = 0; q < kEach; ++q) {
-            const int e = kEach * tid + q;
-            if (e < n_near) {
-                sh.list_node[e] = node[q];
-                sh.list_cost[e] = int64_t(at);
-            }
-            at += uint64_t(pc[q]);
-        }
-        // the order every accepted node needs
-        for (int e = tid; e < n_far; e += kBlock) {
-            int w;
-            const int f = part_of(fw, e, w);
-            const int nd = sh.far_node[w][f];
-            const float4* th = reinterpret_cast<const float4*>(tv.thr + int64_t(nd) * TR);
-            const double cc[3] = {tv.test[nd].c[0], tv.test[nd].c[1], tv.test[nd].c[2]};
-            const float rf = float(box_r2(cc, lo, hi) * (1.0 - 1e-6));
-            int o = 0;
-#pragma unroll
-            for (int q = 0; q < TR / 4; ++q) {
-                const float4 v = th[q];
-                o += (v.x > rf) + (v.y > rf) + (v.z > rf) + (v.w > rf);
-            }
-            sh.list_far[e] = nd;
-            sh.list_order[e] = o < P ? o : P;
-        }
-        __syncthreads();
-        const int64_t total = int64_t((uint64_t(__builtin_amdgcn_readfirstlane(uint32_t(cost >> 32))) << 32) |
-                                      __builtin_amdgcn_readfirstlane(uint32_t(cost)));
-        const int64_t clo = total / parts * part + total % parts * part / parts;
-        const int64_t chi = total / parts * (part + 1) + total % parts * (part + 1) / parts;
-        if (chi > clo) {
-            int a = 0, b = n_near;  // the last node whose cost begins at clo or before
-            while (b - a > 1) {
-                const int mid = (a + b) >> 1;
-                if (sh.list_cost[mid] <= clo) a = mid;
-                else b = mid;
-            }
-            for (int e = __builtin_amdgcn_readfirstlane(a); e < n_near; ++e) {
-                const uint64_t cv = uint64_t(sh.list_cost[e]);
-                int64_t c = int64_t((uint64_t(__builtin_amdgcn_readfirstlane(uint32_t(cv >> 32))) << 32) |
-                                    __builtin_amdgcn_readfirstlane(uint32_t(cv)));
-                if (c >= chi) break;
-                const GLB TreeNode* nd = nodes + __builtin_amdgcn_readfirstlane(sh.list_node[e]);
-                int64_t word = nd->rec_off;
-                tree_run<0, NP, F64>(rec, word, c, nd->cnt[0], clo, chi, cx, cy, cz, tab32, boys64, ve);
-                tree_run<1, NP, F64>(rec, word, c, nd->cnt[1], clo, chi, cx, cy, cz, tab32, boys64, ve);
-                tree_run<2, NP, F64>(rec, word, c, nd->cnt[2], clo, chi, cx, cy, cz, tab32, boys64, ve);
-                tree_run<3, NP, F64>(rec, word, c, nd->cnt[3], clo, chi, cx, cy, cz, tab32, boys64, ve);
-                tree_run<4, NP, F64>(rec, word, c, nd->cnt[4], clo, chi, cx, cy, cz, tab32, boys64, ve);
-                const int nb = nd->nuc_begin;
-                int qa, qb;
-                run_share<kTreeW[kLMax + 1]>(c, nd->nuc_end - nb, clo, chi, qa, qb);
-                for (int q = nb + qa; q < nb + qb; ++q) {
-                    const double qx = nuc[4 * q], qy = nuc[4 * q + 1], qz = nuc[4 * q + 2], qZ = nuc[4 * q + 3];
-#pragma unroll
-                    for (int k = 0; k < NP; ++k) {
-                        const double dx = cx[k] - qx, dy = cy[k] - qy, dz = cz[k] - qz;
-                        ve[k] -= qZ * rsqrt(__builtin_fma(dx, dx, __builtin_fma(dy, dy, dz * dz)));
-                    }
-                }
-            }
-        }
-        constexpr int M = NP < 2 ? NP : 2;
-        for (int e = part; e < n_far; e += parts) {
-            const int nd = __builtin_amdgcn_readfirstlane(sh.list_far[e]);
-            const int p = __builtin_amdgcn_readfirstlane(sh.list_order[e]);
-            const GLB double* co = coef + int64_t(nd) * tree_words(P);
-#pragma unroll
-            for (int k = 0; k < NP; k += M) tree_far<M>(co, beta, P, p, cx + k, cy + k, cz + k, ve + k);
-        }
-    };
-    // Class of a node: 2 accepted, 1 its own items are evaluated, 0 neither
-    // (its parent is accepted, or it has none of its own).
-    auto classify = [&](const TreeTest& t) -> int {
-        const double rp = box_r2(t.pc, lo, hi), r2 = box_r2(t.c, lo, hi);
-        if (rp >= double(t.pr2) && rp < 1e300) return 0;
-        if (r2 >= double(t.r2) && r2 < 1e300) return 2;
-        return t.cost > 0 ? 1 : 0;
-    };
-    auto append = [&](int cls, int nd, int cost) {
-        const uint64_t mf = __builtin_amdgcn_ballot_w64(cls == 2), mn = __builtin_amdgcn_ballot_w64(cls == 1);
-        auto below = [](uint64_t m) {
-            return __builtin_amdgcn_mbcnt_hi(uint32_t(m >> 32), __builtin_amdgcn_mbcnt_lo(uint32_t(m), 0));
-        };
-        if (cls == 2) sh.far_node[wave][nf + below(mf)] = nd;
-        if (cls == 1) {
-            const int f = nn + below(mn);
-            sh.near_node[wave][f] = nd;
-            sh.near_cost[wave][f] = cost;
-        }
-        nf += __popcll(mf);
-        nn += __popcll(mn);
-    };
-    auto room = [&]() { return nn <= kNearWave - 64 && nf <= kFarWave - 64; };
-    // Meeting point of the waves: the lists are evaluated when some wave has
-    // no room for another step or `last` is set; false when some wave has
-    // steps left (`left`).
-    auto meet = [&](bool left, bool last) -> bool {
-        if (lane == 0) {
-            sh.count[wave] = nn | nf << 16;
-            sh.more[wave] = (left ? 1 : 0) | (room() ? 0 : 2);
-        }
-        __syncthreads();
-        const int m = __builtin_amdgcn_readfirstlane(sh.more[0] | sh.more[1] | sh.more[2] | sh.more[3]);
-        if ((m & 2) || (last && !(m & 1))) {
-            evaluate();
-            nn = nf = 0;
-        }
-        __syncthreads();
-        return !(m & 1);
-    };
-
-    for (int t0 = 0; t0 < tv.n_trees; t0 += kBlock) {
-        // roots: accepted, or the tree is open and its nodes are tested in
-        // runs of 64
-        int cls = 0, root = 0, count = 0, cost = 0;
-        if (t0 + tid < tv.n_trees) {
-            root = tv.first[t0 + tid];
-            const TreeTest t = tv.test[root];
-            cls = classify(t);
-            cost = t.cost;
-            if (cls != 2) count = tv.first[t0 + tid + 1] - root - 1;
-        }
-        append(cls, root, cost);
-        uint64_t sum;
-        const int runs = (count + 63) >> 6;
-        const int at = int(block_scan(uint64_t(runs), sh.scan, &sum));
-        const int total = __builtin_amdgcn_readfirstlane(int(sum));
-        for (int w0 = 0; w0 == 0 || w0 < total; w0 += kChunkCap) {
-            for (int r = max(0, w0 - at); r < runs && at + r < w0 + kChunkCap; ++r) {
-                sh.chunk_begin[at + r - w0] = root + 1 + 64 * r;
-                sh.chunk_end[at + r - w0] = root + 1 + min(count, 64 * r + 64);
-            }
-            __syncthreads();
-            const int here = min(kChunkCap, total - w0);
-            const bool final = t0 + kBlock >= tv.n_trees && w0 + kChunkCap >= total;
-            int c = wave;
-            do {
-                if (c < here && room()) {
-                    int nd = sh.chunk_begin[c] + lane, end = sh.chunk_end[c];
-                    TreeTest t;
-                    if (nd < end) t = tv.test[nd];
-                    for (;;) {
-                        // the next run's tests are loaded while this one's are made
-                        const int cn = c + 4;
-                        int ndn = 0, endn = 0;
-                        TreeTest tn;
-                        if (cn < here) {
-                            ndn = sh.chunk_begin[cn] + lane;
-                            endn = sh.chunk_end[cn];
-                            if (ndn < endn) tn = tv.test[ndn];
-                        }
-                        append(nd < end ? classify(t) : 0, nd, t.cost);
-                        c = cn;
-                        if (c >= here || !room()) break;
-                        nd = ndn;
-                        end = endn;
-                        t = tn;
-                    }
-                }
-            } while (!meet(c < here, final));
-        }
-    }
+    block_box<NP>(cx, cy, cz, lo, hi);
+    PotentialEval<NP, F64> ev{cx, cy, cz, tab32, glb(static_cast<const double*>(a.boys)), ve, a.tree.P};
+    tree_walk<F64>(a.tree, s, lo, hi, sh.lists, ev);
     // the waves' sums in wave order
+    __syncthreads();
 #pragma unroll
     for (int k = 0; k < NP; ++k) sh.acc[wave][lane + 64 * k] = ve[k];
     __syncthreads();
     for (int j = tid; j < 64 * NP; j += kBlock) {
         const double v = (sh.acc[0][j] + sh.acc[1][j]) + (sh.acc[2][j] + sh.acc[3][j]);
-        if (base + j < n) {
-            const int64_t o = base + j;
-            out[(int64_t)s * n + (order && tv.S == 1 ? int64_t(order[o]) : o)] = -v;
-        }
+        const int64_t o = base + j;
+        if (o < n) a.out[(int64_t)s * n + (order && a.tree.S == 1 ? int64_t(order[o]) : o)] = -v;
     }
     __syncthreads();  // the next work item writes the lists
 }
 
 template <int NP, bool F64>
-__device__ __forceinline__ void tree_block(const EvalArgs& a, int64_t pblock, int s, const float* tab32,
-                                           TreeShared<NP>& sh) {
-    tree_work<NP, F64>(gpts(a.pts), gpts(a.order), a.n, a.tree, glb(static_cast<const double*>(a.boys)), a.out, pblock, s, tab32, sh);
-}
-
-template <int NP, bool F64>
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) void k_tree_potential(EvalArgs a) {
     __shared__ float tab32[F64 ? 1 : kBoysMaxRowsF32 * kBoysRowF32];
-    __shared__ TreeShared<NP> sh;
+    __shared__ TreeShared<64 * NP> sh;
     load_boys_lds<F64>(a.boys, a.bp.rows32, tab32);
     tree_block<NP, F64>(a, blockIdx.x, blockIdx.y, tab32, sh);
 }
@@ -1142,7 +855,7 @@ __device__ __forceinline__ T load_const(const T* p) {
 template <int NP, bool F64, bool TREE>
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) void k_potential_persistent(BatchArgs b) {
     __shared__ float tab32[F64 ? 1 : kBoysMaxRowsF32 * kBoysRowF32];
-    __shared__ typename std::conditional<TREE, TreeShared<NP>, int>::type sh;
+    __shared__ typename std::conditional<TREE, TreeShared<64 * NP>, int>::type sh;
     __shared__ unsigned long long item_sh;
     load_boys_lds<F64>(b.boys, b.rows32, tab32);
     for (;;) {
@@ -1169,8 +882,12 @@ __host__ __device__ __forceinline__ int devsized_shape(int64_t m, bool fp64, boo
                                                        int* np) {
     *np = tree ? tree_np(m, fp64) : (fp64 ? 2 : 4);
     const int64_t units = (m + 64 * *np - 1) / (64 * *np);
-    if (tree) want = tree_want(units, want);
     int k = 0;
+    if (tree) {
+        int kmax = kMaxSplitLog2;
+        while (kmax > 0 && (m << kmax) > part_cap) --kmax;
+        return tree_klog(units, want, kmax);
+    }
     while (k < kMaxSplitLog2 && (units << k) < want && (m << (k + 1)) <= part_cap) ++k;
     return k;
 }
@@ -1199,7 +916,7 @@ template <bool F64, bool TREE>
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) void k_potential_devsized(DevSizedArgs d) {
     constexpr int NP = TREE || F64 ? 2 : 4;
     __shared__ float tab32[F64 ? 1 : kBoysMaxRowsF32 * kBoysRowF32];
-    __shared__ typename std::conditional<TREE, TreeShared<NP>, int>::type sh;
+    __shared__ typename std::conditional<TREE, TreeShared<64 * NP>, int>::type sh;
     __shared__ unsigned long long item_sh;
     load_boys_lds<F64>(d.a.boys, d.a.bp.rows32, tab32);
     const int64_t m = *d.m;
@@ -1214,7 +931,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) voi
             drain(m, 64 * NP, k, d.counter, &item_sh,
                   [&](int64_t b, int s) { tree_block<NP, F64>(a, b, s, tab32, sh); });
         } else {
-            auto& sh1 = reinterpret_cast<TreeShared<1>&>(sh);
+            auto& sh1 = reinterpret_cast<TreeShared<64>&>(sh);
             drain(m, 64, k, d.counter, &item_sh, [&](int64_t b, int s) { tree_block<1, F64>(a, b, s, tab32, sh1); });
         }
     } else {
@@ -1343,7 +1060,21 @@ __global__ __launch_bounds__(kBlock) void k_sum_splits(const double* __restrict_
     out[order ? int64_t(order[i]) : i] = sum_partials(part + i, S, n);
 }
 
+__global__ __launch_bounds__(kBlock) void k_sum_rows4(const double* __restrict__ part, int S, int64_t n,
+                                                      const uint32_t* __restrict__ order, double* __restrict__ out) {
+    const int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+    if (i >= 4 * n) return;
+    const int64_t o = order ? 4 * int64_t(order[i >> 2]) + (i & 3) : i;
+    out[o] = sum_partials(part + i, S, 4 * n);
+}
+
 }  // namespace
+
+int launch_sum_rows4(const double* partial, int S, int64_t n, const uint32_t* order, double* out, void* stream) {
+    hipLaunchKernelGGL(k_sum_rows4, dim3((unsigned)((4 * n + kBlock - 1) / kBlock)), dim3(kBlock), 0,
+                       static_cast<hipStream_t>(stream), partial, S, n, order, out);
+    return hipGetLastError() == hipSuccess ? 0 : -1;
+}
 
 int launch_potential(const EvalArgs& a, int S, int precision, int np, void* stream) {
     hipStream_t st = static_cast<hipStream_t>(stream);

@@ -42,14 +42,15 @@ constexpr int kB = 256;
 // Doubles of Tree::d_tab: recursion coefficients of the evaluation, factor
 // from moment to evaluation coefficient, weight of |M|^2 in a degree's norm,
 // fold of D_tuv into Q_k^j (35 components x 5 values of j, complex), factor
-// of the step to R_n^m in its recursion.
+// of the step to R_n^m in its recursion, factor of d Q_n / dz.
 constexpr int tab_beta() { return 0; }
 constexpr int tab_fac(int P) { return tree_ncoef(P); }
 constexpr int tab_norm(int P) { return 2 * tree_ncoef(P); }
 constexpr int tab_fold(int P) { return 3 * tree_ncoef(P); }
 constexpr int tab_den(int P) { return tab_fold(P) + 35 * 5 * 2; }
-constexpr int tab_words(int P) { return tab_den(P) + tree_ncoef(P); }
-constexpr int kGeo = 6;   // doubles per node in d_geo: centre, item radius, far radius, pad
+constexpr int tab_gamma(int P) { return tab_den(P) + tree_ncoef(P); }
+constexpr int tab_words(int P) { return tab_gamma(P) + tree_ncoef(P); }
+constexpr int kGeo = 6;   // doubles per node in d_geo: centre, item radius, far radius, field's far radius
 
 __host__ __device__ inline int rec_words_of(int L, bool fp64) { return fp64 ? rec64_words(L) : rec32_words(L); }
 __device__ inline int64_t gid() { return int64_t(blockIdx.x) * kB + threadIdx.x; }
@@ -231,36 +232,41 @@ __global__ __launch_bounds__(kB) void k_tree_centres(const unsigned long long* b
     if (i >= n_nodes) return;
     for (int d = 0; d < 3; ++d)
         geo[kGeo * i + d] = 0.5 * (unordered(box[6 * i + d]) + unordered(box[6 * i + 3 + d]));
-    rad[2 * i] = rad[2 * i + 1] = 0ull;
+    rad[3 * i] = rad[3 * i + 1] = rad[3 * i + 2] = 0ull;
 }
 
-// Largest |item - centre| and largest |item - centre| + far-field radius.
+struct Ratios {
+    double r[kLMax + 2];  // square roots, per type
+};
+
+// Largest |item - centre| and largest |item - centre| + far-field radius (the
+// potential's and the field's).
 __global__ __launch_bounds__(kB) void k_tree_radii(const UpdPair* pairs, const uint32_t* rec, const double* nuc,
                                                    int64_t n_pairs, int64_t n_items, int fp64,
                                                    const int32_t* item_node, const int32_t* parent, const double* geo,
-                                                   unsigned long long* rad) {
+                                                   Ratios ratios, unsigned long long* rad) {
     const int64_t i = gid();
     if (i >= n_items) return;
     double c[3], rf;
     item_geo(pairs, rec, nuc, n_pairs, fp64, i, c, &rf);
+    const double rff = rf * ratios.r[i < n_pairs ? pairs[i].L : kLMax + 1];
     for (int nd = item_node[i]; nd >= 0; nd = parent[nd]) {
         const double* q = geo + kGeo * int64_t(nd);
         const double dx = c[0] - q[0], dy = c[1] - q[1], dz = c[2] - q[2];
         const double d = sqrt(dx * dx + dy * dy + dz * dz) * (1.0 + 1e-12);
         // non-negative doubles order like their bits
-        const unsigned long long a = (unsigned long long)__double_as_longlong(d),
-                                 f = (unsigned long long)__double_as_longlong(d + rf);
-        if (rad[2 * int64_t(nd)] < a) atomicMax(&rad[2 * int64_t(nd)], a);
-        if (rad[2 * int64_t(nd) + 1] < f) atomicMax(&rad[2 * int64_t(nd) + 1], f);
+        const double v[3] = {d, d + rf, d + rff};
+        for (int k = 0; k < 3; ++k) {
+            const unsigned long long b = (unsigned long long)__double_as_longlong(v[k]);
+            if (rad[3 * int64_t(nd) + k] < b) atomicMax(&rad[3 * int64_t(nd) + k], b);
+        }
     }
 }
 
 __global__ __launch_bounds__(kB) void k_tree_radii_out(const unsigned long long* rad, int64_t n_nodes, double* geo) {
     const int64_t i = gid();
     if (i >= n_nodes) return;
-    geo[kGeo * i + 3] = __longlong_as_double((long long)rad[2 * i]);
-    geo[kGeo * i + 4] = __longlong_as_double((long long)rad[2 * i + 1]);
-    geo[kGeo * i + 5] = 0.0;
+    for (int k = 0; k < 3; ++k) geo[kGeo * i + 3 + k] = __longlong_as_double((long long)rad[3 * i + k]);
 }
 
 // ---------------------------------------------------------------- refresh
@@ -301,7 +307,10 @@ struct MomentArgs {
     double* coef;
     float* thr;
     TreeTest* test;
+    float* thr_field;            // with test_field, or nullptr
+    TreeTest* test_field;
     double eps;
+    double nuc_size;             // what a unit of nuclear charge adds to the absolute charge
 };
 
 struct Cplx {
@@ -397,7 +406,7 @@ __device__ __forceinline__ void coef_nm(int t, int& n, int& m) {
 template <int P, bool F64>
 __global__ __launch_bounds__(kB) void k_tree_p2m(MomentArgs A) {
     constexpr int NC = tree_ncoef(P);
-    static_assert(NC <= kB, "one thread per coefficient");
+    constexpr int NT = (NC + kB - 1) / kB;  // coefficients of a thread: t, t + 256, ...
     static_assert(kBatch * (P + 1) <= kB, "one thread per item and order");
     __shared__ Cplx R[kBatch][NC];
     __shared__ Cplx Q[kBatch][15];  // order 4
@@ -409,7 +418,7 @@ __global__ __launch_bounds__(kB) void k_tree_p2m(MomentArgs A) {
     __shared__ double qabs[15 * kBatch];
     const int t = threadIdx.x;
     for (int k = t; k < 350; k += kB) fold[k] = A.tab[tab_fold(P) + k];
-    if (t < NC) den[t] = A.tab[tab_den(P) + t];
+    for (int k = t; k < NC; k += kB) den[k] = A.tab[tab_den(P) + k];
     // (k, j) of this thread's Q
     int qk = 0, qj = t % 15;
     while (qj > qk) qj -= ++qk;
@@ -417,9 +426,13 @@ __global__ __launch_bounds__(kB) void k_tree_p2m(MomentArgs A) {
     const TreeNode node = A.node[ck.node];
     const double* geo = A.geo + kGeo * int64_t(ck.node);
     const double inv = 1.0 / node_scale(geo);
-    int n, m;
-    coef_nm<P>(t, n, m);
-    Cplx acc{0.0, 0.0};
+    int n[NT], m[NT];
+    Cplx acc[NT];
+#pragma unroll
+    for (int k = 0; k < NT; ++k) {
+        coef_nm<P>(t + k * kB, n[k], m[k]);
+        acc[k] = Cplx{0.0, 0.0};
+    }
     double qa = 0.0;
     __syncthreads();
     for (int i0 = ck.begin; i0 < ck.end; i0 += kBatch) {
@@ -450,7 +463,7 @@ __global__ __launch_bounds__(kB) void k_tree_p2m(MomentArgs A) {
             if (L > kLMax) {
                 if (qk == 0) {
                     o.r = -d[3];
-                    size = fabs(d[3]);
+                    size = fabs(d[3]) * A.nuc_size;
                 }
             } else if (qk <= L) {
                 const int nc = kNComp[L];
@@ -482,15 +495,20 @@ __global__ __launch_bounds__(kB) void k_tree_p2m(MomentArgs A) {
             harmonics<P>(xs[it][0], xs[it][1], xs[it][2], t % (P + 1), den, R[it]);
         }
         __syncthreads();
-        if (t < NC)
-            for (int it = 0; it < nb; ++it) shift_add<P, 4>(Q[it], R[it], ls[it] > kLMax ? 0 : ls[it], n, m, acc);
+#pragma unroll
+        for (int k = 0; k < NT; ++k)
+            if (t + k * kB < NC)
+                for (int it = 0; it < nb; ++it)
+                    shift_add<P, 4>(Q[it], R[it], ls[it] > kLMax ? 0 : ls[it], n[k], m[k], acc[k]);
         __syncthreads();
     }
     double* o = A.part + int64_t(part_words(P)) * blockIdx.x;
-    if (t < NC) {
-        o[2 * t] = acc.r;
-        o[2 * t + 1] = acc.i;
-    }
+#pragma unroll
+    for (int k = 0; k < NT; ++k)
+        if (t + k * kB < NC) {
+            o[2 * (t + k * kB)] = acc[k].r;
+            o[2 * (t + k * kB) + 1] = acc[k].i;
+        }
     if (t < 15 * kBatch) qabs[t] = qa;
     __syncthreads();
     if (t == 0) {
@@ -504,18 +522,21 @@ __global__ __launch_bounds__(kB) void k_tree_p2m(MomentArgs A) {
 // shifted ones (fixed order), its evaluation coefficients and accepted
 // radii, and its moments shifted to its parent's centre.  A workgroup per
 // node; bound by latency (the shift's chain on the few nodes of a depth).
+constexpr int node_threads(int P) { return tree_ncoef(P) < kB ? kB : 2 * kB; }
 template <int P>
-__global__ __launch_bounds__(kB) void k_tree_nodes(MomentArgs A) {
+__global__ __launch_bounds__(node_threads(P)) void k_tree_nodes(MomentArgs A) {
     constexpr int NC = tree_ncoef(P);
+    static_assert(NC < node_threads(P), "one thread per coefficient and one for the charge");
     __shared__ Cplx M[NC];
     __shared__ Cplx R[NC];
     __shared__ double den[NC];
     __shared__ double bn[P + 1];
-    __shared__ float thr_sh[tree_thr_row(P)];
+    constexpr int TR = tree_thr_row(P);
+    __shared__ float thr_sh[2][TR];
     const int t = threadIdx.x;
     const int nd = A.by_depth[blockIdx.x];
     const double* geo = A.geo + kGeo * int64_t(nd);
-    const double c0 = geo[0], c1 = geo[1], c2 = geo[2], arad = geo[3], rfar = geo[4];
+    const double c0 = geo[0], c1 = geo[1], c2 = geo[2], arad = geo[3];
     const double s = node_scale(geo);
     int n, m;
     coef_nm<P>(t, n, m);
@@ -529,7 +550,7 @@ __global__ __launch_bounds__(kB) void k_tree_nodes(MomentArgs A) {
         acc.r += q[0];
         acc.i += q[1];
     }
-    double racc = 0.0;
+    double racc = 0.0, racc_field = 0.0;
     for (int c = A.child_begin[nd]; c < A.child_begin[nd + 1]; ++c) {
         const int ch = A.child[c];
         const double* q = A.up + int64_t(part_words(P)) * ch + w;
@@ -537,7 +558,9 @@ __global__ __launch_bounds__(kB) void k_tree_nodes(MomentArgs A) {
         acc.i += q[1];
         const double* cg = A.geo + kGeo * int64_t(ch);
         const double dx = cg[0] - c0, dy = cg[1] - c1, dz = cg[2] - c2;
-        racc = fmax(racc, (sqrt(double(A.test[ch].r2)) + sqrt(dx * dx + dy * dy + dz * dz)) * (1.0 + 1e-9));
+        const double d = sqrt(dx * dx + dy * dy + dz * dz);
+        racc = fmax(racc, (sqrt(double(A.test[ch].r2)) + d) * (1.0 + 1e-9));
+        if (A.test_field) racc_field = fmax(racc_field, (sqrt(double(A.test_field[ch].r2)) + d) * (1.0 + 1e-9));
     }
     if (t < NC) {
         M[t] = acc;
@@ -573,21 +596,27 @@ __global__ __launch_bounds__(kB) void k_tree_nodes(MomentArgs A) {
         bn[t] = sqrt(b);
     }
     __syncthreads();
-    if (t < tree_thr_row(P)) {
-        // smallest radius (at least the far-field radius and outside the
-        // items) from which the degrees above t stay below eps |charge|/R:
-        // sum_{n>t} B_n x^n + tail <= eps |charge|, x = s/R, where the tail
+    // smallest radii from which the orders suffice: the potential's by the
+    // first threads, the field's by the second wave's
+    const int fld = t >> 6, row = t & 63;
+    if (row < TR && (fld == 0 || (fld == 1 && A.thr_field))) {
+        // at least the far-field radius and outside the items, and such that
+        // the degrees above the order stay below eps |charge|/R:
+        // sum_{n>p} w_n B_n x^n + tail <= eps |charge|, x = s/R; w_n = 1, for
+        // the gradient (against |charge|/R^2) sqrt((n+1)(2n+1)) < 1.5 (n+1); the tail
         // beyond P continues the largest of the last three B_n four times over
         const double tol = A.eps * charge;
-        const double rmin = fmax(rfar, 1.02 * arad);
+        const double rmin = fmax(geo[4 + fld], 1.02 * arad);
         double r2 = HUGE_VAL;
-        if (t <= P) {
-            const double tail = 4.0 * fmax(bn[P], fmax(bn[P - 1], bn[P - 2]));
+        if (row <= P) {
+            double tail = 4.0 * fmax(bn[P], fmax(bn[P - 1], bn[P - 2]));
             const double xmax = rmin > 0.0 ? s / rmin : 0.98;
             auto over = [&](double x) {
-                double v = tail * x / (1.0 - x);
-                for (int k = P; k > t; --k) v = (v + bn[k]) * x;
-                for (int k = 0; k < t; ++k) v *= x;
+                const double g = 1.0 / (1.0 - x);
+                double v = tail * x * g;
+                if (fld) v *= 1.5 * (P + 2) * g;
+                for (int k = P; k > row; --k) v = (v + (fld ? 1.5 * (k + 1) : 1.0) * bn[k]) * x;
+                for (int k = 0; k < row; ++k) v *= x;
                 return !(v <= tol);
             };
             if (!over(xmax)) {
@@ -605,9 +634,10 @@ __global__ __launch_bounds__(kB) void k_tree_nodes(MomentArgs A) {
                     r2 *= r2;
                 }
             }
-            r2 = fmax(r2, racc * racc);  // a node is accepted only where all its children would be
+            const double ra = fld ? racc_field : racc;
+            r2 = fmax(r2, ra * ra);  // a node is accepted only where all its children would be
         }
-        thr_sh[t] = float(r2 * (1.0 + 1e-6));
+        thr_sh[fld][row] = float(r2 * (1.0 + 1e-6));
     }
     // meanwhile the other waves shift the moments to the parent's centre
     if (par >= 0) {
@@ -628,13 +658,13 @@ __global__ __launch_bounds__(kB) void k_tree_nodes(MomentArgs A) {
         if (t == 0) o[2 * NC] = charge;
     }
     __syncthreads();
-    if (t < tree_thr_row(P)) {
+    if (row < TR && (fld == 0 || (fld == 1 && A.thr_field))) {
         // radii do not grow with the order
-        float v = thr_sh[t];
-        for (int k = 0; k < t && k <= P; ++k) v = fminf(v, thr_sh[k]);
-        if (t > P) v = 0.0f;
-        A.thr[int64_t(tree_thr_row(P)) * nd + t] = v;
-        if (t == P) {
+        float v = thr_sh[fld][row];
+        for (int k = 0; k < row && k <= P; ++k) v = fminf(v, thr_sh[fld][k]);
+        if (row > P) v = 0.0f;
+        (fld ? A.thr_field : A.thr)[int64_t(TR) * nd + row] = v;
+        if (row == P) {
             TreeTest q;
             q.c[0] = c0;
             q.c[1] = c1;
@@ -644,19 +674,23 @@ __global__ __launch_bounds__(kB) void k_tree_nodes(MomentArgs A) {
             q.pr2 = HUGE_VALF;
             q.cost = A.node[nd].cost;
             q.pad = 0;
-            A.test[nd] = q;
+            (fld ? A.test_field : A.test)[nd] = q;
         }
     }
 }
 
 // Every node's copy of its parent's test.
-__global__ __launch_bounds__(kB) void k_tree_parents(const int32_t* parent, int64_t n_nodes, TreeTest* test) {
+__global__ __launch_bounds__(kB) void k_tree_parents(const int32_t* parent, int64_t n_nodes, TreeTest* test,
+                                                     TreeTest* field) {
     const int64_t i = gid();
     if (i >= n_nodes) return;
     const int p = parent[i];
     if (p < 0) return;
     for (int d = 0; d < 3; ++d) test[i].pc[d] = test[p].c[d];
     test[i].pr2 = test[p].r2;
+    if (!field) return;
+    for (int d = 0; d < 3; ++d) field[i].pc[d] = field[p].c[d];
+    field[i].pr2 = field[p].r2;
 }
 
 // ------------------------------------------------------------------- host
@@ -735,6 +769,7 @@ std::vector<double> tables(int P) {
             t[size_t(tab_fac(P) + i)] = w * lead;
             t[size_t(tab_norm(P) + i)] = w;
             t[size_t(tab_den(P) + i)] = n == m ? (m ? 0.5 / m : 1.0) : 1.0 / (double(n - m) * double(n + m));
+            t[size_t(tab_gamma(P) + i)] = n > m ? (double(n) * n - double(m) * m) / (2.0 * n - 1.0) : 0.0;
             lead *= (2 * n + 1) / (double(n + 1 - m) * double(n + 1 + m));
         }
     }
@@ -820,8 +855,8 @@ int bits_for(uint64_t top) {  // smallest b with 2^b > top
         if (!(x)) return ENV_E_DEVICE;       \
     } while (0)
 
-env_status build(Tree* t, const UpdateState& u, const uint32_t* d_rec, const std::vector<double>& nuc,
-                 const std::vector<int32_t>& nuc_begin, const std::vector<int32_t>& nuc_end) {
+env_status build(Tree* t, const TreeSource& u, const std::vector<double>& nuc, const std::vector<int32_t>& nuc_begin,
+                 const std::vector<int32_t>& nuc_end) {
     hipStream_t st = nullptr;
     if (hipStreamCreateWithFlags(&st, hipStreamNonBlocking) != hipSuccess) return ENV_E_DEVICE;
     struct Guard {
@@ -858,10 +893,10 @@ env_status build(Tree* t, const UpdateState& u, const uint32_t* d_rec, const std
         return ENV_E_NOMEM;
     TREE_CHECK(put(d_nuc0, nuc, st) && put(d_ng, nuc_group, st) && put(d_gnb, nuc_begin, st) &&
                put(d_gne, nuc_end, st));
-    hipLaunchKernelGGL(k_tree_cubes, dim3(unsigned(ng)), dim3(kB), 0, st, u.d_pairs, d_rec, d_nuc0, n_pairs, fp64,
-                       u.d_gpb, d_gnb, d_gne, d_cube);
+    hipLaunchKernelGGL(k_tree_cubes, dim3(unsigned(ng)), dim3(kB), 0, st, u.pairs, u.rec, d_nuc0, n_pairs, fp64,
+                       u.group_pairs, d_gnb, d_gne, d_cube);
     TREE_CHECK(hipGetLastError() == hipSuccess);
-    TREE_LAUNCH(n, k_tree_keys, u.d_pairs, d_rec, d_nuc0, d_ng, n_pairs, n, fp64, d_cube, key, val);
+    TREE_LAUNCH(n, k_tree_keys, u.pairs, u.rec, d_nuc0, d_ng, n_pairs, n, fp64, d_cube, key, val);
     size_t tb = 0;
     const int kb = 37 + bits_for(uint64_t(std::max(ng - 1, 0)));
     TREE_CHECK(hipcub::DeviceRadixSort::SortPairs(nullptr, tb, key, key_s, val, val_s, int(n), 0, kb, st) ==
@@ -962,6 +997,11 @@ env_status build(Tree* t, const UpdateState& u, const uint32_t* d_rec, const std
     t->d_test = keep<TreeTest>(t, nn);
     t->d_node = keep<TreeNode>(t, nn);
     t->d_thr = keep<float>(t, nn * tree_thr_row(P));
+    if (u.field) {
+        t->d_test_field = keep<TreeTest>(t, nn);
+        t->d_thr_field = keep<float>(t, nn * tree_thr_row(P));
+        if (!t->d_test_field || !t->d_thr_field) return ENV_E_NOMEM;
+    }
     t->d_coef = keep<double>(t, nn * tree_words(P));
     t->d_tab = keep<double>(t, tab_words(P));
     t->d_first = keep<int32_t>(t, int64_t(first.size()));
@@ -978,7 +1018,7 @@ env_status build(Tree* t, const UpdateState& u, const uint32_t* d_rec, const std
     t->d_chunk_begin = keep<int32_t>(t, nn + 1);
     uint32_t* d_start = tmp.get<uint32_t>(int64_t(start.size()));
     unsigned long long* d_box = tmp.get<unsigned long long>(6 * nn);
-    unsigned long long* d_rad = tmp.get<unsigned long long>(2 * nn);
+    unsigned long long* d_rad = tmp.get<unsigned long long>(3 * nn);
     if (!t->d_test || !t->d_node || !t->d_thr || !t->d_coef || !t->d_tab || !t->d_first || !t->d_rec || !t->d_nuc ||
         !t->d_word || !t->d_parent || !t->d_child || !t->d_child_begin || !t->d_by_depth || !t->d_geo || !t->d_chunk ||
         !t->d_chunk_begin ||
@@ -1005,9 +1045,13 @@ env_status build(Tree* t, const UpdateState& u, const uint32_t* d_rec, const std
     TREE_LAUNCH(n, k_tree_place, nkey_s, val, d_start, t->d_node, n_pairs, n, fp64, d_nuc0, t->d_word, t->d_nuc,
                 item_node);
     // geometry
-    TREE_LAUNCH(n, k_tree_bounds, u.d_pairs, d_rec, d_nuc0, n_pairs, n, fp64, item_node, t->d_parent, d_box);
+    Ratios ratios{};
+    for (int L = 0; L <= kLMax; ++L) ratios.r[L] = u.field ? std::sqrt(u.field_ratio[L]) * (1.0 + 1e-6) : 1.0;
+    ratios.r[kLMax + 1] = 1.0;
+    TREE_LAUNCH(n, k_tree_bounds, u.pairs, u.rec, d_nuc0, n_pairs, n, fp64, item_node, t->d_parent, d_box);
     TREE_LAUNCH(nn, k_tree_centres, d_box, nn, t->d_geo, d_rad);
-    TREE_LAUNCH(n, k_tree_radii, u.d_pairs, d_rec, d_nuc0, n_pairs, n, fp64, item_node, t->d_parent, t->d_geo, d_rad);
+    TREE_LAUNCH(n, k_tree_radii, u.pairs, u.rec, d_nuc0, n_pairs, n, fp64, item_node, t->d_parent, t->d_geo,
+                ratios, d_rad);
     TREE_LAUNCH(nn, k_tree_radii_out, d_rad, nn, t->d_geo);
     TREE_CHECK(hipStreamSynchronize(st) == hipSuccess);
     return ENV_OK;
@@ -1015,12 +1059,11 @@ env_status build(Tree* t, const UpdateState& u, const uint32_t* d_rec, const std
 
 }  // namespace
 
-Tree* build_tree(const UpdateState& u, const uint32_t* d_rec, const std::vector<double>& nuc,
-                 const std::vector<int32_t>& nuc_begin, const std::vector<int32_t>& nuc_end, bool fp64,
-                 env_status* st) {
+Tree* build_tree(const TreeSource& u, const std::vector<double>& nuc, const std::vector<int32_t>& nuc_begin,
+                 const std::vector<int32_t>& nuc_end, bool fp64, env_status* st) {
     *st = ENV_OK;
     const int64_t n_nuc = int64_t(nuc.size() / 4), n = u.n_pairs + n_nuc;
-    if (u.n_pairs < kTreeMinPairs || n > kTreeMaxItems || u.n_groups <= 0 || u.n_groups >= (1 << 27) ||
+    if (n < kTreeMinItems || n > kTreeMaxItems || u.n_groups <= 0 || u.n_groups >= (1 << 27) ||
         int64_t(nuc_begin.size()) != u.n_groups || int64_t(nuc_end.size()) != u.n_groups)
         return nullptr;
     Tree* t = new (std::nothrow) Tree;
@@ -1029,11 +1072,12 @@ Tree* build_tree(const UpdateState& u, const uint32_t* d_rec, const std::vector<
         return nullptr;
     }
     t->fp64 = fp64;
-    t->P = tree_order(fp64);
+    t->P = u.order;
+    t->eps = u.eps;
     t->n_pairs = u.n_pairs;
     t->n_nuc = n_nuc;
     try {
-        *st = build(t, u, d_rec, nuc, nuc_begin, nuc_end);
+        *st = build(t, u, nuc, nuc_begin, nuc_end);
     } catch (const std::bad_alloc&) {
         *st = ENV_E_NOMEM;
     }
@@ -1050,12 +1094,12 @@ void free_tree(Tree* t) {
     delete t;
 }
 
-int refresh_tree(const Tree& t, const UpdateState& u, const uint32_t* d_rec, void* stream) {
+int refresh_tree(const Tree& t, const TreeSource& u, void* stream) {
     hipStream_t st = static_cast<hipStream_t>(stream);
     if (t.n_pairs > 0) {
         const int per = kB / 16;
-        hipLaunchKernelGGL(k_tree_copy, dim3(unsigned((t.n_pairs + per - 1) / per)), dim3(kB), 0, st, u.d_pairs,
-                           t.d_word, t.n_pairs, t.fp64 ? 1 : 0, d_rec, t.d_rec);
+        hipLaunchKernelGGL(k_tree_copy, dim3(unsigned((t.n_pairs + per - 1) / per)), dim3(kB), 0, st, u.pairs,
+                           t.d_word, t.n_pairs, t.fp64 ? 1 : 0, u.rec, t.d_rec);
         if (hipGetLastError() != hipSuccess) return -1;
     }
     MomentArgs a{};
@@ -1072,28 +1116,39 @@ int refresh_tree(const Tree& t, const UpdateState& u, const uint32_t* d_rec, voi
     a.coef = t.d_coef;
     a.thr = t.d_thr;
     a.test = t.d_test;
-    a.eps = t.fp64 ? kTreeEps64 : kTreeEps32;
+    a.thr_field = t.d_thr_field;
+    a.test_field = t.d_test_field;
+    a.eps = t.eps;
+    a.nuc_size = u.nuc_eps / u.eps;
     const size_t pw = size_t(part_words(t.P)) * sizeof(double);
     if (hipMallocAsync(reinterpret_cast<void**>(&a.part), size_t(t.n_chunks) * pw, st) != hipSuccess) return -1;
     if (hipMallocAsync(reinterpret_cast<void**>(&a.up), size_t(t.n_nodes) * pw, st) != hipSuccess) {
         (void)hipFreeAsync(a.part, st);
         return -1;
     }
-    if (t.fp64) hipLaunchKernelGGL((k_tree_p2m<kTreeOrd64, true>), dim3(unsigned(t.n_chunks)), dim3(kB), 0, st, a);
-    else hipLaunchKernelGGL((k_tree_p2m<kTreeOrd32, false>), dim3(unsigned(t.n_chunks)), dim3(kB), 0, st, a);
-    bool ok = hipGetLastError() == hipSuccess;
+    bool ok = t.P == kTreeOrd32 || t.P == kTreeOrd64 || t.P == kTreeOrdCells32 || t.P == kTreeOrdCells64;
+    const dim3 chunks(unsigned(t.n_chunks));
+    if (t.P == kTreeOrd32) hipLaunchKernelGGL((k_tree_p2m<kTreeOrd32, false>), chunks, dim3(kB), 0, st, a);
+    else if (t.P == kTreeOrd64) hipLaunchKernelGGL((k_tree_p2m<kTreeOrd64, true>), chunks, dim3(kB), 0, st, a);
+    else if (t.P == kTreeOrdCells32) hipLaunchKernelGGL((k_tree_p2m<kTreeOrdCells32, false>), chunks, dim3(kB), 0, st, a);
+    else if (t.P == kTreeOrdCells64) hipLaunchKernelGGL((k_tree_p2m<kTreeOrdCells64, true>), chunks, dim3(kB), 0, st, a);
+    ok = ok && hipGetLastError() == hipSuccess;
     for (int d = int(t.level_begin.size()) - 2; d >= 0 && ok; --d) {
         const int n = t.level_begin[size_t(d) + 1] - t.level_begin[size_t(d)];
         if (n <= 0) continue;
         a.by_depth = t.d_by_depth + t.level_begin[size_t(d)];
-        if (t.fp64) hipLaunchKernelGGL((k_tree_nodes<kTreeOrd64>), dim3(unsigned(n)), dim3(kB), 0, st, a);
-        else hipLaunchKernelGGL((k_tree_nodes<kTreeOrd32>), dim3(unsigned(n)), dim3(kB), 0, st, a);
+        const dim3 nodes = dim3(unsigned(n)), threads = dim3(unsigned(node_threads(t.P)));
+        if (t.P == kTreeOrd32) hipLaunchKernelGGL((k_tree_nodes<kTreeOrd32>), nodes, threads, 0, st, a);
+        else if (t.P == kTreeOrd64) hipLaunchKernelGGL((k_tree_nodes<kTreeOrd64>), nodes, threads, 0, st, a);
+        else if (t.P == kTreeOrdCells32) hipLaunchKernelGGL((k_tree_nodes<kTreeOrdCells32>), nodes, threads, 0, st, a);
+        else hipLaunchKernelGGL((k_tree_nodes<kTreeOrdCells64>), nodes, threads, 0, st, a);
         ok = hipGetLastError() == hipSuccess;
     }
     (void)hipFreeAsync(a.up, st);
     (void)hipFreeAsync(a.part, st);
     if (!ok) return -1;
-    hipLaunchKernelGGL(k_tree_parents, dim3(grid_of(t.n_nodes)), dim3(kB), 0, st, t.d_parent, t.n_nodes, t.d_test);
+    hipLaunchKernelGGL(k_tree_parents, dim3(grid_of(t.n_nodes)), dim3(kB), 0, st, t.d_parent, t.n_nodes, t.d_test,
+                       t.d_test_field);
     return hipGetLastError() == hipSuccess ? 0 : -1;
 }
 
@@ -1108,6 +1163,15 @@ TreeView tree_view(const Tree& t) {
     v.rec = t.d_rec;
     v.nuc = t.d_nuc;
     v.n_trees = t.n_trees;
+    v.P = t.P;
+    v.gamma = t.d_tab + tab_gamma(t.P);
+    return v;
+}
+
+TreeView tree_view_field(const Tree& t) {
+    TreeView v = tree_view(t);
+    v.test = t.d_test_field;
+    v.thr = t.d_thr_field;
     return v;
 }
 

@@ -18,17 +18,27 @@
 
 namespace envpot {
 
-// Highest order of the moments: with cells in step with the pairs' radii an
-// accepted node lies at least about 4 of its radii away, where these orders
-// reach the tolerances below (potential: mean order used 6.5 and 14.3 on the
-// 200-atom ensemble; higher maxima save nothing).
+// Highest order of the moments.  Pairs: with cells in step with the pairs'
+// radii an accepted node lies at least about 4 of its radii away, where
+// these orders reach the tolerances (mean order used 6.5 and 14.3 on the
+// 200-atom ensemble; higher maxima save nothing).  Point charges have no
+// radius of their own, so a higher order accepts nodes nearer by and the
+// points meet fewer of them (268,398 cells, 131,072 points, FP32C: 630 nodes
+// a block with 12, 310 with 16; FP64 1660 with 20, 610 with 28).
 constexpr int kTreeOrd32 = 12;
 constexpr int kTreeOrd64 = 20;
+constexpr int kTreeOrdCells32 = 16;
+constexpr int kTreeOrdCells64 = 28;
+constexpr int kTreeOrdMax = 28;
 // Truncation tolerance of one node, relative to the sum of its items'
 // absolute charges over the distance: a quarter of (FP32C) and half of
 // (FP64) the tolerance of the Boys function's far form (2^-28, 2^-56).
-constexpr double kTreeEps32 = 9.313225746154785e-10;   // 2^-30
-constexpr double kTreeEps64 = 6.938893903907228e-18;   // 2^-57
+// Cells (V measured against 64 bits, without / with the tree): FP32C
+// 1.4e-7 / 1e-8, FP64 3.3e-14 / 3.2e-14.
+constexpr double kTreeEps32 = 9.313225746154785e-10;       // 2^-30
+constexpr double kTreeEps64 = 6.938893903907228e-18;       // 2^-57
+constexpr double kTreeEpsCells32 = 3.725290298461914e-09;  // 2^-28
+constexpr double kTreeEpsCells64 = 5.551115123125783e-17;  // 2^-54
 constexpr double kTreeKappa = 0.2;
 constexpr int kTreeLevels = 10;            // 3 bits of the cell code per level
 constexpr int kTreeTypes = kLMax + 2;      // items of a node: pairs by L, then nuclei
@@ -38,12 +48,11 @@ constexpr int kTreeW[kTreeTypes] = {4, 6, 10, 18, 30, 3};
 // quarter of that joins its parent's own items (a node's evaluation costs as
 // much as about 20 pairs).
 constexpr int64_t kTreeMinCost = 600;
-// Fewer pairs than this are evaluated without a tree, pair by pair in
-// segments (1,830 pairs: 1024 points 46 us without, 78 with).
-constexpr int64_t kTreeMinPairs = 8192;
+// Fewer items than this are evaluated without a tree, one after the other
+// (1,830 pairs: 1024 points 46 us without, 78 with).
+constexpr int64_t kTreeMinItems = 8192;
 constexpr int64_t kTreeMaxItems = int64_t(1) << 26;   // run costs stay below 2^31
 
-constexpr int tree_order(bool fp64) { return fp64 ? kTreeOrd64 : kTreeOrd32; }
 constexpr int tree_ncoef(int P) { return (P + 1) * (P + 2) / 2; }        // (n, m >= 0)
 constexpr int tree_index(int P, int n, int m) { return m * (P + 1) - m * (m - 1) / 2 + (n - m); }
 constexpr int tree_thr_row(int P) { return (P + 1 + 3) & ~3; }           // floats per node
@@ -55,12 +64,24 @@ constexpr int tree_words(int P) { return kTreeHead + 2 * tree_ncoef(P); }// doub
 // 1.78 with four, 1.82 with one; 32 points 53 us with one, 61 with two; FP64
 // 1000 points 0.25 / 0.28 ms with one / two, 131,072 points 5.5 / 5.0).
 constexpr int tree_np(int64_t n, bool fp64) { return n <= (fp64 ? 2048 : 512) ? 1 : 2; }
-// Workgroups that the split factor of a tree evaluation aims for, per compute
-// unit: each of a block's workgroups tests the tree's nodes again, so the
-// fewest that still even out the blocks' different work; few blocks differ
-// little (1000 points FP32C: 0.14 ms with 4, 0.20 with 16; 131,072 points
-// 1.66 ms with 16, 1.90 with 8).
-constexpr int64_t tree_want(int64_t blocks, int64_t cu_count) { return cu_count * (blocks <= 64 ? 4 : 16); }
+// Split factor 2^k of a tree evaluation of that many blocks: each of a
+// block's workgroups tests the tree's nodes again, so the fewest that fill
+// the chip and even out the blocks' different work.  Few blocks differ
+// little: 4 workgroups per compute unit (1000 points FP32C: 0.14 ms with 4,
+// 0.20 with 16); more blocks up to 16 (200 / 5000 atoms, 12,000 points: 0.38 /
+// 0.31 ms with 32 splits, 0.38 / 0.37 with 64; 30,000: 0.61 / 0.56 with 16,
+// 0.60 / 0.59 with 32), and two to four splits where the blocks alone fill
+// the chip (200,003 points: 2.14 ms with four, 2.26 with two).
+constexpr int tree_klog(int64_t blocks, int64_t cu_count, int kmax) {
+    int k = 0;
+    if (blocks <= 64) {
+        while (k < kmax && (blocks << k) < 4 * cu_count) ++k;
+        return k;
+    }
+    while (k < kmax && (blocks << (k + 1)) <= 16 * cu_count) ++k;
+    const int least = blocks < 8 * cu_count ? 2 : 1;
+    return k > least ? k : (least < kmax ? least : kmax);
+}
 
 // Acceptance test of a node: centre and squared accepted radius, its own and
 // its parent's (a root's parent is never accepted: +inf); cost of its own
@@ -82,11 +103,14 @@ struct TreeNode {
 // Device side of one handle's tree.
 struct Tree {
     int P = 0;
+    double eps = 0.0;
     bool fp64 = false;
     int32_t n_trees = 0;
     int64_t n_nodes = 0, n_pairs = 0, n_nuc = 0, rec_words = 0;
     std::vector<int32_t> level_begin;   // nodes by depth: ranges of d_by_depth
     TreeTest* d_test = nullptr;
+    TreeTest* d_test_field = nullptr;   // the same for V and E (pairs only): larger radii
+    float* d_thr_field = nullptr;
     TreeNode* d_node = nullptr;
     float* d_thr = nullptr;
     double* d_coef = nullptr;
@@ -99,7 +123,7 @@ struct Tree {
     int32_t* d_child = nullptr;         // children lists
     int32_t* d_child_begin = nullptr;   // per node + 1
     int32_t* d_by_depth = nullptr;
-    double* d_geo = nullptr;            // per node: centre, item radius, far radius, (pad)
+    double* d_geo = nullptr;            // per node: centre, item radius, far radius, field's far radius
     void* d_chunk = nullptr;            // shares of the nodes' own items
     int32_t* d_chunk_begin = nullptr;   // per node + 1
     int64_t n_chunks = 0;
@@ -107,22 +131,40 @@ struct Tree {
     std::vector<void*> owned;
 };
 
-struct UpdateState;
+struct UpdPair;
 
-// Build the tree of a handle whose records and update tables are on the
-// current device (synchronous).  nullptr with *st == ENV_OK when the input
-// does not fit the tree's index widths: the handle then evaluates pair by
-// pair.  nuc/nuc ranges: the handle's nuclei, grouped.
-Tree* build_tree(const UpdateState& u, const uint32_t* d_rec, const std::vector<double>& nuc,
-                 const std::vector<int32_t>& nuc_begin, const std::vector<int32_t>& nuc_end, bool fp64,
-                 env_status* st);
+// What a tree is built over, on the current device: pairs grouped by
+// fragment, with their records, and nuclei (point charges), grouped alike.
+struct TreeSource {
+    const UpdPair* pairs = nullptr;     // n_pairs: L, group and record word of each
+    int64_t n_pairs = 0;
+    const int64_t* group_pairs = nullptr;  // n_groups + 1: first pair of each group
+    const uint32_t* rec = nullptr;
+    int32_t n_groups = 0;
+    int order = 0;                      // highest order (one of the four above) and tolerance
+    double eps = 0.0;
+    double nuc_eps = 0.0;               // tolerance against the nuclei's charges (FP64 in both precisions)
+    bool field = false;                 // radii for the field too, from ...
+    double field_ratio[kLMax + 1] = {}; // ... squared far-field radius of the field over the record's, per L
+};
+
+// Build the tree (synchronous).  nullptr with *st == ENV_OK when the input
+// does not fit the tree's index widths: the handle then evaluates every item.
+// nuc: n x 4 (position, charge); nuc_begin, nuc_end: range of each group.
+Tree* build_tree(const TreeSource& src, const std::vector<double>& nuc, const std::vector<int32_t>& nuc_begin,
+                 const std::vector<int32_t>& nuc_end, bool fp64, env_status* st);
 void free_tree(Tree* t);
 
-// Copy the handle's records into the tree's order and recompute every
-// node's moments, coefficients and accepted radii (after each density fold),
-// asynchronous on the stream.
-int refresh_tree(const Tree& t, const UpdateState& u, const uint32_t* d_rec, void* stream);
+// Copy the records into the tree's order and recompute every node's moments,
+// coefficients and accepted radii (after the build and after each density
+// fold), asynchronous on the stream.
+int refresh_tree(const Tree& t, const TreeSource& src, void* stream);
 
 TreeView tree_view(const Tree& t);
+TreeView tree_view_field(const Tree& t);
+
+struct UpdateState;
+struct FieldParams;
+TreeSource tree_source(const UpdateState& u, const uint32_t* d_rec, const FieldParams& fp, bool fp64);  // update.cpp
 
 }  // namespace envpot

@@ -294,6 +294,21 @@ UpdateState* make_update_state_device(const PairList& meta, const PairSources& s
     return u;
 }
 
+TreeSource tree_source(const UpdateState& u, const uint32_t* d_rec, const FieldParams& fp, bool fp64) {
+    TreeSource s;
+    s.pairs = u.d_pairs;
+    s.n_pairs = u.n_pairs;
+    s.group_pairs = u.d_gpb;
+    s.rec = d_rec;
+    s.n_groups = u.n_groups;
+    s.order = fp64 ? kTreeOrd64 : kTreeOrd32;
+    s.eps = fp64 ? kTreeEps64 : kTreeEps32;
+    s.nuc_eps = kTreeEps64;
+    s.field = true;
+    for (int L = 0; L <= kLMax; ++L) s.field_ratio[L] = fp64 ? fp.ratio64[L] : double(fp.ratio32[L]);
+    return s;
+}
+
 }  // namespace envpot
 
 using namespace envpot;
@@ -527,7 +542,7 @@ env_status env_potential_update_density(env_potential* h, const env_density* P, 
     if (launch_update_pairs(A, stream) != 0) return fail();
     if (launch_update_members(A, stream) != 0) return fail();
     if (launch_update_clusters(A, stream) != 0) return fail();
-    if (h->tree && refresh_tree(*h->tree, *u, h->d_rec, stream) != 0) return fail();
+    if (h->tree && refresh_tree(*h->tree, tree_source(*u, h->d_rec, h->fp, A.fp64 != 0), stream) != 0) return fail();
     if (hipStreamSynchronize(st) != hipSuccess) return ENV_E_DEVICE;
     lap("scale, records");
     h->info.electrons = electrons;
