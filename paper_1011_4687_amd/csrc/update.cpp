@@ -52,6 +52,7 @@ void free_update_state(UpdateState* u) {
     (void)hipFree(u->d_woff);
     (void)hipFree(u->d_moff);
     (void)hipFree(u->d_hm);
+    (void)hipFree(u->d_member_of);
     (void)hipFree(u->d_exps);
     (void)hipFree(u->d_cnorm);
     (void)hipFree(u->d_W);
@@ -193,6 +194,14 @@ env_status group_tables(UpdateState* u) {
     env_status s = upload_vec(u->group_pair_begin, &u->d_gpb, u->device_bytes);
     if (s == ENV_OK) s = upload_vec(dropb, &u->d_dropb, u->device_bytes);
     if (s == ENV_OK) s = alloc_dev(2 * size_t(std::max(u->n_groups, 1)), &u->d_gq, u->device_bytes);
+    // where each pair's h goes among the clusters' members
+    if (s == ENV_OK) s = alloc_dev(size_t(u->n_pairs), &u->d_member_of, u->device_bytes);
+    if (s == ENV_OK && (u->n_members > int64_t(INT32_MAX) ||
+                        hipMemsetAsync(u->d_member_of, 0xff, size_t(std::max<int64_t>(u->n_pairs, 1)) * sizeof(int32_t),
+                                       nullptr) != hipSuccess ||
+                        launch_member_of(u->d_members, u->n_members, u->d_member_of, nullptr) != 0 ||
+                        hipStreamSynchronize(nullptr) != hipSuccess))
+        s = ENV_E_DEVICE;
     return s;
 }
 
@@ -500,6 +509,7 @@ env_status env_potential_update_density(env_potential* h, const env_density* P, 
     A.members = u->d_members;
     A.moff = u->d_moff;
     A.hm = u->d_hm;
+    A.member_of = u->d_member_of;
     A.n_members = int64_t(u->n_members);
     A.n_clusters = u->n_clusters;
     A.rec = h->d_rec;
@@ -540,7 +550,6 @@ env_status env_potential_update_density(env_potential* h, const env_density* P, 
     // (a trained surrogate) is out of date, even if a launch below fails
     ++h->density_gen;
     if (launch_update_pairs(A, stream) != 0) return fail();
-    if (launch_update_members(A, stream) != 0) return fail();
     if (launch_update_clusters(A, stream) != 0) return fail();
     if (h->tree && refresh_tree(*h->tree, tree_source(*u, h->d_rec, h->fp, A.fp64 != 0), stream) != 0) return fail();
     if (hipStreamSynchronize(st) != hipSuccess) return ENV_E_DEVICE;

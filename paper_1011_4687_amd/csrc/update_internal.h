@@ -120,6 +120,7 @@ struct UpdateArgs {
     const UpdCluster* clusters;
     const int64_t* members;     // pair indices
     const int64_t* moff;        // per member + 1: first word of its h in hm
+    const int32_t* member_of;   // per pair: its place among the members, or -1
     double* hm;                 // members' far-field coefficients (FP64)
     int64_t n_members;
     int64_t n_clusters;
@@ -159,6 +160,7 @@ struct UpdateState {
     int64_t* d_members = nullptr;
     int64_t* d_moff = nullptr;
     double* d_hm = nullptr;
+    int32_t* d_member_of = nullptr;
     double* d_charge = nullptr;
     // device parse of a CSR density (ParseArgs): the basis and block lists
     int32_t* d_shell_of_bf = nullptr;
@@ -233,7 +235,7 @@ int launch_update_charges(const UpdateArgs& a, void* stream);
 int launch_group_charges(const double* charge, const int64_t* gpb, const int64_t* dropb, int64_t n_pairs,
                          int n_groups, double* gq, void* stream);
 int launch_update_pairs(const UpdateArgs& a, void* stream);
-int launch_update_members(const UpdateArgs& a, void* stream);
+int launch_member_of(const int64_t* members, int64_t n, int32_t* member_of, void* stream);
 int launch_update_clusters(const UpdateArgs& a, void* stream);
 
 }  // namespace envpot
