@@ -20,22 +20,11 @@ using namespace envpot;
 
 namespace {
 
+// Workspace of a training step.
 struct Workspace {
     int64_t cap = 0;    // rows (multiple of 32)
-    bool train = false;
-    uint16_t* H[kLayers + 1] = {};
-    float* Z[kLayers] = {};
-    float* y = nullptr;
-    float* dy = nullptr;
-    uint16_t* dZb = nullptr;
-    float* dH = nullptr;
-    float* gpart = nullptr;     // per-workgroup partials of dW: (rows / 128) x 128 x 128
-    float* colb = nullptr;      // per-block column sums (bias gradient)
-    float* colo = nullptr;      // per-block column sums (output weights)
-    double* losspart = nullptr;
-    float* dypart = nullptr;    // per-block sums of dy
+    TrainBuffers tb;
 };
-
 
 template <typename T>
 bool dalloc(T** p, size_t n) {
@@ -43,46 +32,27 @@ bool dalloc(T** p, size_t n) {
 }
 
 void ws_free(Workspace& w) {
-    for (int l = 0; l <= kLayers; ++l) {
-        (void)hipFree(w.H[l]);
-        w.H[l] = nullptr;
-    }
-    for (int l = 0; l < kLayers; ++l) {
-        (void)hipFree(w.Z[l]);
-        w.Z[l] = nullptr;
-    }
-    (void)hipFree(w.y);
-    (void)hipFree(w.dy);
-    (void)hipFree(w.dZb);
-    (void)hipFree(w.dH);
-    (void)hipFree(w.gpart);
-    (void)hipFree(w.colb);
-    (void)hipFree(w.colo);
-    (void)hipFree(w.losspart);
-    (void)hipFree(w.dypart);
+    (void)hipFree(w.tb.HT);
+    (void)hipFree(w.tb.dZT);
+    (void)hipFree(w.tb.gpart);
+    (void)hipFree(w.tb.colsum);
+    (void)hipFree(w.tb.colout);
+    (void)hipFree(w.tb.loss);
+    (void)hipFree(w.tb.dysum);
     w = Workspace();
 }
 
-bool ws_ensure(Workspace& w, int64_t rows, bool train) {
-    if (w.cap >= rows && (w.train || !train)) return true;
-    const int64_t cap = std::max(rows, w.cap);
+bool ws_ensure(Workspace& w, int64_t rows) {
+    if (w.cap >= rows) return true;
     ws_free(w);
-    w.cap = cap;
-    w.train = train;
-    bool ok = true;
-    for (int l = 0; l <= kLayers; ++l) {
-        ok = ok && dalloc(&w.H[l], size_t(cap) * kHidden);
-    }
-    for (int l = 0; l < kLayers; ++l) ok = ok && dalloc(&w.Z[l], size_t(cap) * kHidden);
-    ok = ok && dalloc(&w.y, cap);
-    if (train) {
-        const int64_t nb = (cap + 127) / 128;   // workgroups of the backward layer kernel
-        ok = ok && dalloc(&w.dy, cap) && dalloc(&w.dZb, size_t(cap) * kHidden) &&
-             dalloc(&w.dH, size_t(cap) * kHidden) &&
-             dalloc(&w.gpart, size_t((cap + 127) / 128) * kHidden * kHidden) && dalloc(&w.colb, size_t(nb) * kHidden) &&
-             dalloc(&w.colo, size_t(nb) * kHidden) && dalloc(&w.losspart, size_t((cap + 255) / 256)) &&
-             dalloc(&w.dypart, size_t((cap + 255) / 256));
-    }
+    const size_t chunks = size_t((rows + kChunkRows - 1) / kChunkRows), tiles = size_t(rows / 32);
+    w.cap = rows;
+    w.tb.act_stride = int64_t(chunks) * kHidden * kChunkRows;
+    const bool ok = dalloc(&w.tb.HT, size_t(kLayers) * w.tb.act_stride) &&
+                    dalloc(&w.tb.dZT, size_t(kLayers) * w.tb.act_stride) &&
+                    dalloc(&w.tb.gpart, kLayers * chunks * kHidden * kHidden) &&
+                    dalloc(&w.tb.colsum, kLayers * tiles * kHidden) && dalloc(&w.tb.colout, tiles * kHidden) &&
+                    dalloc(&w.tb.loss, tiles) && dalloc(&w.tb.dysum, tiles);
     if (!ok) ws_free(w);
     return ok;
 }
@@ -122,7 +92,6 @@ struct env_surrogate {
     uint16_t* d_W = nullptr;
     uint16_t* d_WT = nullptr;
     double* d_coef = nullptr;
-    int8_t* d_mono = nullptr;
     uint8_t* d_pass = nullptr;
     int64_t* d_nfb = nullptr;              // gated-out count of the last evaluation
     unsigned long long* d_counter = nullptr;  // work counter of the fallback launch
@@ -136,70 +105,38 @@ struct env_surrogate {
 
 namespace {
 
+// The baseline's coefficients in the order the kernels nest them, padded
+// with zeros to kMaxPolyDegree.
 env_status upload_baseline(env_surrogate* s) {
-    (void)hipFree(s->d_coef);
-    (void)hipFree(s->d_mono);
-    s->d_coef = nullptr;
-    s->d_mono = nullptr;
-    if (!dalloc(&s->d_coef, s->coef.size()) || !dalloc(&s->d_mono, s->mono.size())) return ENV_E_NOMEM;
-    if (hipMemcpy(s->d_coef, s->coef.data(), s->coef.size() * sizeof(double), hipMemcpyHostToDevice) != hipSuccess ||
-        hipMemcpy(s->d_mono, s->mono.data(), s->mono.size(), hipMemcpyHostToDevice) != hipSuccess)
+    std::vector<double> nested;
+    nested.reserve(kPolyCoefs);
+    for (int a = kMaxPolyDegree; a >= 0; --a)
+        for (int b = kMaxPolyDegree - a; b >= 0; --b)
+            for (int c = kMaxPolyDegree - a - b; c >= 0; --c) {
+                double v = 0.0;
+                for (size_t k = 0; k < s->coef.size(); ++k)
+                    if (s->mono[3 * k] == a && s->mono[3 * k + 1] == b && s->mono[3 * k + 2] == c) v = s->coef[k];
+                nested.push_back(v);
+            }
+    if (!s->d_coef && !dalloc(&s->d_coef, kPolyCoefs)) return ENV_E_NOMEM;
+    if (hipMemcpy(s->d_coef, nested.data(), kPolyCoefs * sizeof(double), hipMemcpyHostToDevice) != hipSuccess)
         return ENV_E_DEVICE;
     return ENV_OK;
 }
 
-// Forward pass of rows [0, Np) whose first n are real points, storing what
-// the backward pass reads (H and H^T of every layer, Z, y in ws.y); one launch.
-void forward(env_surrogate* s, const double* pts, int64_t n, int64_t Np, void* st) {
-    Workspace& w = s->ws;
-    sg_forward_train(pts, n, Np, s->d_B, s->d_W, s->d_params, w.H, w.Z, w.y, st);
-}
-
-// Host copies of the intermediate tensors of one training step (see
-// env_surrogate_trace_step); every copy is queued on the step's stream.
-struct TraceCopies {
-    env_surrogate_trace* tr = nullptr;
-    int64_t n = 0;
-    std::vector<uint16_t> dzb;   // staging of the BF16 dZ of every layer
-    bool ok = true;
-    void copy(void* dst, const void* src, size_t bytes, hipStream_t st) {
-        if (ok && dst && hipMemcpyAsync(dst, src, bytes, hipMemcpyDeviceToHost, st) != hipSuccess) ok = false;
-    }
-};
-
-// Loss partials and the full gradient into d_grad (forward must have run with train = true).
-void backward(env_surrogate* s, const float* t, int64_t n, int64_t Np, void* st, TraceCopies* tc = nullptr) {
-    Workspace& w = s->ws;
-    hipStream_t hst = static_cast<hipStream_t>(st);
-    sg_loss(w.y, t, n, Np, w.dy, w.losspart, w.dypart, st);
-    if (tc) tc->copy(tc->tr->dy, w.dy, size_t(n) * sizeof(float), hst);
-    for (int l = kLayers - 1; l >= 0; --l) {
-        const bool top = l == kLayers - 1;
-        if (tc && !top) tc->copy(tc->tr->dH ? tc->tr->dH + size_t(l) * n * kHidden : nullptr, w.dH,
-                                 size_t(n) * kHidden * sizeof(float), hst);
-        // dZ, the bias and output-weight column sums, dH of the layer below
-        // (over w.dH) and the dW partials in one launch
-        const int nb = sg_backward_layer(top, w.dH, w.dy, s->d_params + kOutOffset, w.Z[l], w.H[kLayers],
-                                         s->d_WT + size_t(l) * kHidden * kHidden, w.H[l], Np, l > 0, w.dZb,
-                                         w.gpart, w.colb, w.colo, st);
-        if (tc && tc->tr->dZ)
-            tc->copy(tc->dzb.data() + size_t(l) * n * kHidden, w.dZb, size_t(n) * kHidden * sizeof(uint16_t), hst);
-        float* gl = s->d_grad + size_t(l) * kLayerStride;
-        sg_reduce_rows(w.colb, nb, kHidden, gl + kHidden * kHidden, st);
-        if (top) {
-            sg_reduce_rows(w.colo, nb, kHidden, s->d_grad + kOutOffset, st);
-            sg_reduce_rows(w.dypart, int((Np + 255) / 256), 1, s->d_grad + kOutOffset + kHidden, st);
-        }
-        sg_reduce_rows(w.gpart, nb, int64_t(kHidden) * kHidden, gl, st);
-    }
+// One forward and backward pass: loss partials into the workspace, the full
+// gradient into d_grad.
+void step(env_surrogate* s, const double* pts, const float* t, int64_t n, int64_t Np, void* st,
+          const TrainTrace& trace = TrainTrace()) {
+    sg_train(pts, t, n, Np, s->d_B, s->d_W, s->d_WT, s->d_params, s->ws.tb, trace, s->d_grad, s->fallback->cu_count, st);
 }
 
 // Surrogate values (baseline + network, plus add[i] when add is not null) at
-// n points, in chunks.
+// n points.
 env_status predict(env_surrogate* s, const double* pts, int64_t n, double* out, void* st,
                    const double* add = nullptr) {
-    sg_infer(pts, n, s->d_B, s->d_W, s->d_params, s->d_coef, s->d_mono, int(s->mono.size() / 3), 1.0 / s->radius,
-             s->sigma, add, out, st);
+    sg_infer(pts, n, s->d_B, s->d_W, s->d_params, s->d_coef, 1.0 / s->radius, s->sigma, add, out,
+             s->fallback->cu_count, st);
     return sg_last_error() == 0 ? ENV_OK : ENV_E_DEVICE;
 }
 
@@ -265,7 +202,6 @@ void destroy(env_surrogate* s) {
     (void)hipFree(s->d_W);
     (void)hipFree(s->d_WT);
     (void)hipFree(s->d_coef);
-    (void)hipFree(s->d_mono);
     (void)hipFree(s->d_pass);
     (void)hipFree(s->d_nfb);
     (void)hipFree(s->d_counter);
@@ -364,13 +300,12 @@ env_status env_surrogate_loss_grad(env_surrogate* s, const double* points, const
     if (!s || n <= 0 || !points || !targets) return ENV_E_ARG;
     DeviceGuard g(s->device);
     const int64_t Np = round32(n);
-    if (!ws_ensure(s->ws, Np, true)) return ENV_E_NOMEM;
+    if (!ws_ensure(s->ws, Np)) return ENV_E_NOMEM;
     hipStream_t st = static_cast<hipStream_t>(stream);
-    forward(s, points, n, Np, stream);
-    backward(s, targets, n, Np, stream);
+    step(s, points, targets, n, Np, stream);
     if (sg_last_error() != 0) return ENV_E_DEVICE;
-    std::vector<double> lp((Np + 255) / 256);
-    if (hipMemcpyAsync(lp.data(), s->ws.losspart, lp.size() * sizeof(double), hipMemcpyDeviceToHost, st) !=
+    std::vector<double> lp(size_t(Np / 32));
+    if (hipMemcpyAsync(lp.data(), s->ws.tb.loss, lp.size() * sizeof(double), hipMemcpyDeviceToHost, st) !=
             hipSuccess ||
         (grad_host && hipMemcpyAsync(grad_host, s->d_grad, kNParams * sizeof(float), hipMemcpyDeviceToHost, st) !=
                           hipSuccess) ||
@@ -387,25 +322,51 @@ env_status env_surrogate_trace_step(env_surrogate* s, const double* points, cons
     if (!s || n <= 0 || !points || !targets || !tr) return ENV_E_ARG;
     DeviceGuard g(s->device);
     const int64_t Np = round32(n);
-    if (!ws_ensure(s->ws, Np, true)) return ENV_E_NOMEM;
+    if (!ws_ensure(s->ws, Np)) return ENV_E_NOMEM;
     hipStream_t st = static_cast<hipStream_t>(stream);
-    Workspace& w = s->ws;
-    TraceCopies tc;
-    tc.tr = tr;
-    tc.n = n;
-    std::vector<uint16_t> hb(tr->H ? size_t(kLayers + 1) * n * kHidden : 0);
-    if (tr->dZ) tc.dzb.assign(size_t(kLayers) * n * kHidden, 0);
-    forward(s, points, n, Np, stream);
-    for (int l = 0; l <= kLayers && tr->H; ++l)
-        tc.copy(hb.data() + size_t(l) * n * kHidden, w.H[l], size_t(n) * kHidden * sizeof(uint16_t), st);
-    for (int l = 0; l < kLayers && tr->Z; ++l)
-        tc.copy(tr->Z + size_t(l) * n * kHidden, w.Z[l], size_t(n) * kHidden * sizeof(float), st);
-    tc.copy(tr->y, w.y, size_t(n) * sizeof(float), st);
-    backward(s, targets, n, Np, stream, &tc);
-    tc.copy(tr->grad, s->d_grad, kNParams * sizeof(float), st);
-    std::vector<double> lp((Np + 255) / 256);
-    tc.copy(lp.data(), w.losspart, lp.size() * sizeof(double), st);
-    if (sg_last_error() != 0 || !tc.ok || hipStreamSynchronize(st) != hipSuccess) return ENV_E_DEVICE;
+    const size_t act = size_t(Np) * kHidden, real = size_t(n) * kHidden;
+    TrainTrace t;
+    std::vector<uint16_t> hb(tr->H ? (kLayers + 1) * real : 0), zb(tr->dZ ? kLayers * real : 0);
+    std::vector<double> lp(size_t(Np / 32));
+    bool ok = true;
+    auto room = [&](auto** p, size_t count) { ok = ok && dalloc(p, count); };
+    room(&t.y, size_t(Np));
+    room(&t.dy, size_t(Np));
+    if (tr->H) room(&t.H, (kLayers + 1) * act);
+    if (tr->Z) room(&t.Z, kLayers * act);
+    if (tr->dH) room(&t.dH, kLayers * act);
+    if (tr->dZ) room(&t.dZ, kLayers * act);
+    auto release = [&]() {
+        (void)hipStreamSynchronize(st);
+        for (void* p : {static_cast<void*>(t.y), static_cast<void*>(t.dy), static_cast<void*>(t.H),
+                        static_cast<void*>(t.Z), static_cast<void*>(t.dH), static_cast<void*>(t.dZ)})
+            (void)hipFree(p);
+    };
+    if (!ok) {
+        release();
+        return ENV_E_NOMEM;
+    }
+    step(s, points, targets, n, Np, stream, t);
+    auto copy = [&](void* dst, const void* src, size_t bytes) {
+        if (ok && dst && hipMemcpyAsync(dst, src, bytes, hipMemcpyDeviceToHost, st) != hipSuccess) ok = false;
+    };
+    ok = sg_last_error() == 0;
+    for (size_t l = 0; l <= kLayers && tr->H; ++l) copy(hb.data() + l * real, t.H + l * act, real * sizeof(uint16_t));
+    for (size_t l = 0; l < kLayers; ++l) {
+        if (tr->Z) copy(tr->Z + l * real, t.Z + l * act, real * sizeof(float));
+        if (tr->dH && l + 1 < kLayers) copy(tr->dH + l * real, t.dH + l * act, real * sizeof(float));
+        if (tr->dZ) copy(zb.data() + l * real, t.dZ + l * act, real * sizeof(uint16_t));
+    }
+    std::vector<float> dy(static_cast<size_t>(n)), wo(kHidden);
+    copy(tr->y, t.y, size_t(n) * sizeof(float));
+    copy(dy.data(), t.dy, size_t(n) * sizeof(float));
+    copy(wo.data(), s->d_params + kOutOffset, kHidden * sizeof(float));
+    copy(tr->grad, s->d_grad, kNParams * sizeof(float));
+    copy(lp.data(), s->ws.tb.loss, lp.size() * sizeof(double));
+    ok = hipStreamSynchronize(st) == hipSuccess && ok;
+    release();
+    if (!ok) return ENV_E_DEVICE;
+    if (tr->dy) std::copy(dy.begin(), dy.end(), tr->dy);
     auto widen = [](uint16_t b) {
         const uint32_t u = uint32_t(b) << 16;
         float f;
@@ -413,14 +374,9 @@ env_status env_surrogate_trace_step(env_surrogate* s, const double* points, cons
         return f;
     };
     for (size_t i = 0; i < hb.size(); ++i) tr->H[i] = widen(hb[i]);
-    for (size_t i = 0; i < tc.dzb.size(); ++i) tr->dZ[i] = widen(tc.dzb[i]);
+    for (size_t i = 0; i < zb.size(); ++i) tr->dZ[i] = widen(zb[i]);
     if (tr->dH) {
         // dL/dH of the top layer is dy w_out^T, formed inside the SiLU backward
-        std::vector<float> dy(n), wo(kHidden);
-        if (hipMemcpy(dy.data(), w.dy, size_t(n) * sizeof(float), hipMemcpyDeviceToHost) != hipSuccess ||
-            hipMemcpy(wo.data(), s->d_params + kOutOffset, kHidden * sizeof(float), hipMemcpyDeviceToHost) !=
-                hipSuccess)
-            return ENV_E_DEVICE;
         float* top = tr->dH + size_t(kLayers - 1) * n * kHidden;
         for (int64_t r = 0; r < n; ++r)
             for (int c = 0; c < kHidden; ++c) top[r * kHidden + c] = dy[r] * wo[c];
@@ -462,7 +418,7 @@ env_status env_surrogate_train(env_surrogate* s, env_potential* teacher, const e
         (void)hipFree(d_tb);
     };
     if (!dalloc(&d_pts, 3 * size_t(n)) || !dalloc(&d_V, n) || !dalloc(&d_t, n) || !dalloc(&d_perm, n) ||
-        !dalloc(&d_pb, 3 * size_t(o.batch)) || !dalloc(&d_tb, o.batch) || !ws_ensure(s->ws, o.batch, true)) {
+        !dalloc(&d_pb, 3 * size_t(o.batch)) || !dalloc(&d_tb, o.batch) || !ws_ensure(s->ws, o.batch)) {
         cleanup();
         return ENV_E_NOMEM;
     }
@@ -499,8 +455,7 @@ env_status env_surrogate_train(env_surrogate* s, env_potential* teacher, const e
         cleanup();
         return rc;
     }
-    sg_residual(d_pts, d_V, n, s->d_coef, s->d_mono, int(s->mono.size() / 3), 1.0 / s->radius, 1.0 / s->sigma,
-                d_t, stream);
+    sg_residual(d_pts, d_V, n, s->d_coef, 1.0 / s->radius, 1.0 / s->sigma, d_t, stream);
     // 3. Adam on minibatches, cosine learning-rate decay.  One step (gather,
     // forward, backward, Adam, BF16 pack, step counter) is captured once as
     // a graph on a stream of the library's own and replayed for every step;
@@ -514,7 +469,7 @@ env_status env_surrogate_train(env_surrogate* s, env_potential* teacher, const e
     // two pinned host permutations: the next epoch's is shuffled on the host
     // while the device runs the current one; the last minibatch's loss
     // partials of every epoch are kept on the device and read at the end
-    const int64_t nlp = (o.batch + 255) / 256;
+    const int64_t nlp = o.batch / 32;
     int32_t* hperm[2] = {nullptr, nullptr};
     hipEvent_t copied[2] = {nullptr, nullptr};
     double* d_losshist = nullptr;
@@ -542,8 +497,7 @@ env_status env_surrogate_train(env_surrogate* s, env_potential* teacher, const e
         rc = ENV_E_DEVICE;
     auto one_step = [&](void* sp) {
         sg_gather(d_pts, d_t, d_perm, s->d_tstate, steps_per_epoch, o.batch, d_pb, d_tb, sp);
-        forward(s, d_pb, o.batch, o.batch, sp);
-        backward(s, d_tb, o.batch, o.batch, sp);
+        step(s, d_pb, d_tb, o.batch, o.batch, sp);
         sg_adam(s->d_params, s->d_grad, s->d_m, s->d_v, kNParams, s->d_tstate, o.lr, o.lr_final, total, 0.9f, 0.999f,
                 1e-8f, sp);
         sg_pack(s->d_params, s->d_W, s->d_WT, sp);
@@ -579,7 +533,7 @@ env_status env_surrogate_train(env_surrogate* s, env_potential* teacher, const e
             else if (hipGraphLaunch(step_exec, ts) != hipSuccess) rc = ENV_E_DEVICE;
         }
         s->step += steps_per_epoch;
-        if (rc == ENV_OK && hipMemcpyAsync(d_losshist + size_t(ep) * nlp, s->ws.losspart, size_t(nlp) * sizeof(double),
+        if (rc == ENV_OK && hipMemcpyAsync(d_losshist + size_t(ep) * nlp, s->ws.tb.loss, size_t(nlp) * sizeof(double),
                                            hipMemcpyDeviceToDevice, ts) != hipSuccess)
             rc = ENV_E_DEVICE;
         // next epoch's permutation, on the host while the device works; its

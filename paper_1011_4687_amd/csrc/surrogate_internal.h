@@ -13,10 +13,9 @@ constexpr int kLayerStride = kHidden * kHidden + kHidden;   // W (out x in) then
 constexpr int kOutOffset = kLayers * kLayerStride;          // w_out (128) then b_out
 constexpr int kNParams = kOutOffset + kHidden + 1;          // 66,177
 constexpr int kMaxPolyDegree = 8;
+constexpr int kPolyCoefs = 165;              // monomials up to that degree
+constexpr int kChunkRows = 128;              // rows of one weight-gradient partial
 
-void sg_reduce_rows(const float* part, int P, int64_t L, float* out, void* st);
-void sg_loss(const float* y, const float* t, int64_t n, int64_t Np, float* dy, double* part, float* part_dy,
-             void* st);
 // Device state of a training run: Adam step count so far and its value at
 // the start of the run (the minibatch index and the learning-rate schedule
 // are derived from them on the device, so one captured step graph is
@@ -32,24 +31,39 @@ void sg_advance(TrainState* ts, void* st);
 void sg_pack(const float* params, uint16_t* W, uint16_t* WT, void* st);
 // The whole network at inference (features, four layers, output, baseline,
 // optional exact part) in one launch: out[i] = poly + sigma y (+ add[i]).
+// coef: kPolyCoefs coefficients in nested order (exponents of x, y, z
+// descending from kMaxPolyDegree, zero above the baseline's degree).
 void sg_infer(const double* pts, int64_t n, const double* B, const uint16_t* W, const float* params,
-              const double* coef, const int8_t* mono, int nmono, double inv_r, double sigma, const double* add,
-              double* out, void* st);
-// The forward pass of a training step in one launch: H_0..H_4 (row-major
-// [Np x 128], BF16), Z_0..Z_3 (FP32) and y for the first Np rows (rows >= n
-// have zero features).
-void sg_forward_train(const double* pts, int64_t n, int64_t Np, const double* B, const uint16_t* W,
-                      const float* params, uint16_t* const* H, float* const* Z, float* y, void* st);
-// One layer of the backward pass in one launch: BF16 dZ (to dZb), the
-// per-workgroup column sums of dZ (and, top layer, of dy H_top), dH of the
-// layer below written over dH (when `below`), and per-workgroup 128 x 128
-// partials of dW; returns the number of workgroups (partials).  Np is a
-// multiple of 32.
-int sg_backward_layer(bool top, float* dH, const float* dy, const float* w_out, const float* Z, const uint16_t* Htop,
-                      const uint16_t* WT, const uint16_t* H, int64_t Np, bool below, uint16_t* dZb, float* gpart,
-                      float* colsum, float* colsum_out, void* st);
-void sg_residual(const double* pts, const double* V, int64_t n, const double* coef, const int8_t* mono,
-                 int nmono, double inv_r, double inv_sigma, float* t, void* st);
+              const double* coef, double inv_r, double sigma, const double* add, double* out, int cu_count, void* st);
+
+// Workspace of a training step of Np rows (a multiple of 32).
+struct TrainBuffers {
+    uint16_t* HT = nullptr;    // H_0..H_3, per chunk of kChunkRows rows [feature][row], BF16
+    uint16_t* dZT = nullptr;   // dZ_0..dZ_3, likewise
+    int64_t act_stride = 0;    // values from one layer to the next in both
+    float* gpart = nullptr;    // dW partials: [layer][chunk][128][128]
+    float* colsum = nullptr;   // column sums of dZ: [layer][tile of 32 rows][128]
+    float* colout = nullptr;   // column sums of dy H_4: [tile][128]
+    double* loss = nullptr;    // squared errors per tile
+    float* dysum = nullptr;    // sum of dy per tile
+};
+// Where the intermediate tensors of a step go as well, each or null
+// (row-major, Np rows per layer; dH of the layers below the top).
+struct TrainTrace {
+    uint16_t* H = nullptr;
+    float* Z = nullptr;
+    float* dH = nullptr;
+    uint16_t* dZ = nullptr;
+    float* y = nullptr;
+    float* dy = nullptr;
+};
+// Forward and backward pass of n rows (padded to Np; rows >= n have zero
+// features and no gradient): loss partials and the whole gradient.
+void sg_train(const double* pts, const float* target, int64_t n, int64_t Np, const double* B, const uint16_t* W,
+              const uint16_t* WT, const float* params, const TrainBuffers& tb, const TrainTrace& trace, float* grad,
+              int cu_count, void* st);
+void sg_residual(const double* pts, const double* V, int64_t n, const double* coef, double inv_r, double inv_sigma,
+                 float* t, void* st);
 void sg_sample_ball(uint64_t seed, int64_t n, double R, double* pts, void* st);
 void sg_sample_voxels(uint64_t seed, int G, int m, double R, double* pts, void* st);
 void sg_gather(const double* pts, const float* t, const int32_t* perm, const TrainState* ts,
