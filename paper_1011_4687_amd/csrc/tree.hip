@@ -304,11 +304,12 @@ struct MomentArgs {
     const double* tab;
     double* part;                // per chunk: moments about the node's centre, absolute charge
     double* up;                  // per node: its moments about its parent's centre, absolute charge
+    double* mom;                 // per node: its moments, absolute charge
+    unsigned long long* own;     // per node, potential and field: bits of the radius its moments ask for
+    unsigned long long* radius;  // the same, with its descendants'
     double* coef;
     float* thr;
-    TreeTest* test;
-    float* thr_field;            // with test_field, or nullptr
-    TreeTest* test_field;
+    float* thr_field;            // or nullptr
     double eps;
     double nuc_size;             // what a unit of nuclear charge adds to the absolute charge
 };
@@ -317,7 +318,6 @@ struct Cplx {
     double r, i;
 };
 
-constexpr int kBatch = 8;        // items whose harmonics are in LDS at once
 constexpr int kChunk = 128;      // items per chunk
 constexpr int part_words(int P) { return 2 * tree_ncoef(P) + 2; }
 
@@ -327,8 +327,11 @@ __device__ __forceinline__ double node_scale(const double* geo) {
     return s > 0.0 ? s : 1.0;
 }
 
-// R_n^m(x) for m >= 0 of one x, by the thread of order m, into tab[index].
-template <int P>
+constexpr int full_index(int n, int m) { return n * n + n + m; }
+
+// R_n^m(x) of one x, by the thread of order m >= 0: into tab[tree_index], or
+// with FULL, both signs of m, into tab[full_index].
+template <int P, bool FULL>
 __device__ __forceinline__ void harmonics(double x, double y, double z, int m, const double* den, Cplx* tab) {
     double cr = 1.0, ci = 0.0;
     for (int k = 1; k <= m; ++k) {
@@ -339,45 +342,19 @@ __device__ __forceinline__ void harmonics(double x, double y, double z, int m, c
     const double r2 = x * x + y * y + z * z;
     Cplx a{0.0, 0.0}, b{cr, ci};  // R_{n-1}, R_n
     const int at = tree_index(P, m, m);
-    tab[at] = b;
-    for (int n = m; n < P; ++n) {
+    const double sg = (m & 1) ? -1.0 : 1.0;
+    for (int n = m;; ++n) {
+        if constexpr (FULL) {
+            tab[full_index(n, m)] = b;
+            if (m > 0) tab[full_index(n, -m)] = Cplx{sg * b.r, -sg * b.i};
+        } else {
+            tab[at + n - m] = b;
+        }
+        if (n == P) break;
         const double f = den[at + n + 1 - m], u = (2 * n + 1) * z;
         const Cplx c{(u * b.r - r2 * a.r) * f, (u * b.i - r2 * a.i) * f};
         a = b;
         b = c;
-        tab[at + n + 1 - m] = c;
-    }
-}
-
-// acc += sum_{k <= kmax} sum_j Q_k^j R_{n-k}^{m-j}; Q and R hold their
-// m >= 0 parts at tree_index(PQ, k, j) and tree_index(P, n, m).
-template <int P, int PQ>
-__device__ __forceinline__ void shift_add(const Cplx* Q, const Cplx* R, int kmax, int n, int m, Cplx& acc) {
-    const int kt = kmax < n ? kmax : n;
-    for (int k = 0; k <= kt; ++k) {
-        const int nn = n - k;
-        const int j0 = max(-k, m - nn), j1 = min(k, m + nn);  // |m - j| <= n - k
-        for (int j = j0; j <= j1; ++j) {
-            Cplx q = Q[tree_index(PQ, k, j < 0 ? -j : j)];
-            if (j < 0) {
-                q.i = -q.i;
-                if (j & 1) {
-                    q.r = -q.r;
-                    q.i = -q.i;
-                }
-            }
-            const int mm = m - j;
-            Cplx r = R[tree_index(P, nn, mm < 0 ? -mm : mm)];
-            if (mm < 0) {
-                r.i = -r.i;
-                if (mm & 1) {
-                    r.r = -r.r;
-                    r.i = -r.i;
-                }
-            }
-            acc.r += q.r * r.r - q.i * r.i;
-            acc.i += q.r * r.i + q.i * r.r;
-        }
     }
 }
 
@@ -400,32 +377,76 @@ __device__ __forceinline__ void coef_nm(int t, int& n, int& m) {
     n = m + t;
 }
 
+// Items whose harmonics are in LDS at once, all (n, m) of both signs.
+constexpr int batch_of(int P) { return P <= 16 ? 8 : 4; }
+
+// acc += sum_j Q_k^j R_{n-k}^{m-j}, k fixed at compile time.
+template <int K>
+__device__ __forceinline__ void shift_order(const Cplx* Q, const Cplx* R, int n, int m, Cplx& acc) {
+    const int nn = n - K;
+    if (nn < 0) return;
+    const Cplx* row = R + full_index(nn, m);
+#pragma unroll
+    for (int j = -K; j <= K; ++j)
+        if (m - j <= nn && m - j >= -nn) {
+            const Cplx q = Q[full_index(K, j)], r = row[-j];
+            acc.r = fma(q.r, r.r, fma(-q.i, r.i, acc.r));
+            acc.i = fma(q.r, r.i, fma(q.i, r.r, acc.i));
+        }
+}
+
 // Moments of one chunk of own items about their node's centre; a workgroup
 // per chunk, thread t owns coefficient t.  Bound by the LDS reads of the
-// shifts (two complex values per multiply-add).
+// shifts (two complex values per multiply-add) and their latency: 375,461
+// pairs, FP64 1.14 ms, FP32C 0.56 (1.53 and 1.09 with the signs formed and
+// the index computed per term).
 template <int P, bool F64>
 __global__ __launch_bounds__(kB) void k_tree_p2m(MomentArgs A) {
     constexpr int NC = tree_ncoef(P);
     constexpr int NT = (NC + kB - 1) / kB;  // coefficients of a thread: t, t + 256, ...
-    static_assert(kBatch * (P + 1) <= kB, "one thread per item and order");
-    __shared__ Cplx R[kBatch][NC];
-    __shared__ Cplx Q[kBatch][15];  // order 4
-    __shared__ double xs[kBatch][3];
-    __shared__ const double* item[kBatch];
-    __shared__ int ls[kBatch];
+    constexpr int kBatch = batch_of(P);
+    constexpr int kFold = 16;               // items whose Q are formed at once
+    static_assert(kBatch * (P + 1) <= kB && kFold * 15 <= kB && kFold % kBatch == 0 && kChunk % kFold == 0 && kChunk <= kB,
+                  "one thread per item and order");
+    __shared__ Cplx R[kBatch][(P + 1) * (P + 1)];
+    __shared__ Cplx Q[kFold][25];
+    __shared__ double xs[kChunk][3];
+    __shared__ const double* item[kChunk];
+    __shared__ int ls[kChunk];
     __shared__ double fold[350];
     __shared__ double den[NC];
-    __shared__ double qabs[15 * kBatch];
+    __shared__ double qabs[15 * kFold];
     const int t = threadIdx.x;
-    for (int k = t; k < 350; k += kB) fold[k] = A.tab[tab_fold(P) + k];
-    for (int k = t; k < NC; k += kB) den[k] = A.tab[tab_den(P) + k];
     // (k, j) of this thread's Q
     int qk = 0, qj = t % 15;
     while (qj > qk) qj -= ++qk;
     const Chunk ck = A.chunk[blockIdx.x];
-    const TreeNode node = A.node[ck.node];
+    const int count = ck.end - ck.begin;
     const double* geo = A.geo + kGeo * int64_t(ck.node);
     const double inv = 1.0 / node_scale(geo);
+    if (t < count) {
+        const TreeNode& node = A.node[ck.node];
+        int i = ck.begin + t, L = 0;
+        int64_t w = node.rec_off;
+#pragma unroll
+        for (int l = 0; l <= kLMax; ++l) {
+            const int c = node.cnt[l];
+            if (L == l && i >= c) {
+                i -= c;
+                w += int64_t(c) * rec_words_of(l, F64);
+                ++L;
+            }
+        }
+        const double* d = L <= kLMax ? reinterpret_cast<const double*>(A.rec + w + int64_t(i) * rec_words_of(L, F64))
+                                     : A.nuc + 4 * int64_t(node.nuc_begin + i);
+        item[t] = d;
+        ls[t] = L;
+        xs[t][0] = (d[0] - geo[0]) * inv;
+        xs[t][1] = (d[1] - geo[1]) * inv;
+        xs[t][2] = (d[2] - geo[2]) * inv;
+    }
+    for (int k = t; k < 350; k += kB) fold[k] = A.tab[tab_fold(P) + k];
+    for (int k = t; k < NC; k += kB) den[k] = A.tab[tab_den(P) + k];
     int n[NT], m[NT];
     Cplx acc[NT];
 #pragma unroll
@@ -435,28 +456,11 @@ __global__ __launch_bounds__(kB) void k_tree_p2m(MomentArgs A) {
     }
     double qa = 0.0;
     __syncthreads();
-    for (int i0 = ck.begin; i0 < ck.end; i0 += kBatch) {
-        const int nb = min(kBatch, ck.end - i0);
-        if (t < nb) {
-            int i = i0 + t, L = 0;
-            int64_t w = node.rec_off;
-            while (L <= kLMax && i >= node.cnt[L]) {
-                i -= node.cnt[L];
-                w += int64_t(node.cnt[L]) * rec_words_of(L, F64);
-                ++L;
-            }
-            const double* d = L <= kLMax ? reinterpret_cast<const double*>(A.rec + w + int64_t(i) * rec_words_of(L, F64))
-                                         : A.nuc + 4 * int64_t(node.nuc_begin + i);
-            item[t] = d;
-            ls[t] = L;
-            xs[t][0] = (d[0] - geo[0]) * inv;
-            xs[t][1] = (d[1] - geo[1]) * inv;
-            xs[t][2] = (d[2] - geo[2]) * inv;
-        }
-        __syncthreads();
-        if (t < 15 * nb) {  // Q_k^j of an item, scaled by s^-k, from its components of order k
-            const int it = t / 15, L = ls[it];
-            const double* d = item[it];
+    for (int f0 = 0; f0 < count; f0 += kFold) {
+        const int nf = min(kFold, count - f0);
+        if (t < 15 * nf) {  // Q_k^j of an item, scaled by s^-k, from its components of order k
+            const int it = t / 15, L = ls[f0 + it];
+            const double* d = item[f0 + it];
             const float* f32 = reinterpret_cast<const float*>(d);
             Cplx o{0.0, 0.0};
             double size = 0.0;
@@ -486,21 +490,33 @@ __global__ __launch_bounds__(kB) void k_tree_p2m(MomentArgs A) {
                     size *= ir;
                 }
             }
-            Q[it][tree_index(4, qk, qj)] = o;
+            const double sg = (qj & 1) ? -1.0 : 1.0;
+            Q[it][full_index(qk, qj)] = o;
+            if (qj > 0) Q[it][full_index(qk, -qj)] = Cplx{sg * o.r, -sg * o.i};
             if (qj == 0) qa += size;
         }
-        __syncthreads();
-        if (t < nb * (P + 1)) {
-            const int it = t / (P + 1);
-            harmonics<P>(xs[it][0], xs[it][1], xs[it][2], t % (P + 1), den, R[it]);
-        }
-        __syncthreads();
+        for (int b0 = 0; b0 < nf; b0 += kBatch) {
+            const int nb = min(kBatch, nf - b0);
+            if (t < nb * (P + 1)) {
+                const double* x = xs[f0 + b0 + t / (P + 1)];
+                harmonics<P, true>(x[0], x[1], x[2], t % (P + 1), den, R[t / (P + 1)]);
+            }
+            __syncthreads();
 #pragma unroll
-        for (int k = 0; k < NT; ++k)
-            if (t + k * kB < NC)
-                for (int it = 0; it < nb; ++it)
-                    shift_add<P, 4>(Q[it], R[it], ls[it] > kLMax ? 0 : ls[it], n[k], m[k], acc[k]);
-        __syncthreads();
+            for (int k = 0; k < NT; ++k)
+                if (t + k * kB < NC)
+                    for (int it = 0; it < nb; ++it) {
+                        const Cplx* q = Q[b0 + it];
+                        const int L = __builtin_amdgcn_readfirstlane(ls[f0 + b0 + it]);
+                        shift_order<0>(q, R[it], n[k], m[k], acc[k]);
+                        if (L > kLMax) continue;  // a nucleus
+                        if (L >= 1) shift_order<1>(q, R[it], n[k], m[k], acc[k]);
+                        if (L >= 2) shift_order<2>(q, R[it], n[k], m[k], acc[k]);
+                        if (L >= 3) shift_order<3>(q, R[it], n[k], m[k], acc[k]);
+                        if (L >= 4) shift_order<4>(q, R[it], n[k], m[k], acc[k]);
+                    }
+            __syncthreads();
+        }
     }
     double* o = A.part + int64_t(part_words(P)) * blockIdx.x;
 #pragma unroll
@@ -509,188 +525,227 @@ __global__ __launch_bounds__(kB) void k_tree_p2m(MomentArgs A) {
             o[2 * (t + k * kB)] = acc[k].r;
             o[2 * (t + k * kB) + 1] = acc[k].i;
         }
-    if (t < 15 * kBatch) qabs[t] = qa;
+    if (t < 15 * kFold) qabs[t] = qa;
     __syncthreads();
-    if (t == 0) {
+    if (t < 64) {
         double q = 0.0;
-        for (int k = 0; k < 15 * kBatch; ++k) q += qabs[k];
-        o[2 * NC] = q;
+        for (int k = t; k < 15 * kFold; k += 64) q += qabs[k];
+#pragma unroll
+        for (int w = 32; w > 0; w >>= 1) q += __shfl_xor(q, w);
+        if (t == 0) o[2 * NC] = q;
     }
 }
 
-// One node of a depth: the sum of its chunks' moments and of its children's
-// shifted ones (fixed order), its evaluation coefficients and accepted
-// radii, and its moments shifted to its parent's centre.  A workgroup per
-// node; bound by latency (the shift's chain on the few nodes of a depth).
 constexpr int node_threads(int P) { return tree_ncoef(P) < kB ? kB : 2 * kB; }
+
+// One node of a depth: the sum of its chunks' moments and of its children's
+// shifted ones (fixed order), kept for the radii, its evaluation
+// coefficients, and its moments shifted to its parent's centre.  A workgroup
+// per node; a depth has few, so this is bound by the latency of one shift
+// (up to 231 terms in a thread): only what the next depth waits for is here
+// (200 atoms, per depth: FP64 70 -> 28 us, FP32C 50 -> 14, the radii after it
+// 45 us for all nodes at once).
 template <int P>
 __global__ __launch_bounds__(node_threads(P)) void k_tree_nodes(MomentArgs A) {
-    constexpr int NC = tree_ncoef(P);
+    constexpr int NC = tree_ncoef(P), NF = (P + 1) * (P + 1);
     static_assert(NC < node_threads(P), "one thread per coefficient and one for the charge");
-    __shared__ Cplx M[NC];
-    __shared__ Cplx R[NC];
+    __shared__ Cplx Q[NF];
+    __shared__ Cplx R[NF];
     __shared__ double den[NC];
-    __shared__ double bn[P + 1];
-    constexpr int TR = tree_thr_row(P);
-    __shared__ float thr_sh[2][TR];
     const int t = threadIdx.x;
-    const int nd = A.by_depth[blockIdx.x];
+    const int nd = A.by_depth[blockIdx.x], par = A.parent[nd];
     const double* geo = A.geo + kGeo * int64_t(nd);
-    const double c0 = geo[0], c1 = geo[1], c2 = geo[2], arad = geo[3];
     const double s = node_scale(geo);
+    const int w = t < NC ? 2 * t : 2 * NC;  // every thread past the coefficients adds up the charge
+    if (t < NC) den[t] = A.tab[tab_den(P) + t];
     int n, m;
     coef_nm<P>(t, n, m);
-    const int w = t < NC ? 2 * t : 2 * NC;  // every thread past the coefficients adds up the charge
+    double inv = 0.0, x[3] = {0.0, 0.0, 0.0};
+    if (par >= 0) {
+        const double* pg = A.geo + kGeo * int64_t(par);
+        inv = 1.0 / node_scale(pg);
+        for (int d = 0; d < 3; ++d) x[d] = (geo[d] - pg[d]) * inv;
+    }
     Cplx acc{0.0, 0.0};
-    if (t < NC) den[t] = A.tab[tab_den(P) + t];
-    __syncthreads();
 #pragma unroll 4
     for (int c = A.chunk_begin[nd]; c < A.chunk_begin[nd + 1]; ++c) {
         const double* q = A.part + int64_t(part_words(P)) * c + w;
         acc.r += q[0];
         acc.i += q[1];
     }
-    double racc = 0.0, racc_field = 0.0;
+#pragma unroll 4
     for (int c = A.child_begin[nd]; c < A.child_begin[nd + 1]; ++c) {
-        const int ch = A.child[c];
-        const double* q = A.up + int64_t(part_words(P)) * ch + w;
+        const double* q = A.up + int64_t(part_words(P)) * A.child[c] + w;
         acc.r += q[0];
         acc.i += q[1];
-        const double* cg = A.geo + kGeo * int64_t(ch);
-        const double dx = cg[0] - c0, dy = cg[1] - c1, dz = cg[2] - c2;
-        const double d = sqrt(dx * dx + dy * dy + dz * dz);
-        racc = fmax(racc, (sqrt(double(A.test[ch].r2)) + d) * (1.0 + 1e-9));
-        if (A.test_field) racc_field = fmax(racc_field, (sqrt(double(A.test_field[ch].r2)) + d) * (1.0 + 1e-9));
     }
+    double* mo = A.mom + int64_t(part_words(P)) * nd;
     if (t < NC) {
-        M[t] = acc;
+        mo[2 * t] = acc.r;
+        mo[2 * t + 1] = acc.i;
         double* co = A.coef + int64_t(tree_words(P)) * nd + kTreeHead;
         const double f = A.tab[tab_fac(P) + t];
         co[2 * t] = acc.r * f;
         co[2 * t + 1] = acc.i * f;
     }
-    __shared__ double charge;
-    if (t == NC) charge = acc.r;
-    const int par = A.parent[nd];
-    double ratio = 0.0;
-    if (par >= 0) {
-        const double* pg = A.geo + kGeo * int64_t(par);
-        const double inv = 1.0 / node_scale(pg);
-        ratio = s * inv;
-        if (t <= P) harmonics<P>((c0 - pg[0]) * inv, (c1 - pg[1]) * inv, (c2 - pg[2]) * inv, t, den, R);
-    }
-    if (t == 0) {
+    if (t == NC) {
+        mo[2 * NC] = acc.r;
         double* co = A.coef + int64_t(tree_words(P)) * nd;
-        co[0] = c0;
-        co[1] = c1;
-        co[2] = c2;
+        for (int d = 0; d < 3; ++d) co[d] = geo[d];
         co[3] = s;
     }
-    __syncthreads();
-    if (t <= P) {
-        double b = 0.0;
-        for (int mm = 0; mm <= t; ++mm) {
-            const Cplx v = M[tree_index(P, t, mm)];
-            b += A.tab[tab_norm(P) + tree_index(P, t, mm)] * (v.r * v.r + v.i * v.i);
-        }
-        bn[t] = sqrt(b);
+    if (par < 0) return;
+    if (t < NC) {
+        const double ratio = s * inv, sg = (m & 1) ? -1.0 : 1.0;
+        double f = 1.0;
+        for (int k = 0; k < n; ++k) f *= ratio;
+        const Cplx q{acc.r * f, acc.i * f};
+        Q[full_index(n, m)] = q;
+        Q[full_index(n, -m)] = m ? Cplx{sg * q.r, -sg * q.i} : q;
     }
     __syncthreads();
-    // smallest radii from which the orders suffice: the potential's by the
-    // first threads, the field's by the second wave's
-    const int fld = t >> 6, row = t & 63;
-    if (row < TR && (fld == 0 || (fld == 1 && A.thr_field))) {
-        // at least the far-field radius and outside the items, and such that
-        // the degrees above the order stay below eps |charge|/R:
-        // sum_{n>p} w_n B_n x^n + tail <= eps |charge|, x = s/R; w_n = 1, for
-        // the gradient (against |charge|/R^2) sqrt((n+1)(2n+1)) < 1.5 (n+1); the tail
-        // beyond P continues the largest of the last three B_n four times over
-        const double tol = A.eps * charge;
-        const double rmin = fmax(geo[4 + fld], 1.02 * arad);
-        double r2 = HUGE_VAL;
-        if (row <= P) {
-            double tail = 4.0 * fmax(bn[P], fmax(bn[P - 1], bn[P - 2]));
-            const double xmax = rmin > 0.0 ? s / rmin : 0.98;
-            auto over = [&](double x) {
-                const double g = 1.0 / (1.0 - x);
-                double v = tail * x * g;
-                if (fld) v *= 1.5 * (P + 2) * g;
-                for (int k = P; k > row; --k) v = (v + (fld ? 1.5 * (k + 1) : 1.0) * bn[k]) * x;
-                for (int k = 0; k < row; ++k) v *= x;
-                return !(v <= tol);
-            };
-            if (!over(xmax)) {
-                r2 = s / xmax;
-                r2 *= r2;
-            } else {
-                double lo = 0.0, hi = 40.0;  // x = xmax 2^-lo is too large, 2^-hi small enough
-                if (!over(xmax * exp2(-hi))) {
-                    for (int it = 0; it < 12; ++it) {
-                        const double mid = 0.5 * (lo + hi);
-                        if (over(xmax * exp2(-mid))) lo = mid;
-                        else hi = mid;
-                    }
-                    r2 = s / (xmax * exp2(-hi));
-                    r2 *= r2;
-                }
-            }
-            const double ra = fld ? racc_field : racc;
-            r2 = fmax(r2, ra * ra);  // a node is accepted only where all its children would be
-        }
-        thr_sh[fld][row] = float(r2 * (1.0 + 1e-6));
-    }
-    // meanwhile the other waves shift the moments to the parent's centre
-    if (par >= 0) {
-        __shared__ Cplx Q[NC];
-        if (t < NC) {
-            double f = 1.0;
-            for (int k = 0; k < n; ++k) f *= ratio;
-            Q[t] = Cplx{M[t].r * f, M[t].i * f};
-        }
-        __syncthreads();
+    if (t <= P) harmonics<P, true>(x[0], x[1], x[2], t, den, R);
+    __syncthreads();
+    double* o = A.up + int64_t(part_words(P)) * nd;
+    if (t < NC) {
         Cplx u{0.0, 0.0};
-        if (t < NC) shift_add<P, P>(Q, R, P, n, m, u);
-        double* o = A.up + int64_t(part_words(P)) * nd;
-        if (t < NC) {
-            o[2 * t] = u.r;
-            o[2 * t + 1] = u.i;
+        for (int k = 0; k <= n; ++k) {
+            const int nn = n - k, j0 = max(-k, m - nn), j1 = min(k, m + nn);  // |m - j| <= n - k
+            const Cplx* q = Q + full_index(k, j0);
+            const Cplx* r = R + full_index(nn, m - j0);
+#pragma unroll 4
+            for (int j = j0; j <= j1; ++j, ++q, --r) {
+                u.r = fma(q->r, r->r, fma(-q->i, r->i, u.r));
+                u.i = fma(q->r, r->i, fma(q->i, r->r, u.i));
+            }
         }
-        if (t == 0) o[2 * NC] = charge;
+        o[2 * t] = u.r;
+        o[2 * t + 1] = u.i;
+    }
+    if (t == NC) o[2 * NC] = acc.r;
+}
+
+// Radii of every node from its moments alone, one wave per node: row[p] is
+// the smallest radius (at least the far-field radius and outside the items)
+// from which the degrees above p stay below eps |charge|/R,
+//   sum_{n>p} w_n B_n x^n + tail <= eps |charge|, x = s/R,
+// with B_n the norm of degree n, w_n = 1, for the gradient (against
+// |charge|/R^2) sqrt((n+1)(2n+1)) < 1.5 (n+1), and the tail beyond P the largest of
+// the last three B_n, continued, four times over.  radius: the largest order's.
+template <int P>
+__global__ __launch_bounds__(kB) void k_tree_radius(MomentArgs A, int64_t n_nodes) {
+    constexpr int NC = tree_ncoef(P), TR = tree_thr_row(P);
+    static_assert(2 * TR <= 64, "a lane per order of the potential and of the field");
+    __shared__ double bn[kB / 64][P + 1];
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    const int64_t nd = int64_t(blockIdx.x) * (kB / 64) + wave;
+    const bool live = nd < n_nodes;
+    const double* mo = A.mom + int64_t(part_words(P)) * (live ? nd : 0);
+    if (lane <= P) {
+        double b = 0.0;
+        for (int m = 0; m <= lane; ++m) {
+            const int i = tree_index(P, lane, m);
+            b += A.tab[tab_norm(P) + i] * (mo[2 * i] * mo[2 * i] + mo[2 * i + 1] * mo[2 * i + 1]);
+        }
+        bn[wave][lane] = sqrt(b);
     }
     __syncthreads();
-    if (row < TR && (fld == 0 || (fld == 1 && A.thr_field))) {
-        // radii do not grow with the order
-        float v = thr_sh[fld][row];
-        for (int k = 0; k < row && k <= P; ++k) v = fminf(v, thr_sh[fld][k]);
-        if (row > P) v = 0.0f;
-        (fld ? A.thr_field : A.thr)[int64_t(TR) * nd + row] = v;
-        if (row == P) {
-            TreeTest q;
-            q.c[0] = c0;
-            q.c[1] = c1;
-            q.c[2] = c2;
-            q.r2 = v;
-            q.pc[0] = q.pc[1] = q.pc[2] = 0.0;
-            q.pr2 = HUGE_VALF;
-            q.cost = A.node[nd].cost;
-            q.pad = 0;
-            (fld ? A.test_field : A.test)[nd] = q;
+    if (!live) return;
+    const int fld = lane / TR, row = lane % TR;
+    if (fld > 1 || (fld == 1 && !A.thr_field)) return;
+    const double* b = bn[wave];
+    const double* geo = A.geo + kGeo * nd;
+    const double s = node_scale(geo), tol = A.eps * mo[2 * NC];
+    const double rmin = fmax(geo[4 + fld], 1.02 * geo[3]);
+    const double xmax = rmin > 0.0 ? s / rmin : 0.98;
+    const double tail = 4.0 * fmax(b[P], fmax(b[P - 1], b[P - 2])) * (fld ? 1.5 * (P + 2) : 1.0);
+    auto over = [&](double x) {
+        const double g = 1.0 / (1.0 - x);
+        double v = tail * x * g * (fld ? g : 1.0);
+        for (int k = P; k > row; --k) v = (v + (fld ? 1.5 * (k + 1) : 1.0) * b[k]) * x;
+        for (int k = 0; k < row; ++k) v *= x;
+        return !(v <= tol);
+    };
+    double r = HUGE_VAL;
+    if (row <= P) {
+        if (!over(xmax)) {
+            r = s / xmax;
+        } else {
+            double lo = 0.0, hi = 40.0;  // x = xmax 2^-lo is too large, 2^-hi small enough
+            if (!over(xmax * exp2(-hi))) {
+                for (int it = 0; it < 12; ++it) {
+                    const double mid = 0.5 * (lo + hi);
+                    if (over(xmax * exp2(-mid))) lo = mid;
+                    else hi = mid;
+                }
+                r = s / (xmax * exp2(-hi));
+            }
+        }
+    }
+    float* thr = (fld ? A.thr_field : A.thr) + int64_t(TR) * nd;
+    thr[row] = row <= P ? float(r * (1.0 + 1e-6)) : 0.0f;  // a radius still
+    if (row == P) {
+        const unsigned long long u = (unsigned long long)__double_as_longlong(double(thr[row]));
+        A.own[2 * nd + fld] = u;
+        A.radius[2 * nd + fld] = u;
+    }
+}
+
+// A node is accepted only where its children would be: its radius is at least
+// each child's plus the distance of their centres.  Every node carries its
+// own up to the root (a maximum, so the order does not matter; positive
+// doubles order like their bits).
+__global__ __launch_bounds__(kB) void k_tree_raise(const int32_t* parent, const double* geo, int64_t n_nodes,
+                                                   int fields, const unsigned long long* own,
+                                                   unsigned long long* radius) {
+    const int64_t i = gid();
+    if (i >= n_nodes) return;
+    double r[2] = {0.0, 0.0};
+    for (int f = 0; f < fields; ++f) r[f] = __longlong_as_double((long long)own[2 * i + f]);
+    const double* c = geo + kGeo * i;
+    for (int nd = parent[i]; nd >= 0; nd = parent[nd]) {
+        const double* q = geo + kGeo * int64_t(nd);
+        const double dx = c[0] - q[0], dy = c[1] - q[1], dz = c[2] - q[2];
+        const double d = sqrt(dx * dx + dy * dy + dz * dz);
+        c = q;
+        for (int f = 0; f < fields; ++f) {
+            r[f] = (r[f] + d) * (1.0 + 1e-6);
+            const unsigned long long u = (unsigned long long)__double_as_longlong(r[f]);
+            if (radius[2 * int64_t(nd) + f] < u) atomicMax(&radius[2 * int64_t(nd) + f], u);
         }
     }
 }
 
-// Every node's copy of its parent's test.
-__global__ __launch_bounds__(kB) void k_tree_parents(const int32_t* parent, int64_t n_nodes, TreeTest* test,
-                                                     TreeTest* field) {
+// Squared radii by order, not growing with the order and none below the
+// node's raised radius, and the node's test (its parent's radius included).
+__global__ __launch_bounds__(kB) void k_tree_tests(const int32_t* parent, const double* geo, const TreeNode* node,
+                                                   int64_t n_nodes, int P, const unsigned long long* radius, float* thr,
+                                                   TreeTest* test, int fld) {
     const int64_t i = gid();
     if (i >= n_nodes) return;
-    const int p = parent[i];
-    if (p < 0) return;
-    for (int d = 0; d < 3; ++d) test[i].pc[d] = test[p].c[d];
-    test[i].pr2 = test[p].r2;
-    if (!field) return;
-    for (int d = 0; d < 3; ++d) field[i].pc[d] = field[p].c[d];
-    field[i].pr2 = field[p].r2;
+    auto squared = [&](int64_t nd) {
+        const double r = __longlong_as_double((long long)radius[2 * nd + fld]);
+        return float(r * r * (1.0 + 1e-6));
+    };
+    const float least = squared(i);
+    float* row = thr + int64_t(tree_thr_row(P)) * i;
+    float v = HUGE_VALF;
+    for (int p = 0; p <= P; ++p) {
+        const double r = row[p];
+        v = fminf(v, fmaxf(float(r * r * (1.0 + 1e-6)), least));
+        row[p] = v;
+    }
+    const int par = parent[i];
+    TreeTest q;
+    for (int d = 0; d < 3; ++d) {
+        q.c[d] = geo[kGeo * i + d];
+        q.pc[d] = par >= 0 ? geo[kGeo * int64_t(par) + d] : 0.0;
+    }
+    q.r2 = v;
+    q.pr2 = par >= 0 ? squared(par) : HUGE_VALF;
+    q.cost = node[i].cost;
+    q.pad = 0;
+    test[i] = q;
 }
 
 // ------------------------------------------------------------------- host
@@ -1115,17 +1170,20 @@ int refresh_tree(const Tree& t, const TreeSource& u, void* stream) {
     a.tab = t.d_tab;
     a.coef = t.d_coef;
     a.thr = t.d_thr;
-    a.test = t.d_test;
     a.thr_field = t.d_thr_field;
-    a.test_field = t.d_test_field;
     a.eps = t.eps;
     a.nuc_size = u.nuc_eps / u.eps;
-    const size_t pw = size_t(part_words(t.P)) * sizeof(double);
-    if (hipMallocAsync(reinterpret_cast<void**>(&a.part), size_t(t.n_chunks) * pw, st) != hipSuccess) return -1;
-    if (hipMallocAsync(reinterpret_cast<void**>(&a.up), size_t(t.n_nodes) * pw, st) != hipSuccess) {
-        (void)hipFreeAsync(a.part, st);
+    // chunks' moments, nodes' shifted and own moments, radii
+    const size_t pw = size_t(part_words(t.P)), nn = size_t(t.n_nodes);
+    double* work = nullptr;
+    if (hipMallocAsync(reinterpret_cast<void**>(&work), (size_t(t.n_chunks) * pw + 2 * nn * pw + 4 * nn) * sizeof(double),
+                       st) != hipSuccess)
         return -1;
-    }
+    a.part = work;
+    a.up = a.part + size_t(t.n_chunks) * pw;
+    a.mom = a.up + nn * pw;
+    a.own = reinterpret_cast<unsigned long long*>(a.mom + nn * pw);
+    a.radius = a.own + 2 * nn;
     bool ok = t.P == kTreeOrd32 || t.P == kTreeOrd64 || t.P == kTreeOrdCells32 || t.P == kTreeOrdCells64;
     const dim3 chunks(unsigned(t.n_chunks));
     if (t.P == kTreeOrd32) hipLaunchKernelGGL((k_tree_p2m<kTreeOrd32, false>), chunks, dim3(kB), 0, st, a);
@@ -1144,12 +1202,24 @@ int refresh_tree(const Tree& t, const TreeSource& u, void* stream) {
         else hipLaunchKernelGGL((k_tree_nodes<kTreeOrdCells64>), nodes, threads, 0, st, a);
         ok = hipGetLastError() == hipSuccess;
     }
-    (void)hipFreeAsync(a.up, st);
-    (void)hipFreeAsync(a.part, st);
-    if (!ok) return -1;
-    hipLaunchKernelGGL(k_tree_parents, dim3(grid_of(t.n_nodes)), dim3(kB), 0, st, t.d_parent, t.n_nodes, t.d_test,
-                       t.d_test_field);
-    return hipGetLastError() == hipSuccess ? 0 : -1;
+    if (ok) {
+        const dim3 waves(unsigned((t.n_nodes + kB / 64 - 1) / (kB / 64)));
+        if (t.P == kTreeOrd32) hipLaunchKernelGGL((k_tree_radius<kTreeOrd32>), waves, dim3(kB), 0, st, a, t.n_nodes);
+        else if (t.P == kTreeOrd64) hipLaunchKernelGGL((k_tree_radius<kTreeOrd64>), waves, dim3(kB), 0, st, a, t.n_nodes);
+        else if (t.P == kTreeOrdCells32) hipLaunchKernelGGL((k_tree_radius<kTreeOrdCells32>), waves, dim3(kB), 0, st, a, t.n_nodes);
+        else hipLaunchKernelGGL((k_tree_radius<kTreeOrdCells64>), waves, dim3(kB), 0, st, a, t.n_nodes);
+        const dim3 grid = grid_of(t.n_nodes);
+        hipLaunchKernelGGL(k_tree_raise, grid, dim3(kB), 0, st, t.d_parent, t.d_geo, t.n_nodes, t.d_test_field ? 2 : 1,
+                           a.own, a.radius);
+        hipLaunchKernelGGL(k_tree_tests, grid, dim3(kB), 0, st, t.d_parent, t.d_geo, t.d_node, t.n_nodes, t.P,
+                           a.radius, t.d_thr, t.d_test, 0);
+        if (t.d_test_field)
+            hipLaunchKernelGGL(k_tree_tests, grid, dim3(kB), 0, st, t.d_parent, t.d_geo, t.d_node, t.n_nodes, t.P,
+                               a.radius, t.d_thr_field, t.d_test_field, 1);
+        ok = hipGetLastError() == hipSuccess;
+    }
+    (void)hipFreeAsync(work, st);
+    return ok ? 0 : -1;
 }
 
 TreeView tree_view(const Tree& t) {
