@@ -111,8 +111,9 @@ __global__ __launch_bounds__(kB) void k_tree_cubes(const UpdPair* pairs, const u
     }
 }
 
-// Sort key of every item: group (27 bits), cell code of its level left
-// aligned (30), level (4), type (3): cells come out in preorder.
+// Sort key of every item: group (26 bits), cell code of its level left
+// aligned (30), step (5), type (3): cells come out in preorder, and within a
+// cell the items of larger far-field radius first.
 __global__ __launch_bounds__(kB) void k_tree_keys(const UpdPair* pairs, const uint32_t* rec, const double* nuc,
                                                   const int32_t* nuc_group, int64_t n_pairs, int64_t n_items,
                                                   int fp64, const double* cube, unsigned long long* key,
@@ -145,7 +146,11 @@ __global__ __launch_bounds__(kB) void k_tree_keys(const UpdPair* pairs, const ui
                     << (3 * b);
         }
     }
-    key[i] = ((unsigned long long)g << 37) | (code << 7) | ((unsigned long long)level << 3) |
+    const int steps = tree_steps(fp64 != 0);
+    int step = level * steps;
+    if (level < kTreeLevels)
+        for (int k = 1; k < steps && rf * kTreeKappa <= h * exp2(-double(k) / steps); ++k) ++step;
+    key[i] = ((unsigned long long)g << 38) | (code << 8) | ((unsigned long long)step << 3) |
              (unsigned long long)type;
     val[i] = uint32_t(i);
 }
@@ -752,7 +757,7 @@ __global__ __launch_bounds__(kB) void k_tree_tests(const int32_t* parent, const 
 
 struct Run {
     uint32_t code;
-    int32_t level, type;
+    int32_t step, type;
     int64_t count;
 };
 
@@ -764,6 +769,7 @@ struct HostNode {
 
 struct Builder {
     const std::vector<Run>& runs;
+    const int steps;
     std::vector<int64_t> cost;        // prefix
     std::vector<HostNode> nodes;
     std::vector<int32_t> run_node;
@@ -953,7 +959,7 @@ env_status build(Tree* t, const TreeSource& u, const std::vector<double>& nuc, c
     TREE_CHECK(hipGetLastError() == hipSuccess);
     TREE_LAUNCH(n, k_tree_keys, u.pairs, u.rec, d_nuc0, d_ng, n_pairs, n, fp64, d_cube, key, val);
     size_t tb = 0;
-    const int kb = 37 + bits_for(uint64_t(std::max(ng - 1, 0)));
+    const int kb = 38 + bits_for(uint64_t(std::max(ng - 1, 0)));
     TREE_CHECK(hipcub::DeviceRadixSort::SortPairs(nullptr, tb, key, key_s, val, val_s, int(n), 0, kb, st) ==
                hipSuccess);
     void* work = tmp.get<char>(int64_t(tb));
@@ -985,13 +991,13 @@ env_status build(Tree* t, const TreeSource& u, const std::vector<double>& nuc, c
     std::vector<size_t> group_at;  // first run of every tree
     for (size_t i = 0; i < runs.size(); ++i) {
         runs[i].type = int32_t(rkey[i] & 7ull);
-        runs[i].level = int32_t((rkey[i] >> 3) & 15ull);
-        runs[i].code = uint32_t((rkey[i] >> 7) & 0x3fffffffull);
+        runs[i].step = int32_t((rkey[i] >> 3) & 31ull);
+        runs[i].code = uint32_t((rkey[i] >> 8) & 0x3fffffffull);
         runs[i].count = (i + 1 < runs.size() ? int64_t(rstart[i + 1]) : n) - int64_t(rstart[i]);
-        if (i == 0 || (rkey[i] >> 37) != (rkey[i - 1] >> 37)) group_at.push_back(i);
+        if (i == 0 || (rkey[i] >> 38) != (rkey[i - 1] >> 38)) group_at.push_back(i);
     }
     group_at.push_back(runs.size());
-    Builder b(runs);
+    Builder b(runs, t->fp64);
     std::vector<int32_t> first;
     for (size_t g = 0; g + 1 < group_at.size(); ++g) {
         first.push_back(int32_t(b.nodes.size()));
@@ -1118,7 +1124,7 @@ Tree* build_tree(const TreeSource& u, const std::vector<double>& nuc, const std:
                  const std::vector<int32_t>& nuc_end, bool fp64, env_status* st) {
     *st = ENV_OK;
     const int64_t n_nuc = int64_t(nuc.size() / 4), n = u.n_pairs + n_nuc;
-    if (n < kTreeMinItems || n > kTreeMaxItems || u.n_groups <= 0 || u.n_groups >= (1 << 27) ||
+    if (n < kTreeMinItems || n > kTreeMaxItems || u.n_groups <= 0 || u.n_groups >= (1 << 26) ||
         int64_t(nuc_begin.size()) != u.n_groups || int64_t(nuc_end.size()) != u.n_groups)
         return nullptr;
     Tree* t = new (std::nothrow) Tree;

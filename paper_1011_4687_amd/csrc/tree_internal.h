@@ -41,6 +41,13 @@ constexpr double kTreeEpsCells32 = 3.725290298461914e-09;  // 2^-28
 constexpr double kTreeEpsCells64 = 5.551115123125783e-17;  // 2^-54
 constexpr double kTreeKappa = 0.2;
 constexpr int kTreeLevels = 10;            // 3 bits of the cell code per level
+// Classes of far-field radius per cell: with two, the items of the smaller
+// radii are a node of their own, accepted nearer by.  200 atoms, 131,072 /
+// 16,384 points: FP32C 1.43 / 0.49 ms with two, 1.69 / 0.51 with one (5000
+// atoms, 200,003 points: 1.68 / 1.95); FP64, where fewer items are evaluated
+// in their far form, 4.7 / 1.45 and 5.1 / 1.36, and the twice as many depths
+// cost a density update 0.2 ms.
+constexpr int tree_steps(bool fp64) { return fp64 ? 1 : 2; }
 constexpr int kTreeTypes = kLMax + 2;      // items of a node: pairs by L, then nuclei
 // Cost of one own item by type (an L = 0 pair is 4), for the shares of waves.
 constexpr int kTreeW[kTreeTypes] = {4, 6, 10, 18, 30, 3};
