@@ -774,7 +774,7 @@ struct Builder {
     std::vector<HostNode> nodes;
     std::vector<int32_t> run_node;
 
-    explicit Builder(const std::vector<Run>& r) : runs(r), cost(r.size() + 1, 0), run_node(r.size(), -1) {
+    Builder(const std::vector<Run>& r, bool fp64) : runs(r), steps(tree_steps(fp64)), cost(r.size() + 1, 0), run_node(r.size(), -1) {
         for (size_t i = 0; i < r.size(); ++i) cost[i + 1] = cost[i] + r[i].count * kTreeW[r[i].type];
     }
     static int digit(uint32_t code, int level) { return int((code >> (3 * (kTreeLevels - 1 - level))) & 7u); }
@@ -784,26 +784,30 @@ struct Builder {
             nodes[size_t(nd)].cnt[runs[i].type] += runs[i].count;
         }
     }
-    void build(size_t a, size_t b, int level, int32_t parent, int depth) {
+    void build(size_t a, size_t b, int step, int32_t parent, int depth) {
         const int32_t nd = int32_t(nodes.size());
         nodes.push_back(HostNode{parent, depth, {}});
         if (cost[b] - cost[a] < kTreeMinCost) {
             own(nd, a, b);
             return;
         }
-        for (; level < kTreeLevels; ++level) {
-            size_t i = a;  // the cell's own runs come first
-            while (i < b && runs[i].level == level) ++i;
+        for (; step < kTreeLevels * steps; ++step) {
+            // the next step halves the cell's edge, or keeps the cell and
+            // lowers the radii
+            const int level = step % steps == steps - 1 ? step / steps : -1;
+            auto part = [&](size_t i) { return level < 0 ? 0 : digit(runs[i].code, level); };
+            size_t i = a;  // this step's own runs come first
+            while (i < b && runs[i].step == step) ++i;
             if (i == b) break;
-            // a cell with nothing of its own and one child is that child
-            if (i == a && digit(runs[a].code, level) == digit(runs[b - 1].code, level)) continue;
+            // a step with nothing of its own and one child is that child
+            if (i == a && part(a) == part(b - 1)) continue;
             own(nd, a, i);
             while (i < b) {
                 size_t j = i;
-                const int d = digit(runs[i].code, level);
-                while (j < b && digit(runs[j].code, level) == d) ++j;
+                const int d = part(i);
+                while (j < b && part(j) == d) ++j;
                 if (cost[j] - cost[i] < kTreeMinCost / 4) own(nd, i, j);
-                else build(i, j, level + 1, nd, depth + 1);
+                else build(i, j, step + 1, nd, depth + 1);
                 i = j;
             }
             return;
