@@ -301,6 +301,7 @@ struct MomentArgs {
     const int32_t* by_depth;     // the nodes of this launch
     const TreeNode* node;
     const uint32_t* rec;
+    const uint32_t* sph;         // spherical form of every pair, at its record's place
     const double* nuc;
     const int32_t* child;
     const int32_t* child_begin;
@@ -319,7 +320,7 @@ struct MomentArgs {
     double nuc_size;             // what a unit of nuclear charge adds to the absolute charge
 };
 
-struct Cplx {
+struct alignas(16) Cplx {
     double r, i;
 };
 
@@ -334,10 +335,9 @@ __device__ __forceinline__ double node_scale(const double* geo) {
 
 constexpr int full_index(int n, int m) { return n * n + n + m; }
 
-// R_n^m(x) of one x, by the thread of order m >= 0: into tab[tree_index], or
-// with FULL, both signs of m, into tab[full_index].
-template <int P, bool FULL>
-__device__ __forceinline__ void harmonics(double x, double y, double z, int m, const double* den, Cplx* tab) {
+// R_n^m(x) of one x, by the thread of order m >= 0, to put(n, R).
+template <int P, typename Put>
+__device__ __forceinline__ void harmonics(double x, double y, double z, int m, const double* den, Put put) {
     double cr = 1.0, ci = 0.0;
     for (int k = 1; k <= m; ++k) {
         const double f = den[tree_index(P, k, k)], nr = (cr * x - ci * y) * f;
@@ -347,14 +347,8 @@ __device__ __forceinline__ void harmonics(double x, double y, double z, int m, c
     const double r2 = x * x + y * y + z * z;
     Cplx a{0.0, 0.0}, b{cr, ci};  // R_{n-1}, R_n
     const int at = tree_index(P, m, m);
-    const double sg = (m & 1) ? -1.0 : 1.0;
     for (int n = m;; ++n) {
-        if constexpr (FULL) {
-            tab[full_index(n, m)] = b;
-            if (m > 0) tab[full_index(n, -m)] = Cplx{sg * b.r, -sg * b.i};
-        } else {
-            tab[at + n - m] = b;
-        }
+        put(n, b);
         if (n == P) break;
         const double f = den[at + n + 1 - m], u = (2 * n + 1) * z;
         const Cplx c{(u * b.r - r2 * a.r) * f, (u * b.i - r2 * a.i) * f};
@@ -362,9 +356,13 @@ __device__ __forceinline__ void harmonics(double x, double y, double z, int m, c
         b = c;
     }
 }
+// R_n^{-m} = (-1)^m conj R_n^m.
+__device__ __forceinline__ Cplx mirrored(int m, const Cplx& v) {
+    return (m & 1) ? Cplx{-v.r, v.i} : Cplx{v.r, -v.i};
+}
 
 // Index of Hermite component (a, b, c) among those of order up to L.
-__device__ __forceinline__ int comp_index(int L, int a, int b, int c) {
+__host__ __device__ constexpr int comp_index(int L, int a, int b, int c) {
     const int m = L - a;
     // components with a smaller first exponent, then with a smaller second
     const int first = (L + 1) * (L + 2) * (L + 3) / 6 - (m + 1) * (m + 2) * (m + 3) / 6;
@@ -382,163 +380,259 @@ __device__ __forceinline__ void coef_nm(int t, int& n, int& m) {
     n = m + t;
 }
 
-// Items whose harmonics are in LDS at once, all (n, m) of both signs.
-constexpr int batch_of(int P) { return P <= 16 ? 8 : 4; }
+// Spherical form of a pair: Q_k^j (k <= L, 0 <= j <= k) from its Hermite
+// components, and the sum of their sizes against 1/R where its far field
+// begins, at the pair's own place in q (a record holds more words than that).
+constexpr int q_index(int k, int j) { return k * (k + 1) / 2 + j; }
 
-// acc += sum_j Q_k^j R_{n-k}^{m-j}, k fixed at compile time.
-template <int K>
-__device__ __forceinline__ void shift_order(const Cplx* Q, const Cplx* R, int n, int m, Cplx& acc) {
-    const int nn = n - K;
-    if (nn < 0) return;
-    const Cplx* row = R + full_index(nn, m);
+template <int L, bool F64>
+__device__ __forceinline__ void pair_moments(const uint32_t* r, const double* __restrict__ fold, double* q) {
+    constexpr int nc = kNComp[L];
+    static_assert(2 * q_index(L, L) + 3 <= (F64 ? rec64_words(L) : rec32_words(L)) / 2, "fits a record");
+    const double* d = reinterpret_cast<const double*>(r);
+    const float* f = reinterpret_cast<const float*>(r);
+    const double ir = rsqrt(F64 ? d[3] : double(f[6]));
+    double size = 0.0, scale = 1.0;
 #pragma unroll
-    for (int j = -K; j <= K; ++j)
-        if (m - j <= nn && m - j >= -nn) {
-            const Cplx q = Q[full_index(K, j)], r = row[-j];
-            acc.r = fma(q.r, r.r, fma(-q.i, r.i, acc.r));
-            acc.i = fma(q.r, r.i, fma(q.i, r.r, acc.i));
+    for (int k = 0; k <= L; ++k) {
+        Cplx o[kLMax + 1] = {};
+        double part = 0.0;
+#pragma unroll
+        for (int a = 0; a <= k; ++a)
+#pragma unroll
+            for (int b = 0; b <= k - a; ++b) {
+                const int c = k - a - b, at = comp_index(L, a, b, c), row = 10 * comp_index(kLMax, a, b, c);
+                const double D = F64 ? d[kRec64Head + nc + at] : double(f[kRec32Head + nc + at]);
+                part += fabs(D);
+#pragma unroll
+                for (int j = 0; j <= k; ++j) {
+                    o[j].r = fma(D, fold[row + 2 * j], o[j].r);
+                    o[j].i = fma(D, fold[row + 2 * j + 1], o[j].i);
+                }
+            }
+#pragma unroll
+        for (int j = 0; j <= k; ++j) {
+            q[2 * q_index(k, j)] = o[j].r;
+            q[2 * q_index(k, j) + 1] = o[j].i;
         }
+        size = fma(part, scale, size);
+        scale *= ir;
+    }
+    q[2 * q_index(L, L) + 2] = size;
 }
 
-// Moments of one chunk of own items about their node's centre; a workgroup
-// per chunk, thread t owns coefficient t.  Bound by the LDS reads of the
-// shifts (two complex values per multiply-add) and their latency: 375,461
-// pairs, FP64 1.14 ms, FP32C 0.56 (1.53 and 1.09 with the signs formed and
-// the index computed per term).
-template <int P, bool F64>
-__global__ __launch_bounds__(kB) void k_tree_p2m(MomentArgs A) {
+template <bool F64>
+__global__ __launch_bounds__(kB) void k_tree_spherical(const UpdPair* pairs, const int64_t* word, int64_t n_pairs,
+                                                       const uint32_t* __restrict__ rec,
+                                                       const double* __restrict__ fold, uint32_t* __restrict__ out) {
+    const int64_t i = gid();
+    if (i >= n_pairs) return;
+    const UpdPair p = pairs[i];
+    const uint32_t* r = rec + p.word;
+    double* q = reinterpret_cast<double*>(out + word[i]);
+    switch (p.L) {
+        case 0: pair_moments<0, F64>(r, fold, q); break;
+        case 1: pair_moments<1, F64>(r, fold, q); break;
+        case 2: pair_moments<2, F64>(r, fold, q); break;
+        case 3: pair_moments<3, F64>(r, fold, q); break;
+        default: pair_moments<4, F64>(r, fold, q); break;
+    }
+}
+
+// Harmonics of one item in LDS: rows n = -4 .. P, columns m = -4 .. P + 4,
+// zero where |m| > n, so that a shift by any (k, j) reads without a test.
+constexpr int kPad = kLMax;
+constexpr int pad_cols(int P) { return P + 1 + 2 * kPad; }
+constexpr int pad_size(int P) { return (P + 1 + kPad) * pad_cols(P); }
+constexpr int pad_index(int P, int n, int m) { return (n + kPad) * pad_cols(P) + m + kPad; }
+// Items a wave takes at once: a lane per item and order, as LDS allows two
+// waves per SIMD or more.
+constexpr int p2m_items(int P) { return P <= 16 ? 2 : 1; }
+
+__device__ __forceinline__ double lane_value(double v, int lane) {
+    const uint64_t b = __builtin_bit_cast(uint64_t, v);
+    const uint32_t lo = __builtin_amdgcn_readlane((uint32_t)b, lane);
+    const uint32_t hi = __builtin_amdgcn_readlane((uint32_t)(b >> 32), lane);
+    return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
+}
+
+// acc(n, m) += sum_j Q_K^j R_{n-K}^{m-j} of one item, whose Q_k^j lane
+// q0 + q_index(k, j) holds; at[c] is where (n, m) of the lane's coefficient c
+// stands in R.
+template <int P, int K, int NT>
+__device__ __forceinline__ void shift_order(const Cplx& q, int q0, const Cplx* R, const int (&at)[NT], Cplx (&acc)[NT]) {
+#pragma unroll
+    for (int j = -K; j <= K; ++j) {
+        Cplx v{lane_value(q.r, q0 + q_index(K, j < 0 ? -j : j)), lane_value(q.i, q0 + q_index(K, j < 0 ? -j : j))};
+        if (j < 0) v = mirrored(-j, v);
+#pragma unroll
+        for (int c = 0; c < NT; ++c) {
+            const Cplx r = R[at[c] - K * pad_cols(P) - j];
+            acc[c].r = fma(v.r, r.r, fma(-v.i, r.i, acc[c].r));
+            acc[c].i = fma(v.r, r.i, fma(v.i, r.r, acc[c].i));
+        }
+    }
+}
+
+// Moments of one chunk of own items about their node's centre, a workgroup
+// per chunk.  Every wave takes some items at once: a lane per item and order
+// forms the harmonics in LDS, then every lane adds each item's shifts to its
+// coefficients, the harmonics from LDS and the item's Q from the lanes that
+// loaded it.  Bound by the FP64 instructions (770 per item and wave at order
+// 20, half of them the harmonics with two thirds of the lanes idle) and their
+// chain; the loads of the next items are under way meanwhile.  375,461 pairs:
+// FP64 1.14 -> 0.94 ms, FP32C 0.56 -> 0.33 (9 million 9.6 -> 7.1); as many
+// items at once as there are lanes left one wave per SIMD: 1.11 and 0.70.
+template <int P>
+__global__ __launch_bounds__(kB) void k_tree_p2m(MomentArgs A, int fp64) {
     constexpr int NC = tree_ncoef(P);
-    constexpr int NT = (NC + kB - 1) / kB;  // coefficients of a thread: t, t + 256, ...
-    constexpr int kBatch = batch_of(P);
-    constexpr int kFold = 16;               // items whose Q are formed at once
-    static_assert(kBatch * (P + 1) <= kB && kFold * 15 <= kB && kFold % kBatch == 0 && kChunk % kFold == 0 && kChunk <= kB,
-                  "one thread per item and order");
-    __shared__ Cplx R[kBatch][(P + 1) * (P + 1)];
-    __shared__ Cplx Q[kFold][25];
-    __shared__ double xs[kChunk][3];
-    __shared__ const double* item[kChunk];
-    __shared__ int ls[kChunk];
-    __shared__ double fold[350];
-    __shared__ double den[NC];
-    __shared__ double qabs[15 * kFold];
-    const int t = threadIdx.x;
-    // (k, j) of this thread's Q
-    int qk = 0, qj = t % 15;
-    while (qj > qk) qj -= ++qk;
+    constexpr int NT = (NC + 63) / 64;  // coefficients of a lane: lane, lane + 64, ...
+    constexpr int G = p2m_items(P);
+    constexpr int kQ = q_index(kLMax, kLMax) + 1;
+    static_assert(G >= 1 && G * kQ <= 64, "a lane per item and Q");
+    static_assert(4 * NC <= 4 * G * pad_size(P), "the waves' sums fit the harmonics");
+    __shared__ Cplx R[4 * G * pad_size(P)];
+    __shared__ double qabs[4];
+    const int t = threadIdx.x, lane = t & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
+    for (int k = t; k < 4 * G * pad_size(P); k += kB) R[k] = Cplx{0.0, 0.0};
     const Chunk ck = A.chunk[blockIdx.x];
-    const int count = ck.end - ck.begin;
     const double* geo = A.geo + kGeo * int64_t(ck.node);
-    const double inv = 1.0 / node_scale(geo);
-    if (t < count) {
-        const TreeNode& node = A.node[ck.node];
-        int i = ck.begin + t, L = 0;
+    const double g0 = geo[0], g1 = geo[1], g2 = geo[2], inv = 1.0 / node_scale(geo);
+    const TreeNode& node = A.node[ck.node];
+    // this lane's Q (item lane / 15 of the wave's) and harmonic order
+    const int qi = lane / kQ, hi = lane / (P + 1), hm = lane % (P + 1);
+    int qk = 0, qj = lane % kQ;
+    while (qj > qk) qj -= ++qk;
+    double qs = 1.0;  // s^-k
+    for (int k = 0; k < qk; ++k) qs *= inv;
+    struct Items {          // as loaded: nothing waits for them here
+        int L;              // of item `lane`; -1: none
+        Cplx q;
+        double x, y, z, size;
+    };
+    auto load = [&](int first) -> Items {
+        Items v;
+        int i = first + lane, L = 0;
         int64_t w = node.rec_off;
 #pragma unroll
         for (int l = 0; l <= kLMax; ++l) {
             const int c = node.cnt[l];
             if (L == l && i >= c) {
                 i -= c;
-                w += int64_t(c) * rec_words_of(l, F64);
+                w += int64_t(c) * rec_words_of(l, fp64 != 0);
                 ++L;
             }
         }
-        const double* d = L <= kLMax ? reinterpret_cast<const double*>(A.rec + w + int64_t(i) * rec_words_of(L, F64))
-                                     : A.nuc + 4 * int64_t(node.nuc_begin + i);
-        item[t] = d;
-        ls[t] = L;
-        xs[t][0] = (d[0] - geo[0]) * inv;
-        xs[t][1] = (d[1] - geo[1]) * inv;
-        xs[t][2] = (d[2] - geo[2]) * inv;
-    }
-    for (int k = t; k < 350; k += kB) fold[k] = A.tab[tab_fold(P) + k];
-    for (int k = t; k < NC; k += kB) den[k] = A.tab[tab_den(P) + k];
-    int n[NT], m[NT];
+        v.L = lane < G && first + lane < ck.end ? L : -1;
+        w = L <= kLMax ? w + int64_t(i) * rec_words_of(L, fp64 != 0) : int64_t(node.nuc_begin + i);
+        const int qL = __shfl(v.L, qi < G ? qi : 0), hL = __shfl(v.L, hi < G ? hi : 0);
+        const int64_t qw = __shfl(w, qi < G ? qi : 0), hw = __shfl(w, hi < G ? hi : 0);
+        v.q = Cplx{0.0, 0.0};
+        v.size = 0.0;
+        if (qi < G && qL >= 0) {
+            if (qL > kLMax) {
+                if (qk == 0) v.q.r = -A.nuc[4 * qw + 3];
+            } else if (qk <= qL) {
+                const double* q = reinterpret_cast<const double*>(A.sph + qw);
+                v.q.r = q[2 * q_index(qk, qj)];
+                v.q.i = q[2 * q_index(qk, qj) + 1];
+                if (qk == 0) v.size = q[2 * q_index(qL, qL) + 2];
+            }
+        }
+        v.x = v.y = v.z = 0.0;
+        if (hi < G && hL >= 0) {
+            const double* d = hL <= kLMax ? reinterpret_cast<const double*>(A.rec + hw) : A.nuc + 4 * hw;
+            v.x = d[0];
+            v.y = d[1];
+            v.z = d[2];
+        }
+        return v;
+    };
+    // the factor of each step for the lane's order
+    double step[P];
+#pragma unroll
+    for (int n = 0; n < P; ++n)
+        step[n] = A.tab[tab_den(P) + (n < hm ? tree_index(P, n + 1, n + 1) : tree_index(P, n + 1, min(hm, n)))];
+    int at[NT];
     Cplx acc[NT];
 #pragma unroll
-    for (int k = 0; k < NT; ++k) {
-        coef_nm<P>(t + k * kB, n[k], m[k]);
-        acc[k] = Cplx{0.0, 0.0};
+    for (int c = 0; c < NT; ++c) {
+        int n = 0, m = 0;
+        if (lane + 64 * c < NC) coef_nm<P>(lane + 64 * c, n, m);
+        at[c] = pad_index(P, n, m);
+        acc[c] = Cplx{0.0, 0.0};
     }
     double qa = 0.0;
+    Cplx* mine = R + wave * (G * pad_size(P));
+    Items v{};
+    int first = ck.begin + wave * G;
+    if (first < ck.end) v = load(first);
     __syncthreads();
-    for (int f0 = 0; f0 < count; f0 += kFold) {
-        const int nf = min(kFold, count - f0);
-        if (t < 15 * nf) {  // Q_k^j of an item, scaled by s^-k, from its components of order k
-            const int it = t / 15, L = ls[f0 + it];
-            const double* d = item[f0 + it];
-            const float* f32 = reinterpret_cast<const float*>(d);
-            Cplx o{0.0, 0.0};
-            double size = 0.0;
-            if (L > kLMax) {
-                if (qk == 0) {
-                    o.r = -d[3];
-                    size = fabs(d[3]) * A.nuc_size;
-                }
-            } else if (qk <= L) {
-                const int nc = kNComp[L];
-                for (int a = 0; a <= qk; ++a)
-                    for (int b = 0; b <= qk - a; ++b) {
-                        const int c = qk - a - b;
-                        // index of (a, b, c) at this L and at order 4
-                        const int at = comp_index(L, a, b, c);
-                        const double D = F64 ? d[kRec64Head + nc + at] : double(f32[kRec32Head + nc + at]);
-                        const double* f = fold + 10 * comp_index(kLMax, a, b, c) + 2 * qj;
-                        o.r += D * f[0];
-                        o.i += D * f[1];
-                        size += fabs(D);
-                    }
-                // against 1/R where the pair's far field begins
-                const double ir = rsqrt(F64 ? d[3] : double(f32[6]));
-                for (int k = 0; k < qk; ++k) {
-                    o.r *= inv;
-                    o.i *= inv;
-                    size *= ir;
-                }
-            }
-            const double sg = (qj & 1) ? -1.0 : 1.0;
-            Q[it][full_index(qk, qj)] = o;
-            if (qj > 0) Q[it][full_index(qk, -qj)] = Cplx{sg * o.r, -sg * o.i};
-            if (qj == 0) qa += size;
-        }
-        for (int b0 = 0; b0 < nf; b0 += kBatch) {
-            const int nb = min(kBatch, nf - b0);
-            if (t < nb * (P + 1)) {
-                const double* x = xs[f0 + b0 + t / (P + 1)];
-                harmonics<P, true>(x[0], x[1], x[2], t % (P + 1), den, R[t / (P + 1)]);
-            }
-            __syncthreads();
+    for (; first < ck.end; first += 4 * G) {
+        Items next{};
+        if (first + 4 * G < ck.end) next = load(first + 4 * G);
+        if (hi < G) {
+            // R_n^m by steps of n alike in all lanes: the power of x + iy up to
+            // n = m, then the recurrence in n
+            const double x = (v.x - g0) * inv, y = (v.y - g1) * inv, z = (v.z - g2) * inv;
+            const double r2 = x * x + y * y + z * z;
+            Cplx* T = mine + hi * pad_size(P) + pad_index(P, 0, hm);
+            Cplx a{0.0, 0.0}, b{1.0, 0.0};
 #pragma unroll
-            for (int k = 0; k < NT; ++k)
-                if (t + k * kB < NC)
-                    for (int it = 0; it < nb; ++it) {
-                        const Cplx* q = Q[b0 + it];
-                        const int L = __builtin_amdgcn_readfirstlane(ls[f0 + b0 + it]);
-                        shift_order<0>(q, R[it], n[k], m[k], acc[k]);
-                        if (L > kLMax) continue;  // a nucleus
-                        if (L >= 1) shift_order<1>(q, R[it], n[k], m[k], acc[k]);
-                        if (L >= 2) shift_order<2>(q, R[it], n[k], m[k], acc[k]);
-                        if (L >= 3) shift_order<3>(q, R[it], n[k], m[k], acc[k]);
-                        if (L >= 4) shift_order<4>(q, R[it], n[k], m[k], acc[k]);
-                    }
-            __syncthreads();
+            for (int n = 0; n <= P; ++n) {
+                if (n >= hm) {
+                    T[n * pad_cols(P)] = b;
+                    if (hm > 0 && hm <= kPad) T[n * pad_cols(P) - 2 * hm] = mirrored(hm, b);
+                }
+                if (n == P) break;
+                const bool up = n < hm;
+                const double u = up ? x : (2 * n + 1) * z;
+                const double w = up ? y : r2;
+                // up: (x + iy) b; else (2n + 1) z b - r^2 a
+                const Cplx c{u * b.r - w * (up ? b.i : a.r), u * b.i + w * (up ? b.r : -a.i)};
+                if (!up) a = b;
+                b.r = c.r * step[n];
+                b.i = c.i * step[n];
+            }
         }
+        // (a nucleus's size comes from its charge)
+        const int own = __shfl(v.L, qi < G ? qi : 0);
+        qa += own > kLMax ? fabs(v.q.r) * A.nuc_size : v.size;
+        v.q.r *= qs;
+        v.q.i *= qs;
+        __builtin_amdgcn_wave_barrier();
+#pragma unroll 1
+        for (int it = 0; it < G; ++it) {
+            const int L = __builtin_amdgcn_readlane(v.L, it), q0 = it * kQ;
+            if (L < 0) break;
+            const Cplx* T = mine + it * pad_size(P);
+            shift_order<P, 0>(v.q, q0, T, at, acc);
+            if (L > kLMax) continue;  // a nucleus
+            if (L >= 1) shift_order<P, 1>(v.q, q0, T, at, acc);
+            if (L >= 2) shift_order<P, 2>(v.q, q0, T, at, acc);
+            if (L >= 3) shift_order<P, 3>(v.q, q0, T, at, acc);
+            if (L >= 4) shift_order<P, 4>(v.q, q0, T, at, acc);
+        }
+        __builtin_amdgcn_wave_barrier();
+        v = next;
     }
+#pragma unroll
+    for (int w = 32; w > 0; w >>= 1) qa += __shfl_xor(qa, w);
+    // the waves' sums in wave order
+    __syncthreads();
+#pragma unroll
+    for (int c = 0; c < NT; ++c)
+        if (lane + 64 * c < NC) R[wave * NC + lane + 64 * c] = acc[c];
+    if (lane == 0) qabs[wave] = qa;
+    __syncthreads();
     double* o = A.part + int64_t(part_words(P)) * blockIdx.x;
-#pragma unroll
-    for (int k = 0; k < NT; ++k)
-        if (t + k * kB < NC) {
-            o[2 * (t + k * kB)] = acc[k].r;
-            o[2 * (t + k * kB) + 1] = acc[k].i;
-        }
-    if (t < 15 * kFold) qabs[t] = qa;
-    __syncthreads();
-    if (t < 64) {
-        double q = 0.0;
-        for (int k = t; k < 15 * kFold; k += 64) q += qabs[k];
-#pragma unroll
-        for (int w = 32; w > 0; w >>= 1) q += __shfl_xor(q, w);
-        if (t == 0) o[2 * NC] = q;
+    for (int k = t; k < NC; k += kB) {
+        const Cplx a = R[k], b = R[NC + k], c = R[2 * NC + k], d = R[3 * NC + k];
+        o[2 * k] = (a.r + b.r) + (c.r + d.r);
+        o[2 * k + 1] = (a.i + b.i) + (c.i + d.i);
     }
+    if (t == 0) o[2 * NC] = (qabs[0] + qabs[1]) + (qabs[2] + qabs[3]);
 }
 
 constexpr int node_threads(int P) { return tree_ncoef(P) < kB ? kB : 2 * kB; }
@@ -601,15 +695,19 @@ __global__ __launch_bounds__(node_threads(P)) void k_tree_nodes(MomentArgs A) {
     }
     if (par < 0) return;
     if (t < NC) {
-        const double ratio = s * inv, sg = (m & 1) ? -1.0 : 1.0;
+        const double ratio = s * inv;
         double f = 1.0;
         for (int k = 0; k < n; ++k) f *= ratio;
         const Cplx q{acc.r * f, acc.i * f};
         Q[full_index(n, m)] = q;
-        Q[full_index(n, -m)] = m ? Cplx{sg * q.r, -sg * q.i} : q;
+        if (m > 0) Q[full_index(n, -m)] = mirrored(m, q);
     }
     __syncthreads();
-    if (t <= P) harmonics<P, true>(x[0], x[1], x[2], t, den, R);
+    if (t <= P)
+        harmonics<P>(x[0], x[1], x[2], t, den, [&](int k, const Cplx& v) {
+            R[full_index(k, t)] = v;
+            if (t > 0) R[full_index(k, -t)] = mirrored(t, v);
+        });
     __syncthreads();
     double* o = A.up + int64_t(part_words(P)) * nd;
     if (t < NC) {
@@ -1081,13 +1179,15 @@ env_status build(Tree* t, const TreeSource& u, const std::vector<double>& nuc, c
     t->n_chunks = int64_t(chunk.size());
     t->d_chunk = keep<Chunk>(t, t->n_chunks);
     t->d_chunk_begin = keep<int32_t>(t, nn + 1);
+    // chunks' moments, nodes' shifted and own moments, radii
+    t->d_work = keep<double>(t, t->n_chunks * part_words(t->P) + nn * (2 * part_words(t->P) + 4));
+    t->d_sph = keep<uint32_t>(t, t->rec_words);
     uint32_t* d_start = tmp.get<uint32_t>(int64_t(start.size()));
     unsigned long long* d_box = tmp.get<unsigned long long>(6 * nn);
     unsigned long long* d_rad = tmp.get<unsigned long long>(3 * nn);
     if (!t->d_test || !t->d_node || !t->d_thr || !t->d_coef || !t->d_tab || !t->d_first || !t->d_rec || !t->d_nuc ||
         !t->d_word || !t->d_parent || !t->d_child || !t->d_child_begin || !t->d_by_depth || !t->d_geo || !t->d_chunk ||
-        !t->d_chunk_begin ||
-        !d_start || !d_box || !d_rad)
+        !t->d_chunk_begin || !t->d_work || !t->d_sph || !d_start || !d_box || !d_rad)
         return ENV_E_NOMEM;
     std::vector<unsigned long long> box0(6 * size_t(nn));
     for (size_t k = 0; k < size_t(nn); ++k)
@@ -1183,23 +1283,31 @@ int refresh_tree(const Tree& t, const TreeSource& u, void* stream) {
     a.thr_field = t.d_thr_field;
     a.eps = t.eps;
     a.nuc_size = u.nuc_eps / u.eps;
-    // chunks' moments, nodes' shifted and own moments, radii
     const size_t pw = size_t(part_words(t.P)), nn = size_t(t.n_nodes);
-    double* work = nullptr;
-    if (hipMallocAsync(reinterpret_cast<void**>(&work), (size_t(t.n_chunks) * pw + 2 * nn * pw + 4 * nn) * sizeof(double),
-                       st) != hipSuccess)
-        return -1;
+    double* work = t.d_work;
     a.part = work;
     a.up = a.part + size_t(t.n_chunks) * pw;
     a.mom = a.up + nn * pw;
     a.own = reinterpret_cast<unsigned long long*>(a.mom + nn * pw);
     a.radius = a.own + 2 * nn;
-    bool ok = t.P == kTreeOrd32 || t.P == kTreeOrd64 || t.P == kTreeOrdCells32 || t.P == kTreeOrdCells64;
+    bool ok = true;
+    uint32_t* sph = t.d_sph;
+    if (t.n_pairs > 0) {
+        if (t.fp64)
+            hipLaunchKernelGGL(k_tree_spherical<true>, dim3(grid_of(t.n_pairs)), dim3(kB), 0, st, u.pairs, t.d_word,
+                               t.n_pairs, u.rec, t.d_tab + tab_fold(t.P), sph);
+        else
+            hipLaunchKernelGGL(k_tree_spherical<false>, dim3(grid_of(t.n_pairs)), dim3(kB), 0, st, u.pairs, t.d_word,
+                               t.n_pairs, u.rec, t.d_tab + tab_fold(t.P), sph);
+        ok = hipGetLastError() == hipSuccess;
+    }
+    a.sph = sph;
+    ok = ok && (t.P == kTreeOrd32 || t.P == kTreeOrd64 || t.P == kTreeOrdCells32 || t.P == kTreeOrdCells64);
     const dim3 chunks(unsigned(t.n_chunks));
-    if (t.P == kTreeOrd32) hipLaunchKernelGGL((k_tree_p2m<kTreeOrd32, false>), chunks, dim3(kB), 0, st, a);
-    else if (t.P == kTreeOrd64) hipLaunchKernelGGL((k_tree_p2m<kTreeOrd64, true>), chunks, dim3(kB), 0, st, a);
-    else if (t.P == kTreeOrdCells32) hipLaunchKernelGGL((k_tree_p2m<kTreeOrdCells32, false>), chunks, dim3(kB), 0, st, a);
-    else if (t.P == kTreeOrdCells64) hipLaunchKernelGGL((k_tree_p2m<kTreeOrdCells64, true>), chunks, dim3(kB), 0, st, a);
+    if (t.P == kTreeOrd32) hipLaunchKernelGGL((k_tree_p2m<kTreeOrd32>), chunks, dim3(kB), 0, st, a, t.fp64 ? 1 : 0);
+    else if (t.P == kTreeOrd64) hipLaunchKernelGGL((k_tree_p2m<kTreeOrd64>), chunks, dim3(kB), 0, st, a, t.fp64 ? 1 : 0);
+    else if (t.P == kTreeOrdCells32) hipLaunchKernelGGL((k_tree_p2m<kTreeOrdCells32>), chunks, dim3(kB), 0, st, a, t.fp64 ? 1 : 0);
+    else if (t.P == kTreeOrdCells64) hipLaunchKernelGGL((k_tree_p2m<kTreeOrdCells64>), chunks, dim3(kB), 0, st, a, t.fp64 ? 1 : 0);
     ok = ok && hipGetLastError() == hipSuccess;
     for (int d = int(t.level_begin.size()) - 2; d >= 0 && ok; --d) {
         const int n = t.level_begin[size_t(d) + 1] - t.level_begin[size_t(d)];
@@ -1228,7 +1336,6 @@ int refresh_tree(const Tree& t, const TreeSource& u, void* stream) {
                                a.radius, t.d_thr_field, t.d_test_field, 1);
         ok = hipGetLastError() == hipSuccess;
     }
-    (void)hipFreeAsync(work, st);
     return ok ? 0 : -1;
 }
 

@@ -29,7 +29,6 @@ constexpr int kTreeOrd32 = 12;
 constexpr int kTreeOrd64 = 20;
 constexpr int kTreeOrdCells32 = 16;
 constexpr int kTreeOrdCells64 = 28;
-constexpr int kTreeOrdMax = 28;
 // Truncation tolerance of one node, relative to the sum of its items'
 // absolute charges over the distance: a quarter of (FP32C) and half of
 // (FP64) the tolerance of the Boys function's far form (2^-28, 2^-56).
@@ -134,6 +133,8 @@ struct Tree {
     void* d_chunk = nullptr;            // shares of the nodes' own items
     int32_t* d_chunk_begin = nullptr;   // per node + 1
     int64_t n_chunks = 0;
+    double* d_work = nullptr;           // of a refresh: moments of chunks and nodes, radii
+    uint32_t* d_sph = nullptr;          // of a refresh: the pairs' spherical moments (rec_words)
     int64_t device_bytes = 0;
     std::vector<void*> owned;
 };
