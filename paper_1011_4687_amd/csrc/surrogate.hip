@@ -76,14 +76,13 @@ __global__ __launch_bounds__(256) void k_pack(const float* __restrict__ params, 
 
 constexpr int kLdsLd = kHidden + 8;     // padded LDS rows (bank spread of the 16-byte row reads)
 
-// num / den of den >= 1 (or NaN), correctly rounded up to ties the last step
-// can miss; v_div_fixup handles infinities and NaN.
+// num / den of den >= 1 (or NaN): the quotient of v_rcp_f32 (1 ulp), corrected
+// by its exact remainder, is rounded correctly but for the quotients within
+// 2^-22 of a tie; v_div_fixup handles infinities and NaN.
 __device__ __forceinline__ float div_ge1(float num, float den) {
-    float y = __builtin_amdgcn_rcpf(den);
-    y = __builtin_fmaf(__builtin_fmaf(-den, y, 1.0f), y, y);
-    float q = num * y;
-    q = __builtin_fmaf(__builtin_fmaf(-den, q, num), y, q);
-    return __builtin_amdgcn_div_fixupf(q, den, num);
+    const float y = __builtin_amdgcn_rcpf(den);
+    const float q = num * y;
+    return __builtin_amdgcn_div_fixupf(__builtin_fmaf(__builtin_fmaf(-den, q, num), y, q), den, num);
 }
 
 __device__ __forceinline__ float silu(float z) { return div_ge1(z, 1.0f + __expf(-z)); }
@@ -281,7 +280,7 @@ __device__ __forceinline__ float output_row(const uint16_t* h, const float* w_ou
 // Inference: features, the four layers, the output, the baseline and the
 // optional exact part.  RB row blocks of 32 per tile: two where they fill the
 // chip, so that two independent products are in flight between barriers.
-// 1,000,003 rows 1.19 -> 0.42 ms (its products alone, at the 1.18 PFLOP/s of a
+// 1,000,003 rows 1.19 -> 0.39 ms (its products alone, at the 1.18 PFLOP/s of a
 // large one, 0.11); 8192 rows 60 -> 13 us.  Before, a workgroup's four waves
 // restaged each layer's weights in LDS for every 128 rows, the features took
 // the general FP64 sincos, and the baseline's powers went through scratch.
