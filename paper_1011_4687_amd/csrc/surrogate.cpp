@@ -20,10 +20,15 @@ using namespace envpot;
 
 namespace {
 
+constexpr size_t kHostGrad = (size_t(kNParams) + 15) / 16 * 16;   // floats before the loss partials
+
 // Workspace of a training step.
 struct Workspace {
     int64_t cap = 0;    // rows (multiple of 32)
     TrainBuffers tb;
+    // pinned: the gradient, then the loss partials of a call (a copy to pageable
+    // memory waits for the stream each time and goes through the runtime's own)
+    float* host = nullptr;
 };
 
 template <typename T>
@@ -39,6 +44,7 @@ void ws_free(Workspace& w) {
     (void)hipFree(w.tb.colout);
     (void)hipFree(w.tb.loss);
     (void)hipFree(w.tb.dysum);
+    if (w.host) (void)hipHostFree(w.host);
     w = Workspace();
 }
 
@@ -52,7 +58,9 @@ bool ws_ensure(Workspace& w, int64_t rows) {
                     dalloc(&w.tb.dZT, size_t(kLayers) * w.tb.act_stride) &&
                     dalloc(&w.tb.gpart, kLayers * chunks * kHidden * kHidden) &&
                     dalloc(&w.tb.colsum, kLayers * tiles * kHidden) && dalloc(&w.tb.colout, tiles * kHidden) &&
-                    dalloc(&w.tb.loss, tiles) && dalloc(&w.tb.dysum, tiles);
+                    dalloc(&w.tb.loss, tiles) && dalloc(&w.tb.dysum, tiles) &&
+                    hipHostMalloc(reinterpret_cast<void**>(&w.host), kHostGrad * sizeof(float) + tiles * sizeof(double),
+                                  hipHostMallocDefault) == hipSuccess;
     if (!ok) ws_free(w);
     return ok;
 }
@@ -304,15 +312,16 @@ env_status env_surrogate_loss_grad(env_surrogate* s, const double* points, const
     hipStream_t st = static_cast<hipStream_t>(stream);
     step(s, points, targets, n, Np, stream);
     if (sg_last_error() != 0) return ENV_E_DEVICE;
-    std::vector<double> lp(size_t(Np / 32));
-    if (hipMemcpyAsync(lp.data(), s->ws.tb.loss, lp.size() * sizeof(double), hipMemcpyDeviceToHost, st) !=
-            hipSuccess ||
-        (grad_host && hipMemcpyAsync(grad_host, s->d_grad, kNParams * sizeof(float), hipMemcpyDeviceToHost, st) !=
+    const size_t tiles = size_t(Np / 32);
+    double* lp = reinterpret_cast<double*>(s->ws.host + kHostGrad);
+    if (hipMemcpyAsync(lp, s->ws.tb.loss, tiles * sizeof(double), hipMemcpyDeviceToHost, st) != hipSuccess ||
+        (grad_host && hipMemcpyAsync(s->ws.host, s->d_grad, kNParams * sizeof(float), hipMemcpyDeviceToHost, st) !=
                           hipSuccess) ||
         hipStreamSynchronize(st) != hipSuccess)
         return ENV_E_DEVICE;
+    if (grad_host) std::memcpy(grad_host, s->ws.host, kNParams * sizeof(float));
     double L = 0.0;
-    for (double v : lp) L += v;
+    for (size_t k = 0; k < tiles; ++k) L += lp[k];
     if (loss) *loss = L / double(n);
     return ENV_OK;
 }
