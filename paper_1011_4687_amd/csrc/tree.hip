@@ -868,11 +868,14 @@ struct HostNode {
 struct Builder {
     const std::vector<Run>& runs;
     const int steps;
+    const int64_t min_cost;
     std::vector<int64_t> cost;        // prefix
     std::vector<HostNode> nodes;
     std::vector<int32_t> run_node;
 
-    Builder(const std::vector<Run>& r, bool fp64) : runs(r), steps(tree_steps(fp64)), cost(r.size() + 1, 0), run_node(r.size(), -1) {
+    Builder(const std::vector<Run>& r, bool fp64, int P)
+        : runs(r), steps(tree_steps(fp64)), min_cost(tree_min_cost(P)), cost(r.size() + 1, 0),
+          run_node(r.size(), -1) {
         for (size_t i = 0; i < r.size(); ++i) cost[i + 1] = cost[i] + r[i].count * kTreeW[r[i].type];
     }
     static int digit(uint32_t code, int level) { return int((code >> (3 * (kTreeLevels - 1 - level))) & 7u); }
@@ -885,7 +888,7 @@ struct Builder {
     void build(size_t a, size_t b, int step, int32_t parent, int depth) {
         const int32_t nd = int32_t(nodes.size());
         nodes.push_back(HostNode{parent, depth, {}});
-        if (cost[b] - cost[a] < kTreeMinCost) {
+        if (cost[b] - cost[a] < min_cost) {
             own(nd, a, b);
             return;
         }
@@ -904,7 +907,7 @@ struct Builder {
                 size_t j = i;
                 const int d = part(i);
                 while (j < b && part(j) == d) ++j;
-                if (cost[j] - cost[i] < kTreeMinCost / 4) own(nd, i, j);
+                if (cost[j] - cost[i] < min_cost / 4) own(nd, i, j);
                 else build(i, j, step + 1, nd, depth + 1);
                 i = j;
             }
@@ -1099,7 +1102,7 @@ env_status build(Tree* t, const TreeSource& u, const std::vector<double>& nuc, c
         if (i == 0 || (rkey[i] >> 38) != (rkey[i - 1] >> 38)) group_at.push_back(i);
     }
     group_at.push_back(runs.size());
-    Builder b(runs, t->fp64);
+    Builder b(runs, t->fp64, t->P);
     std::vector<int32_t> first;
     for (size_t g = 0; g + 1 < group_at.size(); ++g) {
         first.push_back(int32_t(b.nodes.size()));

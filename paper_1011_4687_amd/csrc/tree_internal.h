@@ -50,10 +50,13 @@ constexpr int tree_steps(bool fp64) { return fp64 ? 1 : 2; }
 constexpr int kTreeTypes = kLMax + 2;      // items of a node: pairs by L, then nuclei
 // Cost of one own item by type (an L = 0 pair is 4), for the shares of waves.
 constexpr int kTreeW[kTreeTypes] = {4, 6, 10, 18, 30, 3};
-// A subtree cheaper than kTreeMinCost is one node; a child cheaper than a
-// quarter of that joins its parent's own items (a node's evaluation costs as
-// much as about 20 pairs).
-constexpr int64_t kTreeMinCost = 600;
+// A subtree cheaper than this is one node; a child cheaper than a quarter of
+// it joins its parent's own items (a node's evaluation costs as much as about
+// 20 pairs).  Pairs: 131,072 points FP32C 1.69 ms with 600, 1.70 with 300, 1.71
+// with 1500; FP64 5.06, 5.30, 5.17.  Cells: FP32C 1.04 ms with 600, 1.05 with
+// 300, 1.09 with 1200; FP64, whose order 28 costs more, 3.69 ms with 600, 5.01
+// with 300, 3.22 with 1200, 3.54 with 2400.
+constexpr int64_t tree_min_cost(int P) { return P >= kTreeOrdCells64 ? 1200 : 600; }
 // Fewer items than this are evaluated without a tree, one after the other
 // (1,830 pairs: 1024 points 46 us without, 78 with).
 constexpr int64_t kTreeMinItems = 8192;
