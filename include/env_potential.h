@@ -180,10 +180,17 @@ env_status env_potential_create(const env_nucleus* nuclei, int32_t n_nuclei,
  * points: device pointer to n x 3 float64 (x, y, z of each point, contiguous);
  * out: device pointer to n float64.  stream: hipStream_t or NULL.
  * n = 0 is a no-op.  A point exactly on a nucleus gives +inf.
+ * Environments of 8192 screened pairs and nuclei or more carry a multipole
+ * tree: groups of pairs that are far from a block of points (64 or 128) are
+ * evaluated once from their moments, to a truncation below 2^-30 (FP32C) or
+ * 2^-57 (FP64) of their absolute charge over the distance, the others pair by
+ * pair; ENVPOT_NO_TREE=1 at create leaves the tree out.
  * Calls of 32,768 points or more evaluate the points in a spatial (Morton)
  * order and write out in the caller's order (off while the stream is being
- * captured, or with ENVPOT_NO_SORT=1); the same call is bitwise repeatable.
- * A wave of points that is beyond the largest far-field radius of a pair
+ * captured), and so, with a tree, do calls of 129 points or more (also while
+ * it is captured); not with ENVPOT_NO_SORT=1.  The same call is bitwise
+ * repeatable.
+ * Without a tree, a wave of points that is beyond the largest far-field radius of a pair
  * segment's bounding box runs that segment without the per-pair near test
  * (FP32C: with the coordinate differences formed from the wave's first
  * point, at most 3 FP32 ulps of |P - C|); ENVPOT_NO_FARBOX=1 at create turns
@@ -229,10 +236,10 @@ env_status env_potential_eval_field(env_potential* h, const double* points, int6
 
 /* For callers that cannot allocate device memory (code under HIP graph
  * capture, serving loops, harnesses that forbid hipMalloc): the same values
- * as env_potential_eval, with no device allocation and no Morton ordering
- * (the points are evaluated in the caller's order, as env_potential_eval
- * does below 32,768 points).  The split-pair partial sums go to a fixed
- * 64 MiB device array (2^23 float64) that the library holds on each device
+ * as env_potential_eval, with no device allocation and without the Morton
+ * ordering of 32,768 points or more (the order of a smaller call on a handle
+ * with a tree takes the end of the array below).  The split-pair partial sums
+ * go to a fixed 64 MiB device array (2^23 float64) that the library holds on each device
  * it runs this call on until the process ends; the split factor is lowered
  * until split x n fits it.  Every call on one device shares that array, so
  * two calls whose executions overlap on one device (different streams, or
@@ -288,9 +295,10 @@ env_status env_batch_create(env_potential* const* hs, int32_t n_inst, env_batch*
 
 /* points[i]: device n[i] x 3 float64; out[i]: device n[i] float64.
  * Asynchronous on `stream` except when the pointers or counts changed.
- * Instances of 32,768 points or more are evaluated in Morton order (their
- * points are sorted into the plan's buffers before each launch; the values
- * are written back in the caller's order), as env_potential_eval does.
+ * Instances of 32,768 points or more are evaluated in Morton order (they are
+ * sorted before each launch; the values are written in the caller's order),
+ * as env_potential_eval does; on handles with a tree so are those of 129
+ * points or more, by a kernel that the graph holds.
  * While `stream` is being captured by the caller, the launch is recorded
  * into the caller's graph without the sort (the plan's pointers and counts
  * must then be the ones of an earlier call: ENV_E_STATE otherwise). */
@@ -519,8 +527,8 @@ env_status env_surrogate_predict(env_surrogate* s, const double* points, int64_t
  * compacted on the device and one persistent launch of the fallback's
  * kernel reads their count there and picks its split factor from it, so the
  * host never waits (the fallback values equal env_potential_eval's at the
- * compacted points to rounding: the split factor may differ and no Morton
- * ordering is applied).  With an exact part set (env_surrogate_set_near)
+ * compacted points to rounding: the split factor may differ and lists of
+ * 32,768 points or more are not ordered).  With an exact part set (env_surrogate_set_near)
  * every other point gets network + baseline + the exact part's V.  Calls
  * on one surrogate must not overlap (they share its workspace).
  * ENV_E_STATE before training, after the fallback's density was updated

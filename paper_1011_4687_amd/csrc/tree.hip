@@ -5,10 +5,11 @@
 // (group, cell code, level, type); the host turns the unique runs into nodes
 // (a few words per run); a second, stable sort by (node, type) places every
 // record.  Refresh, after each density fold: a copy of the records into the
-// tree's order, the moments of every node's own items (a workgroup per 128
-// items), then one launch per depth from the leaves up, a workgroup per
-// node: the sum with its children's moments, the evaluation coefficients and
-// accepted radii, and the shift to its parent's centre.
+// tree's order and the spherical form of every pair, the moments of every
+// node's own items (a workgroup per 128 items), then one launch per depth from
+// the leaves up, a workgroup per node (the sum with its children's moments,
+// the evaluation coefficients, the shift to its parent's centre), and for all
+// nodes at once the radii, raised along the ancestors, and the tests.
 //
 // Harmonics: R_n^m(x) = r^n P_n^m(cos) e^{i m phi} / (n+m)! without the
 // Condon-Shortley phase, R_m^m = (x+iy)^m / (2^m m!),

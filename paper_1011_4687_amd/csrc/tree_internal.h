@@ -69,7 +69,7 @@ constexpr int kTreeHead = 4;                                             // doub
 constexpr int tree_words(int P) { return kTreeHead + 2 * tree_ncoef(P); }// doubles per node
 
 // Points per lane of a tree evaluation of n points: two, or one where that
-// leaves too few blocks (200 atoms: FP32C 1.66 ms for 131,072 points with two,
+// leaves too few blocks (200 atoms, with one class of radius: FP32C 1.66 ms for 131,072 points with two,
 // 1.78 with four, 1.82 with one; 32 points 53 us with one, 61 with two; FP64
 // 1000 points 0.25 / 0.28 ms with one / two, 131,072 points 5.5 / 5.0).
 constexpr int tree_np(int64_t n, bool fp64) { return n <= (fp64 ? 2048 : 512) ? 1 : 2; }
