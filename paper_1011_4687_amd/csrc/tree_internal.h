@@ -79,8 +79,10 @@ constexpr int tree_np(int64_t n, bool fp64) { return n <= (fp64 ? 2048 : 512) ? 
 // little: 4 workgroups per compute unit (1000 points FP32C: 0.14 ms with 4,
 // 0.20 with 16); more blocks up to 16 (200 / 5000 atoms, 12,000 points: 0.38 /
 // 0.31 ms with 32 splits, 0.38 / 0.37 with 64; 30,000: 0.61 / 0.56 with 16,
-// 0.60 / 0.59 with 32), and two to four splits where the blocks alone fill
-// the chip (200,003 points: 2.14 ms with four, 2.26 with two).
+// 0.60 / 0.59 with 32), and four splits where the blocks alone fill the chip:
+// their near work differs, and the last ones run alone (5000 atoms: 200,003
+// points 1.63 ms with four, 1.92 with two; 400,000 2.90 / 3.30; 1,048,576 6.7 /
+// 7.6, with eight 8.5).
 constexpr int tree_klog(int64_t blocks, int64_t cu_count, int kmax) {
     int k = 0;
     if (blocks <= 64) {
@@ -88,7 +90,7 @@ constexpr int tree_klog(int64_t blocks, int64_t cu_count, int kmax) {
         return k;
     }
     while (k < kmax && (blocks << (k + 1)) <= 16 * cu_count) ++k;
-    const int least = blocks < 8 * cu_count ? 2 : 1;
+    constexpr int least = 2;
     return k > least ? k : (least < kmax ? least : kmax);
 }
 
