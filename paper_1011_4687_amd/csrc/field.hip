@@ -661,8 +661,8 @@ struct FieldEval {
 
 // Split s of the field at point block pblock (64 NP points).  VALU issue as in
 // the potential; one point per lane (field.cpp).  200 atoms, 131,072 points:
-// FP32C 39 -> 1.7 ms on an ensemble's points, 41 -> 2.5 on points of the whole
-// sphere, FP64 73 -> 10.1 there.
+// FP32C 38 -> 1.5 ms on an ensemble's points, 41 -> 2.5 on points of the whole
+// sphere, FP64 73 -> 9.7 there.
 template <int NP, bool F64>
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) void k_tree_field(FieldArgs a) {
     __shared__ float tab32[F64 ? 1 : kFieldMaxRowsF32 * kFieldRowF32];
