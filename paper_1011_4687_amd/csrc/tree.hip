@@ -9,7 +9,8 @@
 // node's own items (a workgroup per 128 items), then one launch per depth from
 // the leaves up, a workgroup per node (the sum with its children's moments,
 // the evaluation coefficients, the shift to its parent's centre), and for all
-// nodes at once the radii, raised along the ancestors, and the tests.
+// nodes at once the bound of the degrees beyond the order, the radii, raised
+// along the ancestors, and the tests.
 //
 // Harmonics: R_n^m(x) = r^n P_n^m(cos) e^{i m phi} / (n+m)! without the
 // Condon-Shortley phase, R_m^m = (x+iy)^m / (2^m m!),
@@ -299,6 +300,10 @@ struct Chunk {
 struct MomentArgs {
     const Chunk* chunk;          // chunks in node order
     const int32_t* chunk_begin;  // per node + 1
+    const int32_t* chunk_end;    // per node: one past its subtree's chunks (preorder: they follow one another)
+    const int32_t* depth;        // per node
+    const int64_t* tail_begin;   // per chunk + 1: its entries in tail, one per ancestor from the root on
+    const int32_t* tail_node;    // per entry: the ancestor
     const int32_t* by_depth;     // the nodes of this launch
     const TreeNode* node;
     const uint32_t* rec;
@@ -312,6 +317,7 @@ struct MomentArgs {
     double* part;                // per chunk: moments about the node's centre, absolute charge
     double* up;                  // per node: its moments about its parent's centre, absolute charge
     double* mom;                 // per node: its moments, absolute charge
+    double* tail;                // per entry: the chunk's share of the ancestor's A_k (k_tree_tails)
     unsigned long long* own;     // per node, potential and field: bits of the radius its moments ask for
     unsigned long long* radius;  // the same, with its descendants'
     double* coef;
@@ -382,14 +388,25 @@ __device__ __forceinline__ void coef_nm(int t, int& n, int& m) {
 }
 
 // Spherical form of a pair: Q_k^j (k <= L, 0 <= j <= k) from its Hermite
-// components, and the sum of their sizes against 1/R where its far field
-// begins, at the pair's own place in q (a record holds more words than that).
+// components, the sum of their sizes against 1/R where its far field begins,
+// and the norms of its orders 1 .. L (order 0 has one component), at the
+// pair's own place in q (a record holds as many words).
 constexpr int q_index(int k, int j) { return k * (k + 1) / 2 + j; }
+constexpr int q_size(int L) { return 2 * q_index(L, L) + 2; }
+constexpr int q_norm(int L, int k) { return q_size(L) + k; }
+
+// Weight of |Q_k^j|^2 (j and -j together) in the squared norm of order k.
+constexpr double norm_weight(int k, int j) {
+    double f = j ? 2.0 : 1.0;
+    for (int i = 2; i <= k - j; ++i) f *= i;
+    for (int i = 2; i <= k + j; ++i) f *= i;
+    return f;
+}
 
 template <int L, bool F64>
 __device__ __forceinline__ void pair_moments(const uint32_t* r, const double* __restrict__ fold, double* q) {
     constexpr int nc = kNComp[L];
-    static_assert(2 * q_index(L, L) + 3 <= (F64 ? rec64_words(L) : rec32_words(L)) / 2, "fits a record");
+    static_assert(q_norm(L, L) < (F64 ? rec64_words(L) : rec32_words(L)) / 2, "fits a record");
     const double* d = reinterpret_cast<const double*>(r);
     const float* f = reinterpret_cast<const float*>(r);
     const double ir = rsqrt(F64 ? d[3] : double(f[6]));
@@ -411,15 +428,18 @@ __device__ __forceinline__ void pair_moments(const uint32_t* r, const double* __
                     o[j].i = fma(D, fold[row + 2 * j + 1], o[j].i);
                 }
             }
+        double norm = 0.0;
 #pragma unroll
         for (int j = 0; j <= k; ++j) {
             q[2 * q_index(k, j)] = o[j].r;
             q[2 * q_index(k, j) + 1] = o[j].i;
+            norm = fma(norm_weight(k, j), fma(o[j].r, o[j].r, o[j].i * o[j].i), norm);
         }
+        if (k > 0) q[q_norm(L, k)] = sqrt(norm);
         size = fma(part, scale, size);
         scale *= ir;
     }
-    q[2 * q_index(L, L) + 2] = size;
+    q[q_size(L)] = size;
 }
 
 template <bool F64>
@@ -538,7 +558,7 @@ __global__ __launch_bounds__(kB) void k_tree_p2m(MomentArgs A, int fp64) {
                 const double* q = reinterpret_cast<const double*>(A.sph + qw);
                 v.q.r = q[2 * q_index(qk, qj)];
                 v.q.i = q[2 * q_index(qk, qj) + 1];
-                if (qk == 0) v.size = q[2 * q_index(qL, qL) + 2];
+                if (qk == 0) v.size = q[q_size(qL)];
             }
         }
         v.x = v.y = v.z = 0.0;
@@ -729,18 +749,100 @@ __global__ __launch_bounds__(node_threads(P)) void k_tree_nodes(MomentArgs A) {
     if (t == NC) o[2 * NC] = acc.r;
 }
 
-// Radii of every node from its moments alone, one wave per node: row[p] is
+// Sums that bound a node's degrees beyond P.  A source of order k and norm q
+// at distance rho from the centre has, in degree n, a norm of at most
+// C(n, k) q rho^(n-k) (attained along its axis), so with s the node's scale,
+// a s the radius of its items and
+//   A_k = sum q_k s^-k (rho / s)^(P+1-k)
+// over all items of the subtree, B_n <= sum_k A_k C(n, k) a^(n-P-1) for n > P,
+// whatever cancels in the degrees up to P (charges on the points of a
+// quadrature of the sphere have none between 0 and its own).  Formed from the
+// items of the subtree themselves: from the children's sums, by the distance of
+// the centres, the radii would grow by up to a half.  A workgroup per chunk
+// loads its items once; eight lanes per ancestor add up an eighth of them each
+// (375,461 pairs, FP32C / FP64, 18 / 9 depths: 25 / 26 us; an item per thread and
+// a sum over the workgroup per ancestor 97 / 54).
+template <int P>
+__global__ __launch_bounds__(kChunk) void k_tree_tails(MomentArgs A, int fp64) {
+    __shared__ double item[3 + kLMax + 1][kChunk];  // position, norms
+    const Chunk ck = A.chunk[blockIdx.x];
+    const TreeNode& node = A.node[ck.node];
+    const int n_items = ck.end - ck.begin;
+    if (int(threadIdx.x) < n_items) {
+        int i = ck.begin + threadIdx.x, L = 0;
+        int64_t w = node.rec_off;
+        while (L <= kLMax && i >= node.cnt[L]) {
+            i -= node.cnt[L];
+            w += int64_t(node.cnt[L]) * rec_words_of(L, fp64 != 0);
+            ++L;
+        }
+        const double *d, *q;
+        if (L <= kLMax) {
+            w += int64_t(i) * rec_words_of(L, fp64 != 0);
+            d = reinterpret_cast<const double*>(A.rec + w);
+            q = reinterpret_cast<const double*>(A.sph + w);
+        } else {
+            d = A.nuc + 4 * int64_t(node.nuc_begin + i);
+            q = d + 3;
+            L = 0;
+        }
+        for (int c = 0; c < 3; ++c) item[c][threadIdx.x] = d[c];
+        item[3][threadIdx.x] = fabs(q[0]);
+#pragma unroll
+        for (int k = 1; k <= kLMax; ++k) item[3 + k][threadIdx.x] = k <= L ? q[q_norm(L, k)] : 0.0;
+    }
+    __syncthreads();
+    const int g = threadIdx.x & 7;
+    for (int64_t e = A.tail_begin[blockIdx.x] + (threadIdx.x >> 3); e < A.tail_begin[blockIdx.x + 1]; e += kChunk / 8) {
+        const double* geo = A.geo + kGeo * int64_t(A.tail_node[e]);
+        const double g0 = geo[0], g1 = geo[1], g2 = geo[2], inv = 1.0 / node_scale(geo);
+        double acc[kLMax + 1] = {};
+        for (int i = g; i < n_items; i += 8) {
+            const double x = (item[0][i] - g0) * inv, y = (item[1][i] - g1) * inv, z = (item[2][i] - g2) * inv;
+            const double rho2 = fma(x, x, fma(y, y, z * z)), rho = sqrt(rho2);
+            double pw = (P + 1 - kLMax) % 2 ? rho : 1.0;  // rho^(P+1-k)
+#pragma unroll
+            for (int n = 0; n < (P + 1 - kLMax) / 2; ++n) pw *= rho2;
+#pragma unroll
+            for (int k = kLMax; k >= 0; --k) {
+                acc[k] = fma(item[3 + k][i], pw, acc[k]);
+                pw *= rho;
+            }
+        }
+        double sk = 1.0;  // s^-k
+#pragma unroll
+        for (int k = 0; k <= kLMax; ++k) {
+            acc[k] *= sk;
+            sk *= inv;
+#pragma unroll
+            for (int o = 1; o < 8; o <<= 1) acc[k] += __shfl_xor(acc[k], o);
+            if (g == 0) A.tail[(kLMax + 1) * e + k] = acc[k];
+        }
+    }
+}
+
+constexpr double binomial(int n, int k) {
+    double c = 1.0;
+    for (int i = 1; i <= k; ++i) c = c * (n - k + i) / i;
+    return c;
+}
+
+// Radii of every node from its moments, one wave per node: row[p] is
 // the smallest radius (at least the far-field radius and outside the items)
 // from which the degrees above p stay below eps |charge|/R,
-//   sum_{n>p} w_n B_n x^n + tail <= eps |charge|, x = s/R,
+//   sum_{P>=n>p} w_n B_n x^n + sum_{n>P} w_n x^n sum_k A_k C(n, k) a^(n-P-1)
+//     <= eps |charge|, x = s/R,
 // with B_n the norm of degree n, w_n = 1, for the gradient (against
-// |charge|/R^2) sqrt((n+1)(2n+1)) < 1.5 (n+1), and the tail beyond P the largest of
-// the last three B_n, continued, four times over.  radius: the largest order's.
+// |charge|/R^2) sqrt((n+1)(2n+1)) < 1.5 (n+1), and A_k of k_tree_tails.  The sum
+// beyond P in closed form, with y = a x and t = y/(1-y):
+//   sum_m C(N+m, k) y^m = 1/(1-y) sum_{j<=k} C(N, k-j) t^j.
+// radius: the largest order's.
 template <int P>
 __global__ __launch_bounds__(kB) void k_tree_radius(MomentArgs A, int64_t n_nodes) {
     constexpr int NC = tree_ncoef(P), TR = tree_thr_row(P);
     static_assert(2 * TR <= 64, "a lane per order of the potential and of the field");
     __shared__ double bn[kB / 64][P + 1];
+    __shared__ double an[kB / 64][kLMax + 1];
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
     const int64_t nd = int64_t(blockIdx.x) * (kB / 64) + wave;
     const bool live = nd < n_nodes;
@@ -753,19 +855,45 @@ __global__ __launch_bounds__(kB) void k_tree_radius(MomentArgs A, int64_t n_node
         }
         bn[wave][lane] = sqrt(b);
     }
+    {
+        // eight lanes per chunk of the subtree, eight chunks at a time
+        double v = 0.0;
+        if (live && (lane & 7) <= kLMax) {
+            const int depth = A.depth[nd];
+#pragma unroll 4
+            for (int c = A.chunk_begin[nd] + (lane >> 3); c < A.chunk_end[nd]; c += 8)
+                v += A.tail[(kLMax + 1) * (A.tail_begin[c] + depth) + (lane & 7)];
+        }
+        for (int o = 8; o < 64; o <<= 1) v += __shfl_xor(v, o);
+        if (lane <= kLMax) an[wave][lane] = v * (1.0 + 1e-9);
+    }
     __syncthreads();
     if (!live) return;
     const int fld = lane / TR, row = lane % TR;
     if (fld > 1 || (fld == 1 && !A.thr_field)) return;
-    const double* b = bn[wave];
+    const double *b = bn[wave], *ak = an[wave];
     const double* geo = A.geo + kGeo * nd;
     const double s = node_scale(geo), tol = A.eps * mo[2 * NC];
     const double rmin = fmax(geo[4 + fld], 1.02 * geo[3]);
     const double xmax = rmin > 0.0 ? s / rmin : 0.98;
-    const double tail = 4.0 * fmax(b[P], fmax(b[P - 1], b[P - 2])) * (fld ? 1.5 * (P + 2) : 1.0);
+    const double a = geo[3] / s;
     auto over = [&](double x) {
-        const double g = 1.0 / (1.0 - x);
-        double v = tail * x * g * (fld ? g : 1.0);
+        const double y = a * x, g = 1.0 / (1.0 - y), t = y * g;
+        double v = 0.0;
+#pragma unroll
+        for (int k = 0; k <= kLMax; ++k) {
+            double c = 0.0;
+            if (fld) {
+                // (n + 1) C(n, k) = (k + 1) C(n + 1, k + 1)
+#pragma unroll
+                for (int j = k + 1; j >= 0; --j) c = fma(c, t, 1.5 * (k + 1) * binomial(P + 2, k + 1 - j));
+            } else {
+#pragma unroll
+                for (int j = k; j >= 0; --j) c = fma(c, t, binomial(P + 1, k - j));
+            }
+            v = fma(ak[k], c, v);
+        }
+        v *= x * g;
         for (int k = P; k > row; --k) v = (v + (fld ? 1.5 * (k + 1) : 1.0) * b[k]) * x;
         for (int k = 0; k < row; ++k) v *= x;
         return !(v <= tol);
@@ -1119,6 +1247,9 @@ env_status build(Tree* t, const TreeSource& u, const std::vector<double>& nuc, c
         child_begin(size_t(nn) + 1, 0);
     std::vector<Chunk> chunk;
     std::vector<int32_t> chunk_begin(size_t(nn) + 1, 0);
+    std::vector<int32_t> chunk_end(static_cast<size_t>(nn)), depth(static_cast<size_t>(nn));
+    std::vector<int64_t> tail_begin(1, 0);
+    std::vector<int32_t> tail_node;
     int64_t words = 0, item = 0, nucs = 0;
     int max_depth = 0;
     for (int64_t k = 0; k < nn; ++k) {
@@ -1159,6 +1290,21 @@ env_status build(Tree* t, const TreeSource& u, const std::vector<double>& nuc, c
         std::vector<int32_t> lv(t->level_begin.begin(), t->level_begin.end() - 1);
         for (int64_t k = 0; k < nn; ++k) by_depth[size_t(lv[size_t(b.nodes[size_t(k)].depth)]++)] = int32_t(k);
     }
+    for (int64_t k = nn - 1; k >= 0; --k) {
+        int32_t& e = chunk_end[size_t(k)];
+        e = std::max(e, chunk_begin[size_t(k) + 1]);
+        if (parent[size_t(k)] >= 0) chunk_end[size_t(parent[size_t(k)])] = std::max(chunk_end[size_t(parent[size_t(k)])], e);
+    }
+    std::vector<int32_t> path;  // the ancestors of node k, from the root to k
+    for (int64_t k = 0; k < nn; ++k) {
+        depth[size_t(k)] = b.nodes[size_t(k)].depth;
+        path.resize(size_t(depth[size_t(k)]));
+        path.push_back(int32_t(k));
+        for (int32_t c = chunk_begin[size_t(k)]; c < chunk_begin[size_t(k) + 1]; ++c) {
+            tail_node.insert(tail_node.end(), path.begin(), path.end());
+            tail_begin.push_back(int64_t(tail_node.size()));
+        }
+    }
     t->rec_words = words;
     const std::vector<double> tab = tables(P);
     t->d_test = keep<TreeTest>(t, nn);
@@ -1183,15 +1329,21 @@ env_status build(Tree* t, const TreeSource& u, const std::vector<double>& nuc, c
     t->n_chunks = int64_t(chunk.size());
     t->d_chunk = keep<Chunk>(t, t->n_chunks);
     t->d_chunk_begin = keep<int32_t>(t, nn + 1);
-    // chunks' moments, nodes' shifted and own moments, radii
-    t->d_work = keep<double>(t, t->n_chunks * part_words(t->P) + nn * (2 * part_words(t->P) + 4));
+    t->d_chunk_end = keep<int32_t>(t, nn);
+    t->d_depth = keep<int32_t>(t, nn);
+    t->d_tail_begin = keep<int64_t>(t, t->n_chunks + 1);
+    t->d_tail_node = keep<int32_t>(t, int64_t(tail_node.size()));
+    // chunks' moments, nodes' shifted and own moments, radii, chunks' shares of the bounds
+    t->d_work = keep<double>(t, t->n_chunks * part_words(t->P) + nn * (2 * part_words(t->P) + 4) +
+                                    int64_t(tail_node.size()) * (kLMax + 1));
     t->d_sph = keep<uint32_t>(t, t->rec_words);
     uint32_t* d_start = tmp.get<uint32_t>(int64_t(start.size()));
     unsigned long long* d_box = tmp.get<unsigned long long>(6 * nn);
     unsigned long long* d_rad = tmp.get<unsigned long long>(3 * nn);
     if (!t->d_test || !t->d_node || !t->d_thr || !t->d_coef || !t->d_tab || !t->d_first || !t->d_rec || !t->d_nuc ||
         !t->d_word || !t->d_parent || !t->d_child || !t->d_child_begin || !t->d_by_depth || !t->d_geo || !t->d_chunk ||
-        !t->d_chunk_begin || !t->d_work || !t->d_sph || !d_start || !d_box || !d_rad)
+        !t->d_chunk_begin || !t->d_chunk_end || !t->d_depth || !t->d_tail_begin ||
+        !t->d_tail_node || !t->d_work || !t->d_sph || !d_start || !d_box || !d_rad)
         return ENV_E_NOMEM;
     std::vector<unsigned long long> box0(6 * size_t(nn));
     for (size_t k = 0; k < size_t(nn); ++k)
@@ -1200,7 +1352,9 @@ env_status build(Tree* t, const TreeSource& u, const std::vector<double>& nuc, c
                put(t->d_parent, parent, st) && put(t->d_child, child, st) && put(t->d_child_begin, child_begin, st) &&
                put(t->d_by_depth, by_depth, st) && put(d_start, start, st) && put(d_run_node, b.run_node, st) &&
                put(d_box, box0, st) && put(static_cast<Chunk*>(t->d_chunk), chunk, st) &&
-               put(t->d_chunk_begin, chunk_begin, st));
+               put(t->d_chunk_begin, chunk_begin, st) && put(t->d_chunk_end, chunk_end, st) &&
+               put(t->d_depth, depth, st) && put(t->d_tail_begin, tail_begin, st) &&
+               put(t->d_tail_node, tail_node, st));
     // records by (node, type), in pair order within
     TREE_LAUNCH(n, k_tree_nodekeys, key_s, runid, d_run_node, n, nkey);
     const int nb = bits_for(uint64_t(nn) * kTreeTypes);
@@ -1294,6 +1448,11 @@ int refresh_tree(const Tree& t, const TreeSource& u, void* stream) {
     a.mom = a.up + nn * pw;
     a.own = reinterpret_cast<unsigned long long*>(a.mom + nn * pw);
     a.radius = a.own + 2 * nn;
+    a.tail = reinterpret_cast<double*>(a.radius + 2 * nn);
+    a.chunk_end = t.d_chunk_end;
+    a.depth = t.d_depth;
+    a.tail_begin = t.d_tail_begin;
+    a.tail_node = t.d_tail_node;
     bool ok = true;
     uint32_t* sph = t.d_sph;
     if (t.n_pairs > 0) {
@@ -1322,6 +1481,15 @@ int refresh_tree(const Tree& t, const TreeSource& u, void* stream) {
         else if (t.P == kTreeOrd64) hipLaunchKernelGGL((k_tree_nodes<kTreeOrd64>), nodes, threads, 0, st, a);
         else if (t.P == kTreeOrdCells32) hipLaunchKernelGGL((k_tree_nodes<kTreeOrdCells32>), nodes, threads, 0, st, a);
         else hipLaunchKernelGGL((k_tree_nodes<kTreeOrdCells64>), nodes, threads, 0, st, a);
+        ok = hipGetLastError() == hipSuccess;
+    }
+    if (ok) {
+        const dim3 block(kChunk);
+        const int fp64 = t.fp64 ? 1 : 0;
+        if (t.P == kTreeOrd32) hipLaunchKernelGGL((k_tree_tails<kTreeOrd32>), chunks, block, 0, st, a, fp64);
+        else if (t.P == kTreeOrd64) hipLaunchKernelGGL((k_tree_tails<kTreeOrd64>), chunks, block, 0, st, a, fp64);
+        else if (t.P == kTreeOrdCells32) hipLaunchKernelGGL((k_tree_tails<kTreeOrdCells32>), chunks, block, 0, st, a, fp64);
+        else hipLaunchKernelGGL((k_tree_tails<kTreeOrdCells64>), chunks, block, 0, st, a, fp64);
         ok = hipGetLastError() == hipSuccess;
     }
     if (ok) {

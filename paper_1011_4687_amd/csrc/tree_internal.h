@@ -138,7 +138,11 @@ struct Tree {
     void* d_chunk = nullptr;            // shares of the nodes' own items
     int32_t* d_chunk_begin = nullptr;   // per node + 1
     int64_t n_chunks = 0;
-    double* d_work = nullptr;           // of a refresh: moments of chunks and nodes, radii
+    int32_t* d_chunk_end = nullptr;     // per node: one past its subtree's chunks
+    int32_t* d_depth = nullptr;         // per node
+    int64_t* d_tail_begin = nullptr;    // per chunk + 1: its shares of its ancestors' bounds
+    int32_t* d_tail_node = nullptr;     // per share: the ancestor
+    double* d_work = nullptr;           // of a refresh: moments of chunks and nodes, radii, bounds
     uint32_t* d_sph = nullptr;          // of a refresh: the pairs' spherical moments (rec_words)
     int64_t device_bytes = 0;
     std::vector<void*> owned;
