@@ -86,6 +86,7 @@ struct env_surrogate {
     env_potential* near = nullptr;   // exactly evaluated part added to the network (may be null)
     uint64_t fallback_gen = 0;   // the fallback's density generation when the network was trained
     int device = -1;
+    int cu_count = 0;            // of the device (the fallback may be gone before the network is)
     double radius = 6.0;
     int degree = 0;
     std::vector<int8_t> mono;
@@ -136,7 +137,7 @@ env_status upload_baseline(env_surrogate* s) {
 // gradient into d_grad.
 void step(env_surrogate* s, const double* pts, const float* t, int64_t n, int64_t Np, void* st,
           const TrainTrace& trace = TrainTrace()) {
-    sg_train(pts, t, n, Np, s->d_B, s->d_W, s->d_WT, s->d_params, s->ws.tb, trace, s->d_grad, s->fallback->cu_count, st);
+    sg_train(pts, t, n, Np, s->d_B, s->d_W, s->d_WT, s->d_params, s->ws.tb, trace, s->d_grad, s->cu_count, st);
 }
 
 // Surrogate values (baseline + network, plus add[i] when add is not null) at
@@ -144,7 +145,7 @@ void step(env_surrogate* s, const double* pts, const float* t, int64_t n, int64_
 env_status predict(env_surrogate* s, const double* pts, int64_t n, double* out, void* st,
                    const double* add = nullptr) {
     sg_infer(pts, n, s->d_B, s->d_W, s->d_params, s->d_coef, 1.0 / s->radius, s->sigma, add, out,
-             s->fallback->cu_count, st);
+             s->cu_count, st);
     return sg_last_error() == 0 ? ENV_OK : ENV_E_DEVICE;
 }
 
@@ -249,6 +250,7 @@ env_status env_surrogate_create(env_potential* fallback, const env_surrogate_spe
     if (!s) return ENV_E_NOMEM;
     s->fallback = fallback;
     s->device = fallback->device;
+    s->cu_count = fallback->cu_count;
     s->radius = spec->radius;
     s->degree = spec->poly_degree;
     s->mono = monomials(s->degree);
