@@ -25,6 +25,14 @@ __device__ __forceinline__ const PTS T* gpts(const T* p) {
     return (const PTS T*)p;
 }
 
+// What the lanes of this wave wrote (LDS) before is seen by all of them after:
+// orders the accesses, without an instruction of its own.
+__device__ __forceinline__ void wave_sync() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 // 1/sqrt(x) from v_rsq_f32 plus one Newton correction y + y (1 - x y^2) / 2.
 __device__ __forceinline__ float rsqrt_refined(float x) {
     const float y = __builtin_amdgcn_rsqf(x);

@@ -33,6 +33,7 @@
 #include <limits>
 #include <new>
 
+#include "device_math.h"
 #include "tree_internal.h"
 #include "update_internal.h"
 
@@ -622,7 +623,7 @@ __global__ __launch_bounds__(kB) void k_tree_p2m(MomentArgs A, int fp64) {
         qa += own > kLMax ? fabs(v.q.r) * A.nuc_size : v.size;
         v.q.r *= qs;
         v.q.i *= qs;
-        __builtin_amdgcn_wave_barrier();
+        wave_sync();
 #pragma unroll 1
         for (int it = 0; it < G; ++it) {
             const int L = __builtin_amdgcn_readlane(v.L, it), q0 = it * kQ;
@@ -635,7 +636,7 @@ __global__ __launch_bounds__(kB) void k_tree_p2m(MomentArgs A, int fp64) {
             if (L >= 3) shift_order<P, 3>(v.q, q0, T, at, acc);
             if (L >= 4) shift_order<P, 4>(v.q, q0, T, at, acc);
         }
-        __builtin_amdgcn_wave_barrier();
+        wave_sync();
         v = next;
     }
 #pragma unroll

@@ -167,6 +167,7 @@ __device__ __forceinline__ void tree_walk(const TreeView& tv, int s, const doubl
     // that depends on the split may move the meeting points of the waves,
     // which cut the own items (the same in every split) into parts.
     auto far_alone = [&]() {
+        wave_sync();
         for (int e0 = 0; e0 < nf; e0 += 64) {
             const int k = min(64, nf - e0);
             int nd = 0, o = 0;
@@ -179,6 +180,7 @@ __device__ __forceinline__ void tree_walk(const TreeView& tv, int s, const doubl
                        __builtin_amdgcn_readlane(o, q));
         }
         nf = 0;
+        wave_sync();
     };
     // Evaluate the collected lists: they are put together in wave order, cut
     // by cost, and every wave evaluates its share.
