@@ -451,6 +451,12 @@ env_status env_potential_create(const env_nucleus* nuclei, int32_t n_nuclei,
             h->tree = build_tree(tree_source(*h->upd, h->d_rec, h->fp, fp64), pl.nuc, pl.group_nuc_begin, pl.group_nuc_end, fp64,
                                  &st);
             if (h->tree) h->device_bytes += h->tree->device_bytes;
+            // (records folded on the host are whole already; the device's are
+            // not before the first update below, which refreshes the tree)
+            if (st == ENV_OK && h->tree && !src.device_fold &&
+                (refresh_tree(*h->tree, tree_source(*h->upd, h->d_rec, h->fp, fp64), nullptr) != 0 ||
+                 hipStreamSynchronize(nullptr) != hipSuccess))
+                st = ENV_E_DEVICE;
             lap("tree");
         }
         // the first fold of the density, on the device
