@@ -184,7 +184,8 @@ env_status env_potential_create(const env_nucleus* nuclei, int32_t n_nuclei,
  * tree: groups of pairs that are far from a block of points (64 or 128) are
  * evaluated once from their moments, to a truncation below 2^-30 (FP32C) or
  * 2^-57 (FP64) of their absolute charge over the distance, the others pair by
- * pair; ENVPOT_NO_TREE=1 at create leaves the tree out.
+ * pair; ENVPOT_NO_TREE=1 at create leaves the tree out, and so does a device
+ * that has no memory for it (ENVPOT_TREE_MAX_MB=N at create: more than N MiB).
  * Calls of 32,768 points or more evaluate the points in a spatial (Morton)
  * order and write out in the caller's order (off while the stream is being
  * captured), and so, with a tree, do calls of 129 points or more (also while

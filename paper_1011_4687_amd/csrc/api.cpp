@@ -460,7 +460,16 @@ env_status env_potential_create(const env_nucleus* nuclei, int32_t n_nuclei,
             lap("tree");
         }
         // the first fold of the density, on the device
-        if (st == ENV_OK && src.device_fold) st = env_potential_update_density(h, P, nullptr);
+        if (st == ENV_OK && src.device_fold) {
+            st = env_potential_update_density(h, P, nullptr);
+            if (st == ENV_E_NOMEM && h->tree) {  // the tree's memory may be enough for it
+                h->device_bytes -= h->tree->device_bytes;
+                free_tree(h->tree);
+                h->tree = nullptr;
+                (void)hipGetLastError();
+                st = env_potential_update_density(h, P, nullptr);
+            }
+        }
         lap("device fold");
     }
     free_device_build(db);

@@ -29,6 +29,7 @@
 
 #include <algorithm>
 #include <cmath>
+#include <cstdlib>
 #include <cstring>
 #include <limits>
 #include <new>
@@ -1103,14 +1104,24 @@ std::vector<double> tables(int P) {
     return t;
 }
 
-// Temporary device memory of the build.
+// Device memory of the build, nullptr when there is not as much or `room`
+// (bytes that are left to the tree) is used up.
+void* device_memory(int64_t& room, size_t nb) {
+    void* q = nullptr;
+    if (int64_t(nb) > room || hipMalloc(&q, nb) != hipSuccess) return nullptr;
+    room -= int64_t(nb);
+    return q;
+}
+
+// Temporary memory of the build.
 struct Temp {
+    int64_t& room;
     std::vector<void*> p;
+    explicit Temp(int64_t& r) : room(r) {}
     template <class T>
     T* get(int64_t n) {
-        void* q = nullptr;
-        if (hipMalloc(&q, size_t(std::max<int64_t>(n, 1)) * sizeof(T)) != hipSuccess) return nullptr;
-        p.push_back(q);
+        void* q = device_memory(room, size_t(std::max<int64_t>(n, 1)) * sizeof(T));
+        if (q) p.push_back(q);
         return static_cast<T*>(q);
     }
     ~Temp() {
@@ -1120,9 +1131,9 @@ struct Temp {
 
 template <class T>
 T* keep(Tree* t, int64_t n) {
-    void* q = nullptr;
     const size_t nb = size_t(std::max<int64_t>(n, 1)) * sizeof(T);
-    if (hipMalloc(&q, nb) != hipSuccess) return nullptr;
+    void* q = device_memory(t->room, nb);
+    if (!q) return nullptr;
     t->owned.push_back(q);
     t->device_bytes += int64_t(nb);
     return static_cast<T*>(q);
@@ -1162,7 +1173,7 @@ env_status build(Tree* t, const TreeSource& u, const std::vector<double>& nuc, c
             (void)hipStreamDestroy(s);
         }
     };
-    Temp tmp;       // freed after the stream has drained (declared before the guard)
+    Temp tmp(t->room);  // freed after the stream has drained (declared before the guard)
     Guard guard{st};
     const int fp64 = t->fp64 ? 1 : 0, P = t->P;
     const int64_t n_pairs = t->n_pairs, n_nuc = t->n_nuc, n = n_pairs + n_nuc;
@@ -1391,15 +1402,14 @@ Tree* build_tree(const TreeSource& u, const std::vector<double>& nuc, const std:
         int64_t(nuc_begin.size()) != u.n_groups || int64_t(nuc_end.size()) != u.n_groups)
         return nullptr;
     Tree* t = new (std::nothrow) Tree;
-    if (!t) {
-        *st = ENV_E_NOMEM;
-        return nullptr;
-    }
+    if (!t) return nullptr;
     t->fp64 = fp64;
     t->P = u.order;
     t->eps = u.eps;
     t->n_pairs = u.n_pairs;
     t->n_nuc = n_nuc;
+    if (const char* e = std::getenv("ENVPOT_TREE_MAX_MB"))
+        if (*e) t->room = std::max<int64_t>(std::atoll(e), 0) << 20;
     try {
         *st = build(t, u, nuc, nuc_begin, nuc_end);
     } catch (const std::bad_alloc&) {
@@ -1407,6 +1417,10 @@ Tree* build_tree(const TreeSource& u, const std::vector<double>& nuc, const std:
     }
     if (*st != ENV_OK) {
         free_tree(t);
+        if (*st == ENV_E_NOMEM) {
+            *st = ENV_OK;              // every item can be evaluated without one
+            (void)hipGetLastError();   // the allocation's
+        }
         return nullptr;
     }
     return t;

@@ -145,6 +145,7 @@ struct Tree {
     double* d_work = nullptr;           // of a refresh: moments of chunks and nodes, radii, bounds
     uint32_t* d_sph = nullptr;          // of a refresh: the pairs' spherical moments (rec_words)
     int64_t device_bytes = 0;
+    int64_t room = INT64_MAX;           // device bytes that the tree may still take
     std::vector<void*> owned;
 };
 
@@ -166,7 +167,8 @@ struct TreeSource {
 };
 
 // Build the tree (synchronous).  nullptr with *st == ENV_OK when the input
-// does not fit the tree's index widths: the handle then evaluates every item.
+// does not fit the tree's index widths, or the memory (ENVPOT_TREE_MAX_MB or the
+// device's) the tree: the handle then evaluates every item.
 // nuc: n x 4 (position, charge); nuc_begin, nuc_end: range of each group.
 Tree* build_tree(const TreeSource& src, const std::vector<double>& nuc, const std::vector<int32_t>& nuc_begin,
                  const std::vector<int32_t>& nuc_end, bool fp64, env_status* st);
