@@ -188,9 +188,10 @@ env_status env_potential_create(const env_nucleus* nuclei, int32_t n_nuclei,
  * that has no memory for it (ENVPOT_TREE_MAX_MB=N at create: more than N MiB).
  * Calls of 32,768 points or more evaluate the points in a spatial (Morton)
  * order and write out in the caller's order (off while the stream is being
- * captured), and so, with a tree, do calls of 129 points or more (also while
- * it is captured); not with ENVPOT_NO_SORT=1.  The same call is bitwise
- * repeatable.
+ * captured), and so, with a tree, do smaller calls of 129 points or more (also
+ * while it is captured); not with ENVPOT_NO_SORT=1.  The same call is bitwise
+ * repeatable.  A captured call records the allocation of its partial sums;
+ * env_potential_eval_noalloc, made for graphs, records none.
  * Without a tree, a wave of points that is beyond the largest far-field radius of a pair
  * segment's bounding box runs that segment without the per-pair near test
  * (FP32C: with the coordinate differences formed from the wave's first
@@ -237,12 +238,13 @@ env_status env_potential_eval_field(env_potential* h, const double* points, int6
 
 /* For callers that cannot allocate device memory (code under HIP graph
  * capture, serving loops, harnesses that forbid hipMalloc): the same values
- * as env_potential_eval, with no device allocation and without the Morton
- * ordering of 32,768 points or more (the order of a smaller call on a handle
- * with a tree takes the end of the array below).  The split-pair partial sums
+ * as env_potential_eval, with no device allocation and without its Morton
+ * sort (on a handle with a tree, calls of 129 points or more have an order of
+ * the library's own kernel, from 32,768 on slice by slice, at the end of the
+ * array below).  The split-pair partial sums
  * go to a fixed 64 MiB device array (2^23 float64) that the library holds on each device
  * it runs this call on until the process ends; the split factor is lowered
- * until split x n fits it.  Every call on one device shares that array, so
+ * until split x n (and the order) fits it.  Every call on one device shares that array, so
  * two calls whose executions overlap on one device (different streams, or
  * different handles on the same device) race and give wrong values: order
  * them on one stream or with events.  points, out, stream: as
@@ -301,8 +303,8 @@ env_status env_batch_create(env_potential* const* hs, int32_t n_inst, env_batch*
  * as env_potential_eval does; on handles with a tree so are those of 129
  * points or more, by a kernel that the graph holds.
  * While `stream` is being captured by the caller, the launch is recorded
- * into the caller's graph without the sort (the plan's pointers and counts
- * must then be the ones of an earlier call: ENV_E_STATE otherwise). */
+ * into the caller's graph without the sort (with trees by the kernel's order,
+ * slice by slice; the plan's pointers and counts must then be the ones of an earlier call: ENV_E_STATE otherwise). */
 env_status env_batch_eval(env_batch* b, const double* const* points, const int64_t* n,
                           double* const* out, void* stream);
 
@@ -528,8 +530,8 @@ env_status env_surrogate_predict(env_surrogate* s, const double* points, int64_t
  * compacted on the device and one persistent launch of the fallback's
  * kernel reads their count there and picks its split factor from it, so the
  * host never waits (the fallback values equal env_potential_eval's at the
- * compacted points to rounding: the split factor may differ and lists of
- * 32,768 points or more are not ordered).  With an exact part set (env_surrogate_set_near)
+ * compacted points to rounding: the split factor and, from 32,768 points on,
+ * the order may differ).  With an exact part set (env_surrogate_set_near)
  * every other point gets network + baseline + the exact part's V.  Calls
  * on one surrogate must not overlap (they share its workspace).
  * ENV_E_STATE before training, after the fallback's density was updated

@@ -95,7 +95,17 @@ void tree_shape(const env_potential* h, int64_t n, int* np, int* k_out) {
     *k_out = tree_klog(blocks, h->cu_count, kMaxSplitLog2);
 }
 
-void choose_shape(const env_potential* h, int64_t n, int* np_out, int* k_out) {
+// Points in no order share few nodes: on small environments every pair is then
+// quicker (131,072 points, FP32C / FP64, the tree's time over every pair's: 13,170
+// pairs 1.10 / 1.32, 22,514 1.25 / 1.29, 32,985 0.96 / 1.12, 67,665 0.64 / 0.83; 16,384 points,
+// 22,514 pairs 1.08 / 1.24, 8192 points 0.96 / 1.23, 4096 points, 13,170 pairs 0.54 / 0.78).
+bool use_tree(const env_potential* h, int64_t n, bool ordered) {
+    if (!h->tree) return false;
+    const bool many = n >= (h->precision == ENV_PREC_FP64 ? 8192 : 16384);
+    return ordered || !many || h->tree->n_pairs + h->tree->n_nuc >= 3 * (int64_t(1) << 14);
+}
+
+void choose_shape(const env_potential* h, int64_t n, bool tree, int* np_out, int* k_out) {
     const bool fp64 = h->precision == ENV_PREC_FP64;
     // a tuned shape for a point count within a factor 2 of n wins
     const env_potential::Tuned* best = nullptr;
@@ -105,7 +115,7 @@ void choose_shape(const env_potential* h, int64_t n, int* np_out, int* k_out) {
         if (d < bestd) { bestd = d; best = &t; }
     }
     int np, k = 0;
-    if (h->tree && !(best && bestd <= std::log(2.0))) {
+    if (tree && !(best && bestd <= std::log(2.0))) {
         tree_shape(h, n, &np, &k);
     } else if (best && bestd <= std::log(2.0)) {
         np = best->np;
@@ -135,7 +145,7 @@ void choose_shape(const env_potential* h, int64_t n, int* np_out, int* k_out) {
     *k_out = k;
 }
 
-EvalArgs make_args(const env_potential* h, const double* points, int64_t n, double* out, int k) {
+EvalArgs make_args(const env_potential* h, const double* points, int64_t n, double* out, int k, bool tree) {
     EvalArgs a;
     a.pts = points;
     a.n = n;
@@ -147,7 +157,7 @@ EvalArgs make_args(const env_potential* h, const double* points, int64_t n, doub
     a.boxes = h->use_boxes ? h->d_boxes : nullptr;
     a.out = out;
     a.bp = h->bp;
-    a.tree = h->tree ? tree_view(*h->tree) : TreeView{};
+    a.tree = tree ? tree_view(*h->tree) : TreeView{};
     a.tree.S = 1 << k;
     a.order = nullptr;
     return a;
@@ -159,7 +169,7 @@ env_status eval_devsized(env_potential* h, const double* points, const int64_t* 
     if (n_max <= 0) return ENV_OK;
     if (part_cap < n_max) return ENV_E_ARG;
     DevSizedArgs d;
-    d.a = make_args(h, points, 0, part, 0);
+    d.a = make_args(h, points, 0, part, 0, h->tree != nullptr);
     d.m = m;
     d.segs_all = h->d_segs;
     d.split_all = h->d_split;
@@ -174,11 +184,13 @@ env_status eval_devsized(env_potential* h, const double* points, const int64_t* 
     DeviceGuard g(h->device);
     hipStream_t st = static_cast<hipStream_t>(stream);
     uint32_t* order = nullptr;
-    if (h->tree && env_int("ENVPOT_NO_SORT", 0) == 0) {
-        if (hipMallocAsync(reinterpret_cast<void**>(&order), size_t(kOrderSmallMax) * sizeof(uint32_t), st) != hipSuccess)
+    // (a captured call has no order from kSortMinPoints on, as env_potential_eval)
+    d.order_max = std::min(n_max, stream_capturing(stream) ? kSortMinPoints - 1 : int64_t(UINT32_MAX));
+    if (h->tree && n_max >= kOrderMin && !sort_disabled()) {
+        if (hipMallocAsync(reinterpret_cast<void**>(&order), size_t(d.order_max) * sizeof(uint32_t), st) != hipSuccess)
             return ENV_E_NOMEM;
         d.a.order = order;
-        if (order_points(points, 0, m, order, stream) != 0) {
+        if (order_points(points, d.order_max, m, order, stream) != 0) {
             (void)hipFreeAsync(order, st);
             return ENV_E_DEVICE;
         }
@@ -493,25 +505,21 @@ env_status env_potential_eval(env_potential* h, const double* points, int64_t n,
     if (h->on_host) return host_eval(h, points, n, out);
     if (!h->on_device) return ENV_E_STATE;
     DeviceGuard g(h->device);
-    const bool no_sort = env_int("ENVPOT_NO_SORT", 0) != 0;
     if (h->tree) {
-        // the kernels read the points through a spatial order (Morton order
-        // for large calls, unless the stream is being captured) and the sum
-        // of the splits writes the values in the caller's order
-        const bool large = n >= kSortMinPoints && n <= int64_t(INT32_MAX) && !stream_capturing(stream);
-        if (no_sort || !(large || order_small(n))) return eval_core(h, points, n, nullptr, out, stream);
+        // the kernels read the points through a spatial order and the sum of
+        // the splits writes the values in the caller's order
+        if (!tree_orders(n, stream)) return eval_core(h, points, n, nullptr, out, stream);
         uint32_t* order = nullptr;
         hipStream_t st = static_cast<hipStream_t>(stream);
         if (hipMallocAsync(reinterpret_cast<void**>(&order), size_t(n) * sizeof(uint32_t), st) != hipSuccess)
             return ENV_E_NOMEM;
-        env_status rc = ENV_OK;
-        if ((large ? sort_order(points, n, order, stream) : order_points(points, n, nullptr, order, stream)) != 0)
-            rc = ENV_E_DEVICE;
+        env_status rc = tree_order(points, n, order, stream) == 0 ? ENV_OK : ENV_E_DEVICE;
         if (rc == ENV_OK) rc = eval_core(h, points, n, order, out, stream);
         (void)hipFreeAsync(order, st);
         return rc;
     }
-    if (n < kSortMinPoints || n > int64_t(INT32_MAX) || no_sort || stream_capturing(stream))
+    if (n < kSortMinPoints || n > int64_t(INT32_MAX) || sort_disabled() ||
+        stream_capturing(stream))
         return eval_core(h, points, n, nullptr, out, stream);
     // large calls: evaluate the points in Morton order, then restore the caller's order
     hipStream_t st = static_cast<hipStream_t>(stream);
@@ -562,11 +570,12 @@ int timed_launch(env_potential* h, const EvalArgs& a, int S, int np, void* strea
 env_status eval_core(env_potential* h, const double* points, int64_t n, const uint32_t* order, double* out,
                      void* stream) {
     int np, k;
-    choose_shape(h, n, &np, &k);
+    const bool tree = use_tree(h, n, order != nullptr);
+    choose_shape(h, n, tree, &np, &k);
     const int S = 1 << k;
     hipStream_t st = static_cast<hipStream_t>(stream);
     if (S == 1) {
-        EvalArgs a = make_args(h, points, n, out, 0);
+        EvalArgs a = make_args(h, points, n, out, 0, tree);
         a.order = order;
         return timed_launch(h, a, 1, np, stream) == 0 ? ENV_OK : ENV_E_DEVICE;
     }
@@ -574,7 +583,7 @@ env_status eval_core(env_potential* h, const double* points, int64_t n, const ui
     if (hipMallocAsync(reinterpret_cast<void**>(&part), size_t(S) * size_t(n) * sizeof(double), st) !=
         hipSuccess)
         return ENV_E_NOMEM;
-    EvalArgs a = make_args(h, points, n, part, k);
+    EvalArgs a = make_args(h, points, n, part, k, tree);
     a.order = order;
     int rc = timed_launch(h, a, S, np, stream);
     if (rc == 0) rc = launch_sum_splits(part, S, n, order, out, stream);

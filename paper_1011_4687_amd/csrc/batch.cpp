@@ -12,7 +12,8 @@
 // and write the values through it, and smaller instances get an order too,
 // from a kernel of the graph.
 // While the caller's stream is being captured the plan uses a second
-// argument table that reads and writes the caller's buffers directly.
+// argument table that reads and writes the caller's buffers directly (with
+// trees through an order that the recorded kernel forms, slice by slice).
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -58,8 +59,9 @@ struct env_batch {
     uint32_t* d_order = nullptr;
     // with trees the kernels read the points through d_order: the large
     // instances' part is sorted outside the graph, the small ones' in it
-    OrderDesc* d_small = nullptr;
+    OrderDesc* d_small = nullptr;       // the small instances', then (direct table) the large ones' slices
     int n_small = 0;
+    int n_slices = 0;
     std::vector<int64_t> small_off;     // offset of a small instance's order, -1: none
     int n_sum = 0;
     int64_t max_n_sum = 0;
@@ -108,12 +110,7 @@ void free_shape(env_batch* b) {
 
 // Instances evaluated in Morton order (the rule of a single evaluation,
 // including its ENVPOT_NO_SORT switch).
-bool sorts_off() {
-    const char* ns = std::getenv("ENVPOT_NO_SORT");
-    return ns && *ns && std::atoi(ns) != 0;
-}
-
-bool sorts(int64_t n) { return n >= kSortMinPoints && n <= int64_t(INT32_MAX) && !sorts_off(); }
+bool sorts(int64_t n) { return n >= kSortMinPoints && n <= int64_t(INT32_MAX) && !sort_disabled(); }
 
 // Work items for point counts n: per instance a split factor such that an
 // item costs at most ~1/gran of a workgroup's fair share, items sorted by
@@ -142,6 +139,7 @@ env_status build_shape(env_batch* b, const int64_t* n) {
     int64_t part_words = 0, sorted = 0, small = 0;
     b->small_off.assign(b->n_inst, -1);
     b->n_small = 0;
+    b->n_slices = 0;
     b->n_sum = 0;
     b->max_n_sum = 0;
     b->n_scat = 0;
@@ -163,7 +161,8 @@ env_status build_shape(env_batch* b, const int64_t* n) {
             sorted += n[i];
             ++b->n_scat;
             b->max_n_scat = std::max(b->max_n_scat, n[i]);
-        } else if (b->tree && order_small(n[i]) && !sorts_off()) {
+            if (b->tree) b->n_slices += int((n[i] + order_slice(n[i]) - 1) / order_slice(n[i]));
+        } else if (b->tree && n[i] >= kOrderMin && n[i] < kSortMinPoints && !sort_disabled()) {
             b->small_off[i] = small;
             small += n[i];
             ++b->n_small;
@@ -196,7 +195,7 @@ env_status build_shape(env_batch* b, const int64_t* n) {
         !dm(&b->d_spts, b->tree ? 0 : size_t(sorted) * 3 * sizeof(double)) ||
         !dm(&b->d_sout, b->tree ? 0 : size_t(sorted) * sizeof(double)) ||
         !dm(&b->d_order, size_t(sorted + small) * sizeof(uint32_t)) ||
-        !dm(&b->d_small, size_t(b->n_small) * sizeof(OrderDesc))) {
+        !dm(&b->d_small, size_t(b->n_small + b->n_slices) * sizeof(OrderDesc))) {
         free_shape(b);
         return ENV_E_NOMEM;
     }
@@ -219,7 +218,7 @@ env_status upload_args(env_batch* b, const double* const* points, double* const*
     std::vector<EvalArgs> args(b->n_inst), direct(b->n_inst);
     std::vector<SumDesc> sums, sums_direct;
     std::vector<ScatterDesc> scat;
-    std::vector<OrderDesc> small;
+    std::vector<OrderDesc> small, slices;
     for (int i = 0; i < b->n_inst; ++i) {
         env_potential* h = b->hs[i];
         const bool split = b->part_off[i] >= 0, sorted = !b->tree && b->sort_off[i] >= 0;
@@ -228,20 +227,23 @@ env_status upload_args(env_batch* b, const double* const* points, double* const*
         const bool by_cell = b->small_off[i] >= 0;
         if (by_cell) order = b->d_order + b->sorted_points + b->small_off[i];
         else if (b->tree && b->sort_off[i] >= 0) order = b->d_order + b->sort_off[i];
-        uint32_t* order_direct = by_cell ? order : nullptr;
-        if (by_cell) small.push_back({points[i], order, b->n[i]});
+        if (by_cell) small.push_back({points[i], order, b->n[i], 0});
+        else if (order)
+            for (int64_t at = 0; at < b->n[i]; at += order_slice(b->n[i]))
+                slices.push_back({points[i] + 3 * at, order + at, std::min(order_slice(b->n[i]), b->n[i] - at), at});
         const double* spts = sorted ? b->d_spts + 3 * b->sort_off[i] : points[i];
         double* sout = sorted ? b->d_sout + b->sort_off[i] : out[i];
-        args[i] = make_args(h, spts, b->n[i], split ? part : sout, b->klog[i]);
-        direct[i] = make_args(h, points[i], b->n[i], split ? part : out[i], b->klog[i]);
+        args[i] = make_args(h, spts, b->n[i], split ? part : sout, b->klog[i], b->tree);
+        direct[i] = make_args(h, points[i], b->n[i], split ? part : out[i], b->klog[i], b->tree);
         args[i].order = order;
-        direct[i].order = order_direct;
+        direct[i].order = order;
         if (split) {
             sums.push_back({part, sout, b->n[i], order, 1 << b->klog[i], 0});
-            sums_direct.push_back({part, out[i], b->n[i], order_direct, 1 << b->klog[i], 0});
+            sums_direct.push_back({part, out[i], b->n[i], order, 1 << b->klog[i], 0});
         }
         if (sorted) scat.push_back({sout, b->d_order + b->sort_off[i], out[i], b->n[i]});
     }
+    small.insert(small.end(), slices.begin(), slices.end());
     auto up = [](void* dst, const void* src, size_t bytes) {
         return bytes == 0 || hipMemcpy(dst, src, bytes, hipMemcpyHostToDevice) == hipSuccess;
     };
@@ -283,7 +285,8 @@ int launch_all(env_batch* b, void* stream, bool sorted) {
     a.boys = b->hs[0]->d_boys;
     a.rows32 = b->hs[0]->bp.rows32;
     a.pad = 0;
-    int rc = order_points_multi(b->d_small, b->n_small, stream);
+    // (the sorted table's large instances have their order from sort_inputs)
+    int rc = order_points_multi(b->d_small, b->n_small + (sorted ? 0 : b->n_slices), stream);
     if (rc == 0) rc = launch_persistent(a, b->grid, b->precision, b->np, b->tree, stream);
     if (rc == 0) rc = launch_sum_multi(sorted ? b->d_sum : b->d_sum_direct, b->n_sum, b->max_n_sum, stream);
     if (rc == 0 && sorted && !b->tree) rc = scatter_values_multi(b->d_scat, b->n_scat, b->max_n_scat, stream);

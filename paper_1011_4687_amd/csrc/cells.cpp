@@ -153,17 +153,13 @@ env_status tree_eval(const env_cells* h, const double* points, int64_t n, double
         if (v >= 0 && v <= kMaxSplitLog2) k = v;
     }
     const int S = 1 << k;
-    const char* ns = std::getenv("ENVPOT_NO_SORT");
-    const bool no_sort = ns && *ns && std::atoi(ns) != 0;
-    const bool large = n >= kSortMinPoints && n <= int64_t(INT32_MAX) && !stream_capturing(stream);
     uint32_t* order = nullptr;
     double* part = nullptr;
     env_status rc = ENV_OK;
-    if (!no_sort && (large || order_small(n))) {
+    if (tree_orders(n, stream)) {
         if (hipMallocAsync(reinterpret_cast<void**>(&order), size_t(n) * sizeof(uint32_t), st) != hipSuccess)
             return ENV_E_NOMEM;
-        if ((large ? sort_order(points, n, order, stream) : order_points(points, n, nullptr, order, stream)) != 0)
-            rc = ENV_E_DEVICE;
+        if (tree_order(points, n, order, stream) != 0) rc = ENV_E_DEVICE;
     }
     if (rc == ENV_OK && S > 1 &&
         hipMallocAsync(reinterpret_cast<void**>(&part), size_t(S) * size_t(n) * sizeof(double), st) != hipSuccess)

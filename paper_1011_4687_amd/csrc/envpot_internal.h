@@ -164,6 +164,7 @@ struct DevSizedArgs {
     int64_t part_cap;              // float64 elements of a.out
     int64_t want;                  // waves the split factor aims for (with a tree: compute units)
     unsigned long long* counter;   // zeroed by a kernel before the launch
+    int64_t order_max;             // with a.order: read for kOrderMin <= m <= order_max
 };
 
 struct SumDesc {                  // fixed-order sum of S partials of one instance

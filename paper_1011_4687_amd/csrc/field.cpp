@@ -65,23 +65,18 @@ env_status env_potential_eval_field(env_potential* h, const double* points, int6
     if (!points || !out) return ENV_E_ARG;
     if (!h->on_device) return ENV_E_STATE;
     DeviceGuard g(h->device);
-    const char* ns = std::getenv("ENVPOT_NO_SORT");
-    const bool no_sort = ns && std::atoi(ns) != 0;
     if (h->tree) {  // the points through a spatial order, as env_potential_eval
-        const bool large = n >= kSortMinPoints && n <= int64_t(INT32_MAX) && !stream_capturing(stream);
-        if (no_sort || !(large || order_small(n))) return field_core(h, points, n, nullptr, out, stream);
+        if (!tree_orders(n, stream)) return field_core(h, points, n, nullptr, out, stream);
         hipStream_t st = static_cast<hipStream_t>(stream);
         uint32_t* order = nullptr;
         if (hipMallocAsync(reinterpret_cast<void**>(&order), size_t(n) * sizeof(uint32_t), st) != hipSuccess)
             return ENV_E_NOMEM;
-        env_status rc = ENV_OK;
-        if ((large ? sort_order(points, n, order, stream) : order_points(points, n, nullptr, order, stream)) != 0)
-            rc = ENV_E_DEVICE;
+        env_status rc = tree_order(points, n, order, stream) == 0 ? ENV_OK : ENV_E_DEVICE;
         if (rc == ENV_OK) rc = field_core(h, points, n, order, out, stream);
         (void)hipFreeAsync(order, st);
         return rc;
     }
-    if (n < kSortMinPoints || n > int64_t(INT32_MAX) || no_sort || stream_capturing(stream))
+    if (n < kSortMinPoints || n > int64_t(INT32_MAX) || sort_disabled() || stream_capturing(stream))
         return field_core(h, points, n, nullptr, out, stream);
     // large calls: evaluate the points in Morton order, then restore the caller's order
     hipStream_t st = static_cast<hipStream_t>(stream);

@@ -75,7 +75,10 @@ struct DeviceGuard {  // restores the caller's current device
 };
 
 // Launch shape of a single evaluation of h at n points.
-void choose_shape(const env_potential* h, int64_t n, int* np, int* klog);
+void choose_shape(const env_potential* h, int64_t n, bool tree, int* np, int* klog);
+
+// Whether a call of n points, in a spatial order or not, goes through the tree.
+bool use_tree(const env_potential* h, int64_t n, bool ordered);
 
 // Host evaluation of an ENV_FORCE_CPU handle (hosteval.cpp): tables at
 // create, then V at n host points into host memory.
@@ -90,6 +93,6 @@ env_status eval_devsized(env_potential* h, const double* points, const int64_t* 
                          double* part, int64_t part_cap, unsigned long long* counter, void* stream);
 
 // Arguments of one evaluation (out = V when S == 1, partials otherwise).
-EvalArgs make_args(const env_potential* h, const double* points, int64_t n, double* out, int klog);
+EvalArgs make_args(const env_potential* h, const double* points, int64_t n, double* out, int klog, bool tree);
 
 }  // namespace envpot

@@ -933,7 +933,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) voi
     a.n = m;
     if constexpr (TREE) {
         a.tree.S = 1 << k;
-        if (!order_small(m)) a.order = nullptr;
+        if (m < kOrderMin || m > d.order_max) a.order = nullptr;
         if (np == NP) {
             drain(m, 64 * NP, k, d.counter, &item_sh,
                   [&](int64_t b, int s) { tree_block<NP, F64>(a, b, s, tab32, sh); });
@@ -955,14 +955,14 @@ __device__ __forceinline__ double sum_partials(const double* __restrict__ part, 
 // out[0, m); the grid covers the largest possible m.
 __global__ __launch_bounds__(kBlock) void k_sum_devsized(const double* __restrict__ part, const int64_t* m_ptr,
                                                          int fp64, int tree, int64_t want, int64_t part_cap,
-                                                         const uint32_t* __restrict__ order,
+                                                         const uint32_t* __restrict__ order, int64_t order_max,
                                                          double* __restrict__ out) {
     const int64_t m = *m_ptr;
     const int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
     if (i >= m) return;
     int np;
     const int S = 1 << devsized_shape(m, fp64 != 0, tree != 0, want, part_cap, &np);
-    const bool ordered = order && order_small(m);
+    const bool ordered = order && m >= kOrderMin && m <= order_max;
     // one split: the partials are the values, in the points' own order
     const int64_t o = ordered && S > 1 ? int64_t(order[i]) : i;
     out[o] = sum_partials(part + i, S, m);
@@ -1163,7 +1163,7 @@ int launch_sum_devsized(const DevSizedArgs& d, int precision, int64_t n_max, dou
     if (n_max <= 0) return 0;
     const dim3 grid((unsigned)((n_max + kBlock - 1) / kBlock));
     hipLaunchKernelGGL(k_sum_devsized, grid, dim3(kBlock), 0, static_cast<hipStream_t>(stream), d.a.out, d.m,
-                       precision == ENV_PREC_FP64 ? 1 : 0, d.a.tree.n_trees > 0 ? 1 : 0, d.want, d.part_cap, d.a.order, out);
+                       precision == ENV_PREC_FP64 ? 1 : 0, d.a.tree.n_trees > 0 ? 1 : 0, d.want, d.part_cap, d.a.order, d.order_max, out);
     return hipGetLastError() == hipSuccess ? 0 : -1;
 }
 

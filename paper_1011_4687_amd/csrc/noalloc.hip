@@ -7,7 +7,6 @@
 // until the process ends; every call on one device uses that device's copy.
 #include <hip/hip_runtime.h>
 
-#include <cstdlib>
 #include <mutex>
 
 #include "handle.h"
@@ -57,22 +56,22 @@ env_status env_potential_eval_noalloc(env_potential* h, const double* points, in
     double* part = nullptr;
     env_status rc = scratch_address(h->device, &part);
     if (rc != ENV_OK) return rc;
-    // the launch shape of env_potential_eval, with the split factor lowered
-    // until the partials fit the array
-    int np = 0, k = 0;
-    choose_shape(h, n, &np, &k);
-    // with a tree, the order of a small call's points takes the array's end
+    // with a tree, the order of the points takes the array's end
     uint32_t* order = nullptr;
     int64_t cap = kScratchDoubles;
-    const char* ns = std::getenv("ENVPOT_NO_SORT");
-    if (h->tree && order_small(n) && !(ns && *ns && std::atoi(ns) != 0)) {
-        cap -= kOrderSmallMax / 2;
+    if (h->tree && n >= kOrderMin && !sort_disabled()) {
+        cap -= (n + 1) / 2;
         order = reinterpret_cast<uint32_t*>(part + cap);
         if (order_points(points, n, nullptr, order, stream) != 0) return ENV_E_DEVICE;
     }
+    // the launch shape of env_potential_eval, with the split factor lowered
+    // until the partials fit the array
+    int np = 0, k = 0;
+    const bool tree = use_tree(h, n, order != nullptr);
+    choose_shape(h, n, tree, &np, &k);
     while (k > 0 && (int64_t(1) << k) * n > cap) --k;
     const int S = 1 << k;
-    EvalArgs a = make_args(h, points, n, S == 1 ? out : part, k);
+    EvalArgs a = make_args(h, points, n, S == 1 ? out : part, k, tree);
     a.order = order;
     if (S == 1) return launch_potential(a, 1, h->precision, np, stream) == 0 ? ENV_OK : ENV_E_DEVICE;
     // every (split, point) partial is written by the potential kernel before

@@ -7,6 +7,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <cstdlib>
 
 #include <hipcub/hipcub.hpp>
 
@@ -95,7 +96,8 @@ __device__ __forceinline__ uint32_t spread5(uint32_t v) {
     return (v & 1u) | ((v & 2u) << 2) | ((v & 4u) << 4) | ((v & 8u) << 6) | ((v & 16u) << 8);
 }
 
-__device__ __forceinline__ void order_small_body(const double* __restrict__ pts, int n, uint32_t* __restrict__ order) {
+__device__ __forceinline__ void order_small_body(const double* __restrict__ pts, int n, uint32_t base,
+                                                 uint32_t* __restrict__ order) {
     __shared__ uint32_t el[kOrderSlots];
     __shared__ uint16_t at[8 * kOrderThreads];
     __shared__ float red[4][13];
@@ -196,12 +198,12 @@ __device__ __forceinline__ void order_small_body(const double* __restrict__ pts,
         }
         if (lane == 63) wsum[wave] = inc;
         __syncthreads();
-        uint32_t base = inc - sum;
-        for (int w = 0; w < wave; ++w) base += wsum[w];
+        uint32_t place = inc - sum;
+        for (int w = 0; w < wave; ++w) place += wsum[w];
 #pragma unroll
         for (int k = 0; k < 8; ++k) {
-            at[8 * t + k] = uint16_t(base);
-            base += x[k];
+            at[8 * t + k] = uint16_t(place);
+            place += x[k];
         }
         __syncthreads();
 #pragma unroll
@@ -218,21 +220,23 @@ __device__ __forceinline__ void order_small_body(const double* __restrict__ pts,
             }
     }
     __syncthreads();
-    for (int i = t; i < n; i += kOrderThreads) order[i] = el[slot(i)] & 0x7fffu;
+    for (int i = t; i < n; i += kOrderThreads) order[i] = base + (el[slot(i)] & 0x7fffu);
 }
 
-// Counts outside the range are left alone (their order is not read).
+// A workgroup per slice; counts outside the range (up to n_host, which the grid
+// and the buffer are for) are left alone: their order is not read.
 __global__ __launch_bounds__(kOrderThreads) void k_order_small(const double* __restrict__ pts, int64_t n_host,
                                                                const int64_t* __restrict__ n_dev,
                                                                uint32_t* __restrict__ order) {
-    const int64_t n = n_dev ? *n_dev : n_host;
-    if (order_small(n)) order_small_body(pts, int(n), order);
+    const int64_t n = n_dev ? *n_dev : n_host, per = order_slice(n), base = blockIdx.x * per;
+    if (n < kOrderMin || n > n_host || base >= n) return;
+    order_small_body(pts + 3 * base, int(min(per, n - base)), uint32_t(base), order + base);
 }
 
-// One workgroup per instance.
+// One workgroup per instance or slice.
 __global__ __launch_bounds__(kOrderThreads) void k_order_multi(const OrderDesc* __restrict__ d) {
     const OrderDesc q = d[blockIdx.x];
-    if (order_small(q.n)) order_small_body(q.pts, int(q.n), q.order);
+    if (q.n > 0 && q.n <= kOrderSmallMax) order_small_body(q.pts, int(q.n), uint32_t(q.base), q.order);
 }
 
 unsigned blocks(int64_t n) { return unsigned((n + kSortBlock - 1) / kSortBlock); }
@@ -275,8 +279,10 @@ int sort_points(const double* pts, int64_t n, double* sorted, uint32_t* order, v
 }
 
 int order_points(const double* pts, int64_t n, const int64_t* n_dev, uint32_t* order, void* stream) {
-    hipLaunchKernelGGL(k_order_small, dim3(1), dim3(kOrderThreads), 0, static_cast<hipStream_t>(stream), pts, n, n_dev,
-                       order);
+    if (n <= 0 || n > int64_t(UINT32_MAX)) return -1;
+    const int64_t slices = (n + order_slice(n) - 1) / order_slice(n);
+    hipLaunchKernelGGL(k_order_small, dim3(unsigned(slices)), dim3(kOrderThreads), 0, static_cast<hipStream_t>(stream), pts,
+                       n, n_dev, order);
     return hipGetLastError() == hipSuccess ? 0 : -1;
 }
 
@@ -285,6 +291,20 @@ int order_points_multi(const OrderDesc* d, int n_desc, void* stream) {
     hipLaunchKernelGGL(k_order_multi, dim3(unsigned(n_desc)), dim3(kOrderThreads), 0, static_cast<hipStream_t>(stream),
                        d);
     return hipGetLastError() == hipSuccess ? 0 : -1;
+}
+
+bool sort_disabled() {
+    const char* ns = std::getenv("ENVPOT_NO_SORT");
+    return ns && *ns && std::atoi(ns) != 0;
+}
+
+bool tree_orders(int64_t n, void* stream) {
+    if (n < kOrderMin || n > int64_t(INT32_MAX) || sort_disabled()) return false;
+    return n < kSortMinPoints || !stream_capturing(stream);
+}
+
+int tree_order(const double* pts, int64_t n, uint32_t* order, void* stream) {
+    return n < kSortMinPoints ? order_points(pts, n, nullptr, order, stream) : sort_order(pts, n, order, stream);
 }
 
 bool stream_capturing(void* stream) {
