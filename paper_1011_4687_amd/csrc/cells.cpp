@@ -141,6 +141,41 @@ void cells_shape(const env_cells* h, int64_t n, int* np, int* klog) {
     *klog = k;
 }
 
+// Fewest cells and nuclei of a batched evaluation of n points through the
+// tree; with fewer the sum over all cells is as quick.  One or two blocks share
+// a tree's latency among few points; from 129 points on the points are ordered
+// first (20 us); many points amortise both.  The tree's time over that of every
+// cell, nuclei and cells as in the paper's benchmark:
+//   FP32C  cells    64    600   1500   4096  16384  131072 points
+//           9,051  0.89   1.64   1.73   0.98   1.27   1.08
+//          15,701  0.73   1.32   1.64   0.84   1.04   0.79
+//          30,642  0.75   1.56   0.80   0.74   0.87   0.52
+//          72,562  0.54   1.09   0.59   0.66   0.55   0.27
+//   FP64   30,642  1.43   2.22   1.25   1.26   1.34   0.88
+//          72,562  0.92   2.00   1.37   1.08   0.97   0.57
+//         125,424  0.67   1.45   1.18   0.86   0.70   0.38
+//         268,398  0.40   0.87   0.72   0.54   0.40   0.22
+// Points in no order, 131,072: FP32C 1.03 with 30,642 cells, 0.63 with 72,562; FP64
+// 1.07 with 72,562, 0.82 with 125,424.
+struct TreeLine {
+    int64_t points, items;
+};
+constexpr TreeLine kLines32[] = {{1, 8192},      {129, 65536},    {1500, 24576},
+                                 {2048, 8192},   {16384, 16384},  {131072, 12288}};
+constexpr TreeLine kLines64[] = {{1, 65536},     {129, 262144},   {1536, 131072},
+                                 {4096, 98304},  {8192, 65536},   {131072, 24576}};
+constexpr int64_t kUnordered = 8192;   // points from which an order counts
+
+int64_t tree_from(int64_t n, bool fp64, bool ordered) {
+    int64_t items = 0;
+    for (const TreeLine& l : fp64 ? kLines64 : kLines32)
+        if (n >= l.points) items = l.items;
+    if (!ordered && n >= kUnordered) items = std::max<int64_t>(items, fp64 ? 98304 : 49152);
+    return items;
+}
+// Fewer items than this have no use for a tree at any n.
+constexpr int64_t tree_least(bool fp64) { return fp64 ? 24576 : 8192; }
+
 // Batched evaluation through the tree: the potential kernel on a tree
 // without pairs.
 env_status tree_eval(const env_cells* h, const double* points, int64_t n, double* out, void* stream) {
@@ -254,7 +289,8 @@ env_status env_cells_create(const env_nucleus* nuclei, int32_t n_nuclei, const d
         if (st == ENV_OK && hipMemset(h->d_ticket, 0, sizeof(unsigned int)) != hipSuccess) st = ENV_E_DEVICE;
         // the tree's charges: the nuclei, then minus the cells, one group
         const char* nt = std::getenv("ENVPOT_NO_TREE");
-        if (st == ENV_OK && !(nt && *nt && std::atoi(nt) != 0)) {
+        if (st == ENV_OK && !(nt && *nt && std::atoi(nt) != 0) &&
+            int64_t(h->n_nuc) + n_cells >= tree_least(h->precision == ENV_PREC_FP64)) {
             nuc.reserve(nuc.size() + 4 * size_t(n_cells));
             for (int64_t m = 0; m < n_cells; ++m)
                 nuc.insert(nuc.end(), {cells[4 * m], cells[4 * m + 1], cells[4 * m + 2], -cells[4 * m + 3]});
@@ -293,11 +329,8 @@ env_status env_cells_eval(env_cells* h, const double* points, int64_t n, double*
     if (n == 0) return ENV_OK;
     if (!points || !out) return ENV_E_ARG;
     DeviceGuard g(h->device);
-    // FP64 calls of a few hundred points are quicker cell by cell (268,398
-    // cells: 300 points 0.18 ms against 0.20, 1000 0.22 against 0.26; 64
-    // points 0.18 against 0.10, 4000 0.60 against 0.54)
-    const bool direct = h->precision == ENV_PREC_FP64 && n > 128 && n < 2048;
-    if (h->tree && !direct) return tree_eval(h, points, n, out, stream);
+    if (h->tree && h->tree->n_nuc >= tree_from(n, h->precision == ENV_PREC_FP64, envpot::tree_orders(n, stream)))
+        return tree_eval(h, points, n, out, stream);
     int np, k;
     cells_shape(h, n, &np, &k);
     const int S = 1 << k;
