@@ -208,6 +208,7 @@ env_status eval_devsized(env_potential* h, const double* points, const int64_t* 
 namespace {
 env_status eval_core(env_potential* h, const double* points, int64_t n, const uint32_t* order, double* out,
                      void* stream);
+env_status eval_piece(env_potential* h, const double* points, int64_t n, double* out, void* stream);
 }  // namespace
 
 extern "C" {
@@ -506,16 +507,9 @@ env_status env_potential_eval(env_potential* h, const double* points, int64_t n,
     if (!h->on_device) return ENV_E_STATE;
     DeviceGuard g(h->device);
     if (h->tree) {
-        // the kernels read the points through a spatial order and the sum of
-        // the splits writes the values in the caller's order
-        if (!tree_orders(n, stream)) return eval_core(h, points, n, nullptr, out, stream);
-        uint32_t* order = nullptr;
-        hipStream_t st = static_cast<hipStream_t>(stream);
-        if (hipMallocAsync(reinterpret_cast<void**>(&order), size_t(n) * sizeof(uint32_t), st) != hipSuccess)
-            return ENV_E_NOMEM;
-        env_status rc = tree_order(points, n, order, stream) == 0 ? ENV_OK : ENV_E_DEVICE;
-        if (rc == ENV_OK) rc = eval_core(h, points, n, order, out, stream);
-        (void)hipFreeAsync(order, st);
+        env_status rc = ENV_OK;
+        for (int64_t at = 0; at < n && rc == ENV_OK; at += tree_call_max(1))
+            rc = eval_piece(h, points + 3 * at, std::min(n - at, tree_call_max(1)), out + at, stream);
         return rc;
     }
     if (n < kSortMinPoints || n > int64_t(INT32_MAX) || sort_disabled() ||
@@ -564,6 +558,20 @@ int timed_launch(env_potential* h, const EvalArgs& a, int S, int np, void* strea
     if (on && hipEventRecord(e0, st) != hipSuccess) return -1;
     const int rc = launch_potential(a, S, h->precision, np, stream);
     if (on && rc == 0 && hipEventRecord(e1, st) != hipSuccess) return -1;
+    return rc;
+}
+
+// One launch of a handle with a tree: the kernels read the points through a
+// spatial order and the sum of the splits writes the values in the caller's.
+env_status eval_piece(env_potential* h, const double* points, int64_t n, double* out, void* stream) {
+    if (!tree_orders(n, stream)) return eval_core(h, points, n, nullptr, out, stream);
+    uint32_t* order = nullptr;
+    hipStream_t st = static_cast<hipStream_t>(stream);
+    if (hipMallocAsync(reinterpret_cast<void**>(&order), size_t(n) * sizeof(uint32_t), st) != hipSuccess)
+        return ENV_E_NOMEM;
+    env_status rc = tree_order(points, n, order, stream) == 0 ? ENV_OK : ENV_E_DEVICE;
+    if (rc == ENV_OK) rc = eval_core(h, points, n, order, out, stream);
+    (void)hipFreeAsync(order, st);
     return rc;
 }
 

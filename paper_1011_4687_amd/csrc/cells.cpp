@@ -329,8 +329,12 @@ env_status env_cells_eval(env_cells* h, const double* points, int64_t n, double*
     if (n == 0) return ENV_OK;
     if (!points || !out) return ENV_E_ARG;
     DeviceGuard g(h->device);
-    if (h->tree && h->tree->n_nuc >= tree_from(n, h->precision == ENV_PREC_FP64, envpot::tree_orders(n, stream)))
-        return tree_eval(h, points, n, out, stream);
+    if (h->tree && h->tree->n_nuc >= tree_from(n, h->precision == ENV_PREC_FP64, envpot::tree_orders(n, stream))) {
+        env_status rc = ENV_OK;
+        for (int64_t at = 0; at < n && rc == ENV_OK; at += envpot::tree_call_max(1))
+            rc = tree_eval(h, points + 3 * at, std::min(n - at, envpot::tree_call_max(1)), out + at, stream);
+        return rc;
+    }
     int np, k;
     cells_shape(h, n, &np, &k);
     const int S = 1 << k;

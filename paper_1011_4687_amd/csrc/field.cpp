@@ -54,6 +54,7 @@ using namespace envpot;
 namespace {
 env_status field_core(env_potential* h, const double* points, int64_t n, const uint32_t* order, double* out,
                       void* stream);
+env_status field_piece(env_potential* h, const double* points, int64_t n, double* out, void* stream);
 }  // namespace
 
 extern "C" {
@@ -65,15 +66,10 @@ env_status env_potential_eval_field(env_potential* h, const double* points, int6
     if (!points || !out) return ENV_E_ARG;
     if (!h->on_device) return ENV_E_STATE;
     DeviceGuard g(h->device);
-    if (h->tree) {  // the points through a spatial order, as env_potential_eval
-        if (!tree_orders(n, stream)) return field_core(h, points, n, nullptr, out, stream);
-        hipStream_t st = static_cast<hipStream_t>(stream);
-        uint32_t* order = nullptr;
-        if (hipMallocAsync(reinterpret_cast<void**>(&order), size_t(n) * sizeof(uint32_t), st) != hipSuccess)
-            return ENV_E_NOMEM;
-        env_status rc = tree_order(points, n, order, stream) == 0 ? ENV_OK : ENV_E_DEVICE;
-        if (rc == ENV_OK) rc = field_core(h, points, n, order, out, stream);
-        (void)hipFreeAsync(order, st);
+    if (h->tree) {
+        env_status rc = ENV_OK;
+        for (int64_t at = 0; at < n && rc == ENV_OK; at += tree_call_max(4))
+            rc = field_piece(h, points + 3 * at, std::min(n - at, tree_call_max(4)), out + 4 * at, stream);
         return rc;
     }
     if (n < kSortMinPoints || n > int64_t(INT32_MAX) || sort_disabled() || stream_capturing(stream))
@@ -100,6 +96,19 @@ env_status env_potential_eval_field(env_potential* h, const double* points, int6
 }  // extern "C"
 
 namespace {
+
+// One launch with a tree: the points through a spatial order, as env_potential_eval.
+env_status field_piece(env_potential* h, const double* points, int64_t n, double* out, void* stream) {
+    if (!tree_orders(n, stream)) return field_core(h, points, n, nullptr, out, stream);
+    hipStream_t st = static_cast<hipStream_t>(stream);
+    uint32_t* order = nullptr;
+    if (hipMallocAsync(reinterpret_cast<void**>(&order), size_t(n) * sizeof(uint32_t), st) != hipSuccess)
+        return ENV_E_NOMEM;
+    env_status rc = tree_order(points, n, order, stream) == 0 ? ENV_OK : ENV_E_DEVICE;
+    if (rc == ENV_OK) rc = field_core(h, points, n, order, out, stream);
+    (void)hipFreeAsync(order, st);
+    return rc;
+}
 
 env_status field_core(env_potential* h, const double* points, int64_t n, const uint32_t* order, double* out,
                       void* stream) {

@@ -94,6 +94,12 @@ constexpr int tree_klog(int64_t blocks, int64_t cu_count, int kmax) {
     return k > least ? k : (least < kmax ? least : kmax);
 }
 
+// Points of one launch of a tree evaluation; more are taken piece by piece.  A
+// workgroup's 256 threads stand for 64 or 128 points, so that 2^30 points would
+// pass the 2^32 threads of a launch, and the partials of four splits stay
+// within 1 GiB (`values` doubles per point).
+constexpr int64_t tree_call_max(int values) { return (int64_t(1) << 25) / values; }
+
 // Acceptance test of a node: centre and squared accepted radius, its own and
 // its parent's (a root's parent is never accepted: +inf); cost of its own
 // items.
