@@ -291,20 +291,19 @@ env_status env_cells_create(const env_nucleus* nuclei, int32_t n_nuclei, const d
         const char* nt = std::getenv("ENVPOT_NO_TREE");
         if (st == ENV_OK && !(nt && *nt && std::atoi(nt) != 0) &&
             int64_t(h->n_nuc) + n_cells >= tree_least(h->precision == ENV_PREC_FP64)) {
-            nuc.reserve(nuc.size() + 4 * size_t(n_cells));
-            for (int64_t m = 0; m < n_cells; ++m)
-                nuc.insert(nuc.end(), {cells[4 * m], cells[4 * m + 1], cells[4 * m + 2], -cells[4 * m + 3]});
             int64_t* no_pairs = nullptr;
             if (hipMalloc(reinterpret_cast<void**>(&no_pairs), 2 * sizeof(int64_t)) != hipSuccess) st = ENV_E_NOMEM;
             if (st == ENV_OK && hipMemset(no_pairs, 0, 2 * sizeof(int64_t)) != hipSuccess) st = ENV_E_DEVICE;
             envpot::TreeSource src;
             src.group_pairs = no_pairs;
             src.n_groups = 1;
+            src.cells = cells;
+            src.n_cells = n_cells;
             const bool fp64 = h->precision == ENV_PREC_FP64;
             src.order = fp64 ? envpot::kTreeOrdCells64 : envpot::kTreeOrdCells32;
             src.eps = fp64 ? envpot::kTreeEpsCells64 : envpot::kTreeEpsCells32;
             src.nuc_eps = src.eps;
-            const int32_t count = int32_t(std::min<size_t>(nuc.size() / 4, size_t(INT32_MAX)));
+            const int32_t count = int32_t(std::min<int64_t>(h->n_nuc + n_cells, INT32_MAX));
             if (st == ENV_OK && hipStreamSynchronize(nullptr) == hipSuccess)
                 h->tree = envpot::build_tree(src, nuc, {0}, {count}, fp64, &st);
             if (st == ENV_OK && h->tree &&

@@ -79,15 +79,28 @@ __device__ inline void item_geo(const UpdPair* pairs, const uint32_t* rec, const
     }
 }
 
-// Cube of each group's items: smallest corner and edge.
-__global__ __launch_bounds__(kB) void k_tree_cubes(const UpdPair* pairs, const uint32_t* rec, const double* nuc,
+// Doubles as unsigned integers of the same order (for atomic min and max).
+__device__ inline unsigned long long ordered(double x) {
+    const unsigned long long b = (unsigned long long)__double_as_longlong(x);
+    return (b >> 63) ? ~b : (b | 0x8000000000000000ull);
+}
+__host__ __device__ inline double unordered(unsigned long long u) {
+    const unsigned long long b = (u >> 63) ? (u & 0x7fffffffffffffffull) : ~u;
+    double d;
+    __builtin_memcpy(&d, &b, 8);
+    return d;
+}
+
+// Box of each group's items (a group's by blockIdx.x, its parts by blockIdx.y).
+__global__ __launch_bounds__(kB) void k_tree_boxes(const UpdPair* pairs, const uint32_t* rec, const double* nuc,
                                                    int64_t n_pairs, int fp64, const int64_t* gpb,
-                                                   const int32_t* gnb, const int32_t* gne, double* cube) {
+                                                   const int32_t* gnb, const int32_t* gne, unsigned long long* box) {
     __shared__ double red[6][kB];
     const int g = blockIdx.x, t = threadIdx.x;
     double v[6] = {HUGE_VAL, HUGE_VAL, HUGE_VAL, -HUGE_VAL, -HUGE_VAL, -HUGE_VAL};
     const int64_t np = gpb[g + 1] - gpb[g], nn = gne[g] - gnb[g];
-    for (int64_t k = t; k < np + nn; k += kB) {
+    if (int64_t(blockIdx.y) * kB >= np + nn) return;
+    for (int64_t k = int64_t(blockIdx.y) * kB + t; k < np + nn; k += int64_t(gridDim.y) * kB) {
         double c[3], rf;
         item_geo(pairs, rec, nuc, n_pairs, fp64, k < np ? gpb[g] + k : n_pairs + gnb[g] + (k - np), c, &rf);
         for (int d = 0; d < 3; ++d) {
@@ -105,14 +118,26 @@ __global__ __launch_bounds__(kB) void k_tree_cubes(const UpdPair* pairs, const u
             }
         __syncthreads();
     }
-    if (t == 0) {
-        double e = 0.0;
-        for (int d = 0; d < 3; ++d) {
-            cube[4 * g + d] = red[d][0];
-            e = fmax(e, red[3 + d][0] - red[d][0]);
-        }
-        cube[4 * g + 3] = np + nn > 0 ? e * (1.0 + 1e-9) : 0.0;
+    if (t < 3) atomicMin(&box[6 * int64_t(g) + t], ordered(red[t][0]));
+    else if (t < 6) atomicMax(&box[6 * int64_t(g) + t], ordered(red[t][0]));
+}
+
+// Cube of each group: smallest corner and edge.
+__global__ __launch_bounds__(kB) void k_tree_cubes(const unsigned long long* box, int64_t n_groups, double* cube) {
+    const int64_t g = gid();
+    if (g >= n_groups) return;
+    double e = 0.0;
+    for (int d = 0; d < 3; ++d) {
+        cube[4 * g + d] = unordered(box[6 * g + d]);
+        e = fmax(e, unordered(box[6 * g + 3 + d]) - unordered(box[6 * g + d]));
     }
+    cube[4 * g + 3] = e > 0.0 ? e * (1.0 + 1e-9) : 0.0;
+}
+
+// Boxes of n nodes or groups, empty.
+__global__ __launch_bounds__(kB) void k_tree_no_boxes(int64_t n, unsigned long long* box) {
+    const int64_t i = gid();
+    if (i < 6 * n) box[i] = i % 6 < 3 ? ~0ull : 0ull;
 }
 
 // Sort key of every item: group (26 bits), cell code of its level left
@@ -157,6 +182,41 @@ __global__ __launch_bounds__(kB) void k_tree_keys(const UpdPair* pairs, const ui
     key[i] = ((unsigned long long)g << 38) | (code << 8) | ((unsigned long long)step << 3) |
              (unsigned long long)type;
     val[i] = uint32_t(i);
+}
+
+// A tree of point charges alone: every key stands at the last level, finer than
+// any leaf.  Its code cut to the cells that the host can meet: the children of a
+// cell of `least` items or more (a cell of fewer is one node).  keys: sorted.
+__global__ __launch_bounds__(kB) void k_tree_cut(const unsigned long long* __restrict__ keys, int64_t n, int steps,
+                                                 int64_t least, unsigned long long* __restrict__ cut) {
+    const int64_t i = gid();
+    if (i >= n) return;
+    const unsigned long long k = keys[i];
+    int level = kTreeLevels;
+    for (; level > 0; --level) {  // the parent of the cell at `level`
+        const int shift = 8 + 3 * (kTreeLevels - level + 1);
+        const unsigned long long lo = k >> shift << shift, hi = lo + (1ull << shift);
+        int64_t a = 0, b = i;     // first key of the cell
+        while (a < b) {
+            const int64_t m = (a + b) >> 1;
+            if (keys[m] < lo) a = m + 1;
+            else b = m;
+        }
+        int64_t c = i, d = n;     // one past its last
+        while (c < d) {
+            const int64_t m = (c + d) >> 1;
+            if (keys[m] < hi) c = m + 1;
+            else d = m;
+        }
+        if (c - a >= least) break;
+    }
+    const int shift = 8 + 3 * (kTreeLevels - level);
+    cut[i] = (k >> shift << shift) | ((unsigned long long)(level * steps) << 3) | (k & 7ull);
+}
+
+__global__ __launch_bounds__(kB) void k_tree_negate(double* nuc, int64_t n) {
+    const int64_t i = gid();
+    if (i < n) nuc[4 * i + 3] = -nuc[4 * i + 3];
 }
 
 __global__ __launch_bounds__(kB) void k_tree_heads(const unsigned long long* key, int64_t n, int32_t* head) {
@@ -205,20 +265,8 @@ __global__ __launch_bounds__(kB) void k_tree_place(const uint32_t* nkey, const u
     }
 }
 
-// Doubles as unsigned integers of the same order (for atomic min and max).
-__device__ inline unsigned long long ordered(double x) {
-    const unsigned long long b = (unsigned long long)__double_as_longlong(x);
-    return (b >> 63) ? ~b : (b | 0x8000000000000000ull);
-}
-__host__ __device__ inline double unordered(unsigned long long u) {
-    const unsigned long long b = (u >> 63) ? (u & 0x7fffffffffffffffull) : ~u;
-    double d;
-    __builtin_memcpy(&d, &b, 8);
-    return d;
-}
-
-// Bounding box of every node's subtree: each item climbs its ancestors until
-// it changes nothing (minimum and maximum do not depend on the order).
+// Bounding box of every node's subtree: each item climbs its ancestors to the
+// root (minimum and maximum do not depend on the order).
 __global__ __launch_bounds__(kB) void k_tree_bounds(const UpdPair* pairs, const uint32_t* rec, const double* nuc,
                                                     int64_t n_pairs, int64_t n_items, int fp64,
                                                     const int32_t* item_node, const int32_t* parent,
@@ -1113,31 +1161,63 @@ void* device_memory(int64_t& room, size_t nb) {
     return q;
 }
 
-// Temporary memory of the build.
+size_t aligned(size_t nb) { return (std::max<size_t>(nb, 1) + 255) & ~size_t(255); }
+
+// Temporary memory of the build, cut from few allocations (each takes 30 to 60 us,
+// and as much to free).
 struct Temp {
     int64_t& room;
     std::vector<void*> p;
+    char* at = nullptr;
+    size_t left = 0;
     explicit Temp(int64_t& r) : room(r) {}
+    bool reserve(size_t nb) {
+        void* q = device_memory(room, nb);
+        if (!q) return false;
+        p.push_back(q);
+        at = static_cast<char*>(q);
+        left = nb;
+        return true;
+    }
     template <class T>
     T* get(int64_t n) {
-        void* q = device_memory(room, size_t(std::max<int64_t>(n, 1)) * sizeof(T));
-        if (q) p.push_back(q);
-        return static_cast<T*>(q);
+        const size_t nb = aligned(size_t(std::max<int64_t>(n, 0)) * sizeof(T));
+        if (nb > left && !reserve(std::max(nb, size_t(1) << 20))) return nullptr;
+        T* q = reinterpret_cast<T*>(at);
+        at += nb;
+        left -= nb;
+        return q;
     }
     ~Temp() {
         for (void* q : p) (void)hipFree(q);
     }
 };
 
-template <class T>
-T* keep(Tree* t, int64_t n) {
-    const size_t nb = size_t(std::max<int64_t>(n, 1)) * sizeof(T);
-    void* q = device_memory(t->room, nb);
-    if (!q) return nullptr;
-    t->owned.push_back(q);
-    t->device_bytes += int64_t(nb);
-    return static_cast<T*>(q);
-}
+// The arrays that stay with the tree, one allocation.
+struct Keep {
+    struct Part {
+        void** p;
+        size_t nb;
+    };
+    std::vector<Part> parts;
+    template <class T>
+    void add(T** p, int64_t n) {
+        parts.push_back({reinterpret_cast<void**>(p), aligned(size_t(std::max<int64_t>(n, 0)) * sizeof(T))});
+    }
+    bool allocate(Tree* t) const {
+        size_t all = 0;
+        for (const Part& q : parts) all += q.nb;
+        char* at = static_cast<char*>(device_memory(t->room, all));
+        if (!at) return false;
+        t->owned = at;
+        t->device_bytes += int64_t(all);
+        for (const Part& q : parts) {
+            *q.p = at;
+            at += q.nb;
+        }
+        return true;
+    }
+};
 
 template <class T>
 bool put(T* d, const std::vector<T>& v, hipStream_t st) {
@@ -1178,14 +1258,17 @@ env_status build(Tree* t, const TreeSource& u, const std::vector<double>& nuc, c
     const int fp64 = t->fp64 ? 1 : 0, P = t->P;
     const int64_t n_pairs = t->n_pairs, n_nuc = t->n_nuc, n = n_pairs + n_nuc;
     const int ng = u.n_groups;
-    std::vector<int32_t> nuc_group(size_t(n_nuc), 0);
+    std::vector<int32_t> nuc_group(nuc.size() / 4, 0);
     for (int g = 0; g < ng; ++g)
-        for (int32_t k = nuc_begin[g]; k < nuc_end[g]; ++k) nuc_group[size_t(k)] = g;
+        for (int32_t k = nuc_begin[g]; k < nuc_end[g] && size_t(k) < nuc_group.size(); ++k) nuc_group[size_t(k)] = g;
+    // the arrays of all items, and about what the sort takes
+    if (!tmp.reserve(size_t(n) * 80 + size_t(n_nuc) * 40 + size_t(ng) * 128 + (size_t(1) << 20))) return ENV_E_NOMEM;
     double* d_nuc0 = tmp.get<double>(4 * n_nuc);
     int32_t* d_ng = tmp.get<int32_t>(n_nuc);
     int32_t* d_gnb = tmp.get<int32_t>(ng);
     int32_t* d_gne = tmp.get<int32_t>(ng);
     double* d_cube = tmp.get<double>(4 * int64_t(ng));
+    unsigned long long* d_gbox = tmp.get<unsigned long long>(6 * int64_t(ng));
     unsigned long long* key = tmp.get<unsigned long long>(n);
     unsigned long long* key_s = tmp.get<unsigned long long>(n);
     uint32_t* val = tmp.get<uint32_t>(n);
@@ -1195,14 +1278,24 @@ env_status build(Tree* t, const TreeSource& u, const std::vector<double>& nuc, c
     uint32_t* nkey = tmp.get<uint32_t>(n);
     uint32_t* nkey_s = tmp.get<uint32_t>(n);
     int32_t* item_node = tmp.get<int32_t>(n);
-    if (!d_nuc0 || !d_ng || !d_gnb || !d_gne || !d_cube || !key || !key_s || !val || !val_s || !head || !runid ||
+    if (!d_nuc0 || !d_ng || !d_gnb || !d_gne || !d_cube || !d_gbox || !key || !key_s || !val || !val_s || !head || !runid ||
         !nkey || !nkey_s || !item_node)
         return ENV_E_NOMEM;
+    if (u.n_cells > 0) {
+        const int64_t at = n_nuc - u.n_cells;
+        TREE_CHECK(hipMemcpyAsync(d_nuc0 + 4 * at, u.cells, size_t(u.n_cells) * 4 * sizeof(double), hipMemcpyHostToDevice,
+                                  st) == hipSuccess &&
+                   hipMemsetAsync(d_ng + at, 0, size_t(u.n_cells) * sizeof(int32_t), st) == hipSuccess);
+        TREE_LAUNCH(u.n_cells, k_tree_negate, d_nuc0 + 4 * at, u.n_cells);
+    }
     TREE_CHECK(put(d_nuc0, nuc, st) && put(d_ng, nuc_group, st) && put(d_gnb, nuc_begin, st) &&
                put(d_gne, nuc_end, st));
-    hipLaunchKernelGGL(k_tree_cubes, dim3(unsigned(ng)), dim3(kB), 0, st, u.pairs, u.rec, d_nuc0, n_pairs, fp64,
-                       u.group_pairs, d_gnb, d_gne, d_cube);
+    TREE_LAUNCH(6 * int64_t(ng), k_tree_no_boxes, int64_t(ng), d_gbox);
+    // (parts of 4096 items, as many as a group of all items would have)
+    hipLaunchKernelGGL(k_tree_boxes, dim3(unsigned(ng), unsigned(std::min<int64_t>((n + 4095) / 4096, 256))), dim3(kB), 0, st,
+                       u.pairs, u.rec, d_nuc0, n_pairs, fp64, u.group_pairs, d_gnb, d_gne, d_gbox);
     TREE_CHECK(hipGetLastError() == hipSuccess);
+    TREE_LAUNCH(int64_t(ng), k_tree_cubes, d_gbox, int64_t(ng), d_cube);
     TREE_LAUNCH(n, k_tree_keys, u.pairs, u.rec, d_nuc0, d_ng, n_pairs, n, fp64, d_cube, key, val);
     size_t tb = 0;
     const int kb = 38 + bits_for(uint64_t(std::max(ng - 1, 0)));
@@ -1212,6 +1305,11 @@ env_status build(Tree* t, const TreeSource& u, const std::vector<double>& nuc, c
     if (!work) return ENV_E_NOMEM;
     TREE_CHECK(hipcub::DeviceRadixSort::SortPairs(work, tb, key, key_s, val, val_s, int(n), 0, kb, st) ==
                hipSuccess);
+    if (n_pairs == 0) {
+        const int64_t w = kTreeW[kTreeTypes - 1];
+        TREE_LAUNCH(n, k_tree_cut, key_s, n, tree_steps(t->fp64), (tree_min_cost(P) + w - 1) / w, key);
+        std::swap(key, key_s);
+    }
     TREE_LAUNCH(n, k_tree_heads, key_s, n, head);
     size_t ts = 0;
     TREE_CHECK(hipcub::DeviceScan::InclusiveSum(nullptr, ts, head, runid, int(n), st) == hipSuccess);
@@ -1319,51 +1417,44 @@ env_status build(Tree* t, const TreeSource& u, const std::vector<double>& nuc, c
     }
     t->rec_words = words;
     const std::vector<double> tab = tables(P);
-    t->d_test = keep<TreeTest>(t, nn);
-    t->d_node = keep<TreeNode>(t, nn);
-    t->d_thr = keep<float>(t, nn * tree_thr_row(P));
-    if (u.field) {
-        t->d_test_field = keep<TreeTest>(t, nn);
-        t->d_thr_field = keep<float>(t, nn * tree_thr_row(P));
-        if (!t->d_test_field || !t->d_thr_field) return ENV_E_NOMEM;
-    }
-    t->d_coef = keep<double>(t, nn * tree_words(P));
-    t->d_tab = keep<double>(t, tab_words(P));
-    t->d_first = keep<int32_t>(t, int64_t(first.size()));
-    t->d_rec = keep<uint32_t>(t, words);
-    t->d_nuc = keep<double>(t, 4 * n_nuc);
-    t->d_word = keep<int64_t>(t, n_pairs);
-    t->d_parent = keep<int32_t>(t, nn);
-    t->d_child = keep<int32_t>(t, int64_t(child.size()));
-    t->d_child_begin = keep<int32_t>(t, nn + 1);
-    t->d_by_depth = keep<int32_t>(t, nn);
-    t->d_geo = keep<double>(t, nn * kGeo);
     t->n_chunks = int64_t(chunk.size());
-    t->d_chunk = keep<Chunk>(t, t->n_chunks);
-    t->d_chunk_begin = keep<int32_t>(t, nn + 1);
-    t->d_chunk_end = keep<int32_t>(t, nn);
-    t->d_depth = keep<int32_t>(t, nn);
-    t->d_tail_begin = keep<int64_t>(t, t->n_chunks + 1);
-    t->d_tail_node = keep<int32_t>(t, int64_t(tail_node.size()));
+    Chunk* d_chunk = nullptr;
+    Keep keep;
+    keep.add(&t->d_test, nn);
+    keep.add(&t->d_node, nn);
+    keep.add(&t->d_thr, nn * tree_thr_row(P));
+    if (u.field) {
+        keep.add(&t->d_test_field, nn);
+        keep.add(&t->d_thr_field, nn * tree_thr_row(P));
+    }
+    keep.add(&t->d_coef, nn * tree_words(P));
+    keep.add(&t->d_tab, tab_words(P));
+    keep.add(&t->d_first, int64_t(first.size()));
+    keep.add(&t->d_rec, words);
+    keep.add(&t->d_nuc, 4 * n_nuc);
+    keep.add(&t->d_word, n_pairs);
+    keep.add(&t->d_parent, nn);
+    keep.add(&t->d_child, int64_t(child.size()));
+    keep.add(&t->d_child_begin, nn + 1);
+    keep.add(&t->d_by_depth, nn);
+    keep.add(&t->d_geo, nn * kGeo);
+    keep.add(&d_chunk, t->n_chunks);
+    keep.add(&t->d_chunk_begin, nn + 1);
+    keep.add(&t->d_chunk_end, nn);
+    keep.add(&t->d_depth, nn);
+    keep.add(&t->d_tail_begin, t->n_chunks + 1);
+    keep.add(&t->d_tail_node, int64_t(tail_node.size()));
     // chunks' moments, nodes' shifted and own moments, radii, chunks' shares of the bounds
-    t->d_work = keep<double>(t, t->n_chunks * part_words(t->P) + nn * (2 * part_words(t->P) + 4) +
-                                    int64_t(tail_node.size()) * (kLMax + 1));
-    t->d_sph = keep<uint32_t>(t, t->rec_words);
+    keep.add(&t->d_work, t->n_chunks * part_words(P) + nn * (2 * part_words(P) + 4) + int64_t(tail_node.size()) * (kLMax + 1));
+    keep.add(&t->d_sph, t->rec_words);
     uint32_t* d_start = tmp.get<uint32_t>(int64_t(start.size()));
     unsigned long long* d_box = tmp.get<unsigned long long>(6 * nn);
     unsigned long long* d_rad = tmp.get<unsigned long long>(3 * nn);
-    if (!t->d_test || !t->d_node || !t->d_thr || !t->d_coef || !t->d_tab || !t->d_first || !t->d_rec || !t->d_nuc ||
-        !t->d_word || !t->d_parent || !t->d_child || !t->d_child_begin || !t->d_by_depth || !t->d_geo || !t->d_chunk ||
-        !t->d_chunk_begin || !t->d_chunk_end || !t->d_depth || !t->d_tail_begin ||
-        !t->d_tail_node || !t->d_work || !t->d_sph || !d_start || !d_box || !d_rad)
-        return ENV_E_NOMEM;
-    std::vector<unsigned long long> box0(6 * size_t(nn));
-    for (size_t k = 0; k < size_t(nn); ++k)
-        for (int d = 0; d < 6; ++d) box0[6 * k + size_t(d)] = d < 3 ? ~0ull : 0ull;
+    if (!keep.allocate(t) || !d_start || !d_box || !d_rad) return ENV_E_NOMEM;
+    t->d_chunk = d_chunk;
     TREE_CHECK(put(t->d_node, node, st) && put(t->d_tab, tab, st) && put(t->d_first, first, st) &&
                put(t->d_parent, parent, st) && put(t->d_child, child, st) && put(t->d_child_begin, child_begin, st) &&
-               put(t->d_by_depth, by_depth, st) && put(d_start, start, st) && put(d_run_node, b.run_node, st) &&
-               put(d_box, box0, st) && put(static_cast<Chunk*>(t->d_chunk), chunk, st) &&
+               put(t->d_by_depth, by_depth, st) && put(d_start, start, st) && put(d_run_node, b.run_node, st) && put(d_chunk, chunk, st) &&
                put(t->d_chunk_begin, chunk_begin, st) && put(t->d_chunk_end, chunk_end, st) &&
                put(t->d_depth, depth, st) && put(t->d_tail_begin, tail_begin, st) &&
                put(t->d_tail_node, tail_node, st));
@@ -1383,6 +1474,7 @@ env_status build(Tree* t, const TreeSource& u, const std::vector<double>& nuc, c
     Ratios ratios{};
     for (int L = 0; L <= kLMax; ++L) ratios.r[L] = u.field ? std::sqrt(u.field_ratio[L]) * (1.0 + 1e-6) : 1.0;
     ratios.r[kLMax + 1] = 1.0;
+    TREE_LAUNCH(6 * nn, k_tree_no_boxes, nn, d_box);
     TREE_LAUNCH(n, k_tree_bounds, u.pairs, u.rec, d_nuc0, n_pairs, n, fp64, item_node, t->d_parent, d_box);
     TREE_LAUNCH(nn, k_tree_centres, d_box, nn, t->d_geo, d_rad);
     TREE_LAUNCH(n, k_tree_radii, u.pairs, u.rec, d_nuc0, n_pairs, n, fp64, item_node, t->d_parent, t->d_geo,
@@ -1397,7 +1489,7 @@ env_status build(Tree* t, const TreeSource& u, const std::vector<double>& nuc, c
 Tree* build_tree(const TreeSource& u, const std::vector<double>& nuc, const std::vector<int32_t>& nuc_begin,
                  const std::vector<int32_t>& nuc_end, bool fp64, env_status* st) {
     *st = ENV_OK;
-    const int64_t n_nuc = int64_t(nuc.size() / 4), n = u.n_pairs + n_nuc;
+    const int64_t n_nuc = int64_t(nuc.size() / 4) + u.n_cells, n = u.n_pairs + n_nuc;
     if (n < kTreeMinItems || n > kTreeMaxItems || u.n_groups <= 0 || u.n_groups >= (1 << 26) ||
         int64_t(nuc_begin.size()) != u.n_groups || int64_t(nuc_end.size()) != u.n_groups)
         return nullptr;
@@ -1428,7 +1520,7 @@ Tree* build_tree(const TreeSource& u, const std::vector<double>& nuc, const std:
 
 void free_tree(Tree* t) {
     if (!t) return;
-    for (void* p : t->owned) (void)hipFree(p);
+    (void)hipFree(t->owned);
     delete t;
 }
 

@@ -152,7 +152,7 @@ struct Tree {
     uint32_t* d_sph = nullptr;          // of a refresh: the pairs' spherical moments (rec_words)
     int64_t device_bytes = 0;
     int64_t room = INT64_MAX;           // device bytes that the tree may still take
-    std::vector<void*> owned;
+    void* owned = nullptr;              // the one allocation behind all of these
 };
 
 struct UpdPair;
@@ -165,6 +165,8 @@ struct TreeSource {
     const int64_t* group_pairs = nullptr;  // n_groups + 1: first pair of each group
     const uint32_t* rec = nullptr;
     int32_t n_groups = 0;
+    const double* cells = nullptr;      // host, n_cells x 4: x, y, z, electrons; items of group 0 after the nuclei
+    int64_t n_cells = 0;
     int order = 0;                      // highest order (one of the four above) and tolerance
     double eps = 0.0;
     double nuc_eps = 0.0;               // tolerance against the nuclei's charges (FP64 in both precisions)
