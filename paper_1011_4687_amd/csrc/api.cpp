@@ -617,10 +617,14 @@ env_status env_potential_autotune(env_potential* h, const double* points, int64_
         return ENV_E_DEVICE;
     }
     const bool fp64 = h->precision == ENV_PREC_FP64;
+    // (a tree's points per lane are one or two, and it splits in four where its
+    // blocks fill the chip: the default shape is always one of these)
     const int nps32[] = {2, 4}, nps64[] = {1, 2};
-    const int* nps = fp64 ? nps64 : nps32;
+    const int* nps = fp64 || h->tree ? nps64 : nps32;
+    const int k_any = h->tree ? 2 : 0;
     float best = 1e30f;
     env_potential::Tuned bestc{n, fp64 ? 2 : 4, 0};
+    if (h->tree) tree_shape(h, n, &bestc.np, &bestc.klog);
     env_status rc = ENV_OK;
     // drop an earlier entry for this size, then time every candidate shape
     h->tuned.erase(std::remove_if(h->tuned.begin(), h->tuned.end(),
@@ -630,7 +634,7 @@ env_status env_potential_autotune(env_potential* h, const double* points, int64_
         for (int k = 0; k <= kMaxSplitLog2 && rc == ENV_OK; ++k) {
             // (a workgroup of a tree evaluation has four waves for one block)
             const int64_t waves = (((n + 64 * nps[a] - 1) / (64 * nps[a])) << k) * (h->tree ? 4 : 1);
-            if (waves < int64_t(h->cu_count) * 4 || (k > 0 && waves > int64_t(h->cu_count) * 4 * 96))
+            if (waves < int64_t(h->cu_count) * 4 || (k > k_any && waves > int64_t(h->cu_count) * 4 * 96))
                 continue;
             h->tuned.push_back({n, nps[a], k});
             float ms = 0.0f;
