@@ -285,7 +285,8 @@ typedef struct {
     int64_t launches;         /* direct launches */
     int64_t captures;         /* graph captures */
     int64_t graph_launches;   /* graph replays */
-    int32_t granularity;      /* work items per workgroup's fair share of the work */
+    int32_t granularity;      /* work items per workgroup's fair share of the work
+                                 (with trees: 16ths of the default splits) */
     int32_t reserved;
     int64_t sorted_points;    /* points of the instances evaluated in Morton order */
     int64_t sorts;            /* evaluations that sorted points */

@@ -17,6 +17,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <cmath>
 #include <cstdlib>
 #include <cstring>
 #include <new>
@@ -33,7 +34,8 @@ struct env_batch {
     int precision = ENV_PREC_FP32C;
     bool tree = false;  // every handle has a multipole tree
     int np = 4;
-    int gran = 16;      // items per workgroup's fair share of the work (split granularity;
+    int gran = 16;      // items per workgroup's fair share of the work (split granularity, with
+                        // trees 16ths of the default splits;
                         // the autotuner's pick on the 64-instance workload)
     int grid = 0;
     int cu_count = 256;
@@ -112,9 +114,29 @@ void free_shape(env_batch* b) {
 // including its ENVPOT_NO_SORT switch).
 bool sorts(int64_t n) { return n >= kSortMinPoints && n <= int64_t(INT32_MAX) && !sort_disabled(); }
 
+// Cost that a work item of a plan with trees aims at: that of a point block
+// over S.  Every item tests the nodes of its instance's trees again, so S falls
+// with the blocks B of all instances, as the square root of their number.  By
+// measurement, S: 13,170 to 20,000 pairs per instance, B = 126, FP64: 128 1230 us, 32 571,
+// 8 664; B = 1005, FP32C: 32 1151, 16 1085, 8 1176; B = 1256, FP32C / FP64: 16 788 / 1818, 8
+// 820 / 1696, 4 1031 / 1963; 600 atoms, FP64: B = 57: 256 2980, 64 1392, 16 1553; B = 5628: 4
+// 21.3 ms, 2 22.1, 1 27.7.  (16 items per resident workgroup, as without trees,
+// took S = 128, 32, 16, 256 and 4 there.)
+double tree_target(const env_batch* b, const std::vector<double>& pcost, const int64_t* n, int per) {
+    double blocks = 0.0, cost = 0.0;
+    for (int i = 0; i < b->n_inst; ++i) {
+        const double nb = double((n[i] + per - 1) / per);
+        blocks += nb;
+        cost += nb * per * pcost[i];
+    }
+    if (blocks <= 0.0) return 1.0;
+    const double S = std::sqrt(640.0 * b->cu_count / blocks) * b->gran / 16.0;
+    return std::max(1.0, cost / blocks / S);
+}
+
 // Work items for point counts n: per instance a split factor such that an
-// item costs at most ~1/gran of a workgroup's fair share, items sorted by
-// decreasing cost.
+// item costs at most ~1/gran of a workgroup's fair share (with trees: about
+// tree_target), items sorted by decreasing cost.
 env_status build_shape(env_batch* b, const int64_t* n) {
     free_shape(b);
     const int per = (b->tree ? 64 : kBlock) * b->np;
@@ -129,7 +151,9 @@ env_status build_shape(env_batch* b, const int64_t* n) {
         if (b->tree) pcost[i] = std::min(pcost[i], 2.0e4) + 50.0 * in.n_groups;
         total += double(n[i]) * pcost[i];
     }
-    const double target = std::max(1.0, total / (double(b->gran) * b->grid));
+    // (with trees the nearest power of two, without the next)
+    const double target = b->tree ? std::sqrt(2.0) * tree_target(b, pcost, n, per)
+                                  : std::max(1.0, total / (double(b->gran) * b->grid));
     b->n.assign(n, n + b->n_inst);
     b->klog.assign(b->n_inst, 0);
     b->part_off.assign(b->n_inst, -1);
