@@ -229,7 +229,9 @@ env_status env_potential_update_density(env_potential* h, const env_density* P, 
  * and for a nucleus Z (C - R_A) / |C - R_A|^3.
  * points: device n x 3 float64; out: device n x 4 float64 row-major
  * (V, E_x, E_y, E_z per point, hartree/e and hartree/(e bohr)).  Same
- * handle, precision and stream semantics as env_potential_eval; the
+ * handle, precision and stream semantics as env_potential_eval, its multipole
+ * tree included (a node is then also far enough for the gradient, to the same
+ * fraction of its absolute charge over the squared distance); the
  * precision's far-field switch is applied one Boys order higher.  A point on
  * a nucleus gives non-finite values.  n = 0 is a no-op.
  * Errors: as env_potential_eval. */
@@ -301,18 +303,20 @@ env_status env_batch_create(env_potential* const* hs, int32_t n_inst, env_batch*
  * Asynchronous on `stream` except when the pointers or counts changed.
  * Instances of 32,768 points or more are evaluated in Morton order (they are
  * sorted before each launch; the values are written in the caller's order),
- * as env_potential_eval does; on handles with a tree so are those of 129
- * points or more, by a kernel that the graph holds.
+ * as env_potential_eval does; where every handle of the plan has a tree so are
+ * those of 129 points or more, by a kernel that the graph holds (one handle
+ * without a tree, and the plan evaluates every pair of all of them).
  * While `stream` is being captured by the caller, the launch is recorded
  * into the caller's graph without the sort (with trees by the kernel's order,
- * slice by slice; the plan's pointers and counts must then be the ones of an earlier call: ENV_E_STATE otherwise). */
+ * slice by slice; the plan's pointers and counts must then be the ones of an
+ * earlier call: ENV_E_STATE otherwise). */
 env_status env_batch_eval(env_batch* b, const double* const* points, const int64_t* n,
                           double* const* out, void* stream);
 
 /* Pick the plan's launch shape for these pointers and counts: every pair of
  * points per lane (FP32C 2 or 4, FP64 1 or 2) and split granularity (4, 8 or
- * 16 work items per workgroup's fair share) is timed over two graph
- * replays; the fastest is kept for later calls with the same counts.
+ * 16 work items per workgroup's fair share; with trees a quarter, half or all
+ * of the default splits) is timed over two graph replays; the fastest is kept for later calls with the same counts.
  * Writes out as env_batch_eval does.  Synchronous; stream must not be NULL.
  * Errors: as env_batch_eval, ENV_E_ARG for a NULL stream. */
 env_status env_batch_autotune(env_batch* b, const double* const* points, const int64_t* n,
@@ -614,9 +618,17 @@ env_status env_cells_create(const env_nucleus* nuclei, int32_t n_nuclei, const d
                             int64_t n_cells, const env_options* options, env_cells** out);
 
 /* V at n device points (n x 3 float64, row-major) into out (device, n
- * float64), asynchronous on `stream`.  Every point against every cell and
- * nucleus (a point on a nucleus gives +inf, a point on a cell a non-finite
- * value).  n = 0 is a no-op.
+ * float64), asynchronous on `stream`.  A point on a nucleus gives +inf, a point
+ * on a cell a non-finite value.  n = 0 is a no-op.
+ * Every point against every cell and nucleus, or, where points and cells are
+ * enough of them (from 8192 to 65,536 cells in FP32C, 24,576 to 262,144 in FP64, by
+ * the number of points), through a multipole tree over both that create builds:
+ * charges far from a block of points are taken together, to a truncation below
+ * 2^-28 (FP32C) or 2^-54 (FP64) of their absolute charge over the distance, the
+ * others one by one.  ENVPOT_NO_TREE=1 at create leaves the tree out, and so does
+ * a device without memory for it (ENVPOT_TREE_MAX_MB=N: more than N MiB).  Through
+ * the tree points are ordered as by env_potential_eval, and the positions and
+ * charges are FP64 in both precisions.
  * Errors: ENV_E_ARG, ENV_E_DEVICE, ENV_E_NOMEM (split partials). */
 env_status env_cells_eval(env_cells* h, const double* points, int64_t n, double* out,
                           void* stream);
