@@ -810,7 +810,7 @@ __global__ __launch_bounds__(node_threads(P)) void k_tree_nodes(MomentArgs A) {
 // items of the subtree themselves: from the children's sums, by the distance of
 // the centres, the radii would grow by up to a half.  A workgroup per chunk
 // loads its items once; eight lanes per ancestor add up an eighth of them each
-// (375,461 pairs, FP32C / FP64, 18 / 9 depths: 25 / 26 us; an item per thread and
+// (375,461 pairs, FP32C / FP64, 18 / 9 depths: 23 / 24 us; an item per thread and
 // a sum over the workgroup per ancestor 97 / 54).
 template <int P>
 __global__ __launch_bounds__(kChunk) void k_tree_tails(MomentArgs A, int fp64) {
@@ -849,7 +849,9 @@ __global__ __launch_bounds__(kChunk) void k_tree_tails(MomentArgs A, int fp64) {
         double acc[kLMax + 1] = {};
         for (int i = g; i < n_items; i += 8) {
             const double x = (item[0][i] - g0) * inv, y = (item[1][i] - g1) * inv, z = (item[2][i] - g2) * inv;
-            const double rho2 = fma(x, x, fma(y, y, z * z)), rho = sqrt(rho2);
+            // (from above: the instruction's relative error is below 2^-22)
+            const double rho2 = fma(x, x, fma(y, y, z * z)),
+                         rho = rho2 > 0.0 ? rho2 * __builtin_amdgcn_rsq(rho2) * (1.0 + 1e-6) : 0.0;
             double pw = (P + 1 - kLMax) % 2 ? rho : 1.0;  // rho^(P+1-k)
 #pragma unroll
             for (int n = 0; n < (P + 1 - kLMax) / 2; ++n) pw *= rho2;
@@ -882,8 +884,11 @@ constexpr double binomial(int n, int k) {
 // from which the degrees above p stay below eps |charge|/R,
 //   sum_{P>=n>p} w_n B_n x^n + sum_{n>P} w_n x^n sum_k A_k C(n, k) a^(n-P-1)
 //     <= eps |charge|, x = s/R,
-// with B_n the norm of degree n, w_n = 1, for the gradient (against
-// |charge|/R^2) sqrt((n+1)(2n+1)) < 1.5 (n+1), and A_k of k_tree_tails.  The sum
+// with B_n the norm of degree n (no value of its potential times R^(n+1)
+// is larger), w_n = 1, for the gradient (against |charge|/R^2) n + 1 (along a
+// great circle a degree is a trigonometric polynomial f of degree n, so
+// f'^2 + n^2 f^2 <= n^2 B_n^2, and the radial derivative is (n+1) f), and A_k of
+// k_tree_tails.  The sum
 // beyond P in closed form, with y = a x and t = y/(1-y):
 //   sum_m C(N+m, k) y^m = 1/(1-y) sum_{j<=k} C(N, k-j) t^j.
 // radius: the largest order's.
@@ -936,7 +941,7 @@ __global__ __launch_bounds__(kB) void k_tree_radius(MomentArgs A, int64_t n_node
             if (fld) {
                 // (n + 1) C(n, k) = (k + 1) C(n + 1, k + 1)
 #pragma unroll
-                for (int j = k + 1; j >= 0; --j) c = fma(c, t, 1.5 * (k + 1) * binomial(P + 2, k + 1 - j));
+                for (int j = k + 1; j >= 0; --j) c = fma(c, t, (k + 1) * binomial(P + 2, k + 1 - j));
             } else {
 #pragma unroll
                 for (int j = k; j >= 0; --j) c = fma(c, t, binomial(P + 1, k - j));
@@ -944,7 +949,7 @@ __global__ __launch_bounds__(kB) void k_tree_radius(MomentArgs A, int64_t n_node
             v = fma(ak[k], c, v);
         }
         v *= x * g;
-        for (int k = P; k > row; --k) v = (v + (fld ? 1.5 * (k + 1) : 1.0) * b[k]) * x;
+        for (int k = P; k > row; --k) v = (v + (fld ? double(k + 1) : 1.0) * b[k]) * x;
         for (int k = 0; k < row; ++k) v *= x;
         return !(v <= tol);
     };
