@@ -206,9 +206,7 @@ env_status eval_devsized(env_potential* h, const double* points, const int64_t* 
 }  // namespace envpot
 
 namespace {
-env_status eval_core(env_potential* h, const double* points, int64_t n, const uint32_t* order, double* out,
-                     void* stream);
-env_status eval_piece(env_potential* h, const double* points, int64_t n, double* out, void* stream);
+env_status eval_core(env_potential* h, const double* points, int64_t n, bool ordered, double* out, void* stream);
 }  // namespace
 
 extern "C" {
@@ -508,13 +506,15 @@ env_status env_potential_eval(env_potential* h, const double* points, int64_t n,
     DeviceGuard g(h->device);
     if (h->tree) {
         env_status rc = ENV_OK;
-        for (int64_t at = 0; at < n && rc == ENV_OK; at += tree_call_max(1))
-            rc = eval_piece(h, points + 3 * at, std::min(n - at, tree_call_max(1)), out + at, stream);
+        for (int64_t at = 0; at < n && rc == ENV_OK; at += tree_call_max(1)) {
+            const int64_t m = std::min(n - at, tree_call_max(1));
+            rc = eval_core(h, points + 3 * at, m, tree_orders(m, stream), out + at, stream);
+        }
         return rc;
     }
     if (n < kSortMinPoints || n > int64_t(INT32_MAX) || sort_disabled() ||
         stream_capturing(stream))
-        return eval_core(h, points, n, nullptr, out, stream);
+        return eval_core(h, points, n, false, out, stream);
     // large calls: evaluate the points in Morton order, then restore the caller's order
     hipStream_t st = static_cast<hipStream_t>(stream);
     double *spts = nullptr, *sout = nullptr;
@@ -526,7 +526,7 @@ env_status env_potential_eval(env_potential* h, const double* points, int64_t n,
         hipMallocAsync(reinterpret_cast<void**>(&order), size_t(n) * sizeof(uint32_t), st) != hipSuccess)
         rc = ENV_E_NOMEM;
     if (rc == ENV_OK && sort_points(points, n, spts, order, stream) != 0) rc = ENV_E_DEVICE;
-    if (rc == ENV_OK) rc = eval_core(h, spts, n, nullptr, sout, stream);
+    if (rc == ENV_OK) rc = eval_core(h, spts, n, false, sout, stream);
     if (rc == ENV_OK && scatter_values(sout, order, n, out, stream) != 0) rc = ENV_E_DEVICE;
     (void)hipFreeAsync(order, st);
     (void)hipFreeAsync(sout, st);
@@ -561,41 +561,26 @@ int timed_launch(env_potential* h, const EvalArgs& a, int S, int np, void* strea
     return rc;
 }
 
-// One launch of a handle with a tree: the kernels read the points through a
-// spatial order and the sum of the splits writes the values in the caller's.
-env_status eval_piece(env_potential* h, const double* points, int64_t n, double* out, void* stream) {
-    if (!tree_orders(n, stream)) return eval_core(h, points, n, nullptr, out, stream);
-    uint32_t* order = nullptr;
-    hipStream_t st = static_cast<hipStream_t>(stream);
-    if (hipMallocAsync(reinterpret_cast<void**>(&order), size_t(n) * sizeof(uint32_t), st) != hipSuccess)
-        return ENV_E_NOMEM;
-    env_status rc = tree_order(points, n, order, stream) == 0 ? ENV_OK : ENV_E_DEVICE;
-    if (rc == ENV_OK) rc = eval_core(h, points, n, order, out, stream);
-    (void)hipFreeAsync(order, st);
-    return rc;
-}
-
-env_status eval_core(env_potential* h, const double* points, int64_t n, const uint32_t* order, double* out,
-                     void* stream) {
+// One launch and the sum of its splits.  ordered (with a tree): the kernels
+// read the points through a spatial order and the values are written in the
+// caller's.  The partials and the order are one allocation.
+env_status eval_core(env_potential* h, const double* points, int64_t n, bool ordered, double* out, void* stream) {
     int np, k;
-    const bool tree = use_tree(h, n, order != nullptr);
+    const bool tree = use_tree(h, n, ordered);
     choose_shape(h, n, tree, &np, &k);
     const int S = 1 << k;
     hipStream_t st = static_cast<hipStream_t>(stream);
-    if (S == 1) {
-        EvalArgs a = make_args(h, points, n, out, 0, tree);
-        a.order = order;
-        return timed_launch(h, a, 1, np, stream) == 0 ? ENV_OK : ENV_E_DEVICE;
-    }
-    double* part = nullptr;
-    if (hipMallocAsync(reinterpret_cast<void**>(&part), size_t(S) * size_t(n) * sizeof(double), st) !=
-        hipSuccess)
-        return ENV_E_NOMEM;
-    EvalArgs a = make_args(h, points, n, part, k, tree);
+    const size_t part = S > 1 ? size_t(S) * size_t(n) * sizeof(double) : 0;
+    const size_t all = part + (ordered ? size_t(n) * sizeof(uint32_t) : 0);
+    char* mem = nullptr;
+    if (all > 0 && hipMallocAsync(reinterpret_cast<void**>(&mem), all, st) != hipSuccess) return ENV_E_NOMEM;
+    EvalArgs a = make_args(h, points, n, S > 1 ? reinterpret_cast<double*>(mem) : out, k, tree);
+    uint32_t* order = ordered ? reinterpret_cast<uint32_t*>(mem + part) : nullptr;
     a.order = order;
-    int rc = timed_launch(h, a, S, np, stream);
-    if (rc == 0) rc = launch_sum_splits(part, S, n, order, out, stream);
-    (void)hipFreeAsync(part, st);
+    int rc = ordered ? tree_order(points, n, order, stream) : 0;
+    if (rc == 0) rc = timed_launch(h, a, S, np, stream);
+    if (rc == 0 && S > 1) rc = launch_sum_splits(a.out, S, n, order, out, stream);
+    if (mem) (void)hipFreeAsync(mem, st);
     return rc == 0 ? ENV_OK : ENV_E_DEVICE;
 }
 

@@ -188,30 +188,24 @@ env_status tree_eval(const env_cells* h, const double* points, int64_t n, double
         if (v >= 0 && v <= kMaxSplitLog2) k = v;
     }
     const int S = 1 << k;
-    uint32_t* order = nullptr;
-    double* part = nullptr;
-    env_status rc = ENV_OK;
-    if (tree_orders(n, stream)) {
-        if (hipMallocAsync(reinterpret_cast<void**>(&order), size_t(n) * sizeof(uint32_t), st) != hipSuccess)
-            return ENV_E_NOMEM;
-        if (tree_order(points, n, order, stream) != 0) rc = ENV_E_DEVICE;
-    }
-    if (rc == ENV_OK && S > 1 &&
-        hipMallocAsync(reinterpret_cast<void**>(&part), size_t(S) * size_t(n) * sizeof(double), st) != hipSuccess)
-        rc = ENV_E_NOMEM;
+    const bool ordered = tree_orders(n, stream);
+    const size_t part = S > 1 ? size_t(S) * size_t(n) * sizeof(double) : 0;
+    const size_t all = part + (ordered ? size_t(n) * sizeof(uint32_t) : 0);
+    char* mem = nullptr;
+    if (all > 0 && hipMallocAsync(reinterpret_cast<void**>(&mem), all, st) != hipSuccess) return ENV_E_NOMEM;
+    uint32_t* order = ordered ? reinterpret_cast<uint32_t*>(mem + part) : nullptr;
     EvalArgs a{};
     a.pts = points;
     a.n = n;
-    a.out = S > 1 ? part : out;
+    a.out = S > 1 ? reinterpret_cast<double*>(mem) : out;
     a.tree = tree_view(*h->tree);
     a.tree.S = S;
     a.order = order;
-    if (rc == ENV_OK && (launch_potential(a, S, h->precision, np, stream) != 0 ||
-                         (S > 1 && launch_sum_splits(part, S, n, order, out, stream) != 0)))
-        rc = ENV_E_DEVICE;
-    if (part) (void)hipFreeAsync(part, st);
-    if (order) (void)hipFreeAsync(order, st);
-    return rc;
+    int rc = ordered ? tree_order(points, n, order, stream) : 0;
+    if (rc == 0) rc = launch_potential(a, S, h->precision, np, stream);
+    if (rc == 0 && S > 1) rc = launch_sum_splits(a.out, S, n, order, out, stream);
+    if (mem) (void)hipFreeAsync(mem, st);
+    return rc == 0 ? ENV_OK : ENV_E_DEVICE;
 }
 
 }  // namespace

@@ -52,9 +52,7 @@ void build_field_tables(const BoysParams& bp, std::vector<float>& t32, std::vect
 using namespace envpot;
 
 namespace {
-env_status field_core(env_potential* h, const double* points, int64_t n, const uint32_t* order, double* out,
-                      void* stream);
-env_status field_piece(env_potential* h, const double* points, int64_t n, double* out, void* stream);
+env_status field_core(env_potential* h, const double* points, int64_t n, bool ordered, double* out, void* stream);
 }  // namespace
 
 extern "C" {
@@ -68,12 +66,14 @@ env_status env_potential_eval_field(env_potential* h, const double* points, int6
     DeviceGuard g(h->device);
     if (h->tree) {
         env_status rc = ENV_OK;
-        for (int64_t at = 0; at < n && rc == ENV_OK; at += tree_call_max(4))
-            rc = field_piece(h, points + 3 * at, std::min(n - at, tree_call_max(4)), out + 4 * at, stream);
+        for (int64_t at = 0; at < n && rc == ENV_OK; at += tree_call_max(4)) {
+            const int64_t m = std::min(n - at, tree_call_max(4));
+            rc = field_core(h, points + 3 * at, m, tree_orders(m, stream), out + 4 * at, stream);
+        }
         return rc;
     }
     if (n < kSortMinPoints || n > int64_t(INT32_MAX) || sort_disabled() || stream_capturing(stream))
-        return field_core(h, points, n, nullptr, out, stream);
+        return field_core(h, points, n, false, out, stream);
     // large calls: evaluate the points in Morton order, then restore the caller's order
     hipStream_t st = static_cast<hipStream_t>(stream);
     double *spts = nullptr, *sout = nullptr;
@@ -85,7 +85,7 @@ env_status env_potential_eval_field(env_potential* h, const double* points, int6
         hipMallocAsync(reinterpret_cast<void**>(&order), size_t(n) * sizeof(uint32_t), st) != hipSuccess)
         rc = ENV_E_NOMEM;
     if (rc == ENV_OK && sort_points(points, n, spts, order, stream) != 0) rc = ENV_E_DEVICE;
-    if (rc == ENV_OK) rc = field_core(h, spts, n, nullptr, sout, stream);
+    if (rc == ENV_OK) rc = field_core(h, spts, n, false, sout, stream);
     if (rc == ENV_OK && scatter_rows4(sout, order, n, out, stream) != 0) rc = ENV_E_DEVICE;
     (void)hipFreeAsync(order, st);
     (void)hipFreeAsync(sout, st);
@@ -97,21 +97,8 @@ env_status env_potential_eval_field(env_potential* h, const double* points, int6
 
 namespace {
 
-// One launch with a tree: the points through a spatial order, as env_potential_eval.
-env_status field_piece(env_potential* h, const double* points, int64_t n, double* out, void* stream) {
-    if (!tree_orders(n, stream)) return field_core(h, points, n, nullptr, out, stream);
-    hipStream_t st = static_cast<hipStream_t>(stream);
-    uint32_t* order = nullptr;
-    if (hipMallocAsync(reinterpret_cast<void**>(&order), size_t(n) * sizeof(uint32_t), st) != hipSuccess)
-        return ENV_E_NOMEM;
-    env_status rc = tree_order(points, n, order, stream) == 0 ? ENV_OK : ENV_E_DEVICE;
-    if (rc == ENV_OK) rc = field_core(h, points, n, order, out, stream);
-    (void)hipFreeAsync(order, st);
-    return rc;
-}
-
-env_status field_core(env_potential* h, const double* points, int64_t n, const uint32_t* order, double* out,
-                      void* stream) {
+// One launch and the sum of its splits; ordered (with a tree): as a potential's.
+env_status field_core(env_potential* h, const double* points, int64_t n, bool ordered, double* out, void* stream) {
     // two points per lane at four waves per SIMD (mid workload: FP32C 46 ms
     // against 53 ms with one; FP64 79 against 81 ms); with a tree one (its
     // blocks are half as wide and the far form holds more per point: FP32C
@@ -149,20 +136,18 @@ env_status field_core(env_potential* h, const double* points, int64_t n, const u
     a.fp = h->fp;
     a.tree = h->tree ? tree_view_field(*h->tree) : TreeView{};
     a.tree.S = S;
-    a.order = order;
     hipStream_t st = static_cast<hipStream_t>(stream);
-    if (S == 1) {
-        a.out = out;
-        return launch_field(a, 1, h->precision, np, stream) == 0 ? ENV_OK : ENV_E_DEVICE;
-    }
-    double* part = nullptr;
-    if (hipMallocAsync(reinterpret_cast<void**>(&part), size_t(S) * size_t(n) * 4 * sizeof(double), st) !=
-        hipSuccess)
-        return ENV_E_NOMEM;
-    a.out = part;
-    int rc = launch_field(a, S, h->precision, np, stream);
-    if (rc == 0) rc = launch_sum_rows4(part, S, n, order, out, stream);
-    (void)hipFreeAsync(part, st);
+    const size_t part = S > 1 ? size_t(S) * size_t(n) * 4 * sizeof(double) : 0;
+    const size_t all = part + (ordered ? size_t(n) * sizeof(uint32_t) : 0);
+    char* mem = nullptr;
+    if (all > 0 && hipMallocAsync(reinterpret_cast<void**>(&mem), all, st) != hipSuccess) return ENV_E_NOMEM;
+    a.out = S > 1 ? reinterpret_cast<double*>(mem) : out;
+    uint32_t* order = ordered ? reinterpret_cast<uint32_t*>(mem + part) : nullptr;
+    a.order = order;
+    int rc = ordered ? tree_order(points, n, order, stream) : 0;
+    if (rc == 0) rc = launch_field(a, S, h->precision, np, stream);
+    if (rc == 0 && S > 1) rc = launch_sum_rows4(a.out, S, n, order, out, stream);
+    if (mem) (void)hipFreeAsync(mem, st);
     return rc == 0 ? ENV_OK : ENV_E_DEVICE;
 }
 
