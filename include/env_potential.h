@@ -316,7 +316,8 @@ env_status env_batch_eval(env_batch* b, const double* const* points, const int64
 /* Pick the plan's launch shape for these pointers and counts: every pair of
  * points per lane (FP32C 2 or 4, FP64 1 or 2) and split granularity (4, 8 or
  * 16 work items per workgroup's fair share; with trees a quarter, half or all
- * of the default splits) is timed over two graph replays; the fastest is kept for later calls with the same counts.
+ * of the default splits) is timed over two graph replays; the fastest is kept
+ * for later calls with the same counts.
  * Writes out as env_batch_eval does.  Synchronous; stream must not be NULL.
  * Errors: as env_batch_eval, ENV_E_ARG for a NULL stream. */
 env_status env_batch_autotune(env_batch* b, const double* const* points, const int64_t* n,

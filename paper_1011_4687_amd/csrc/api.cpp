@@ -622,15 +622,15 @@ env_status env_potential_autotune(env_potential* h, const double* points, int64_
             if (waves < int64_t(h->cu_count) * 4 || (k > k_any && waves > int64_t(h->cu_count) * 4 * 96))
                 continue;
             h->tuned.push_back({n, nps[a], k});
-            float ms = 0.0f;
-            for (int rep = 0; rep < 3 && rc == ENV_OK; ++rep) {  // first run warms up
+            float ms = 1e30f;  // the least: what else runs only adds to a time
+            for (int rep = 0; rep < 5 && rc == ENV_OK; ++rep) {  // first run warms up
                 if (hipEventRecord(e0, st) != hipSuccess) rc = ENV_E_DEVICE;
                 if (rc == ENV_OK) rc = env_potential_eval(h, points, n, out, stream);
                 if (rc == ENV_OK && hipEventRecord(e1, st) != hipSuccess) rc = ENV_E_DEVICE;
                 if (rc == ENV_OK && hipEventSynchronize(e1) != hipSuccess) rc = ENV_E_DEVICE;
                 float t = 0.0f;
                 if (rc == ENV_OK && hipEventElapsedTime(&t, e0, e1) != hipSuccess) rc = ENV_E_DEVICE;
-                if (rep > 0) ms += t;
+                if (rep > 0) ms = std::min(ms, t);
             }
             h->tuned.pop_back();
             if (rc == ENV_OK && ms < best) {
